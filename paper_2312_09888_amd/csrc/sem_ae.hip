@@ -14,10 +14,8 @@
 // with rows = element x output position, and the parameter layouts
 // W[(d Cin + i) Cout + o] (conv) and W[(i 8 + d) Cout + o] (convT).
 //
-// Training: forward (GEMMs with fused bias / tanh / binary16 rounding of the
-// latent), output gradient and loss, backward GEMMs (input gradients with
-// the tanh derivative fused; weight gradients as split reductions summed in
-// a fixed order), Adam.  Initialisation: layer-wise principal components
+// Training: forward, loss and gradient in sem_ae_train.hip, Adam here.
+// Initialisation: layer-wise principal components
 // from FP64 Gram matrices and a cyclic Jacobi eigensolver.  Compression:
 // encode, decode, per-element error check, raw blocks compacted by an
 // exclusive scan; decompression reverses it.
@@ -177,32 +175,25 @@ ae_pack(int64_t e_begin, const float* __restrict__ u, const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// GEMM with strided operands and fused epilogue (FP32)
+// One layer as a GEMM with a fused epilogue (FP32)
 // ---------------------------------------------------------------------------
 //
-// C[z][m][n] = sum_{k in split z} A(m, k) B(k, n), A(m, k) = A[m a_sm + k a_sk],
-// B(k, n) = B[k b_sk + n b_sn].  Epilogue (flags): + bias[n % bias_mod], tanh,
-// binary16 rounding, times (1 - D[m][n]^2).  16-deep k steps.
+// C[m][n] = sum_k A[m][k] B[k][n] + bias[n % bias_mod], row-major operands,
+// then (flags) tanh and binary16 rounding.  16-deep k steps.
 
-enum : int { kEpiTanh = 1, kEpiHalf = 2, kEpiTanhGrad = 4 };
+enum : int { kEpiTanh = 1, kEpiHalf = 2 };
 constexpr int kBK = 16;
 
 struct GemmArgs {
   int64_t M;
   int N;
-  int64_t K;
-  const float* A;
-  int64_t a_sm, a_sk;
-  const float* B;
-  int64_t b_sk, b_sn;
-  float* C;
-  int64_t ldc;
-  int64_t k_split;       // reduction length per grid.z slice
-  int64_t c_split;       // stride between the slices' C
+  int K;
+  const float* A;        // [M][K]
+  const float* B;        // [K][N]
+  float* C;              // [M][N]
   const float* bias;
   int bias_mod;
   int flags;
-  const float* D;        // tanh-derivative source, layout of C
 };
 
 // BM x BN tile on the matrix cores: four waves in a 2 x 2 arrangement, each
@@ -226,33 +217,23 @@ __global__ void __launch_bounds__(kT) gemm_f32(GemmArgs g) {
   const int lr = lane & 15, lk = lane >> 4;
   const int64_t m0 = (int64_t)blockIdx.x * BM;   // rows on x: up to 2^31 - 1 tiles
   const int n0 = blockIdx.y * BN;
-  const int64_t kb = (int64_t)blockIdx.z * g.k_split;
-  const int64_t ke = kb + g.k_split < g.K ? kb + g.k_split : g.K;
   f32x4 acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int64_t k0 = kb; k0 < ke; k0 += kBK) {
-    // A tile: BM x kBK; the index order follows the contiguous operand axis
+  for (int k0 = 0; k0 < g.K; k0 += kBK) {
 #pragma unroll
     for (int q = 0; q < (BM * kBK) / kT; ++q) {
-      const int idx = t + q * kT;
-      int mm, kk;
-      if (g.a_sk == 1) { kk = idx % kBK; mm = idx / kBK; }
-      else { mm = idx % BM; kk = idx / BM; }
-      const int64_t m = m0 + mm, k = k0 + kk;
-      As[kk][mm] = (m < g.M && k < ke) ? g.A[m * g.a_sm + k * g.a_sk] : 0.f;
+      const int idx = t + q * kT, kk = idx % kBK, mm = idx / kBK;
+      const int64_t m = m0 + mm;
+      As[kk][mm] = (m < g.M && k0 + kk < g.K) ? g.A[m * g.K + k0 + kk] : 0.f;
     }
 #pragma unroll
     for (int q = 0; q < (BN * kBK) / kT; ++q) {
-      const int idx = t + q * kT;
-      int nn, kk;
-      if (g.b_sn == 1) { nn = idx % BN; kk = idx / BN; }
-      else { kk = idx % kBK; nn = idx / kBK; }
+      const int idx = t + q * kT, nn = idx % BN, kk = idx / BN;
       const int n = n0 + nn;
-      const int64_t k = k0 + kk;
-      Bs[kk][nn] = (n < g.N && k < ke) ? g.B[k * g.b_sk + (int64_t)n * g.b_sn] : 0.f;
+      Bs[kk][nn] = (n < g.N && k0 + kk < g.K) ? g.B[(int64_t)(k0 + kk) * g.N + n] : 0.f;
     }
     __syncthreads();
 #pragma unroll
@@ -270,7 +251,6 @@ __global__ void __launch_bounds__(kT) gemm_f32(GemmArgs g) {
     }
     __syncthreads();
   }
-  float* C = g.C + (int64_t)blockIdx.z * g.c_split;
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
 #pragma unroll
@@ -282,166 +262,18 @@ __global__ void __launch_bounds__(kT) gemm_f32(GemmArgs g) {
         const int n = n0 + wn + 16 * j + lr;
         if (n >= g.N) continue;
         float v = acc[i][j][r];
-        if (g.bias) v += g.bias[n % g.bias_mod];
+        v += g.bias[n % g.bias_mod];
         if (g.flags & kEpiTanh) v = tanhf(v);
         if (g.flags & kEpiHalf) v = half_round(v);
-        if (g.flags & kEpiTanhGrad) {
-          const float d = g.D[m * g.ldc + n];
-          v *= 1.f - d * d;
-        }
-        C[m * g.ldc + n] = v;
+        g.C[m * g.N + n] = v;
       }
     }
   }
 }
 
-// out[i] = sum_z part[z][i] in order z = 0, 1, ... (deterministic)
-__global__ void sum_splits(const float* __restrict__ part, int64_t n, int splits,
-                           float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int z = 0; z < splits; ++z) s += part[(int64_t)z * n + i];
-  out[i] = s;
-}
-
-// part[z][col] = sum of G[rows of slice z][col]: the block's threads split
-// into column lanes and row groups (coalesced rows), then the row groups'
-// sums are added in a fixed order.
-__global__ void __launch_bounds__(kT)
-colsum_splits(const float* __restrict__ G, int64_t rows, int cols, int64_t rows_per,
-              float* __restrict__ part) {
-  __shared__ float red[kT];
-  const int64_t r0 = (int64_t)blockIdx.y * rows_per;
-  const int64_t r1 = r0 + rows_per < rows ? r0 + rows_per : rows;
-  const int lanes = cols < kT ? cols : kT;       // cols is 32, 64, 256 or 512
-  const int groups = kT / lanes;
-  const int lane = threadIdx.x % lanes, grp = threadIdx.x / lanes;
-  for (int c0 = 0; c0 < cols; c0 += lanes) {
-    float s = 0.f;
-    for (int64_t r = r0 + grp; r < r1; r += groups) s += G[r * cols + c0 + lane];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (grp == 0) {
-      float t = 0.f;
-      for (int q = 0; q < groups; ++q) t += red[q * lanes + lane];
-      part[(int64_t)blockIdx.y * cols + c0 + lane] = t;
-    }
-    __syncthreads();
-  }
-}
-
-// db[o] = sum_z sum_d part[z][d * cout + o] (fold = 8 for convT, 1 for conv)
-__global__ void fold_bias(const float* __restrict__ part, int splits, int cols, int cout,
-                          float* __restrict__ db) {
-  const int o = blockIdx.x * kT + threadIdx.x;
-  if (o >= cout) return;
-  float s = 0.f;
-  for (int z = 0; z < splits; ++z)
-    for (int d = 0; d < cols / cout; ++d) s += part[(int64_t)z * cols + d * cout + o];
-  db[o] = s;
-}
-
 // ---------------------------------------------------------------------------
-// loss, gather, Adam, binary16 conversion
+// Adam, binary16 conversion
 // ---------------------------------------------------------------------------
-
-// g = 2 (y - x) / count; per-block partial sums of (y - x)^2 in FP64
-__global__ void __launch_bounds__(kT)
-out_grad(const float* __restrict__ y, const float* __restrict__ x, int64_t n, float inv2,
-         float* __restrict__ g, double* __restrict__ part) {
-  __shared__ double red[kT / 64];
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  double sq = 0.0;
-  if (i < n) {
-    const float d = y[i] - x[i];
-    g[i] = inv2 * d;
-    sq = (double)d * d;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
-  __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
-// Max-error loss, one block of 512 nodes x 4 channels per workgroup: per
-// channel m = max |y - x| over the nodes; part[b] = sum_c m^2; the gradient
-// is inv2 m sign(y - x) at the nodes where |y - x| = m (shared equally by
-// tied nodes; none when m = 0), 0 elsewhere.  inv2 = 2 / (blocks x 4).
-__global__ void __launch_bounds__(kT)
-out_grad_max(const float* __restrict__ y, const float* __restrict__ x, float inv2,
-             float* __restrict__ g, double* __restrict__ part) {
-  __shared__ float red[kT / 64];
-  __shared__ int ired[kT / 64];
-  const int64_t b = blockIdx.x;
-  const float4* yb = reinterpret_cast<const float4*>(y + b * 2048);
-  const float4* xb = reinterpret_cast<const float4*>(x + b * 2048);
-  float4* gb = reinterpret_cast<float4*>(g + b * 2048);
-  float d[2][4];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const float4 a = yb[threadIdx.x + 256 * h], c = xb[threadIdx.x + 256 * h];
-    d[h][0] = a.x - c.x;
-    d[h][1] = a.y - c.y;
-    d[h][2] = a.z - c.z;
-    d[h][3] = a.w - c.w;
-  }
-  float m[4], share[4];
-  double sq = 0.0;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const float a0 = fabsf(d[0][c]), a1 = fabsf(d[1][c]);
-    m[c] = block_max_pos(a0 > a1 ? a0 : a1, red);
-    int k = (a0 == m[c]) + (a1 == m[c]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) k += __shfl_xor(k, off);
-    if ((threadIdx.x & 63) == 0) ired[threadIdx.x >> 6] = k;
-    __syncthreads();
-    k = ired[0] + ired[1] + ired[2] + ired[3];
-    __syncthreads();
-    share[c] = m[c] > 0.f ? inv2 * m[c] / (float)k : 0.f;
-    sq += (double)m[c] * m[c];
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    float o[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      o[c] = (m[c] > 0.f && fabsf(d[h][c]) == m[c]) ? copysignf(share[c], d[h][c]) : 0.f;
-    gb[threadIdx.x + 256 * h] = make_float4(o[0], o[1], o[2], o[3]);
-  }
-  if (threadIdx.x == 0) part[b] = sq;
-}
-
-__global__ void __launch_bounds__(1024)
-loss_reduce(const double* __restrict__ part, int64_t nb, double inv_n, float* __restrict__ loss) {
-  __shared__ double red[16];
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < nb; i += 1024) s += part[i];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-    for (int i = 0; i < 16; ++i) tot += red[i];
-    *loss = (float)(tot * inv_n);
-  }
-}
-
-__global__ void gather_blocks(const float* __restrict__ pool, const int64_t* __restrict__ idx,
-                              int64_t n, int64_t n_pool, float* __restrict__ out,
-                              int32_t* __restrict__ status) {
-  const int64_t r = blockIdx.x;
-  const int64_t src = idx ? idx[r] : r;
-  if (src < 0 || src >= n_pool) {
-    if (threadIdx.x == 0 && status) atomicOr(status, SEM_FLAG_BAD_ID);
-    for (int q = threadIdx.x; q < 2048; q += kT) out[r * 2048 + q] = 0.f;
-    return;
-  }
-  for (int q = threadIdx.x; q < 2048; q += kT) out[r * 2048 + q] = pool[src * 2048 + q];
-}
 
 __global__ void adam_step(int64_t n, float* __restrict__ p, const float* __restrict__ g,
                           float* __restrict__ m, float* __restrict__ v, float lr, float b1,
@@ -454,11 +286,6 @@ __global__ void adam_step(int64_t n, float* __restrict__ p, const float* __restr
   m[i] = mi;
   v[i] = vi;
   p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-}
-
-__global__ void to_half_bits(const float* __restrict__ z, int64_t n, uint16_t* __restrict__ h) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i < n) h[i] = __half_as_ushort(__float2half_rn(z[i]));
 }
 
 __global__ void from_half_bits(const uint16_t* __restrict__ h, int64_t n, float* __restrict__ z) {
@@ -1291,14 +1118,13 @@ int in_width(int l) {
   return L.conv ? 8 * L.cin : L.cin;
 }
 
-hipError_t gemm(const GemmArgs& g0, int splits, hipStream_t s) {
-  GemmArgs g = g0;
+hipError_t gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.N <= 32) {
-    dim3 grid((unsigned)cdiv(g.M, 128), (unsigned)cdiv(g.N, 32), (unsigned)splits);
+    dim3 grid((unsigned)cdiv(g.M, 128), (unsigned)cdiv(g.N, 32));
     hipLaunchKernelGGL((gemm_f32<128, 32>), grid, dim3(kT), 0, s, g);
   } else {
-    dim3 grid((unsigned)cdiv(g.M, 64), (unsigned)cdiv(g.N, 64), (unsigned)splits);
+    dim3 grid((unsigned)cdiv(g.M, 64), (unsigned)cdiv(g.N, 64));
     hipLaunchKernelGGL((gemm_f32<64, 64>), grid, dim3(kT), 0, s, g);
   }
   return hipGetLastError();
@@ -1313,36 +1139,26 @@ hipError_t layer_forward(int l, int64_t n, const float* params, const float* x, 
   g.K = in_width(l);
   g.N = out_width(l);
   g.A = x;
-  g.a_sm = g.K;
-  g.a_sk = 1;
   g.B = params + L.w_off;
-  g.b_sk = g.N;
-  g.b_sn = 1;
   g.C = y;
-  g.ldc = g.N;
-  g.k_split = g.K;
-  g.c_split = 0;
   g.bias = params + L.b_off;
   g.bias_mod = L.cout;
   g.flags = flags;
-  return gemm(g, 1, s);
+  return gemm(g, s);
 }
 
-constexpr int64_t kSplitRows = 512;   // rows per weight-gradient slice
+constexpr int64_t kSplitRows = 512;   // least rows per Gram-matrix slice
 
 struct AeWs {
   float* act[kLayers + 1];   // act[0] = input blocks, act[l + 1] = layer l output
-  float* g0;                 // gradient ping-pong
-  float* g1;
-  float* part;               // weight-gradient split partials
-  double* lpart;
+  float* g;                  // output gradient
+  float* slices;             // weight-gradient slice per workgroup
+  double* lpart;             // loss partial per workgroup
   int64_t n;
   size_t bytes;
 };
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
-
-int64_t max_splits(int64_t n) { return cdiv(n * 64, kSplitRows); }
 
 AeWs ae_layout(void* base, int64_t n) {
   AeWs w{};
@@ -1356,11 +1172,9 @@ AeWs ae_layout(void* base, int64_t n) {
   w.act[0] = reinterpret_cast<float*>(take((size_t)n * 2048 * 4));
   for (int l = 0; l < kLayers; ++l)
     w.act[l + 1] = reinterpret_cast<float*>(take((size_t)out_rows(l, n) * out_width(l) * 4));
-  w.g0 = reinterpret_cast<float*>(take((size_t)n * 2048 * 4));
-  w.g1 = reinterpret_cast<float*>(take((size_t)n * 2048 * 4));
-  // largest weight-gradient partial: splits x (8 Cin x Cout) = splits x 16384
-  w.part = reinterpret_cast<float*>(take((size_t)max_splits(n) * 16384 * 4));
-  w.lpart = reinterpret_cast<double*>(take((size_t)cdiv(n * 2048, kT) * 8));
+  w.g = reinterpret_cast<float*>(take((size_t)n * 2048 * 4));
+  w.slices = reinterpret_cast<float*>(take((size_t)ae_net_groups(n) * kAeNetParams * 4));
+  w.lpart = reinterpret_cast<double*>(take((size_t)ae_net_groups(n) * 8));
   w.n = n;
   w.bytes = off;
   return w;
@@ -1370,16 +1184,6 @@ int act_flags(int l, int tanh_mask) {
   int f = ((tanh_mask >> l) & 1) ? kEpiTanh : 0;
   if (l == 2) f |= kEpiHalf;   // the latent is binary16
   return f;
-}
-
-hipError_t forward_all(int64_t n, const float* params, int tanh_mask, const AeWs& w,
-                       hipStream_t s) {
-  for (int l = 0; l < kLayers; ++l) {
-    const hipError_t e = layer_forward(l, n, params, w.act[l], w.act[l + 1],
-                                       act_flags(l, tanh_mask), s);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
 }
 
 }  // namespace
@@ -1415,103 +1219,17 @@ hipError_t launch_ae_pack(int64_t e_begin, int64_t n, const float* const* f, con
 }
 
 hipError_t launch_ae_forward(int64_t n, const float* blocks, const float* params, int tanh_mask,
-                             float* recon, uint16_t* latent, void* ws, hipStream_t s) {
-  AeWs w = ae_layout(ws, n);
-  if (n <= 0) return hipSuccess;
-  hipError_t e = hipMemcpyAsync(w.act[0], blocks, (size_t)n * 2048 * 4, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess) e = forward_all(n, params, tanh_mask, w, s);
-  if (e != hipSuccess) return e;
-  if (latent)
-    hipLaunchKernelGGL(to_half_bits, dim3((unsigned)cdiv(n * 32, kT)), dim3(kT), 0, s, w.act[3],
-                       n * 32, latent);
-  if (recon)
-    e = hipMemcpyAsync(recon, w.act[kLayers], (size_t)n * 2048 * 4, hipMemcpyDeviceToDevice, s);
-  return e != hipSuccess ? e : hipGetLastError();
+                             float* recon, uint16_t* latent, hipStream_t s) {
+  return n <= 0 ? hipSuccess : launch_net_forward(n, blocks, params, tanh_mask, recon, latent, s);
 }
 
 hipError_t launch_ae_grad(int64_t n, const float* pool, int64_t n_pool, const int64_t* idx,
                           const float* params, int tanh_mask, int loss_kind, float* grad,
                           float* loss, void* ws, int32_t* status, hipStream_t s) {
-  AeWs w = ae_layout(ws, n);
+  const AeWs w = ae_layout(ws, n);
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gather_blocks, dim3((unsigned)n), dim3(kT), 0, s, pool, idx, n, n_pool,
-                     w.act[0], status);
-  hipError_t e = forward_all(n, params, tanh_mask, w, s);
-  if (e != hipSuccess) return e;
-  if (loss_kind == SEM_AE_LOSS_MAX) {
-    hipLaunchKernelGGL(out_grad_max, dim3((unsigned)n), dim3(kT), 0, s, w.act[kLayers],
-                       w.act[0], (float)(2.0 / (4.0 * (double)n)), w.g0, w.lpart);
-    if (loss)
-      hipLaunchKernelGGL(loss_reduce, dim3(1), dim3(1024), 0, s, w.lpart, n,
-                         1.0 / (4.0 * (double)n), loss);
-  } else {
-    const int64_t cnt = n * 2048;
-    const int64_t nb = cdiv(cnt, kT);
-    hipLaunchKernelGGL(out_grad, dim3((unsigned)nb), dim3(kT), 0, s, w.act[kLayers], w.act[0],
-                       cnt, (float)(2.0 / (double)cnt), w.g0, w.lpart);
-    if (loss)
-      hipLaunchKernelGGL(loss_reduce, dim3(1), dim3(1024), 0, s, w.lpart, nb, 1.0 / (double)cnt,
-                         loss);
-  }
-  float* g = w.g0;      // dL/d(output of layer l), tanh factor not yet applied
-  float* gn = w.g1;
-  for (int l = kLayers - 1; l >= 0; --l) {
-    const Layer& L = layers()[l];
-    const int64_t rows = out_rows(l, n);
-    const int kin = in_width(l), nout = out_width(l);
-    // the tanh derivative of layer l itself is applied by the previous step's
-    // epilogue (or here for the output layer, which is linear)
-    // weight gradient: dW[kin][nout] = A^T G, split over rows
-    const int splits = (int)cdiv(rows, kSplitRows);
-    GemmArgs gw{};
-    gw.M = kin;
-    gw.N = nout;
-    gw.K = rows;
-    gw.A = w.act[l];
-    gw.a_sm = 1;
-    gw.a_sk = kin;
-    gw.B = g;
-    gw.b_sk = nout;
-    gw.b_sn = 1;
-    gw.C = w.part;
-    gw.ldc = nout;
-    gw.k_split = kSplitRows;
-    gw.c_split = (int64_t)kin * nout;
-    e = gemm(gw, splits, s);
-    if (e != hipSuccess) return e;
-    const int64_t wn = (int64_t)kin * nout;
-    hipLaunchKernelGGL(sum_splits, dim3((unsigned)cdiv(wn, kT)), dim3(kT), 0, s, w.part, wn,
-                       splits, grad + L.w_off);
-    // bias gradient
-    hipLaunchKernelGGL(colsum_splits, dim3(1, (unsigned)splits), dim3(kT), 0, s, g, rows, nout,
-                       kSplitRows, w.part);
-    hipLaunchKernelGGL(fold_bias, dim3((unsigned)cdiv(L.cout, kT)), dim3(kT), 0, s, w.part,
-                       splits, nout, L.cout, grad + L.b_off);
-    if (l == 0) break;
-    // input gradient: dX[rows][kin] = G W^T, times tanh' of layer l - 1
-    GemmArgs gx{};
-    gx.M = rows;
-    gx.N = kin;
-    gx.K = nout;
-    gx.A = g;
-    gx.a_sm = nout;
-    gx.a_sk = 1;
-    gx.B = params + L.w_off;
-    gx.b_sk = 1;
-    gx.b_sn = nout;
-    gx.C = gn;
-    gx.ldc = kin;
-    gx.k_split = nout;
-    gx.c_split = 0;
-    gx.flags = ((tanh_mask >> (l - 1)) & 1) ? kEpiTanhGrad : 0;
-    gx.D = w.act[l];
-    e = gemm(gx, 1, s);
-    if (e != hipSuccess) return e;
-    float* tmp = g;
-    g = gn;
-    gn = tmp;
-  }
-  return hipGetLastError();
+  return launch_net_grad(n, pool, n_pool, idx, params, tanh_mask, loss_kind, w.act, w.g, w.slices,
+                         w.lpart, grad, loss, status, s);
 }
 
 hipError_t launch_ae_adam(int64_t n, float* p, const float* g, float* m, float* v, int step,
@@ -1706,10 +1424,9 @@ hipError_t launch_ae_compress(int64_t n_elem, const float* const* f, const float
     const int64_t n = n_elem - b < kChunk ? n_elem - b : kChunk;
     e = launch_ae_pack(b, n, f, scale, c.ae.act[0], s);
     if (e != hipSuccess) return e;
-    e = forward_all(n, params, tanh_mask, c.ae, s);
+    e = launch_net_forward(n, c.ae.act[0], params, tanh_mask, c.ae.act[kLayers],
+                           latent + b * 32, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(to_half_bits, dim3((unsigned)cdiv(n * 32, kT)), dim3(kT), 0, s,
-                       c.ae.act[3], n * 32, latent + b * 32);
     hipLaunchKernelGGL(ae_check, dim3((unsigned)n), dim3(kT), 0, s, b, f[0], f[1], f[2], f[3],
                        scale, c.gmax, c.ae.act[kLayers], c.flag);
   }

@@ -869,7 +869,7 @@ int sem_ae_forward(int64_t n, const float* blocks, const float* params, int tanh
   if (n == 0) return SEM_OK;
   if (!blocks || !params || (!recon && !latent)) return SEM_ERR_ARG;
   if (!workspace || workspace_bytes < ae_workspace_bytes(n)) return SEM_ERR_WORKSPACE;
-  return launch_ae_forward(n, blocks, params, tanh_mask, recon, latent, workspace,
+  return launch_ae_forward(n, blocks, params, tanh_mask, recon, latent,
                            static_cast<hipStream_t>(stream)) == hipSuccess
              ? SEM_OK
              : SEM_ERR_HIP;

@@ -265,7 +265,18 @@ hipError_t launch_ae_scales(int64_t n_elem, const float* const* f, float* scale,
 hipError_t launch_ae_pack(int64_t e_begin, int64_t n, const float* const* f, const float* scale,
                           float* x, hipStream_t s);
 hipError_t launch_ae_forward(int64_t n, const float* blocks, const float* params, int tanh_mask,
-                             float* recon, uint16_t* latent, void* ws, hipStream_t s);
+                             float* recon, uint16_t* latent, hipStream_t s);
+// The fused network kernels (sem_ae_train.hip): workgroups of a pass over n
+// blocks (eight blocks each, at most one workgroup per CU), values of the
+// parameter vector.
+constexpr int kAeNetParams = 67812;
+constexpr int ae_net_groups(int64_t n) { return n < 256 * 8 ? (int)((n + 7) / 8) : 256; }
+hipError_t launch_net_forward(int64_t n, const float* blocks, const float* params, int tanh_mask,
+                              float* recon, uint16_t* latent, hipStream_t s);
+hipError_t launch_net_grad(int64_t n, const float* pool, int64_t n_pool, const int64_t* idx,
+                           const float* params, int tanh_mask, int loss_kind, float* const* act,
+                           float* g, float* slices, double* lpart, float* grad, float* loss,
+                           int32_t* status, hipStream_t s);
 hipError_t launch_ae_grad(int64_t n, const float* pool, int64_t n_pool, const int64_t* idx,
                           const float* params, int tanh_mask, int loss_kind, float* grad,
                           float* loss, void* ws, int32_t* status, hipStream_t s);

@@ -144,6 +144,38 @@ def test_gradient_matches_oracle(mask, loss_kind):
             off += n
 
 
+@pytest.mark.parametrize("loss_kind", [sem.SEM_AE_LOSS_MSE, sem.SEM_AE_LOSS_MAX])
+@pytest.mark.parametrize("n", [3, 9, 2061])
+def test_gradient_over_passes_and_partial_workgroups(n, loss_kind):
+    """Batches of three blocks repeated: part of a workgroup's eight, one
+    block over, and more than one pass of every workgroup with a partial
+    last one.  The mean over the repeats is the three blocks' own loss and
+    gradient (tolerance as above)."""
+    r = np.random.default_rng(16)
+    params = (ae.init_params(15) + r.normal(scale=0.02, size=ae.param_count())).astype(np.float32)
+    pool = r.uniform(-1, 1, size=(4, 4, 8, 8, 8)).astype(np.float32)
+    idx = np.resize(np.array([2, 0, 3], dtype=np.int64), n)
+    loss, grad = sem.ae_grad(dev(to_morton(pool)), dev(params), idx=dev(idx),
+                             loss_kind=loss_kind)
+    ol, og = ae.gradient(params, pool[idx[:3]], quantize=True, loss_kind=loss_kind)
+    assert abs(float(loss.item()) - ol) <= 1e-5 * ol
+    assert normwise(grad.cpu().numpy().astype(np.float64), og) <= 2e-4
+
+
+def test_gradient_of_a_bad_index_is_that_of_a_zero_block():
+    r = np.random.default_rng(17)
+    params = ae.init_params(18)
+    pool = r.uniform(-1, 1, size=(2, 4, 8, 8, 8)).astype(np.float32)
+    zero = np.concatenate([pool, np.zeros_like(pool[:1])])
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    got = sem.ae_grad(dev(to_morton(pool)), dev(params),
+                      idx=dev(np.array([1, 2, -1], dtype=np.int64)), status=status)
+    want = sem.ae_grad(dev(to_morton(zero)), dev(params),
+                       idx=dev(np.array([1, 2, 2], dtype=np.int64)))
+    assert int(status.item()) == sem.SEM_FLAG_BAD_ID
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def test_gradient_flags_bad_indices():
     pool = dev(np.zeros((3, 512, 4), dtype=np.float32))
     st = torch.zeros(1, dtype=torch.int32, device=DEV)
