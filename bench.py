@@ -40,19 +40,21 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SRC = os.path.join(ROOT, "paper_2312_09888_amd", "csrc", "sem_kernels.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_2312_09888_amd", "csrc", f)
+              for f in ("sem_kernels.hip", "sem_lines.h")]
 CALIBRATION_BYTES = 1 << 30
 
 
 def traffic_file(kernel, dtype):
-    # named for the kernel without its template arguments
-    base = kernel.split("<")[0]
+    # named for the kernel without its template arguments; the order-7 FP64
+    # summaries keep the name of the kernel they were first taken of
+    base = "qcount_dma7" if kernel == "qcount_lines<7, double>" else kernel.split("<")[0]
     return os.path.join(ROOT, "profiles", f"{base}_channel65536_{dtype}_traffic.json")
 
 
 # kernel that runs the Q phase of sem_extract for order 7
 def q_kernel_name(dtype):
-    return "qcount_dma7<true>" if dtype == "f64" else "qcrit_pencil<7, float>"
+    return "qcount_lines<7, double>" if dtype == "f64" else "qcount_lines<7, float>"
 
 
 def parse():
@@ -92,8 +94,11 @@ def log(args, *msg):
 
 
 def kernel_sha():
-    with open(KERNEL_SRC, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SRC:
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
 
 
 def measured_traffic(kernel, dtype, n_launch_points):

@@ -34,7 +34,6 @@ struct DeviceTables {
   const float* d32[kMaxOrder + 1];
   const uint8_t* ntri;                // [256]
   const int8_t* tri;                  // [256][kMcMaxTri][3]
-  const double* eo7;                  // N = 7 even-odd form of D: A[4][4], B[4][4]
   int cu_count;                       // compute units (persistent grids)
   void* scratch;                      // device address of this GPU's copy of the
                                       // fixed scratch array (sem_noalloc.hip)
@@ -111,16 +110,15 @@ struct BatchSnap {
   void* om;
   void* qmm;
   const void* dmat;     // D and its halves in the line sums' type (d64 or d32)
-  const void* eo;       // even-odd halves of D (order 7)
 };
 constexpr int kBatchMaxSnap = 4096;
 size_t batch_plan_bytes(int n_snap);
 // Batch variants: 0, 1, 2 = LDS-tile form with 1, 2, 4 elements per work
-// item (256 threads); 3 = register-pencil form (N <= 7); 4 = direct-to-LDS
-// form (N = 7, FP64); 5 = one thread per node.  Variants 3-5 take one
-// element per work item and are the per-element kernels of sem_qcrit.
+// item (256 threads); 3 = line-exchange form (the body of sem_qcrit's
+// kernels); 4 (N = 7, FP64 only) and 5 name the same form: they are the
+// defaults of orders whose sem_qcrit once had forms of their own.
 constexpr int kBatchVariants = 6;
-enum BatchForm { kBatchChunk = 0, kBatchPencil = 1, kBatchDma7 = 2, kBatchNodeTile = 3 };
+enum BatchForm { kBatchChunk = 0, kBatchLines = 1 };
 bool batch_variant_ok(int order, sem_dtype dt, int variant);
 int batch_variant_chunk(int order, sem_dtype dt, int variant);   // elements per work item
 int batch_variant_form(int variant);

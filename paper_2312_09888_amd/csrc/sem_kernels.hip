@@ -31,7 +31,6 @@ struct Shape {
   static constexpr int P = N + 1;
   static constexpr int NP = P * P * P;                // nodes per element
   static constexpr int NC = N * N * N;                // cells per element
-  static constexpr int kNodeThreads = ((NP + 63) / 64) * 64;
   static constexpr int kCellThreads = ((NC + 63) / 64) * 64;
 };
 
@@ -172,13 +171,6 @@ __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* scra
   return before + inc - v;
 }
 
-// A value the compiler can no longer trace to its source (no instruction).
-template <typename V>
-__device__ __forceinline__ V opaque(V x) {
-  asm("" : "+v"(x));
-  return x;
-}
-
 // Coefficient type of the line sums: FP64 with the FP64 D for FP64 fields;
 // for FP32 fields FP32 with the FP32-rounded D up to order kF32SumOrder
 // (within the FP32 bound there; FP32 FMAs need no conversions and half the
@@ -286,177 +278,6 @@ __device__ __forceinline__ double sqrt_refined(double x) {
 __device__ __forceinline__ float vort_root(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double vort_root(double x) { return sqrt_refined(x); }
 
-// The adjugate of J (det J times J^-1, same layout as InvJac) and 1 / det J.
-__device__ __forceinline__ bool adjugate_jacobian(double xr, double xs, double xt, double yr,
-                                                  double ys, double yt, double zr, double zs,
-                                                  double zt, InvJac<double>& k, double& inv) {
-  k.rx = ys * zt - yt * zs;
-  k.sx = yt * zr - yr * zt;
-  k.tx = yr * zs - ys * zr;
-  const double det = xr * k.rx + xs * k.sx + xt * k.tx;
-  inv = recip_refined(det);
-  k.ry = xt * zs - xs * zt;
-  k.rz = xs * yt - xt * ys;
-  k.sy = xr * zt - xt * zr;
-  k.sz = xt * yr - xr * yt;
-  k.ty = xs * zr - xr * zs;
-  k.tz = xr * ys - xs * yr;
-  return det > 0.0;
-}
-
-// ---------------------------------------------------------------------------
-// gradient / Q-criterion: one workgroup per element, tiles staged in LDS
-// ---------------------------------------------------------------------------
-
-template <int N, typename T>
-__global__ void __launch_bounds__(Shape<N>::kNodeThreads)
-derivs_tile(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x, const T* __restrict__ y,
-            const T* __restrict__ z, const T* __restrict__ f, T* __restrict__ gx,
-            T* __restrict__ gy, T* __restrict__ gz, int32_t* __restrict__ status) {
-  using S = Shape<N>;
-  __shared__ coef_t<N, T> sd[S::P * S::P];
-  __shared__ T sf[4][S::NP];
-  const int t = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * S::NP;
-  if (t < S::P * S::P) sd[t] = dmat[t];
-  if (t < S::NP) {
-    sf[0][t] = x[base + t];
-    sf[1][t] = y[base + t];
-    sf[2][t] = z[base + t];
-    sf[3][t] = f[base + t];
-  }
-  __syncthreads();
-  int bad = 0;
-  if (t < S::NP) {
-    const int i = t % S::P, j = (t / S::P) % S::P, k = t / (S::P * S::P);
-    T xr, xs, xt, yr, ys, yt, zr, zs, zt, fr, fs, ft;
-    ref_derivs<N>(sf[0], sd, i, j, k, xr, xs, xt);
-    ref_derivs<N>(sf[1], sd, i, j, k, yr, ys, yt);
-    ref_derivs<N>(sf[2], sd, i, j, k, zr, zs, zt);
-    ref_derivs<N>(sf[3], sd, i, j, k, fr, fs, ft);
-    InvJac<T> kk;
-    bad = !invert_jacobian(xr, xs, xt, yr, ys, yt, zr, zs, zt, kk);
-    gx[base + t] = fr * kk.rx + fs * kk.sx + ft * kk.tx;
-    gy[base + t] = fr * kk.ry + fs * kk.sy + ft * kk.ty;
-    gz[base + t] = fr * kk.rz + fs * kk.sz + ft * kk.tz;
-  }
-  bad = __syncthreads_or(bad);
-  if (bad && t == 0 && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
-}
-
-template <int N, typename T>
-__device__ __forceinline__ void qcrit_tile_elem(
-    int64_t e, int t, const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
-    const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
-    const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q, T* __restrict__ om,
-    T* __restrict__ qmm, int32_t* __restrict__ status) {
-  using S = Shape<N>;
-  __shared__ coef_t<N, T> sd[S::P * S::P];
-  __shared__ T sf[6][S::NP];
-  __shared__ T red[2 * (S::kNodeThreads / 64)];
-  const int64_t base = e * S::NP;
-  if (t < S::P * S::P) sd[t] = dmat[t];
-  if (t < S::NP) {
-    sf[0][t] = x[base + t];
-    sf[1][t] = y[base + t];
-    sf[2][t] = z[base + t];
-    sf[3][t] = u[base + t];
-    sf[4][t] = v[base + t];
-    sf[5][t] = w[base + t];
-  }
-  __syncthreads();
-  int bad = 0;
-  T qv = neg_inf<T>();
-  if (t < S::NP) {
-    const int i = t % S::P, j = (t / S::P) % S::P, k = t / (S::P * S::P);
-    T xr, xs, xt, yr, ys, yt, zr, zs, zt;
-    ref_derivs<N>(sf[0], sd, i, j, k, xr, xs, xt);
-    ref_derivs<N>(sf[1], sd, i, j, k, yr, ys, yt);
-    ref_derivs<N>(sf[2], sd, i, j, k, zr, zs, zt);
-    InvJac<T> kk;
-    bad = !invert_jacobian(xr, xs, xt, yr, ys, yt, zr, zs, zt, kk);
-    T a[3][3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      T fr, fs, ft;
-      ref_derivs<N>(sf[3 + c], sd, i, j, k, fr, fs, ft);
-      a[c][0] = fr * kk.rx + fs * kk.sx + ft * kk.tx;
-      a[c][1] = fr * kk.ry + fs * kk.sy + ft * kk.ty;
-      a[c][2] = fr * kk.rz + fs * kk.sz + ft * kk.tz;
-    }
-    const T tr2 = a[0][0] * a[0][0] + a[1][1] * a[1][1] + a[2][2] * a[2][2] +
-                  T(2) * (a[0][1] * a[1][0] + a[0][2] * a[2][0] + a[1][2] * a[2][1]);
-    const T w1 = a[2][1] - a[1][2], w2 = a[0][2] - a[2][0], w3 = a[1][0] - a[0][1];
-    qv = T(-0.5) * tr2;
-    if (q) q[base + t] = qv;
-    if (om) om[base + t] = vort_root(w1 * w1 + w2 * w2 + w3 * w3);
-    if (qv != qv) qv = neg_inf<T>();
-  }
-  bad = __syncthreads_or(bad);
-  if (bad && t == 0 && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
-  if (qmm) {
-    T mn = t < S::NP ? qv : pos_inf<T>();
-    T mx = qv;
-    block_minmax<T, S::kNodeThreads>(mn, mx, red);
-    if (t == 0) {
-      qmm[2 * e] = mn;
-      qmm[2 * e + 1] = mx;
-    }
-  }
-}
-
-template <int N, typename T>
-__global__ void __launch_bounds__(Shape<N>::kNodeThreads)
-qcrit_tile(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x, const T* __restrict__ y,
-           const T* __restrict__ z, const T* __restrict__ u, const T* __restrict__ v,
-           const T* __restrict__ w, T* __restrict__ q, T* __restrict__ om,
-           T* __restrict__ qmm, int32_t* __restrict__ status) {
-  qcrit_tile_elem<N, T>(blockIdx.x, threadIdx.x, dmat, x, y, z, u, v, w, q, om, qmm, status);
-}
-
-// ---------------------------------------------------------------------------
-// gradient / Q-criterion, pencil form: two halves of LT threads per element
-// ---------------------------------------------------------------------------
-//
-// A half is one wave for N <= 7 ((N+1)^2 <= 64 lines) and two waves for
-// N = 8, 9.  Thread p < (N+1)^2 of each half owns the r-line
-// (j, k) = (p % P, p / P) of the element; half h owns the nodes i in
-// [h*H0, h*H0 + H0) of that line, so every node belongs to exactly one
-// thread.  Per field:
-//   1. each thread loads its whole r-line from HBM (both halves read the
-//      same line; the second read hits the cache) and applies D along r for
-//      its half -- D entries are uniform across the wave;
-//   2. the owners write their nodes to an LDS tile;
-//   3. half 0 applies D along s (thread p owns the s-line (i, k)), half 1
-//      along t (thread p owns the t-line (i, j)); results go to two LDS
-//      tiles;
-//   4. the owners read back f_s, f_t at their nodes.
-// Each line is read once and each derivative crosses LDS once, instead of
-// P LDS reads of the field and P of D per output.  LDS tiles use a padded
-// row stride of P + 1.
-
-template <int N, int E = 1>
-struct Pen {
-  static constexpr int P = N + 1;
-  static constexpr int NP = P * P;        // lines per direction and element
-  static constexpr int LE = E * NP;       // lines per half (E elements)
-  static constexpr int LT = 64 * ((LE + 63) / 64);  // threads per half
-  static constexpr int TH = 2 * LT;       // threads per workgroup
-  static constexpr int H0 = (P + 1) / 2;  // nodes per thread and half
-  static constexpr int RS = P + 1;        // LDS row stride (j)
-  static constexpr int SS = P * RS;       // LDS slab stride (k)
-  static constexpr int SZ = P * SS;       // padded tile of one element
-  static_assert(LE <= LT && TH <= 1024, "one line per thread of a half");
-  __device__ static constexpr int at(int i, int j, int k) { return i + RS * j + SS * k; }
-  // element of line p (lines of consecutive elements follow each other)
-  __device__ static constexpr int elem(int p) { return E == 1 ? 0 : p / NP; }
-  // half of thread t, wave-uniform and visibly 0 or 1 (so that the compiler
-  // resolves the node-range checks h * H0 + ii < P without branches)
-  __device__ static int half(int t) {
-    return __builtin_amdgcn_readfirstlane(t >= LT ? 1 : 0) != 0 ? 1 : 0;
-  }
-};
-
 // Coefficient tables (D, its even-odd halves) are read through the
 // constant address space: the index is wave-uniform, so every read is a
 // scalar load whatever stores precede it in the kernel.
@@ -469,19 +290,8 @@ __device__ __forceinline__ float coef(const float* p, int idx) {
   return ((const_f32)p)[idx];
 }
 
-// Line-shifted derivative of a P-point line: out[i] = sum_m D[i][m] (g_m - g_0),
-// summed in the coefficient type C (as ref_derivs).
-template <int P, typename T, typename C>
-__device__ __forceinline__ T line_deriv(const C* __restrict__ d, int i, const T (&g)[P]) {
-  C acc = C(0);
-  const C g0 = g[0];
-#pragma unroll
-  for (int m = 1; m < P; ++m) acc = fma(coef(d, i * P + m), (C)g[m] - g0, acc);
-  return (T)acc;
-}
-
-// All P outputs of one line (line-shifted as line_deriv) through the
-// even-odd halves of D stored after D itself: an output pair (i, P-1-i)
+// All P outputs of one line (line-shifted, summed in the coefficient type C,
+// as ref_derivs) through the even-odd halves of D stored after D itself: an output pair (i, P-1-i)
 // costs P multiply-adds instead of 2 (P - 1).
 template <int P, typename T, typename C>
 __device__ __forceinline__ void line_deriv_all(const C* __restrict__ d, const T (&g)[P],
@@ -519,227 +329,6 @@ __device__ __forceinline__ void line_deriv_all(const C* __restrict__ d, const T 
   }
 }
 
-// One field through the pencil scheme; owner gets (f_r, f_s, f_t) at its
-// H0 nodes.  `gf` points at the element's first value.
-// Load the owner's r-line of one field (issued early so that several
-// fields' loads are in flight at once).
-// Line p of a block of elements is the P values at gf + P p; lines from nl
-// on (past the last element) are not loaded.
-template <int N, typename T>
-__device__ __forceinline__ void pencil_load(const T* __restrict__ gf, int p, int nl,
-                                            T (&f)[N + 1]) {
-  constexpr int P = N + 1;
-  if (p < nl) {
-#pragma unroll
-    for (int m = 0; m < P; ++m) f[m] = gf[p * P + m];
-  }
-}
-
-template <int N, int E = 1, typename T>
-__device__ __forceinline__ void pencil_pass(const T (&f)[N + 1],
-                                            const coef_t<N, T>* __restrict__ d,
-                                            T* __restrict__ F, T* __restrict__ S,
-                                            T* __restrict__ Tt, int h, int p,
-                                            T (&fr)[Pen<N>::H0], T (&fs)[Pen<N>::H0],
-                                            T (&ft)[Pen<N>::H0]) {
-  using Q = Pen<N, E>;
-  constexpr int P = Q::P, H0 = Q::H0;
-  const bool valid = p < Q::LE;
-  const int el = Q::elem(p), line = p - el * Q::NP;
-  F += el * Q::SZ;
-  S += el * Q::SZ;
-  Tt += el * Q::SZ;
-  const int j = line % P, k = line / P;
-  if (valid) {
-#pragma unroll
-    for (int ii = 0; ii < H0; ++ii) {
-      const int i = h * H0 + ii;
-      if (i < P) {
-        fr[ii] = line_deriv<P>(d, i, f);
-        // f[i] by one select on the wave-uniform half (an index into the
-        // line would become a compare-and-select over all P values); at odd
-        // P the two values are made opaque first, or the select of two
-        // loads is folded into one load at a selected index, which keeps
-        // the line in memory
-        const T f0 = f[ii], f1 = f[H0 + ii < P ? H0 + ii : P - 1];
-        if constexpr (P % 2 == 1) F[Q::at(i, j, k)] = h == 0 ? opaque(f0) : opaque(f1);
-        else F[Q::at(i, j, k)] = h == 0 ? f0 : f1;
-      }
-    }
-  }
-  __syncthreads();
-  if (valid) {
-    const int a = j, b = k;
-    T g[P], out[P];
-    if (h == 0) {  // s-line at (i, k) = (a, b)
-#pragma unroll
-      for (int m = 0; m < P; ++m) g[m] = F[Q::at(a, m, b)];
-      line_deriv_all<P>(d, g, out);
-#pragma unroll
-      for (int jj = 0; jj < P; ++jj) S[Q::at(a, jj, b)] = out[jj];
-    } else {       // t-line at (i, j) = (a, b)
-#pragma unroll
-      for (int m = 0; m < P; ++m) g[m] = F[Q::at(a, b, m)];
-      line_deriv_all<P>(d, g, out);
-#pragma unroll
-      for (int kk = 0; kk < P; ++kk) Tt[Q::at(a, b, kk)] = out[kk];
-    }
-  }
-  __syncthreads();
-  if (valid) {
-#pragma unroll
-    for (int ii = 0; ii < H0; ++ii) {
-      const int i = h * H0 + ii;
-      if (i < P) {
-        fs[ii] = S[Q::at(i, j, k)];
-        ft[ii] = Tt[Q::at(i, j, k)];
-      }
-    }
-  }
-}
-
-template <int N, typename T, int E = 1>
-struct PencilTiles {
-  T F[E * Pen<N>::SZ];
-  T S[E * Pen<N>::SZ];
-  T Tt[E * Pen<N>::SZ];
-  T red[2 * Pen<N, E>::TH / 64];
-  int flag;
-};
-
-// Geometry of the owner's nodes: J^-1 from the three coordinate passes.
-// The coordinate tiles land in FX, FY, FZ (the same tile when they are not
-// needed afterwards).
-template <int N, int E = 1, typename T>
-__device__ __forceinline__ bool pencil_geometry(const T (&lx)[N + 1], const T (&ly)[N + 1],
-                                                const T (&lz)[N + 1],
-                                                const coef_t<N, T>* __restrict__ d,
-                                                PencilTiles<N, T, E>& sm, T* FX, T* FY, T* FZ,
-                                                int h, int p, InvJac<T> (&kk)[Pen<N>::H0]) {
-  constexpr int H0 = Pen<N>::H0, P = Pen<N>::P;
-  T xr[H0], xs[H0], xt[H0], yr[H0], ys[H0], yt[H0], zr[H0], zs[H0], zt[H0];
-  pencil_pass<N, E>(lx, d, FX, sm.S, sm.Tt, h, p, xr, xs, xt);
-  pencil_pass<N, E>(ly, d, FY, sm.S, sm.Tt, h, p, yr, ys, yt);
-  pencil_pass<N, E>(lz, d, FZ, sm.S, sm.Tt, h, p, zr, zs, zt);
-  bool ok = true;
-#pragma unroll
-  for (int ii = 0; ii < H0; ++ii) {
-    const bool good = invert_jacobian(xr[ii], xs[ii], xt[ii], yr[ii], ys[ii], yt[ii], zr[ii],
-                                      zs[ii], zt[ii], kk[ii]);
-    if (h * H0 + ii < P) ok = ok && good;   // odd P: half 1 owns one node fewer
-  }
-  return ok;
-}
-
-template <int N, typename T>
-__global__ void __launch_bounds__(Pen<N>::TH)
-derivs_pencil(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x, const T* __restrict__ y,
-              const T* __restrict__ z, const T* __restrict__ f, T* __restrict__ gx,
-              T* __restrict__ gy, T* __restrict__ gz, int32_t* __restrict__ status) {
-  using Q = Pen<N>;
-  constexpr int P = Q::P, H0 = Q::H0;
-  __shared__ PencilTiles<N, T> sm;
-  const int h = Q::half(threadIdx.x);
-  const int p = threadIdx.x % Q::LT;
-  const int64_t base = (int64_t)blockIdx.x * (P * P * P);
-  T lx[P], ly[P], lz[P], lf[P];
-  pencil_load<N>(x + base, p, Q::NP, lx);
-  pencil_load<N>(y + base, p, Q::NP, ly);
-  pencil_load<N>(z + base, p, Q::NP, lz);
-  pencil_load<N>(f + base, p, Q::NP, lf);
-  InvJac<T> kk[H0];
-  int bad = !pencil_geometry<N>(lx, ly, lz, dmat, sm, sm.F, sm.F, sm.F, h, p, kk);
-  T fr[H0], fs[H0], ft[H0];
-  pencil_pass<N>(lf, dmat, sm.F, sm.S, sm.Tt, h, p, fr, fs, ft);
-  const bool valid = p < Q::NP;
-  if (!valid) bad = 0;
-  if (valid) {
-    const int j = p % P, k = p / P;
-#pragma unroll
-    for (int ii = 0; ii < H0; ++ii) {
-      const int i = h * H0 + ii;
-      if (i < P) {
-        const int64_t o = base + (k * P + j) * P + i;
-        gx[o] = fr[ii] * kk[ii].rx + fs[ii] * kk[ii].sx + ft[ii] * kk[ii].tx;
-        gy[o] = fr[ii] * kk[ii].ry + fs[ii] * kk[ii].sy + ft[ii] * kk[ii].ty;
-        gz[o] = fr[ii] * kk[ii].rz + fs[ii] * kk[ii].sz + ft[ii] * kk[ii].tz;
-      }
-    }
-  }
-  bad = __syncthreads_or(bad);
-  if (bad && threadIdx.x == 0 && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
-}
-
-// Q and |omega| at the owner's nodes; the velocity-gradient rows are folded
-// into Q = -(sum_ij A_ij A_ji)/2 and |omega|^2 as they are produced.
-template <int N, int E = 1, typename T>
-__device__ __forceinline__ bool pencil_qcrit(const T* gx, const T* gy, const T* gz,
-                                             const T* gu, const T* gv, const T* gw,
-                                             const coef_t<N, T>* __restrict__ d,
-                                             PencilTiles<N, T, E>& sm, T* FX, T* FY, T* FZ,
-                                             int h, int p, int nl, T (&qv)[Pen<N>::H0],
-                                             T (&om)[Pen<N>::H0]) {
-  constexpr int H0 = Pen<N>::H0, P = Pen<N>::P;
-  // N <= 7 and FP32: all six lines are requested before any arithmetic;
-  // FP64 at N = 8, 9: the velocity lines are requested just before their
-  // pass (their values would otherwise hold 60 more registers through the
-  // geometry). FP32 at N = 9 stays at 187 registers either way, and the
-  // early requests took its Q phase on the batch benchmark's order-9
-  // snapshots from 3.96 to 3.64 ms.
-  constexpr bool kEarly = N <= 7 || std::is_same<T, float>::value;
-  T lx[P], ly[P], lz[P], lu[P], lv[P], lw[P];
-  pencil_load<N>(gx, p, nl, lx);
-  pencil_load<N>(gy, p, nl, ly);
-  pencil_load<N>(gz, p, nl, lz);
-  if constexpr (kEarly) {
-    pencil_load<N>(gu, p, nl, lu);
-    pencil_load<N>(gv, p, nl, lv);
-    pencil_load<N>(gw, p, nl, lw);
-  }
-  InvJac<T> kk[H0];
-  const bool ok = pencil_geometry<N, E>(lx, ly, lz, d, sm, FX, FY, FZ, h, p, kk);
-  T fr[H0], fs[H0], ft[H0];
-  T a01[H0], a02[H0], a12[H0];
-  // row 0 (u)
-  if constexpr (!kEarly) pencil_load<N>(gu, p, nl, lu);
-  pencil_pass<N, E>(lu, d, sm.F, sm.S, sm.Tt, h, p, fr, fs, ft);
-#pragma unroll
-  for (int ii = 0; ii < H0; ++ii) {
-    const InvJac<T>& K = kk[ii];
-    const T a00 = fr[ii] * K.rx + fs[ii] * K.sx + ft[ii] * K.tx;
-    a01[ii] = fr[ii] * K.ry + fs[ii] * K.sy + ft[ii] * K.ty;
-    a02[ii] = fr[ii] * K.rz + fs[ii] * K.sz + ft[ii] * K.tz;
-    qv[ii] = a00 * a00;
-  }
-  // row 1 (v)
-  if constexpr (!kEarly) pencil_load<N>(gv, p, nl, lv);
-  pencil_pass<N, E>(lv, d, sm.F, sm.S, sm.Tt, h, p, fr, fs, ft);
-#pragma unroll
-  for (int ii = 0; ii < H0; ++ii) {
-    const InvJac<T>& K = kk[ii];
-    const T a10 = fr[ii] * K.rx + fs[ii] * K.sx + ft[ii] * K.tx;
-    const T a11 = fr[ii] * K.ry + fs[ii] * K.sy + ft[ii] * K.ty;
-    a12[ii] = fr[ii] * K.rz + fs[ii] * K.sz + ft[ii] * K.tz;
-    qv[ii] = qv[ii] + a11 * a11 + T(2) * (a01[ii] * a10);
-    const T w3 = a10 - a01[ii];
-    om[ii] = w3 * w3;
-  }
-  // row 2 (w)
-  if constexpr (!kEarly) pencil_load<N>(gw, p, nl, lw);
-  pencil_pass<N, E>(lw, d, sm.F, sm.S, sm.Tt, h, p, fr, fs, ft);
-#pragma unroll
-  for (int ii = 0; ii < H0; ++ii) {
-    const InvJac<T>& K = kk[ii];
-    const T a20 = fr[ii] * K.rx + fs[ii] * K.sx + ft[ii] * K.tx;
-    const T a21 = fr[ii] * K.ry + fs[ii] * K.sy + ft[ii] * K.ty;
-    const T a22 = fr[ii] * K.rz + fs[ii] * K.sz + ft[ii] * K.tz;
-    qv[ii] = T(-0.5) * (qv[ii] + a22 * a22 + T(2) * (a02[ii] * a20 + a12[ii] * a21));
-    const T w1 = a21 - a12[ii], w2 = a02[ii] - a20;
-    om[ii] = vort_root(om[ii] + w1 * w1 + w2 * w2);
-  }
-  return ok;
-}
-
 // Counting four isovalues at a time. A node's word holds bit (q > c_s) at
 // bit 8s for the isovalues g .. g + 3 below n (a NaN compares below every
 // isovalue); the eight corner words of a cell, each shifted by its vertex
@@ -761,9 +350,6 @@ __device__ __forceinline__ uint32_t cell_word(const uint32_t* bits, int n0) {
   for (int vtx = 0; vtx < 8; ++vtx)
     w += bits[n0 + (vtx & 1) + RS * ((vtx >> 1) & 1) + SS * (vtx >> 2)] << vtx;
   return w;
-}
-__device__ __forceinline__ int case_count_entry(int cs, uint8_t nt) {
-  return (int)nt + ((cs != 0 && cs != 255) << 16);
 }
 // Sum over the 16 lanes of each row of the wave, by DPP row shifts (lanes
 // shifted in from outside the row read 0): lane 15 of the row ends with the
@@ -810,8 +396,7 @@ __device__ __forceinline__ int case_count_entry8(int cs, uint8_t nt) {
 template <int NW>
 __device__ __forceinline__ void publish_rows(uint32_t (&pw)[2], int m, int g, int t,
                                              uint32_t* s_rows, int32_t* __restrict__ cnt,
-                                             int64_t n_elem, int64_t e,
-                                             int64_t* __restrict__ active) {
+                                             int64_t n_elem, int64_t e) {
   static_assert(NW >= 1 && NW <= 4, "at most 16 rows");
   const int h = t >> 6, p = t & 63;
   pw[0] = row_sum16(pw[0]);
@@ -826,11 +411,7 @@ __device__ __forceinline__ void publish_rows(uint32_t (&pw)[2], int m, int g, in
     const uint32_t f =
         row < 4 * NW ? (s_rows[2 * row + (s >> 1)] >> (16 * (s & 1))) & 0xffffu : 0u;
     const uint32_t sum = row_sum16((f & 255u) | ((f >> 8) << 16));
-    if (row == 15 && s < m) {
-      cnt[(int64_t)(g + s) * n_elem + e] = (int)(sum & 0xffffu);
-      const unsigned a = sum >> 16;
-      if (active && a) atomicAdd((unsigned long long*)&active[g + s], (unsigned long long)a);
-    }
+    if (row == 15 && s < m) cnt[(int64_t)(g + s) * n_elem + e] = (int)sum;
   }
 }
 // Where a Q kernel also counts each isovalue's triangles and active cells per
@@ -840,292 +421,38 @@ struct CountSink {
   int n_iso;
   IsoList<T> iso;
   const uint8_t* ntri;     // [256] triangles per case
-  int32_t* cnt;            // [n_iso][n_elem]
-  int64_t* active;         // [n_iso] active-cell totals (may be NULL)
+  int32_t* cnt;            // [n_iso][n_elem], packed (below)
+  int64_t* active;         // [n_iso] active-cell totals (may be NULL): set to 0
+                           // here, summed by the scan's first kernel
   int64_t n_elem;
 };
 
-// Ranges and counts of a workgroup of E > 1 elements: wave w takes the
-// elements w, w + waves, ...; an element's range from its lines' partial
-// (min, max) in part (both halves), its cells' cases from the node words in
-// F (one element tile after another).
-template <int N, typename T, bool COUNT, int E>
-__device__ __forceinline__ void pencil_multi_tail(int64_t e, int t, int ne,
-                                                  const T (&qv)[Pen<N>::H0], T* F,
-                                                  const T* part, T* emm, const int32_t* tab,
-                                                  T* __restrict__ qmm,
-                                                  const CountSink<T>* sink) {
-  using Q = Pen<N, E>;
-  constexpr int P = Q::P, H0 = Q::H0, NW = Q::TH / 64;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-  for (int el = wave; el < ne; el += NW) {
-    T a = pos_inf<T>(), b = neg_inf<T>();
-    for (int q2 = lane; q2 < 2 * Q::NP; q2 += 64) {
-      const int idx = (q2 < Q::NP ? 0 : Q::LT - Q::NP) + el * Q::NP + q2;
-      a = part[idx] < a ? part[idx] : a;
-      b = part[Q::TH + idx] > b ? part[Q::TH + idx] : b;
-    }
-    wave_minmax(a, b);
-    if (lane == 63) {
-      if (qmm) {
-        qmm[2 * (e + el)] = a;
-        qmm[2 * (e + el) + 1] = b;
-      }
-      if constexpr (COUNT) {
-        emm[2 * el] = a;
-        emm[2 * el + 1] = b;
-      }
-    }
-  }
-  if constexpr (COUNT) {
-    constexpr int NC = N * N * N;
-    uint32_t* bits = reinterpret_cast<uint32_t*>(F);
-    const int h = Q::half(t);
-    const int p = t % Q::LT;
-    const bool valid = p < ne * Q::NP;
-    const int n_iso = sink->n_iso;
-    __syncthreads();   // publishes emm
-    for (int g = 0; g < n_iso; g += 4) {
-      const int m = n_iso - g < 4 ? n_iso - g : 4;
-      if (g > 0) {
-        __syncthreads();   // every wave is done with the previous words
-        if (valid) {
-          const int el = Q::elem(p), line = p - el * Q::NP;
-          const int j = line % P, k = line / P;
-#pragma unroll
-          for (int ii = 0; ii < H0; ++ii) {
-            const int i = h * H0 + ii;
-            if (i < P)
-              bits[el * Q::SZ + Q::at(i, j, k)] = iso_bits4<T>(qv[ii], sink->iso, g, n_iso);
-          }
-        }
-        __syncthreads();
-      }
-      for (int el = wave; el < ne; el += NW) {
-        // elements outside every isovalue's range of the group have only
-        // trivial cases (NaN nodes count as below; the minimum is -inf then)
-        const T emn = emm[2 * el], emx = emm[2 * el + 1];
-        bool live = false;
-        for (int s = 0; s < m; ++s)
-          live |= (emx > sink->iso.v[g + s]) && !(emn > sink->iso.v[g + s]);
-        int packed[4] = {0, 0, 0, 0};
-        if (live) {
-          for (int c = lane; c < NC; c += 64) {
-            const int n0 = el * Q::SZ + Q::at(c % N, (c / N) % N, c / (N * N));
-            const uint32_t word = cell_word<Q::RS, Q::SS>(bits, n0);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-              if (s < m) packed[s] += tab[(word >> (8 * s)) & 255];
-          }
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          if (s < m) {
-            const int sum = (int)wave_sum_to63((uint32_t)packed[s]);
-            if (lane == 63) {
-              sink->cnt[(int64_t)(g + s) * sink->n_elem + e + el] = sum & 0xffff;
-              const int a = sum >> 16;
-              if (sink->active && a)
-                atomicAdd((unsigned long long*)&sink->active[g + s], (unsigned long long)a);
-            }
-          }
-        }
-      }
-    }
-  }
+// A count slot holds an element's triangles (at most 5 x 729) and, from bit
+// 16 on, its active cells (at most 729).  The totals of the active cells
+// come from the scan, which reads the slots anyway: one atomic per element
+// and isovalue on the n_iso totals instead bound the count kernels (all of
+// them hit one cache line; 155,344 order-2 elements at three isovalues took
+// 650 us, the Q kernel among it 76 us).
+__device__ __forceinline__ int slot_tris(int32_t v) { return v & 0xffff; }
+__device__ __forceinline__ int slot_active(int32_t v) { return v >> 16; }
+__device__ __forceinline__ void clear_active(int64_t* active, int n_iso) {
+  if (active && blockIdx.x == 0 && (int)threadIdx.x < n_iso) active[threadIdx.x] = 0;
 }
 
-// One workgroup over the elements e .. e + ne - 1 (E of them at most).
-template <int N, typename T, bool COUNT = false, int E = 1>
-__device__ __forceinline__ void qcrit_pencil_elem(
-    int64_t e, int t, const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
-    const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
-    const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q, T* __restrict__ om,
-    T* __restrict__ qmm, int32_t* __restrict__ status, const CountSink<T>* sink = nullptr,
-    int ne = 1) {
-  using Q = Pen<N, E>;
-  constexpr int P = Q::P, H0 = Q::H0;
-  __shared__ PencilTiles<N, T, E> sm;
-  __shared__ int32_t s_tab[COUNT ? 256 : 1];
-  __shared__ uint32_t s_rows[COUNT && E == 1 ? 2 * Q::TH / 64 * 4 : 1];
-  __shared__ T s_part[E > 1 ? 2 * Q::TH : 1];   // per-thread (min, max) of Q
-  __shared__ T s_emm[E > 1 && COUNT ? 2 * E : 1];
-  const int h = Q::half(t);
-  const int p = t % Q::LT;
-  const int64_t base = e * (P * P * P);
-  const int nl = E == 1 ? Q::NP : ne * Q::NP;   // lines of elements that exist
-  // triangle counts of the 256 cases: requested here, written to LDS after
-  // the passes (published by the barrier after the Q tile), so that the
-  // loads overlap the field loads instead of delaying them
-  constexpr int TR = COUNT ? (256 + Q::TH - 1) / Q::TH : 1;
-  uint8_t tab_v[TR];
-  if constexpr (COUNT) {
-#pragma unroll
-    for (int r = 0; r < TR; ++r)
-      if (t + r * Q::TH < 256) tab_v[r] = sink->ntri[t + r * Q::TH];
-  }
-  T qv[H0], ov[H0];
-  int bad = !pencil_qcrit<N, E>(x + base, y + base, z + base, u + base, v + base, w + base,
-                                dmat, sm, sm.F, sm.F, sm.F, h, p, nl, qv, ov);
-  if constexpr (COUNT) {
-    // the several-element tail packs active cells at bit 16, the
-    // one-element form at bit 8
-#pragma unroll
-    for (int r = 0; r < TR; ++r) {
-      const int c = t + r * Q::TH;
-      if (c < 256) s_tab[c] = E == 1 ? case_count_entry8(c, tab_v[r]) : case_count_entry(c, tab_v[r]);
-    }
-  }
-  const bool valid = p < nl;
-  T mn = pos_inf<T>(), mx = neg_inf<T>();
-  if (!valid) bad = 0;
-  if (valid) {
-    const int el = Q::elem(p), line = p - el * Q::NP;
-    const int j = line % P, k = line / P;
-#pragma unroll
-    for (int ii = 0; ii < H0; ++ii) {
-      const int i = h * H0 + ii;
-      if (i < P) {
-        const int64_t o = base + (int64_t)p * P + i;   // line p of the block, node i
-        if (q) q[o] = qv[ii];
-        if (om) om[o] = ov[ii];
-        if constexpr (COUNT)   // F is free after the last pass
-          reinterpret_cast<uint32_t*>(sm.F)[el * Q::SZ + Q::at(i, j, k)] =
-              iso_bits4<T>(qv[ii], sink->iso, 0, sink->n_iso);
-        const T c = qv[ii] != qv[ii] ? neg_inf<T>() : qv[ii];
-        mn = c < mn ? c : mn;
-        mx = c > mx ? c : mx;
-      }
-    }
-  }
-  if constexpr (E > 1) {
-    s_part[t] = mn;
-    s_part[Q::TH + t] = mx;
-  }
-  // an inverted element (rare) is flagged by its own lanes: no block vote
-  if (bad && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
-  __syncthreads();               // publishes the Q tile
-  if constexpr (E > 1) {
-    pencil_multi_tail<N, T, COUNT, E>(e, t, ne, qv, sm.F, s_part, s_emm, s_tab, qmm, sink);
-    return;
-  }
-  if (qmm || COUNT) {
-    block_minmax<T, Q::TH>(mn, mx, sm.red);
-    if (qmm && t == 0) {
-      qmm[2 * e] = mn;
-      qmm[2 * e + 1] = mx;
-    }
-  }
-  if constexpr (COUNT && E == 1) {
-    // cells t, t + TH, ...; node words in F
-    constexpr int NC = N * N * N, R = (NC + Q::TH - 1) / Q::TH, NW = Q::TH / 64;
-    uint32_t* bits = reinterpret_cast<uint32_t*>(sm.F);
-    static_assert(R <= 3, "publish_rows takes at most three cells per lane");
-    int n0[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int cc = t + r * Q::TH < NC ? t + r * Q::TH : 0;
-      n0[r] = Q::at(cc % N, (cc / N) % N, cc / (N * N));
-    }
-    const int n_iso = sink->n_iso;
-    for (int g = 0; g < n_iso; g += 4) {
-      const int m = n_iso - g < 4 ? n_iso - g : 4;
-      if (g > 0) {   // every read of the previous words is behind the last barrier
-        if (valid) {
-          const int j = p % P, k = p / P;
-#pragma unroll
-          for (int ii = 0; ii < H0; ++ii) {
-            const int i = h * H0 + ii;
-            if (i < P) bits[Q::at(i, j, k)] = iso_bits4<T>(qv[ii], sink->iso, g, n_iso);
-          }
-        }
-        __syncthreads();
-      }
-      // elements outside every isovalue's range of the group have only
-      // trivial cases (NaN nodes count as below; mn is -inf then)
-      bool live = false;
-      for (int s = 0; s < m; ++s)
-        live |= (mx > sink->iso.v[g + s]) && !(mn > sink->iso.v[g + s]);
-      uint32_t pw[2] = {0u, 0u};
-      if (live) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (t + r * Q::TH >= NC) continue;
-          const uint32_t word = cell_word<Q::RS, Q::SS>(bits, n0[r]);
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-            if (s < m) pw[s >> 1] += (uint32_t)s_tab[(word >> (8 * s)) & 255] << (16 * (s & 1));
-        }
-      }
-      publish_rows<NW>(pw, m, g, t, s_rows, sink->cnt, sink->n_elem, e, sink->active);
-    }
-  }
-}
-
-// Elements per workgroup of the pencil Q kernels: enough that the lines of
-// the low orders fill whole waves ((N + 1)^2 lines per element and half).
-// FP32 N = 6 and 8 stay at one: there the larger workgroup costs a wave of
-// occupancy per SIMD (143 and 129 registers) and measured slower (34.2
-// against 26.6 and 26.0 against 25.4 ps per point). FP64 N = 5, 6 (over 200
-// registers) keep workgroups of at most four waves: with eight, the batched
-// kernel's registers spill.
-constexpr int pencil_elems_of(int n, bool f64) {
-  constexpr int e64[kMaxOrder + 1] = {1, 16, 7, 4, 5, 3, 1, 1, 1, 1};
-  constexpr int e32[kMaxOrder + 1] = {1, 16, 7, 4, 5, 7, 1, 1, 1, 1};
-  return f64 ? e64[n] : e32[n];
-}
-template <int N, typename T>
-constexpr int pencil_elems() {
-  return pencil_elems_of(N, std::is_same<T, double>::value);
-}
-template <int N, typename T>
-constexpr int pencil_threads() {
-  return Pen<N, pencil_elems<N, T>()>::TH;
-}
-
-template <int N, typename T>
-__global__ void __launch_bounds__((pencil_threads<N, T>()))
-qcrit_pencil(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x, const T* __restrict__ y,
-             const T* __restrict__ z, const T* __restrict__ u, const T* __restrict__ v,
-             const T* __restrict__ w, T* __restrict__ q, T* __restrict__ om,
-             T* __restrict__ qmm, int32_t* __restrict__ status, int64_t n_elem) {
-  constexpr int E = pencil_elems<N, T>();
-  const int64_t e0 = (int64_t)blockIdx.x * E;
-  const int ne = n_elem - e0 < E ? (int)(n_elem - e0) : E;
-  qcrit_pencil_elem<N, T, false, E>(e0, threadIdx.x, dmat, x, y, z, u, v, w, q, om, qmm,
-                                    status, nullptr, ne);
-}
-
-// Q, |omega|, range and the per-(isovalue, element) counts in one pass.
-template <int N, typename T>
-__global__ void __launch_bounds__((pencil_threads<N, T>()))
-qcount_pencil(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
-              const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
-              const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
-              T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
-              CountSink<T> sink) {
-  constexpr int E = pencil_elems<N, T>();
-  const int64_t e0 = (int64_t)blockIdx.x * E;
-  const int ne = sink.n_elem - e0 < E ? (int)(sink.n_elem - e0) : E;
-  qcrit_pencil_elem<N, T, true, E>(e0, threadIdx.x, dmat, x, y, z, u, v, w, q, om, qmm,
-                                   status, &sink, ne);
-}
+#include "sem_lines.h"
 
 // ---------------------------------------------------------------------------
-// N = 7, FP64: element tiles staged in LDS by direct global->LDS loads
+// element tiles fetched by direct global->LDS loads (emission and counts)
 // ---------------------------------------------------------------------------
 //
-// Each element's six tiles (4 KiB each) are fetched with global_load_lds
-// (16 bytes per lane, 1 KiB per wave instruction, fully coalesced, no
-// registers held while the data is in flight).  A lane may fetch any
-// 16-byte chunk (two neighbouring i) and it lands at LDS slot
-// base + lane, so the chunk placement is chosen freely:
+// A tile is fetched with global_load_lds (16 bytes per lane, 1 KiB per wave
+// instruction, fully coalesced, no registers held while the data is in
+// flight).  A lane may fetch any 16-byte chunk (two neighbouring i of an
+// order-7 FP64 element) and it lands at LDS slot base + lane, so the chunk
+// placement is chosen freely:
 //   slot(k, j, ip) = 4 (8k + (j ^ (k & 1))) + (ip ^ ((j >> 1) & 3)),
 // i.e. rows j <-> j^1 swapped in odd slabs and the four chunks of a row
-// rotated by j >> 1.  With 32 four-byte banks this makes the r-line reads
-// (16 bytes per lane, fixed chunk, lanes over j), the s-line reads (8 bytes,
-// lanes over i and a pair of k) and the t-line reads (8 bytes, lanes over i
-// and a pair of j) free of bank conflicts.
+// rotated by j >> 1, which spreads reads along any direction over the banks.
 
 namespace dma7 {
 __device__ __forceinline__ constexpr int slot(int k, int j, int ip) {
@@ -1185,13 +512,6 @@ __device__ __forceinline__ void barrier_after_wait() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-}
-
-// Workgroup barrier for ordinary LDS traffic while direct loads may still be
-// in flight: wait for this wave's LDS operations only, then s_barrier.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0); vmcnt and expcnt untouched
-  barrier_after_wait();
 }
 
 // ---------------------------------------------------------------------------
@@ -1344,6 +664,7 @@ iso_count(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ mm,
   __shared__ uint32_t s_ntri4[64];
   __shared__ T red[2 * (TH / 64)];
   __shared__ int32_t sred[TH / 64];
+  clear_active(active_total, n_iso);
   const int t = threadIdx.x;
   const int64_t e = blockIdx.x;
   const int64_t base = e * S::NP;
@@ -1397,10 +718,7 @@ iso_count(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ mm,
       int sum = 0;
 #pragma unroll
       for (int q = 0; q < TH / 64; ++q) sum += sred[q];
-      cnt[(int64_t)s * n_elem + e] = sum & 0xffff;
-      const int act = sum >> 16;
-      if (active_total && act) atomicAdd((unsigned long long*)&active_total[s],
-                                         (unsigned long long)act);
+      cnt[(int64_t)s * n_elem + e] = sum;
     }
     __syncthreads();
   }
@@ -1426,7 +744,7 @@ iso_emit(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
   const int t = threadIdx.x;
   const int64_t e = blockIdx.x;
   bool any = false;
-  for (int s = 0; s < n_iso; ++s) any = any || cnt[(int64_t)s * n_elem + e] > 0;
+  for (int s = 0; s < n_iso; ++s) any = any || slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
   if (!any) return;
   const int64_t base = e * S::NP;
   for (int q = t; q < 256; q += TH) s_ntri[q] = ntri_tab[q];
@@ -1440,7 +758,7 @@ iso_emit(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
   __syncthreads();
   for (int s = 0; s < n_iso; ++s) {
     const int64_t flat = (int64_t)s * n_elem + e;
-    if (cnt[flat] == 0) continue;
+    if (slot_tris(cnt[flat]) == 0) continue;
     int64_t g = offs[flat];
     T* dst = out.ptr[0];
     int64_t cap = out.cap[0];
@@ -1462,20 +780,46 @@ iso_emit(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
 
 constexpr int kScanThreads = 256;
 
-// Tile sums; a tile is kScanThreads x ITEMS counts (scan_tile).
-template <int ITEMS>
+// Tile sums; a tile is kScanThreads x ITEMS counts (scan_tile).  PACKED: the
+// counts are slots of triangles and active cells; the active cells of the
+// isovalues that the tile holds (n_elem slots each) are added to `active`.
+template <int ITEMS, bool PACKED>
 __global__ void __launch_bounds__(kScanThreads)
-scan_reduce(const int32_t* __restrict__ cnt, int64_t count, int64_t* __restrict__ partial) {
+scan_reduce(const int32_t* __restrict__ cnt, int64_t count, int64_t* __restrict__ partial,
+            int64_t* __restrict__ active, int64_t n_elem) {
   __shared__ int64_t sred[kScanThreads / 64];
   const int64_t start = (int64_t)blockIdx.x * (kScanThreads * ITEMS);
+  int32_t v[ITEMS];
   int64_t s = 0;
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     const int64_t idx = start + r * kScanThreads + threadIdx.x;
-    if (idx < count) s += cnt[idx];
+    v[r] = idx < count ? cnt[idx] : 0;
+    // packed: both sums at once (a tile's stay below 2^24)
+    if constexpr (PACKED) s += (int64_t)slot_tris(v[r]) | ((int64_t)slot_active(v[r]) << 32);
+    else s += v[r];
   }
   s = block_sum<kScanThreads>(s, sred);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  if (threadIdx.x == 0) partial[blockIdx.x] = PACKED ? (int64_t)(uint32_t)s : s;
+  if constexpr (PACKED) {
+    if (!active) return;
+    const int64_t end = start + kScanThreads * ITEMS < count ? start + kScanThreads * ITEMS : count;
+    const int64_t i0 = start / n_elem, i1 = (end - 1) / n_elem;
+    for (int64_t i = i0; i <= i1; ++i) {
+      int64_t a = s >> 32;
+      if (i0 != i1) {
+        a = 0;
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+          const int64_t idx = start + r * kScanThreads + threadIdx.x;
+          if (idx >= i * n_elem && idx < (i + 1) * n_elem) a += slot_active(v[r]);
+        }
+        a = block_sum<kScanThreads>(a, sred);
+      }
+      if (threadIdx.x == 0 && a)
+        atomicAdd((unsigned long long*)&active[i], (unsigned long long)a);
+    }
+  }
 }
 
 __global__ void __launch_bounds__(1024)
@@ -1497,7 +841,7 @@ scan_partials(int64_t* __restrict__ partial, int64_t nb) {
 // scanned (nb <= kScanFold), and each workgroup adds up the sums of the
 // tiles before it, which saves the one-workgroup scan of the partials.
 constexpr int64_t kScanFold = 1024;
-template <bool FOLD, int ITEMS>
+template <bool FOLD, int ITEMS, bool PACKED>
 __global__ void __launch_bounds__(kScanThreads)
 scan_apply(const int32_t* __restrict__ cnt, int64_t count, const int64_t* __restrict__ partial,
            int64_t nb, int64_t* __restrict__ offs) {
@@ -1509,6 +853,7 @@ scan_apply(const int32_t* __restrict__ cnt, int64_t count, const int64_t* __rest
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     v[r] = (start + r < count) ? cnt[start + r] : 0;
+    if constexpr (PACKED) v[r] = slot_tris(v[r]);
     s += v[r];
   }
   int64_t base;
@@ -1558,323 +903,8 @@ __global__ void fill_i64(int64_t* __restrict__ p, int n, int64_t value) {
 }
 
 // ---------------------------------------------------------------------------
-// N = 7, FP64 extraction: Q + triangle counts, scan, emission
+// emission from element tiles fetched by direct global->LDS loads
 // ---------------------------------------------------------------------------
-//
-// qcount_dma7 computes Q and |omega| from the six staged tiles, keeps Q in
-// LDS and counts every isovalue's triangles and active cells per element.
-// The counts then go through the device-wide exclusive scan, and emit_direct
-// re-stages the Q and coordinate tiles of the elements that have triangles
-// and writes them at their offsets.  (A single pass with a decoupled
-// look-back saves that re-read, but on MI355X its chain of device-scope
-// polls across the eight XCDs cost more than the re-read does.)
-//
-// qcount_dma7 runs four waves per element on the swizzled tile layout
-// above, wave h (0..3) owning nodes i = h and 7 - h of r-line (j, k) =
-// lane.  Waves 0, 1 differentiate the s-lines and waves 2, 3 the t-lines,
-// half a line each, in the even-odd form of D.  With two nodes per lane
-// (112 VGPRs) four waves fit on a SIMD to hide the load and LDS latencies.
-
-// One 4 KiB tile with four waves: wave h issues chunk group h.
-__device__ __forceinline__ void dma_tile4(const double* __restrict__ src, double* raw, int h,
-                                          int lane) {
-  const int s = 64 * h + lane;
-  const int row = s >> 2, k = row >> 3, j = (row & 7) ^ (k & 1);
-  const int ip = (s & 3) ^ ((j >> 1) & 3);
-  lds_load16(src + 2 * (ip + 4 * j + 32 * k), raw + 128 * h);
-}
-
-// Even-odd form of an 8-point line derivative (D[7-i][7-m] = -D[i][m]):
-// with e_m = g_m + g_{7-m}, o_m = g_m - g_{7-m} (m < 4),
-// A[i][m] = (D[i][m] + D[i][7-m]) / 2 and B[i][m] = (D[i][m] - D[i][7-m]) / 2,
-//   (D g)_i = R_i + P_i,  (D g)_{7-i} = R_i - P_i  (i < 4),
-//   P_i = sum_m A[i][m] e_m,  R_i = sum_m B[i][m] o_m.
-// Half the multiplies of the direct form, and a pair of outputs needs one
-// row of A and B only.
-__device__ __forceinline__ void eo_split(const double (&g)[8], double (&e)[4], double (&o)[4]) {
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    e[m] = g[m] + g[7 - m];
-    o[m] = g[m] - g[7 - m];
-  }
-}
-__device__ __forceinline__ void eo_pair(const double* __restrict__ eo, int i,
-                                        const double (&e)[4], const double (&o)[4],
-                                        double& lo, double& hi) {
-  double P = coef(eo, 4 * i) * e[0], R = coef(eo, 16 + 4 * i) * o[0];
-#pragma unroll
-  for (int m = 1; m < 4; ++m) {
-    P = fma(coef(eo, 4 * i + m), e[m], P);
-    R = fma(coef(eo, 16 + 4 * i + m), o[m], R);
-  }
-  lo = R + P;
-  hi = R - P;
-}
-
-// A lane's tile offsets in the swizzled layout, the same for every field:
-// its r-line's four 16-byte chunks and the eight nodes of its s-line (waves
-// 0, 1) or t-line (waves 2, 3).  Computed once per element and held in
-// registers (the swizzle costs several instructions per offset).
-struct Dma7Lane {
-  int r[4];
-  int g[8];
-};
-__device__ __forceinline__ Dma7Lane dma7_lane(int h, int p) {
-  const int j = p & 7, k = p >> 3;
-  Dma7Lane L;
-#pragma unroll
-  for (int ip = 0; ip < 4; ++ip) {
-    L.r[ip] = 2 * dma7::slot(k, j, ip);
-    asm volatile("" : "+v"(L.r[ip]));
-  }
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    L.g[m] = h < 2 ? dma7::at(j, m, k) : dma7::at(j, k, m);
-    asm volatile("" : "+v"(L.g[m]));
-  }
-  return L;
-}
-
-// One field with four waves: wave h owns nodes i = h and 7 - h of r-line
-// (j, k) = lane; waves 0, 1 differentiate s-lines, waves 2, 3 t-lines, each
-// the output pairs (r, 7 - r) for r = 2(h&1) and 2(h&1) + 1.
-__device__ __forceinline__ void dma_pass4(const double* __restrict__ raw,
-                                          const double* __restrict__ eo, double* __restrict__ S,
-                                          double* __restrict__ Tt, int h, int p,
-                                          const Dma7Lane& L, double (&fr)[2], double (&fs)[2],
-                                          double (&ft)[2]) {
-  using Q = Pen<7>;
-  const int j = p & 7, k = p >> 3;
-  double f[8], e[4], o[4];
-#pragma unroll
-  for (int ip = 0; ip < 4; ++ip) {
-    const double2 v = *reinterpret_cast<const double2*>(raw + L.r[ip]);
-    f[2 * ip] = v.x;
-    f[2 * ip + 1] = v.y;
-  }
-  eo_split(f, e, o);
-  eo_pair(eo, h, e, o, fr[0], fr[1]);
-  double g[8], out[4];
-  const int r0 = 2 * (h & 1);
-  // s-line at (i, k) = (j, k) of this lane's index (h < 2), else t-line at
-  // (i, j) = (j, k)
-#pragma unroll
-  for (int m = 0; m < 8; ++m) g[m] = raw[L.g[m]];
-  eo_split(g, e, o);
-  eo_pair(eo, r0, e, o, out[0], out[1]);
-  eo_pair(eo, r0 + 1, e, o, out[2], out[3]);
-  const int idx[4] = {r0, 7 - r0, r0 + 1, 6 - r0};
-  if (h < 2) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) S[Q::at(j, idx[q], k)] = out[q];
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) Tt[Q::at(j, k, idx[q])] = out[q];
-  }
-  lds_barrier();
-  fs[0] = S[Q::at(h, j, k)];
-  fs[1] = S[Q::at(7 - h, j, k)];
-  ft[0] = Tt[Q::at(h, j, k)];
-  ft[1] = Tt[Q::at(7 - h, j, k)];
-  lds_barrier();
-}
-
-// Keep a value materialised here (the compiler may not defer its
-// computation past later barriers, which would keep its inputs live).
-__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
-
-// COUNT: also count every isovalue's triangles and active cells per element
-// from the Q tile (sem_extract); otherwise Q, |omega| and the range only.
-template <bool COUNT>
-__device__ __forceinline__ void qcount_dma7_elem(
-    int64_t e, int t, int64_t n_elem, const double* __restrict__ eo, const double* __restrict__ x,
-    const double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ u,
-    const double* __restrict__ v, const double* __restrict__ w, double* __restrict__ q,
-    double* __restrict__ om, double* __restrict__ qmm, int n_iso, const IsoList<double>& iso,
-    const uint8_t* __restrict__ ntri_tab, int32_t* __restrict__ cnt,
-    int64_t* __restrict__ active, int32_t* __restrict__ status) {
-  __builtin_assume(t >= 0 && t < 256);
-  __builtin_assume(e >= 0);
-  constexpr int NC = 343;
-  __shared__ double s_xyz[3][512];
-  __shared__ double s_uvw[3][512];
-  __shared__ double s_S[Pen<7>::SZ];
-  __shared__ double s_T[Pen<7>::SZ];
-  __shared__ double s_red[8];
-  __shared__ uint32_t s_rows[32];
-  const int h = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int p = t & 63;
-  const int64_t base = e * 512;
-  // the case-table entry is loaded first and stored once every load is in
-  const uint8_t nt_own = COUNT ? ntri_tab[t] : 0;
-  dma_tile4(x + base, s_xyz[0], h, p);
-  dma_tile4(y + base, s_xyz[1], h, p);
-  dma_tile4(z + base, s_xyz[2], h, p);
-  dma_tile4(u + base, s_uvw[0], h, p);
-  dma_tile4(v + base, s_uvw[1], h, p);
-  dma_tile4(w + base, s_uvw[2], h, p);
-  // coordinate tiles (the three velocity loads may stay in flight)
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(3));
-  barrier_after_wait();
-  double xr[2], xs[2], xt[2], yr[2], ys[2], yt[2], zr[2], zs[2], zt[2];
-  const Dma7Lane lane_off = dma7_lane(h, p);
-  dma_pass4(s_xyz[0], eo, s_S, s_T, h, p, lane_off, xr, xs, xt);
-  dma_pass4(s_xyz[1], eo, s_S, s_T, h, p, lane_off, yr, ys, yt);
-  dma_pass4(s_xyz[2], eo, s_S, s_T, h, p, lane_off, zr, zs, zt);
-  // the chain rule runs on the adjugate of J (det J times J^-1); Q takes
-  // the factor 1 / det^2 and |omega| the factor 1 / |det| once per node
-  InvJac<double> kk[2];
-  double inv[2];
-  int bad = 0;
-#pragma unroll
-  for (int ii = 0; ii < 2; ++ii)
-    bad |= !adjugate_jacobian(xr[ii], xs[ii], xt[ii], yr[ii], ys[ii], yt[ii], zr[ii], zs[ii],
-                              zt[ii], kk[ii], inv[ii]);
-#pragma unroll
-  for (int ii = 0; ii < 2; ++ii) {
-    pin(kk[ii].rx); pin(kk[ii].ry); pin(kk[ii].rz); pin(kk[ii].sx); pin(kk[ii].sy);
-    pin(kk[ii].sz); pin(kk[ii].tx); pin(kk[ii].ty); pin(kk[ii].tz); pin(inv[ii]);
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
-  barrier_after_wait();
-  double fr[2], fs[2], ft[2], a01[2], a02[2], a12[2], qv[2], ov[2];
-  dma_pass4(s_uvw[0], eo, s_S, s_T, h, p, lane_off, fr, fs, ft);
-#pragma unroll
-  for (int ii = 0; ii < 2; ++ii) {
-    const InvJac<double>& K = kk[ii];
-    const double a00 = fr[ii] * K.rx + fs[ii] * K.sx + ft[ii] * K.tx;
-    a01[ii] = fr[ii] * K.ry + fs[ii] * K.sy + ft[ii] * K.ty;
-    a02[ii] = fr[ii] * K.rz + fs[ii] * K.sz + ft[ii] * K.tz;
-    qv[ii] = a00 * a00;
-    pin(qv[ii]); pin(a01[ii]); pin(a02[ii]);
-  }
-  dma_pass4(s_uvw[1], eo, s_S, s_T, h, p, lane_off, fr, fs, ft);
-#pragma unroll
-  for (int ii = 0; ii < 2; ++ii) {
-    const InvJac<double>& K = kk[ii];
-    const double a10 = fr[ii] * K.rx + fs[ii] * K.sx + ft[ii] * K.tx;
-    const double a11 = fr[ii] * K.ry + fs[ii] * K.sy + ft[ii] * K.ty;
-    a12[ii] = fr[ii] * K.rz + fs[ii] * K.sz + ft[ii] * K.tz;
-    qv[ii] = qv[ii] + a11 * a11 + 2.0 * (a01[ii] * a10);
-    const double w3 = a10 - a01[ii];
-    ov[ii] = w3 * w3;
-    pin(qv[ii]); pin(ov[ii]); pin(a12[ii]);
-  }
-  dma_pass4(s_uvw[2], eo, s_S, s_T, h, p, lane_off, fr, fs, ft);
-#pragma unroll
-  for (int ii = 0; ii < 2; ++ii) {
-    const InvJac<double>& K = kk[ii];
-    const double a20 = fr[ii] * K.rx + fs[ii] * K.sx + ft[ii] * K.tx;
-    const double a21 = fr[ii] * K.ry + fs[ii] * K.sy + ft[ii] * K.ty;
-    const double a22 = fr[ii] * K.rz + fs[ii] * K.sz + ft[ii] * K.tz;
-    qv[ii] = -0.5 * (qv[ii] + a22 * a22 + 2.0 * (a02[ii] * a20 + a12[ii] * a21)) *
-             (inv[ii] * inv[ii]);
-    const double w1 = a21 - a12[ii], w2 = a02[ii] - a20;
-    ov[ii] = sqrt_refined(ov[ii] + w1 * w1 + w2 * w2) * fabs(inv[ii]);
-  }
-  const int j = p & 7, k = p >> 3;
-  // Q and |omega| go out through LDS tiles (free after the u and v passes):
-  // each lane then stores 16 contiguous bytes, a wave 1 KiB
-  double* QT = s_uvw[0];
-  double* OT = s_uvw[1];
-  double mn = pos_inf<double>(), mx = neg_inf<double>();
-#pragma unroll
-  for (int ii = 0; ii < 2; ++ii) {
-    QT[dma7::at(ii ? 7 - h : h, j, k)] = qv[ii];
-    OT[dma7::at(ii ? 7 - h : h, j, k)] = ov[ii];
-    const double c = qv[ii] != qv[ii] ? neg_inf<double>() : qv[ii];
-    mn = c < mn ? c : mn;
-    mx = c > mx ? c : mx;
-  }
-  wave_minmax(mn, mx);
-  if (p == 63) {
-    s_red[h] = mn;
-    s_red[4 + h] = mx;
-  }
-  // Counting works on isovalues four at a time: a node's word holds bit
-  // (Q > c_s) at bit 8s, so the eight corner words of a cell, each shifted
-  // by its vertex number and summed, give the four cell cases as bytes. The
-  // derivative tiles are free now: S holds the node words, T the case table
-  // as triangles + (1 << 8) per non-trivial case.
-  uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_S);
-  int32_t* s_tab = reinterpret_cast<int32_t*>(s_T);
-  const int node0 = h + 8 * j + 64 * k, node1 = 7 - h + 8 * j + 64 * k;
-  if constexpr (COUNT) {
-    s_tab[t] = case_count_entry8(t, nt_own);
-    s_bits[node0] = iso_bits4(qv[0], iso, 0, n_iso);
-    s_bits[node1] = iso_bits4(qv[1], iso, 0, n_iso);
-  }
-  // an inverted element (rare) is flagged by its own lanes: no block vote
-  if (bad && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
-  __syncthreads();               // publishes the tiles, s_red and the node words
-  {
-    // node pair (2t, 2t + 1) of the natural layout sits in one 16-byte slot
-    const int n = 2 * t;
-    const int sl = 2 * dma7::slot(n >> 6, (n >> 3) & 7, (n & 7) >> 1);
-    if (q) *reinterpret_cast<double2*>(q + base + n) = *reinterpret_cast<const double2*>(QT + sl);
-    if (om)
-      *reinterpret_cast<double2*>(om + base + n) = *reinterpret_cast<const double2*>(OT + sl);
-  }
-  mn = fmin(fmin(s_red[0], s_red[1]), fmin(s_red[2], s_red[3]));
-  mx = fmax(fmax(s_red[4], s_red[5]), fmax(s_red[6], s_red[7]));
-  if (qmm && t == 0) {
-    qmm[2 * e] = mn;
-    qmm[2 * e + 1] = mx;
-  }
-  if constexpr (COUNT) {
-    // cell t, and cell t + 256 for the threads t < 87 (waves 0 and 1 only);
-    // corner 0 of a cell at its natural node index, the others at fixed
-    // offsets from it
-    constexpr int NC2 = NC - 256;
-    const bool two = t < NC2;
-    const int c1 = two ? t + 256 : t;
-    const int cb[2] = {cell_base7(t), cell_base7(c1)};
-    for (int g = 0; g < n_iso; g += 4) {
-      const int m = n_iso - g < 4 ? n_iso - g : 4;
-      if (g > 0) {   // every read of the previous words is behind the last barrier
-        s_bits[node0] = iso_bits4(qv[0], iso, g, n_iso);
-        s_bits[node1] = iso_bits4(qv[1], iso, g, n_iso);
-        __syncthreads();
-      }
-      // an element outside every isovalue's range of the group has only
-      // trivial cases (NaN nodes count as below; mn is -inf then)
-      bool live = false;
-      for (int s = 0; s < m; ++s) live |= (mx > iso.v[g + s]) && !(mn > iso.v[g + s]);
-      // a lane's cells: per isovalue s, triangles + (active << 8) in the
-      // 16-bit half s & 1 of word s >> 1 (publish_rows)
-      uint32_t pw[2] = {0u, 0u};
-      if (live) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          if (r == 1 && h >= 2) break;
-          uint32_t word = 0;
-#pragma unroll
-          for (int vtx = 0; vtx < 8; ++vtx)
-            word += s_bits[cb[r] + (vtx & 1) + 8 * ((vtx >> 1) & 1) + 64 * (vtx >> 2)] << vtx;
-          if (r == 0 || two) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-              if (s < m) pw[s >> 1] += (uint32_t)s_tab[(word >> (8 * s)) & 255] << (16 * (s & 1));
-          }
-        }
-      }
-      publish_rows<4>(pw, m, g, t, s_rows, cnt, n_elem, e, active);
-    }
-  }
-}
-
-template <bool COUNT>
-__global__ void __launch_bounds__(256)
-qcount_dma7(int64_t n_elem, const double* __restrict__ eo, const double* __restrict__ x,
-             const double* __restrict__ y, const double* __restrict__ z,
-             const double* __restrict__ u, const double* __restrict__ v,
-             const double* __restrict__ w, double* __restrict__ q, double* __restrict__ om,
-             double* __restrict__ qmm, int n_iso, IsoList<double> iso,
-             const uint8_t* __restrict__ ntri_tab, int32_t* __restrict__ cnt,
-             int64_t* __restrict__ active, int32_t* __restrict__ status) {
-  qcount_dma7_elem<COUNT>(blockIdx.x, threadIdx.x, n_elem, eo, x, y, z, u, v, w, q, om, qmm,
-                          n_iso, iso, ntri_tab, cnt, active, status);
-}
 
 // Emission for N = 7, FP64: elements with triangles stage their field and
 // coordinate tiles with direct loads and emit through emit_element.
@@ -1948,7 +978,7 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
   const int h = __builtin_amdgcn_readfirstlane(t >> 6);
   const int p = t & 63;
   bool any = false;
-  for (int s = 0; s < n_iso; ++s) any = any || cnt[(int64_t)s * n_elem + e] > 0;
+  for (int s = 0; s < n_iso; ++s) any = any || slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
   if (!any) return;
   const int64_t base = e * NP;
   // the triangle counts (256 B) and the tiles arrive by direct loads before
@@ -1979,7 +1009,7 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
   barrier_after_wait();
   for (int s = 0; s < n_iso; ++s) {
     const int64_t flat = (int64_t)s * n_elem + e;
-    if (cnt[flat] == 0) continue;
+    if (slot_tris(cnt[flat]) == 0) continue;
     int64_t g = offs[flat];
     T* dst = out.ptr[0];
     int64_t cap = out.cap[0];
@@ -2024,7 +1054,6 @@ __device__ __forceinline__ void count_elem(int64_t e, int t, int64_t n_elem,
                                            int n_iso, const IL& iso,
                                            const uint8_t* __restrict__ ntri_tab,
                                            int32_t* __restrict__ cnt,
-                                           int64_t* __restrict__ active_total,
                                            uint8_t* __restrict__ case_idx) {
   constexpr int P = N + 1, NP = P * P * P, NC = N * N * N, R = (NC + 127) / 128;
   __shared__ __attribute__((aligned(16))) T sf[NP];
@@ -2109,11 +1138,7 @@ __device__ __forceinline__ void count_elem(int64_t e, int t, int64_t n_elem,
     if (lane == 63) s_sum[h] = packed;
     __syncthreads();
     if (t == 0) {
-      const int sum = s_sum[0] + s_sum[1];
-      cnt[(int64_t)s * n_elem + e] = sum & 0xffff;
-      const int act = sum >> 16;
-      if (active_total && act)
-        atomicAdd((unsigned long long*)&active_total[s], (unsigned long long)act);
+      cnt[(int64_t)s * n_elem + e] = s_sum[0] + s_sum[1];
     }
     __syncthreads();
   }
@@ -2125,8 +1150,9 @@ count_direct(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ 
              int n_iso, IsoList<T> iso, const uint8_t* __restrict__ ntri_tab,
              int32_t* __restrict__ cnt, int64_t* __restrict__ active_total,
              uint8_t* __restrict__ case_idx) {
+  clear_active(active_total, n_iso);
   count_elem<N, T>(blockIdx.x, threadIdx.x, n_elem, field, mm, n_iso, iso, ntri_tab, cnt,
-                   active_total, case_idx);
+                   case_idx);
 }
 
 // ---------------------------------------------------------------------------
@@ -2315,6 +1341,7 @@ mixed7(const double* __restrict__ dmat, const float* __restrict__ x,
   __shared__ float s_red[8];
   __shared__ int32_t s_tab[COUNT ? 256 : 1];
   __shared__ uint32_t s_rows[COUNT ? 32 : 1];
+  if constexpr (COUNT) clear_active(sink.active, sink.n_iso);
   const int t = threadIdx.x, lane = t & 63;
   __builtin_assume(t >= 0 && t < 256);
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -2452,7 +1479,7 @@ mixed7(const double* __restrict__ dmat, const float* __restrict__ x,
               if (s < m) pw[s >> 1] += (uint32_t)s_tab[(word >> (8 * s)) & 255] << (16 * (s & 1));
           }
         }
-        publish_rows<4>(pw, m, g, t, s_rows, sink.cnt, sink.n_elem, e, sink.active);
+        publish_rows<4>(pw, m, g, t, s_rows, sink.cnt, sink.n_elem, e);
       }
     }
   }
@@ -2573,18 +1600,16 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t x) {
 }
 
 // One instantiation per (order, precision, form), so that no form's register
-// demand limits another's occupancy.  kBatchNodeTile and kBatchDma7 run the
-// per-element bodies of qcrit_tile and qcount_dma7 on one element per work
-// item, kBatchPencil the body of qcrit_pencil on its workgroup's elements.
+// demand limits another's occupancy.  kBatchLines runs the body of
+// qcrit_lines on its workgroup's elements.
 template <int N, typename T, int FORM>
 constexpr int batch_threads() {
-  return FORM == kBatchPencil     ? pencil_threads<N, T>()
-         : FORM == kBatchNodeTile ? Shape<N>::kNodeThreads
-                                  : kBatchThreads;
+  return FORM == kBatchLines ? LineOf<N, T>::TH : kBatchThreads;
 }
 
 template <int N, typename T, int FORM>
-__global__ void __launch_bounds__((batch_threads<N, T, FORM>()))
+__global__ void __launch_bounds__((batch_threads<N, T, FORM>()),
+                                  (FORM == kBatchLines ? line_waves(N, sizeof(T) == 8) : 1))
 qcrit_batch(const BatchHeader* __restrict__ hdr, const BatchSnap* __restrict__ snaps,
             int32_t* __restrict__ status) {
   const int s0 = hdr->snap_begin[N], s1 = hdr->snap_begin[N + 1];
@@ -2597,7 +1622,6 @@ qcrit_batch(const BatchHeader* __restrict__ hdr, const BatchSnap* __restrict__ s
   int64_t begin = 0, next_begin = 0, n_elem = 0;
   int chunk = 1;
   const coef_t<N, T>* dmat = nullptr;
-  const double* eo = nullptr;
   const T *f0 = nullptr, *f1 = nullptr, *f2 = nullptr, *f3 = nullptr, *f4 = nullptr,
           *f5 = nullptr;
   T *oq = nullptr, *oom = nullptr, *oqmm = nullptr;
@@ -2616,7 +1640,6 @@ qcrit_batch(const BatchHeader* __restrict__ hdr, const BatchSnap* __restrict__ s
       n_elem = uniform_i64(sn.n_elem);
       chunk = __builtin_amdgcn_readfirstlane(sn.chunk);
       dmat = uniform_ptr(static_cast<const coef_t<N, T>*>(sn.dmat));
-      eo = uniform_ptr(static_cast<const double*>(sn.eo));
       f0 = uniform_ptr(static_cast<const T*>(sn.f[0]));
       f1 = uniform_ptr(static_cast<const T*>(sn.f[1]));
       f2 = uniform_ptr(static_cast<const T*>(sn.f[2]));
@@ -2639,18 +1662,12 @@ qcrit_batch(const BatchHeader* __restrict__ hdr, const BatchSnap* __restrict__ s
       const int ne = (int)(left < chunk ? left : chunk);
       const T* fp[6] = {f0, f1, f2, f3, f4, f5};
       bad |= batch_chunk<N, T>(dmat, fp, oq, oom, oqmm, e0, ne, tiles, sd);
-    } else if constexpr (FORM == kBatchNodeTile) {
-      qcrit_tile_elem<N, T>(e0, t, dmat, f0, f1, f2, f3, f4, f5, oq, oom, oqmm, status);
-    } else if constexpr (FORM == kBatchPencil) {
-      constexpr int E = pencil_elems<N, T>();   // the item's chunk
+    } else {
+      constexpr int E = LineOf<N, T>::E;   // the item's chunk
       const int64_t left = n_elem - e0;
       const int ne = (int)(left < E ? left : E);
-      qcrit_pencil_elem<N, T, false, E>(e0, t, dmat, f0, f1, f2, f3, f4, f5, oq, oom, oqmm,
-                                        status, nullptr, ne);
-    } else {
-      static_assert(N == 7 && std::is_same<T, double>::value, "direct-to-LDS form: N = 7, FP64");
-      qcount_dma7_elem<false>(e0, t, 0, eo, f0, f1, f2, f3, f4, f5, oq, oom, oqmm, 0,
-                              IsoList<double>{}, nullptr, nullptr, nullptr, status);
+      qcrit_lines_elem<N, T, false>(e0, t, ne, dmat, f0, f1, f2, f3, f4, f5, oq, oom, oqmm,
+                                    status);
     }
     __syncthreads();                   // the next item reuses the LDS
   }
@@ -2738,8 +1755,7 @@ struct JobCursor {
 template <int N, typename T>
 __global__ void __launch_bounds__(128)
 iso_batch_count(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __restrict__ jobs,
-                const uint8_t* __restrict__ ntri_tab, int32_t* __restrict__ cnt,
-                int64_t* __restrict__ active) {
+                const uint8_t* __restrict__ ntri_tab, int32_t* __restrict__ cnt) {
   const int j0 = hdr->job_begin[N], j1 = hdr->job_begin[N + 1];
   const int64_t total = hdr->items[N];
   JobCursor<T> c;
@@ -2748,7 +1764,7 @@ iso_batch_count(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __res
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
     count_elem<N, T>(item - c.begin, t, c.n_elem, c.field, c.mm, c.n_iso, IsoPtr<T>{c.iso},
-                     ntri_tab, cnt + c.slot, active ? active + 4 * c.job : nullptr, nullptr);
+                     ntri_tab, cnt + c.slot, nullptr);
     __syncthreads();                   // the next item reuses the LDS
   }
 }
@@ -2793,10 +1809,20 @@ iso_batch_totals(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __re
   if (idx == 0 && status && offs[hdr->n_slots] > cap) atomicOr(status, SEM_FLAG_TRI_OVERFLOW);
 }
 
-__global__ void __launch_bounds__(256) fill_i64_n(int64_t* __restrict__ p, int64_t n,
-                                                  int64_t value) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = value;
+// Active cells of (job, isovalue) blockIdx.x: its slots' sum (0 past the
+// job's isovalues).
+__global__ void __launch_bounds__(256)
+iso_batch_active(const IsoBatchJob* __restrict__ jobs, const int32_t* __restrict__ cnt,
+                 int64_t* __restrict__ active) {
+  __shared__ int64_t sred[256 / 64];
+  const IsoBatchJob& jb = jobs[blockIdx.x >> 2];
+  const int s = blockIdx.x & 3;
+  int64_t a = 0;
+  if (s < jb.n_iso)
+    for (int64_t e = threadIdx.x; e < jb.n_elem; e += 256)
+      a += slot_active(cnt[jb.slot_begin + s * jb.n_elem + e]);
+  a = block_sum<256>(a, sred);
+  if (threadIdx.x == 0) active[4 * jb.job + s] = a;
 }
 
 // Synthetic unit-cube elements on a 16 x 16 x ... lattice with node
@@ -2824,17 +1850,17 @@ __global__ void tune_fill(int order, int64_t n_elem, T* x, T* y, T* z, T* u, T* 
 // dispatch over the order
 // ---------------------------------------------------------------------------
 
-#define SEM_ORDER_SWITCH(order, BODY) \
+#define SEM_ORDER_SWITCH(order, ...) \
   switch (order) {                    \
-    case 1: { constexpr int N = 1; BODY; } break; \
-    case 2: { constexpr int N = 2; BODY; } break; \
-    case 3: { constexpr int N = 3; BODY; } break; \
-    case 4: { constexpr int N = 4; BODY; } break; \
-    case 5: { constexpr int N = 5; BODY; } break; \
-    case 6: { constexpr int N = 6; BODY; } break; \
-    case 7: { constexpr int N = 7; BODY; } break; \
-    case 8: { constexpr int N = 8; BODY; } break; \
-    case 9: { constexpr int N = 9; BODY; } break; \
+    case 1: { constexpr int N = 1; __VA_ARGS__; } break; \
+    case 2: { constexpr int N = 2; __VA_ARGS__; } break; \
+    case 3: { constexpr int N = 3; __VA_ARGS__; } break; \
+    case 4: { constexpr int N = 4; __VA_ARGS__; } break; \
+    case 5: { constexpr int N = 5; __VA_ARGS__; } break; \
+    case 6: { constexpr int N = 6; __VA_ARGS__; } break; \
+    case 7: { constexpr int N = 7; __VA_ARGS__; } break; \
+    case 8: { constexpr int N = 8; __VA_ARGS__; } break; \
+    case 9: { constexpr int N = 9; __VA_ARGS__; } break; \
     default: return hipErrorInvalidValue;          \
   }
 
@@ -2850,15 +1876,10 @@ hipError_t derivs_t(int order, const DeviceTables& tab, int64_t n_elem, const vo
                     const void* y, const void* z, const void* f, void* gx, void* gy, void* gz,
                     int32_t* status, hipStream_t s) {
   SEM_ORDER_SWITCH(order, {
-    if constexpr (N <= 7) {
-      hipLaunchKernelGGL((derivs_pencil<N, T>), dim3((unsigned)n_elem), dim3(Pen<N>::TH), 0, s, dmat_of<N, T>(tab),
-                         (const T*)x, (const T*)y, (const T*)z, (const T*)f, (T*)gx, (T*)gy,
-                         (T*)gz, status);
-    } else {
-      hipLaunchKernelGGL((derivs_tile<N, T>), dim3((unsigned)n_elem),
-                         dim3(Shape<N>::kNodeThreads), 0, s, dmat_of<N, T>(tab), (const T*)x, (const T*)y,
-                         (const T*)z, (const T*)f, (T*)gx, (T*)gy, (T*)gz, status);
-    }
+    using C = LineOf<N, T>;
+    hipLaunchKernelGGL((derivs_lines<N, T>), dim3((unsigned)((n_elem + C::E - 1) / C::E)),
+                       dim3(C::TH), 0, s, dmat_of<N, T>(tab), (const T*)x, (const T*)y,
+                       (const T*)z, (const T*)f, (T*)gx, (T*)gy, (T*)gz, status, n_elem);
   });
   return hipGetLastError();
 }
@@ -2868,35 +1889,13 @@ hipError_t qcrit_t(int order, const DeviceTables& tab, int64_t n_elem, const voi
                    const void* y, const void* z, const void* u, const void* v, const void* w,
                    void* q, void* om, void* qmm, int32_t* status, hipStream_t s) {
   const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
-  bool done = false;
-  if constexpr (std::is_same<T, double>::value) {
-    if (order == 7) {
-      hipExtLaunchKernelGGL(qcount_dma7<false>, dim3((unsigned)n_elem), dim3(256), 0, s,
-                            pt.start, pt.stop, 0, n_elem, tab.eo7, (const T*)x, (const T*)y,
-                            (const T*)z, (const T*)u, (const T*)v, (const T*)w, (T*)q, (T*)om,
-                            (T*)qmm, 0, IsoList<double>{}, (const uint8_t*)nullptr,
-                            (int32_t*)nullptr, (int64_t*)nullptr, status);
-      done = true;
-    }
-  }
-  if (!done) {
-    SEM_ORDER_SWITCH(order, {
-      // pencil form wherever it is the faster one: every order in FP32,
-      // N <= 7 in FP64 (at N = 8, 9 its FP64 registers spill)
-      if constexpr (N <= 7 || !std::is_same<T, double>::value) {
-        constexpr int E = (pencil_elems<N, T>());
-        hipExtLaunchKernelGGL((qcrit_pencil<N, T>), dim3((unsigned)((n_elem + E - 1) / E)),
-                              dim3(pencil_threads<N, T>()), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
-                              (const T*)x, (const T*)y, (const T*)z, (const T*)u, (const T*)v,
-                              (const T*)w, (T*)q, (T*)om, (T*)qmm, status, n_elem);
-      } else {
-        hipExtLaunchKernelGGL((qcrit_tile<N, T>), dim3((unsigned)n_elem),
-                              dim3(Shape<N>::kNodeThreads), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
-                              (const T*)x, (const T*)y, (const T*)z, (const T*)u, (const T*)v,
-                              (const T*)w, (T*)q, (T*)om, (T*)qmm, status);
-      }
-    });
-  }
+  SEM_ORDER_SWITCH(order, {
+    using C = LineOf<N, T>;
+    hipExtLaunchKernelGGL((qcrit_lines<N, T>), dim3((unsigned)((n_elem + C::E - 1) / C::E)),
+                          dim3(C::TH), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
+                          (const T*)x, (const T*)y, (const T*)z, (const T*)u, (const T*)v,
+                          (const T*)w, (T*)q, (T*)om, (T*)qmm, status, n_elem);
+  });
   phase_done(pt);
   return hipGetLastError();
 }
@@ -2954,39 +1953,48 @@ IsoList<T> make_isolist(int n_iso, const double* iso_host) {
 // Tiles of 1,024 counts up to kScanSmall counts (always folded), else of
 // 4,096 (scan_tile).  `start` and `stop` (may be null) stamp the first and
 // the last kernel.
-template <int ITEMS>
+template <int ITEMS, bool PACKED>
 void scan_kernels_t(const int32_t* cnt, int64_t count, int64_t* partial, int64_t* offs,
-                    hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+                    int64_t* active, int64_t n_elem, hipStream_t s, hipEvent_t start,
+                    hipEvent_t stop) {
   static_assert(kScanThreads * ITEMS == 1024 || kScanThreads * ITEMS == 4096, "scan_tile");
   const int64_t nb = scan_blocks(count);
-  hipExtLaunchKernelGGL(scan_reduce<ITEMS>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, start,
-                        nullptr, 0, cnt, count, partial);
+  hipExtLaunchKernelGGL((scan_reduce<ITEMS, PACKED>), dim3((unsigned)nb), dim3(kScanThreads), 0, s,
+                        start, nullptr, 0, cnt, count, partial, active, n_elem);
   if (nb <= kScanFold) {
-    hipExtLaunchKernelGGL((scan_apply<true, ITEMS>), dim3((unsigned)nb), dim3(kScanThreads), 0,
-                          s, nullptr, stop, 0, cnt, count, (const int64_t*)partial, nb, offs);
+    hipExtLaunchKernelGGL((scan_apply<true, ITEMS, PACKED>), dim3((unsigned)nb),
+                          dim3(kScanThreads), 0, s, nullptr, stop, 0, cnt, count,
+                          (const int64_t*)partial, nb, offs);
   } else {
     hipLaunchKernelGGL(scan_partials, dim3(1), dim3(1024), 0, s, partial, nb);
-    hipExtLaunchKernelGGL((scan_apply<false, ITEMS>), dim3((unsigned)nb), dim3(kScanThreads), 0,
-                          s, nullptr, stop, 0, cnt, count, (const int64_t*)partial, nb, offs);
+    hipExtLaunchKernelGGL((scan_apply<false, ITEMS, PACKED>), dim3((unsigned)nb),
+                          dim3(kScanThreads), 0, s, nullptr, stop, 0, cnt, count,
+                          (const int64_t*)partial, nb, offs);
   }
 }
+// PACKED: count slots (active, if not NULL, receives the n_iso totals of the
+// active cells, n_elem slots each); otherwise plain counts.
+template <bool PACKED>
 void scan_kernels(const int32_t* cnt, int64_t count, int64_t* partial, int64_t* offs,
-                  hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+                  int64_t* active, int64_t n_elem, hipStream_t s, hipEvent_t start,
+                  hipEvent_t stop) {
   if (scan_tile(count) == 1024)
-    scan_kernels_t<1024 / kScanThreads>(cnt, count, partial, offs, s, start, stop);
+    scan_kernels_t<1024 / kScanThreads, PACKED>(cnt, count, partial, offs, active, n_elem, s,
+                                                start, stop);
   else
-    scan_kernels_t<4096 / kScanThreads>(cnt, count, partial, offs, s, start, stop);
+    scan_kernels_t<4096 / kScanThreads, PACKED>(cnt, count, partial, offs, active, n_elem, s,
+                                                start, stop);
 }
 
 template <typename T>
 hipError_t iso_scan_emit(int order, const DeviceTables& tab, int64_t n_elem, const void* x,
                          const void* y, const void* z, const void* field, int n_iso,
                          const IsoList<T>& iso, const IsoOut<T>& out, uint64_t* keys,
-                         int64_t* tri_count, const IsoWorkspace& ws, int32_t* status,
-                         hipStream_t s) {
+                         int64_t* tri_count, int64_t* active, const IsoWorkspace& ws,
+                         int32_t* status, hipStream_t s) {
   const int64_t count = (int64_t)n_iso * n_elem;
   const PhaseTimer ps = phase_timer(SEM_PHASE_SCAN);
-  scan_kernels(ws.cnt, count, ws.partial, ws.offs, s, ps.start, ps.stop);
+  scan_kernels<true>(ws.cnt, count, ws.partial, ws.offs, active, n_elem, s, ps.start, ps.stop);
   phase_done(ps);
   bool any_cap = false;
   for (int q = 0; q < (out.per_iso ? n_iso : 1); ++q) any_cap = any_cap || out.cap[q] > 0;
@@ -3025,7 +2033,6 @@ hipError_t iso_pipeline(int order, const DeviceTables& tab, int64_t n_elem, cons
                         uint8_t* case_idx, const IsoWorkspace& ws, int32_t* status,
                         hipStream_t s) {
   const IsoList<T> iso = make_isolist<T>(n_iso, iso_host);
-  if (active) hipLaunchKernelGGL(fill_i64, dim3(1), dim3(64), 0, s, active, n_iso, (int64_t)0);
   const PhaseTimer pt = phase_timer(SEM_PHASE_COUNT);
   SEM_ORDER_SWITCH(order, {
     if constexpr (N % 2 == 1) {
@@ -3041,7 +2048,7 @@ hipError_t iso_pipeline(int order, const DeviceTables& tab, int64_t n_elem, cons
   });
   phase_done(pt);
   return iso_scan_emit<T>(order, tab, n_elem, x, y, z, field, n_iso, iso, out, keys, tri_count,
-                          ws, status, s);
+                          active, ws, status, s);
 }
 
 template <typename T>
@@ -3074,83 +2081,37 @@ hipError_t extract_t(int order, sem_dtype dt, const DeviceTables& tab, int64_t n
     out.cap[k] = cap[k];
   }
   out.per_iso = 1;
-  const IsoList<T> iso = make_isolist<T>(n_iso, iso_host);
-  if constexpr (std::is_same<T, double>::value) {
-    if (order == 7) {
-      if (active)
-        hipLaunchKernelGGL(fill_i64, dim3(1), dim3(64), 0, s, active, n_iso, (int64_t)0);
-      const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
-      hipExtLaunchKernelGGL(qcount_dma7<true>, dim3((unsigned)n_elem), dim3(256), 0, s,
-                            pt.start, pt.stop, 0, n_elem, tab.eo7, (const T*)x, (const T*)y,
-                            (const T*)z, (const T*)u, (const T*)v, (const T*)w, (T*)q, (T*)om,
-                            (T*)qmm, n_iso, iso, tab.ntri, ws.cnt, active, status);
-      phase_done(pt);
-      return iso_scan_emit<T>(order, tab, n_elem, x, y, z, q, n_iso, iso, out, nullptr,
-                              tri_count, ws, status, s);
-    }
-  }
-  hipError_t err;
-  bool fused = false;
-  if (!is_mixed(dt)) {
-    // pencil forms (sem_qcrit's choice: every order in FP32, N <= 6 in FP64
-    // here) count in the Q kernel
-    CountSink<T> sink;
-    sink.n_iso = n_iso;
-    sink.iso = iso;
-    sink.ntri = tab.ntri;
-    sink.cnt = ws.cnt;
-    sink.active = active;
-    sink.n_elem = n_elem;
-    SEM_ORDER_SWITCH(order, {
-      if constexpr (N <= 7 || !std::is_same<T, double>::value) {
-        if (active)
-          hipLaunchKernelGGL(fill_i64, dim3(1), dim3(64), 0, s, active, n_iso, (int64_t)0);
-        const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
-        constexpr int E = (pencil_elems<N, T>());
-        hipExtLaunchKernelGGL((qcount_pencil<N, T>), dim3((unsigned)((n_elem + E - 1) / E)),
-                              dim3(pencil_threads<N, T>()), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
-                              (const T*)x, (const T*)y,
-                              (const T*)z, (const T*)u, (const T*)v, (const T*)w, (T*)q,
-                              (T*)om, (T*)qmm, status, sink);
-        phase_done(pt);
-        fused = true;
-      }
-    });
-  }
-  if (fused) {
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    return iso_scan_emit<T>(order, tab, n_elem, x, y, z, q, n_iso, iso, out, nullptr,
-                            tri_count, ws, status, s);
-  }
-  if (is_mixed(dt)) {
-    if constexpr (std::is_same<T, float>::value) {
-      if (active)
-        hipLaunchKernelGGL(fill_i64, dim3(1), dim3(64), 0, s, active, n_iso, (int64_t)0);
-      CountSink<float> sink;
-      sink.n_iso = n_iso;
-      sink.iso = iso;
-      sink.ntri = tab.ntri;
-      sink.cnt = ws.cnt;
-      sink.active = active;
-      sink.n_elem = n_elem;
-      const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
+  CountSink<T> sink;
+  sink.n_iso = n_iso;
+  sink.iso = make_isolist<T>(n_iso, iso_host);
+  sink.ntri = tab.ntri;
+  sink.cnt = ws.cnt;
+  sink.active = active;
+  sink.n_elem = n_elem;
+  const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
+  hipError_t err = hipSuccess;
+  bool done = false;
+  if constexpr (std::is_same<T, float>::value) {
+    if (is_mixed(dt)) {
       err = mixed_t<true>(dt, tab, n_elem, x, y, z, u, v, w, q, om, nullptr, qmm, status, s, pt,
                           &sink);
-      phase_done(pt);
-      if (err != hipSuccess) return err;
-      return iso_scan_emit<T>(order, tab, n_elem, x, y, z, q, n_iso, iso, out, nullptr,
-                              tri_count, ws, status, s);
+      done = true;
     }
-    const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
-    err = mixed_t<true>(dt, tab, n_elem, x, y, z, u, v, w, q, om, nullptr, qmm, status, s, pt);
-    phase_done(pt);
-  } else {
-    err = qcrit_t<T>(order, tab, n_elem, x, y, z, u, v, w, q, om, qmm, status, s);
   }
+  if (!done) {
+    SEM_ORDER_SWITCH(order, {
+      using C = LineOf<N, T>;
+      hipExtLaunchKernelGGL((qcount_lines<N, T>), dim3((unsigned)((n_elem + C::E - 1) / C::E)),
+                            dim3(C::TH), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
+                            (const T*)x, (const T*)y, (const T*)z, (const T*)u, (const T*)v,
+                            (const T*)w, (T*)q, (T*)om, (T*)qmm, status, sink);
+    });
+  }
+  phase_done(pt);
+  if (err == hipSuccess) err = hipGetLastError();
   if (err != hipSuccess) return err;
-  return iso_pipeline<T>(order, tab, n_elem, x, y, z, q, qmm, n_iso, iso_host, out, nullptr,
-                         tri_count, active, nullptr, ws, status, s);
+  return iso_scan_emit<T>(order, tab, n_elem, x, y, z, q, n_iso, sink.iso, out, nullptr, tri_count,
+                          active, ws, status, s);
 }
 
 }  // namespace
@@ -3163,25 +2124,22 @@ size_t batch_plan_bytes(int n_snap) {
 
 int batch_variant_chunk(int order, sem_dtype dt, int variant) {
   if (variant < 3) return 1 << variant;
-  return batch_variant_form(variant) == kBatchPencil ? pencil_elems_of(order, dt == SEM_F64) : 1;
+  return batch_variant_form(variant) == kBatchLines ? line_cfg(order, dt == SEM_F64, 0) : 1;
 }
 
 int batch_variant_form(int variant) {
-  static const int form[kBatchVariants] = {kBatchChunk, kBatchChunk, kBatchChunk, kBatchPencil,
-                                           kBatchDma7, kBatchNodeTile};
+  static const int form[kBatchVariants] = {kBatchChunk, kBatchChunk, kBatchChunk, kBatchLines,
+                                           kBatchLines, kBatchLines};
   return form[variant];
 }
 
 bool batch_variant_ok(int order, sem_dtype dt, int variant) {
   if (variant < 0 || variant >= kBatchVariants) return false;
   if (order < 1 || order > kMaxOrder) return false;
+  if (variant == 4 && (order != 7 || dt != SEM_F64)) return false;
   const int p3 = (order + 1) * (order + 1) * (order + 1);
-  switch (batch_variant_form(variant)) {
-    case kBatchChunk: return batch_variant_chunk(order, dt, variant) * p3 <= kBatchTile / 6;
-    case kBatchPencil: return true;
-    case kBatchNodeTile: return true;
-    default: return order == 7 && dt == SEM_F64;
-  }
+  return batch_variant_form(variant) != kBatchChunk ||
+         batch_variant_chunk(order, dt, variant) * p3 <= kBatchTile / 6;
 }
 
 // untuned: the form sem_qcrit itself uses for this order and precision
@@ -3192,23 +2150,14 @@ int batch_default_variant(int order, sem_dtype dt) {
 
 template <int N, typename T>
 const void* batch_kernel_nt(int form) {
-  if (form == kBatchPencil)
-    return reinterpret_cast<const void*>(&qcrit_batch<N, T, kBatchPencil>);
-  if constexpr (N == 7 && std::is_same<T, double>::value) {
-    if (form == kBatchDma7)
-      return reinterpret_cast<const void*>(&qcrit_batch<7, double, kBatchDma7>);
-  }
-  if (form == kBatchNodeTile)
-    return reinterpret_cast<const void*>(&qcrit_batch<N, T, kBatchNodeTile>);
+  if (form == kBatchLines)
+    return reinterpret_cast<const void*>(&qcrit_batch<N, T, kBatchLines>);
   return form == kBatchChunk ? reinterpret_cast<const void*>(&qcrit_batch<N, T, kBatchChunk>)
                              : nullptr;
 }
 
 int batch_threads_of(int n, bool f64, int form) {
-  if (form == kBatchPencil)
-    return 128 * ((pencil_elems_of(n, f64) * (n + 1) * (n + 1) + 63) / 64);
-  if (form == kBatchNodeTile) return (((n + 1) * (n + 1) * (n + 1) + 63) / 64) * 64;
-  return kBatchThreads;
+  return form == kBatchLines ? line_cfg(n, f64, 1) : kBatchThreads;
 }
 
 template <int N>
@@ -3283,7 +2232,7 @@ namespace {
 template <int N>
 hipError_t iso_batch_phase(bool f64, bool emit, const IsoBatchHeader* hdr,
                            const IsoBatchJob* jobs, const DeviceTables& tab,
-                           const IsoWorkspace& ws, int64_t* active, void* tri, int64_t cap,
+                           const IsoWorkspace& ws, void* tri, int64_t cap,
                            hipStream_t s, hipEvent_t a, hipEvent_t b) {
   const void* fn;
   if (emit)
@@ -3295,7 +2244,7 @@ hipError_t iso_batch_phase(bool f64, bool emit, const IsoBatchHeader* hdr,
   const uint8_t* ntri = tab.ntri;
   int32_t* cnt = ws.cnt;
   int64_t* offs = ws.offs;
-  void* count_args[] = {&hdr, &jobs, &ntri, &cnt, &active};
+  void* count_args[] = {&hdr, &jobs, &ntri, &cnt};
   void* emit_args[] = {&hdr, &jobs, &ntri, &cnt, &offs, &tri, &cap};
   // Four times the workgroups the CUs hold at once: the cost of an element
   // varies with its triangles, and with a grid of exactly the resident
@@ -3317,9 +2266,6 @@ hipError_t launch_iso_batch(sem_dtype dt, const DeviceTables& tab, const void* p
   const IsoBatchJob* jobs =
       reinterpret_cast<const IsoBatchJob*>(static_cast<const char*>(plan) + 256);
   const bool f64 = dt == SEM_F64;
-  if (active && n_job > 0)
-    hipLaunchKernelGGL(fill_i64_n, dim3((unsigned)((4 * (int64_t)n_job + 255) / 256)), dim3(256),
-                       0, s, active, 4 * (int64_t)n_job, (int64_t)0);
   int first = -1, last = -1;
   for (int n = 1; n <= kMaxOrder; ++n)
     if (launch_code >> n & 1u) {
@@ -3333,15 +2279,15 @@ hipError_t launch_iso_batch(sem_dtype dt, const DeviceTables& tab, const void* p
       hipEvent_t a = n == first ? pt.start : nullptr, b = n == last ? pt.stop : nullptr;
       hipError_t err = hipSuccess;
       switch (n) {
-        case 1: err = iso_batch_phase<1>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 2: err = iso_batch_phase<2>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 3: err = iso_batch_phase<3>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 4: err = iso_batch_phase<4>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 5: err = iso_batch_phase<5>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 6: err = iso_batch_phase<6>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 7: err = iso_batch_phase<7>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 8: err = iso_batch_phase<8>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
-        case 9: err = iso_batch_phase<9>(f64, pass, hdr, jobs, tab, ws, active, tri, cap, s, a, b); break;
+        case 1: err = iso_batch_phase<1>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 2: err = iso_batch_phase<2>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 3: err = iso_batch_phase<3>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 4: err = iso_batch_phase<4>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 5: err = iso_batch_phase<5>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 6: err = iso_batch_phase<6>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 7: err = iso_batch_phase<7>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 8: err = iso_batch_phase<8>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
+        case 9: err = iso_batch_phase<9>(f64, pass, hdr, jobs, tab, ws, tri, cap, s, a, b); break;
         default: err = hipErrorInvalidValue;
       }
       if (err != hipSuccess) return err;
@@ -3351,12 +2297,15 @@ hipError_t launch_iso_batch(sem_dtype dt, const DeviceTables& tab, const void* p
       // one exclusive scan over every count slot, then the per-(job,
       // isovalue) totals
       const PhaseTimer ps = phase_timer(SEM_PHASE_SCAN);
-      scan_kernels(ws.cnt, n_slots, ws.partial, ws.offs, s, ps.start, nullptr);
+      scan_kernels<true>(ws.cnt, n_slots, ws.partial, ws.offs, nullptr, 1, s, ps.start, nullptr);
       const unsigned tb = (unsigned)((4 * (int64_t)n_job + 255) / 256);
       hipExtLaunchKernelGGL(iso_batch_totals, dim3(tb > 0 ? tb : 1), dim3(256), 0, s, nullptr,
                             ps.stop, 0, hdr, jobs, (const int64_t*)ws.offs, tri_offset,
                             tri_count, cap, status);
       phase_done(ps);
+      if (active)
+        hipLaunchKernelGGL(iso_batch_active, dim3(4 * (unsigned)n_job), dim3(256), 0, s, jobs,
+                           (const int32_t*)ws.cnt, active);
       if (cap <= 0) break;
     }
   }
@@ -3380,7 +2329,7 @@ hipError_t launch_tune_fill(sem_dtype dt, int order, int64_t n_elem, void* const
 
 hipError_t launch_exclusive_scan(const int32_t* cnt, int64_t count, int64_t* partial,
                                  int64_t* offs, hipStream_t s) {
-  scan_kernels(cnt, count, partial, offs, s, nullptr, nullptr);
+  scan_kernels<false>(cnt, count, partial, offs, nullptr, 1, s, nullptr, nullptr);
   return hipGetLastError();
 }
 

@@ -1,0 +1,499 @@
+// Line-exchange kernels for Q, the counts and the gradient (part of
+// sem_kernels.hip; every order, FP64 and FP32).
+//
+// A workgroup of TH threads takes E elements (P = N + 1).  Every thread plays
+// two roles: it owns the nodes t, t + TH, ... of the block, consecutive in
+// memory, so that loads and stores touch whole cache lines; and it
+// differentiates lines t, t + TH, ... of the 3 P^2 lines per element (r-, s-
+// and t-lines together).  LDS holds every line's P values side by side: an
+// owner writes its node's value to the three lines through the node, the
+// line's thread replaces the values by their derivative in place (even-odd
+// form, all outputs of a line), the owner reads its three derivatives back.
+// A location belongs to one owner and one line thread, so a pass takes two
+// barriers, and an owner writes the next field's value where it has just
+// read.
+//
+// Bound: HBM (8 values per node for Q), with the vector ALU close behind:
+// some 24 multiply-adds per node and field in the even-odd form, as many
+// instructions again for the chain rule and the exchange.  The forms this
+// replaced were bound by what they did beside that: a register pencil of two
+// halves per element left 28 of 128 lanes idle at N = 9, held five nodes'
+// geometry per thread (187 registers, two waves per SIMD) and applied D along
+// r in the plain form; the node-per-thread tile of FP64 N = 8, 9 read D and
+// three lines from LDS per node (LDS bound).
+template <int N, int E_, int TH_, int PI_, int NF_>
+struct LineCfg {
+  static constexpr int P = N + 1, NP = P * P * P, LN = 3 * P * P;
+  static constexpr int E = E_, TH = TH_;
+  static constexpr int PI = PI_;                           // LDS pitch of a line
+  static constexpr int NF = NF_;                           // fields per pass, 1 or 3
+  static constexpr int NL = E * LN, NN = E * NP;
+  static constexpr int R = (NN + TH - 1) / TH;             // nodes per thread
+  static constexpr int SZ = NL * PI;                       // LDS values of a field
+  static constexpr int NW = TH / 64;
+  static_assert(TH % 64 == 0 && TH <= 1024 && PI >= P, "whole waves, whole lines");
+  // Every thread owns a node in round r whatever the number of elements (the
+  // last workgroup may have fewer than E).
+  static constexpr bool full(int r) { return (r + 1) * TH <= NP; }
+};
+
+// Workgroup shapes {elements, threads, pitch, fields per pass}, from a sweep
+// of Q alone (16,384 to 2^21 elements).  Two rules came out of it.  Threads:
+// so many that two owner rounds (three at N = 8) nearly fill, whatever the
+// lines do (line rounds leave whole waves idle, which cost nothing, while a
+// third or fourth round costs registers): FP64 N = 9 took 27.6 ps per point
+// with 384 threads and 18.0 with 512, N = 8 22.8 with 384 and 15.9 with 256;
+// small elements keep one or two waves (a barrier of one wave is free).
+// Pitch: the one that spreads a wave's lines over the banks (odd, or 4 or 20
+// modulo 64 words for wide accesses): FP32 N = 7 10.4 with 8 and 7.0 with 9.
+// Three fields per pass halve the barriers where LDS allows it without losing
+// a wave (FP64 N = 4 17.6 against 14.1), one where it does not (FP64 N = 8
+// 16.5 against 17.9).  ps per point, this form against the fastest of the
+// replaced ones, on one box: FP32 N = 1..9 12.2 / 9.8 / 7.2 / 8.1 / 8.5 / 8.1
+// / 7.3 / 7.9 / 13.1 against 12.3 / 10.3 / 7.5 / 9.5 / 10.9 / 13.9 / 9.3 /
+// 13.9 / 21.6; FP64 18.0 / 14.8 / 13.1 / 14.1 / 14.9 / 15.2 / 14.3 / 16.5 /
+// 17.8 against 18.2 / 21.7 / 13.6 / 22.9 / 22.4 / 27.8 / 15.1 / 42.1 / 39.4
+// (6.4 and 12.8 are the bytes at 5 TB/s; N = 7 FP64 had a form of its own,
+// four waves on swizzled tiles fetched by direct loads: Q with the counts of
+// the 65,536-element snapshot 0.55 ms, here 0.44 with the packed slots).
+constexpr int kLineCfg64[kMaxOrder + 1][4] = {
+    {0, 0, 0, 0},   {32, 256, 2, 3}, {9, 256, 3, 3},  {1, 64, 6, 3},  {1, 128, 5, 3},
+    {1, 256, 6, 3}, {1, 128, 7, 3},  {1, 256, 10, 1}, {1, 256, 9, 1}, {1, 512, 10, 1}};
+constexpr int kLineCfg32[kMaxOrder + 1][4] = {
+    {0, 0, 0, 0},  {16, 128, 3, 3}, {9, 256, 3, 3}, {1, 64, 4, 3},  {2, 128, 5, 3},
+    {1, 64, 7, 1}, {1, 128, 7, 3},  {1, 256, 9, 3}, {1, 256, 9, 3}, {1, 512, 10, 1}};
+constexpr int line_cfg(int n, bool f64, int k) {
+  return f64 ? kLineCfg64[n][k] : kLineCfg32[n][k];
+}
+template <int N, typename T>
+using LineOf = LineCfg<N, line_cfg(N, sizeof(T) == 8, 0), line_cfg(N, sizeof(T) == 8, 1),
+                       line_cfg(N, sizeof(T) == 8, 2), line_cfg(N, sizeof(T) == 8, 3)>;
+
+// Waves per SIMD to hold (launch bound): FP64 N = 6..9 sit a few registers
+// around the limits of three and four waves; elsewhere the compiler's choice.
+constexpr int line_waves(int n, bool f64) {
+  return !f64 || n < 6 ? 1 : (n == 6 || n == 8) ? 3 : 4;
+}
+
+// Offsets of an owner's nodes in their three lines.
+template <class C>
+struct LineOwner {
+  int a[C::R][3];
+  __device__ __forceinline__ explicit LineOwner(int t) {
+    constexpr int P = C::P;
+#pragma unroll
+    for (int r = 0; r < C::R; ++r) {
+      const int o = t + r * C::TH;
+      const int el = C::E == 1 ? 0 : o / C::NP, n = o - el * C::NP;
+      const int i = n % P, j = (n / P) % P, k = n / (P * P);
+      const int base = el * C::LN;
+      a[r][0] = (base + j + P * k) * C::PI + i;
+      a[r][1] = (base + P * P + i + P * k) * C::PI + j;
+      a[r][2] = (base + 2 * P * P + i + P * j) * C::PI + k;
+    }
+  }
+};
+
+// F fields through the exchange: values at the owner's nodes in f, reference
+// derivatives (r, s, t) there in g.  nn nodes and nl lines exist.
+template <int N, class C, int F, typename T>
+__device__ __forceinline__ void line_pass(const T (*f)[C::R], const LineOwner<C>& own,
+                                          const coef_t<N, T>* __restrict__ d, T* tile, int t,
+                                          int nn, int nl, T (*g)[C::R][3]) {
+  constexpr int P = C::P, TASKS = F * C::NL;
+#pragma unroll
+  for (int c = 0; c < F; ++c)
+#pragma unroll
+    for (int r = 0; r < C::R; ++r)
+      if (C::full(r) || t + r * C::TH < nn) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) tile[c * C::SZ + own.a[r][x]] = f[c][r];
+      }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < (TASKS + C::TH - 1) / C::TH; ++q) {
+    const int task = t + q * C::TH;
+    bool live = (q + 1) * C::TH <= TASKS || task < TASKS;
+    if constexpr (C::E > 1) live = live && (F == 1 ? task : task % C::NL) < nl;
+    if (live) {
+      T* line = tile + task * C::PI;
+      T v[P], out[P];
+#pragma unroll
+      for (int m = 0; m < P; ++m) v[m] = line[m];
+      line_deriv_all<P>(d, v, out);
+#pragma unroll
+      for (int m = 0; m < P; ++m) line[m] = out[m];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < F; ++c)
+#pragma unroll
+    for (int r = 0; r < C::R; ++r)
+      if (C::full(r) || t + r * C::TH < nn) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) g[c][r][x] = tile[c * C::SZ + own.a[r][x]];
+      }
+}
+
+// Three fields, C::NF at a time.
+template <int N, class C, typename T>
+__device__ __forceinline__ void line_pass3(const T (&f)[3][C::R], const LineOwner<C>& own,
+                                           const coef_t<N, T>* __restrict__ d, T* tile, int t,
+                                           int nn, int nl, T (&g)[3][C::R][3]) {
+#pragma unroll
+  for (int c = 0; c < 3; c += C::NF)
+    line_pass<N, C, C::NF>(f + c, own, d, tile, t, nn, nl, g + c);
+}
+
+template <class C, typename T>
+__device__ __forceinline__ void line_load(const T* __restrict__ src, int t, int nn,
+                                          T (&f)[C::R]) {
+#pragma unroll
+  for (int r = 0; r < C::R; ++r)
+    if (C::full(r) || t + r * C::TH < nn) f[r] = src[t + r * C::TH];
+}
+
+// 1 / det J: FP32 the hardware reciprocal (1 ulp), FP64 the refined one.
+__device__ __forceinline__ float line_recip(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double line_recip(double x) { return recip_refined(x); }
+
+// J^-1 at the owner's nodes from the coordinates; false if det J is not
+// positive at one of them.
+template <int N, class C, typename T>
+__device__ __forceinline__ bool line_geometry(const T (&f)[3][C::R], const LineOwner<C>& own,
+                                              const coef_t<N, T>* __restrict__ d, T* tile, int t,
+                                              int nn, int nl, InvJac<T> (&kk)[C::R]) {
+  T g[3][C::R][3];
+  line_pass3<N, C>(f, own, d, tile, t, nn, nl, g);
+  bool ok = true;
+#pragma unroll
+  for (int r = 0; r < C::R; ++r) {
+    InvJac<T>& K = kk[r];
+    const T xr = g[0][r][0], xs = g[0][r][1], xt = g[0][r][2];
+    const T yr = g[1][r][0], ys = g[1][r][1], yt = g[1][r][2];
+    const T zr = g[2][r][0], zs = g[2][r][1], zt = g[2][r][2];
+    const T c0 = ys * zt - yt * zs, c1 = yt * zr - yr * zt, c2 = yr * zs - ys * zr;
+    const T det = xr * c0 + xs * c1 + xt * c2;
+    const T inv = line_recip(det);
+    K.rx = c0 * inv;
+    K.ry = (xt * zs - xs * zt) * inv;
+    K.rz = (xs * yt - xt * ys) * inv;
+    K.sx = c1 * inv;
+    K.sy = (xr * zt - xt * zr) * inv;
+    K.sz = (xt * yr - xr * yt) * inv;
+    K.tx = c2 * inv;
+    K.ty = (xs * zr - xr * zs) * inv;
+    K.tz = (xr * ys - xs * yr) * inv;
+    if (C::full(r) || t + r * C::TH < nn) ok = ok && det > T(0);
+  }
+  return ok;
+}
+
+// ---------------------------------------------------------------------------
+// counting from node values held by their owners
+// ---------------------------------------------------------------------------
+//
+// The bits (value > c) of 64 consecutive nodes are one ballot; the ballots of
+// a block's nodes, written to LDS in node order, are a bit string in which a
+// row of P nodes is P consecutive bits.  A wave takes one (isovalue, element)
+// and a lane a row of N cells: the four rows of bits around it give by bit
+// operations the cells whose corners differ, and only those (a few per cent)
+// look their case up.  Against a word per node holding four isovalues' bits
+// and eight reads per cell whatever its case, the counts cost about half the
+// instructions.
+
+constexpr int kBitGroup = 4;     // isovalues per round
+template <class C>
+struct LineBits {
+  static constexpr int W = (C::NN + 63) / 64;      // ballots per isovalue
+  uint64_t bits[kBitGroup][W + 1];                 // one word past the last row's
+};
+
+// P bits from bit b on.
+__device__ __forceinline__ uint32_t bit_row(const uint32_t* bits, int b) {
+  const uint32_t* w = bits + (b >> 5);
+  return __builtin_amdgcn_alignbit(w[1], w[0], b & 31);
+}
+
+// Triangles + (active cells << 16) of one element at one isovalue, summed
+// over the wave into lane 63; bits: the isovalue's bit string, bit0: the
+// element's first node.  dump: the element's cells' cases (optional).
+template <int N>
+__device__ __forceinline__ uint32_t count_rows(const uint32_t* bits, int bit0, int lane,
+                                               const uint8_t* tab, uint8_t* dump = nullptr) {
+  constexpr int P = N + 1;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int q = 0; q < (N * N + 63) / 64; ++q) {
+    const int row = lane + 64 * q;
+    if (row < N * N) {
+      const int j = row % N, k = row / N;
+      const int b = bit0 + (j + P * k) * P;
+      const uint32_t r0 = bit_row(bits, b), r1 = bit_row(bits, b + P);
+      const uint32_t r2 = bit_row(bits, b + P * P), r3 = bit_row(bits, b + P * P + P);
+      uint32_t any = r0 | r1 | r2 | r3, all = r0 & r1 & r2 & r3;
+      any |= any >> 1;
+      all &= all >> 1;
+      uint32_t act = any & ~all & ((1u << N) - 1);
+      sum += (uint32_t)__builtin_popcount(act) << 16;
+      if (dump) {
+        for (int i = 0; i < N; ++i)
+          dump[row * N + i] = (uint8_t)(((r0 >> i) & 3) | (((r1 >> i) & 3) << 2) |
+                                        (((r2 >> i) & 3) << 4) | (((r3 >> i) & 3) << 6));
+      }
+      while (act) {
+        const int i = __builtin_ctz(act);
+        act &= act - 1;
+        sum += tab[((r0 >> i) & 3) | (((r1 >> i) & 3) << 2) | (((r2 >> i) & 3) << 4) |
+                   (((r3 >> i) & 3) << 6)];
+      }
+    }
+  }
+  return wave_sum_to63(sum);
+}
+
+// Counts of the block's elements e .. e + ne - 1 at every isovalue from the
+// owners' values qv (NaN as -inf, or NaN: both compare below).  tab: the 256
+// triangle counts in LDS, published by the caller or by the first barrier.
+template <int N, class C, typename T>
+__device__ __forceinline__ void line_count(const T (&qv)[C::R], int64_t e, int t, int ne, int nn,
+                                           const CountSink<T>& sink, LineBits<C>& sb,
+                                           const uint8_t* tab) {
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  for (int g = 0; g < sink.n_iso; g += kBitGroup) {
+    const int m = sink.n_iso - g < kBitGroup ? sink.n_iso - g : kBitGroup;
+    if (g > 0) __syncthreads();   // every wave is done with the previous bits
+#pragma unroll
+    for (int s = 0; s < kBitGroup; ++s) {
+      if (s < m) {
+        const T c = sink.iso.v[g + s];
+#pragma unroll
+        for (int r = 0; r < C::R; ++r) {
+          const uint64_t b = __ballot((C::full(r) || t + r * C::TH < nn) && qv[r] > c);
+          const int w = wave + r * C::NW;
+          if (lane == 0 && w < LineBits<C>::W) sb.bits[s][w] = b;
+        }
+      }
+    }
+    __syncthreads();
+    for (int p = wave; p < m * ne; p += C::NW) {
+      const int s = C::E == 1 ? p : p / ne, el = C::E == 1 ? 0 : p - s * ne;
+      const uint32_t sum = count_rows<N>(reinterpret_cast<const uint32_t*>(sb.bits[s]),
+                                         el * C::NP, lane, tab);
+      if (lane == 63) sink.cnt[(int64_t)(g + s) * sink.n_elem + e + el] = (int)sum;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Q, |omega|, ranges and counts
+// ---------------------------------------------------------------------------
+
+template <int N, typename T, bool COUNT>
+__device__ __forceinline__ void qcrit_lines_elem(
+    int64_t e, int t, int ne, const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
+    const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
+    const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q, T* __restrict__ om,
+    T* __restrict__ qmm, int32_t* __restrict__ status, const CountSink<T>* sink = nullptr) {
+  using C = LineOf<N, T>;
+  constexpr int NP = C::NP, R = C::R, NW = C::NW;
+  __shared__ __align__(16) T tile[C::NF * C::SZ];
+  __shared__ T red[2 * NW];
+  __shared__ uint32_t s_tab[COUNT ? 64 : 1];
+  const int64_t base = e * NP;
+  const int nn = C::E == 1 ? C::NN : ne * NP, nl = C::E == 1 ? C::NL : ne * C::LN;
+  const LineOwner<C> own(t);
+  T fx[3][R], fu[3][R];
+  line_load<C>(x + base, t, nn, fx[0]);
+  line_load<C>(y + base, t, nn, fx[1]);
+  line_load<C>(z + base, t, nn, fx[2]);
+  line_load<C>(u + base, t, nn, fu[0]);
+  line_load<C>(v + base, t, nn, fu[1]);
+  line_load<C>(w + base, t, nn, fu[2]);
+  uint32_t tab4 = 0;
+  if (COUNT && t < 64) tab4 = reinterpret_cast<const uint32_t*>(sink->ntri)[t];
+  InvJac<T> kk[R];
+  const bool ok = line_geometry<N, C>(fx, own, dmat, tile, t, nn, nl, kk);
+  T qv[R], ov[R];
+  if constexpr (C::NF == 3) {
+    T g[3][R][3];
+    line_pass3<N, C>(fu, own, dmat, tile, t, nn, nl, g);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const InvJac<T>& K = kk[r];
+      T a[3][3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        a[c][0] = g[c][r][0] * K.rx + g[c][r][1] * K.sx + g[c][r][2] * K.tx;
+        a[c][1] = g[c][r][0] * K.ry + g[c][r][1] * K.sy + g[c][r][2] * K.ty;
+        a[c][2] = g[c][r][0] * K.rz + g[c][r][1] * K.sz + g[c][r][2] * K.tz;
+      }
+      qv[r] = T(-0.5) * (a[0][0] * a[0][0] + a[1][1] * a[1][1] + T(2) * (a[0][1] * a[1][0]) +
+                         a[2][2] * a[2][2] + T(2) * (a[0][2] * a[2][0] + a[1][2] * a[2][1]));
+      const T w1 = a[2][1] - a[1][2], w2 = a[0][2] - a[2][0], w3 = a[1][0] - a[0][1];
+      ov[r] = vort_root(w3 * w3 + w1 * w1 + w2 * w2);
+    }
+  } else {
+    // rows of the velocity gradient folded into Q and |omega|^2 as they come
+    T a01[R], a02[R], a12[R], g[1][R][3];
+    line_pass<N, C, 1>(fu, own, dmat, tile, t, nn, nl, g);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const InvJac<T>& K = kk[r];
+      const T fr = g[0][r][0], fs = g[0][r][1], ft = g[0][r][2];
+      const T a00 = fr * K.rx + fs * K.sx + ft * K.tx;
+      a01[r] = fr * K.ry + fs * K.sy + ft * K.ty;
+      a02[r] = fr * K.rz + fs * K.sz + ft * K.tz;
+      qv[r] = a00 * a00;
+    }
+    line_pass<N, C, 1>(fu + 1, own, dmat, tile, t, nn, nl, g);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const InvJac<T>& K = kk[r];
+      const T fr = g[0][r][0], fs = g[0][r][1], ft = g[0][r][2];
+      const T a10 = fr * K.rx + fs * K.sx + ft * K.tx;
+      const T a11 = fr * K.ry + fs * K.sy + ft * K.ty;
+      a12[r] = fr * K.rz + fs * K.sz + ft * K.tz;
+      qv[r] = qv[r] + a11 * a11 + T(2) * (a01[r] * a10);
+      const T w3 = a10 - a01[r];
+      ov[r] = w3 * w3;
+    }
+    line_pass<N, C, 1>(fu + 2, own, dmat, tile, t, nn, nl, g);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const InvJac<T>& K = kk[r];
+      const T fr = g[0][r][0], fs = g[0][r][1], ft = g[0][r][2];
+      const T a20 = fr * K.rx + fs * K.sx + ft * K.tx;
+      const T a21 = fr * K.ry + fs * K.sy + ft * K.ty;
+      const T a22 = fr * K.rz + fs * K.sz + ft * K.tz;
+      qv[r] = T(-0.5) * (qv[r] + a22 * a22 + T(2) * (a02[r] * a20 + a12[r] * a21));
+      const T w1 = a21 - a12[r], w2 = a02[r] - a20;
+      ov[r] = vort_root(ov[r] + w1 * w1 + w2 * w2);
+    }
+  }
+  T mn = pos_inf<T>(), mx = neg_inf<T>();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (C::full(r) || t + r * C::TH < nn) {
+      const int64_t o = base + t + r * C::TH;
+      if (q) q[o] = qv[r];
+      if (om) om[o] = ov[r];
+      qv[r] = qv[r] != qv[r] ? neg_inf<T>() : qv[r];
+      mn = qv[r] < mn ? qv[r] : mn;
+      mx = qv[r] > mx ? qv[r] : mx;
+    }
+  }
+  // an inverted element (rare) is flagged by its own lanes: no block vote
+  if (!ok && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
+  if (COUNT && t < 64) s_tab[t] = tab4;
+  if constexpr (C::E == 1) {
+    wave_minmax(mn, mx);
+    if ((t & 63) == 63) {
+      red[t >> 6] = mn;
+      red[NW + (t >> 6)] = mx;
+    }
+    __syncthreads();
+    if (qmm && t == 0) {
+      mn = red[0];
+      mx = red[NW];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) {
+        mn = fmin(mn, red[i]);
+        mx = fmax(mx, red[NW + i]);
+      }
+      qmm[2 * e] = mn;
+      qmm[2 * e + 1] = mx;
+    }
+  } else {
+    // ranges: the values through LDS, a wave per element
+    __syncthreads();   // every derivative of the last pass is read
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (C::full(r) || t + r * C::TH < nn) tile[t + r * C::TH] = qv[r];
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    for (int el = wave; qmm && el < ne; el += NW) {
+      T a = pos_inf<T>(), b = neg_inf<T>();
+      for (int n = lane; n < NP; n += 64) {
+        const T c = tile[el * NP + n];
+        a = c < a ? c : a;
+        b = c > b ? c : b;
+      }
+      wave_minmax(a, b);
+      if (lane == 63) {
+        qmm[2 * (e + el)] = a;
+        qmm[2 * (e + el) + 1] = b;
+      }
+    }
+  }
+  if constexpr (COUNT) {
+    clear_active(sink->active, sink->n_iso);
+    __shared__ LineBits<C> sb;
+    line_count<N, C>(qv, e, t, ne, nn, *sink, sb, reinterpret_cast<const uint8_t*>(s_tab));
+  }
+}
+
+template <int N, typename T>
+__global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) == 8)))
+qcrit_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
+            const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
+            const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
+            T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
+            int64_t n_elem) {
+  constexpr int E = LineOf<N, T>::E;
+  const int64_t e0 = (int64_t)blockIdx.x * E;
+  const int ne = n_elem - e0 < E ? (int)(n_elem - e0) : E;
+  qcrit_lines_elem<N, T, false>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status);
+}
+
+// Q, |omega|, range and the per-(isovalue, element) counts in one pass.
+template <int N, typename T>
+__global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) == 8)))
+qcount_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
+             const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
+             const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
+             T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
+             CountSink<T> sink) {
+  constexpr int E = LineOf<N, T>::E;
+  const int64_t e0 = (int64_t)blockIdx.x * E;
+  const int ne = sink.n_elem - e0 < E ? (int)(sink.n_elem - e0) : E;
+  qcrit_lines_elem<N, T, true>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status,
+                               &sink);
+}
+
+// Physical gradient of f.
+template <int N, typename T>
+__global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) == 8)))
+derivs_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
+             const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ f,
+             T* __restrict__ gx, T* __restrict__ gy, T* __restrict__ gz,
+             int32_t* __restrict__ status, int64_t n_elem) {
+  using C = LineOf<N, T>;
+  constexpr int R = C::R;
+  __shared__ __align__(16) T tile[C::NF * C::SZ];
+  const int t = threadIdx.x;
+  const int64_t e0 = (int64_t)blockIdx.x * C::E, base = e0 * C::NP;
+  const int ne = C::E == 1 || n_elem - e0 >= C::E ? C::E : (int)(n_elem - e0);
+  const int nn = C::E == 1 ? C::NN : ne * C::NP, nl = C::E == 1 ? C::NL : ne * C::LN;
+  const LineOwner<C> own(t);
+  T fx[3][R], ff[1][R], g[1][R][3];
+  line_load<C>(x + base, t, nn, fx[0]);
+  line_load<C>(y + base, t, nn, fx[1]);
+  line_load<C>(z + base, t, nn, fx[2]);
+  line_load<C>(f + base, t, nn, ff[0]);
+  InvJac<T> kk[R];
+  const bool ok = line_geometry<N, C>(fx, own, dmat, tile, t, nn, nl, kk);
+  line_pass<N, C, 1>(ff, own, dmat, tile, t, nn, nl, g);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (C::full(r) || t + r * C::TH < nn) {
+      const InvJac<T>& K = kk[r];
+      const int64_t o = base + t + r * C::TH;
+      gx[o] = g[0][r][0] * K.rx + g[0][r][1] * K.sx + g[0][r][2] * K.tx;
+      gy[o] = g[0][r][0] * K.ry + g[0][r][1] * K.sy + g[0][r][2] * K.ty;
+      gz[o] = g[0][r][0] * K.rz + g[0][r][1] * K.sz + g[0][r][2] * K.tz;
+    }
+  }
+  if (!ok && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
+}

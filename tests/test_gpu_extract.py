@@ -94,6 +94,41 @@ def test_extract_many_isovalues(n, dt):
         _check_against_oracle(arrs, isos, dt, n)
 
 
+@pytest.mark.parametrize("n, shape, dt", [
+    (1, (31, 1, 1), np.float64), (1, (11, 3, 1), np.float64), (1, (13, 5, 1), np.float32),
+    (2, (2, 2, 2), np.float64), (2, (5, 2, 1), np.float64), (2, (19, 1, 1), np.float32),
+    (4, (1, 1, 1), np.float32), (4, (3, 1, 1), np.float32), (4, (3, 1, 1), np.float64)])
+def test_extract_partial_workgroups(n, shape, dt):
+    """Element counts around multiples of the elements per workgroup (32 and
+    16 at order 1, nine at order 2, two at order 4 FP32)."""
+    arrs = _inputs(n, shape, 60 + n)
+    oq, _, _ = osem.qcrit(*arrs, gll.diff_matrix(n))
+    _check_against_oracle(arrs, [float(v) for v in np.percentile(oq, [30, 50, 80])], dt, n)
+
+
+@pytest.mark.parametrize("elems, n_iso", [(3, 64), (341, 6), (1024, 3), (2100, 2)])
+def test_active_totals_over_scan_tiles(elems, n_iso):
+    """The active-cell totals come from the scan's tiles of 1,024 counts: many
+    isovalues in one tile, tiles that end inside an isovalue or exactly at
+    its end, isovalues of several tiles; the caller's buffer need not be
+    clear."""
+    arrs = _inputs(1, (elems, 1, 1), 7)
+    t = [dev(a) for a in arrs]
+    q, _, mm = sem.qcrit(*t)
+    isos = [float(v) for v in np.percentile(host(q), np.linspace(2, 98, n_iso))]
+    o = mc.extract(*arrs[:3], host(q), isos)
+    ws = torch.empty(sem.extract_workspace_bytes(elems, 1, n_iso), dtype=torch.uint8, device=DEV)
+    cnt = torch.full((n_iso,), -7, dtype=torch.int64, device=DEV)
+    act = torch.full((n_iso,), 1 << 40, dtype=torch.int64, device=DEV)
+    for _ in range(2):
+        sem.extract_into(*t, isos, [None] * n_iso, cnt, ws, active=act)
+    np.testing.assert_array_equal(host(cnt), o["tri_count"])
+    np.testing.assert_array_equal(host(act), o["active"])
+    iws = torch.empty(sem.workspace_bytes(elems, 1, n_iso), dtype=torch.uint8, device=DEV)
+    act.fill_(-3)
+    sem.isosurface_into(*t[:3], q, isos, None, cnt, iws, minmax=mm, active=act)
+    np.testing.assert_array_equal(host(act), o["active"])
+
 @pytest.mark.parametrize("dt", [np.float64, np.float32])
 def test_extract_equals_qcrit_then_isosurface(dt):
     n = 7
