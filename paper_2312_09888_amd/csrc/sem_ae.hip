@@ -532,7 +532,7 @@ __global__ void __launch_bounds__(kT)
 ae_check(int64_t e_begin, const float* __restrict__ u, const float* __restrict__ v,
          const float* __restrict__ w, const float* __restrict__ th,
          const float* __restrict__ scale, const uint32_t* __restrict__ gmax_bits,
-         const float* __restrict__ xhat, int32_t* __restrict__ flag) {
+         const float* __restrict__ xhat, uint8_t* __restrict__ flag) {
   __shared__ float red[kT / 64];
   const int64_t e = e_begin + blockIdx.x;
   const float* f[4] = {u, v, w, th};
@@ -556,30 +556,22 @@ ae_check(int64_t e_begin, const float* __restrict__ u, const float* __restrict__
 }
 
 // raw[offs[e]] = the element's four channels (GLL layout) for flagged e.
-// A workgroup takes kPackE consecutive elements: their flags go out as bytes
-// (one coalesced store), then wave w copies the flagged elements w, w + 4,
-// ... of the group (8 KiB each, 16-byte loads and stores).
-constexpr int kPackE = 64;
+// A workgroup takes `per` consecutive elements, wave w the flagged ones of
+// w, w + 4, ... (8 KiB each, 16-byte loads and stores).  The number of
+// flagged elements goes out as n_raw.
 __global__ void __launch_bounds__(kT)
-pack_raw(int64_t n_elem, const float* __restrict__ u, const float* __restrict__ v,
+pack_raw(int64_t n_elem, int per, const float* __restrict__ u, const float* __restrict__ v,
          const float* __restrict__ w, const float* __restrict__ th,
-         const int32_t* __restrict__ flag, const int64_t* __restrict__ offs, int64_t cap,
-         float* __restrict__ raw, uint8_t* __restrict__ flag_out,
-         int32_t* __restrict__ status) {
-  __shared__ int32_t s_fl[kPackE];
+         const uint8_t* __restrict__ flag, const int64_t* __restrict__ offs, int64_t cap,
+         float* __restrict__ raw, int64_t* __restrict__ n_raw, int32_t* __restrict__ status) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t e0 = (int64_t)blockIdx.x * kPackE;
-  const int ne = n_elem - e0 < kPackE ? (int)(n_elem - e0) : kPackE;
-  if (t < ne) {
-    const int fl = flag[e0 + t];
-    s_fl[t] = fl;
-    if (flag_out) flag_out[e0 + t] = (uint8_t)fl;
-  }
-  __syncthreads();
+  const int64_t e0 = (int64_t)blockIdx.x * per;
+  const int ne = n_elem - e0 < per ? (int)(n_elem - e0) : per;
+  if (blockIdx.x == 0 && t == 0 && n_raw) *n_raw = offs[n_elem];
   const float* f[4] = {u, v, w, th};
   for (int q = wv; q < ne; q += kT / 64) {
-    if (!s_fl[q]) continue;
     const int64_t e = e0 + q;
+    if (!flag[e]) continue;
     const int64_t o = offs[e];
     if (o >= cap) {
       if (lane == 0 && status) atomicOr(status, SEM_FLAG_RAW_OVERFLOW);
@@ -599,22 +591,10 @@ pack_raw(int64_t n_elem, const float* __restrict__ u, const float* __restrict__ 
   }
 }
 
-__global__ void flags_u8_to_i32(const uint8_t* __restrict__ f8, int64_t n,
-                                int32_t* __restrict__ f32) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i < n) f32[i] = f8[i] ? 1 : 0;
-}
-
-__global__ void flags_i32_to_u8_k(const int32_t* __restrict__ f32, int64_t n,
-                                  uint8_t* __restrict__ f8) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i < n) f8[i] = f32[i] ? 1 : 0;
-}
-
 // fields of elements e_begin + r: raw copy if flagged, else s * xhat
 __global__ void __launch_bounds__(kT)
 ae_unpack(int64_t e_begin, const float* __restrict__ xhat, const float* __restrict__ scale,
-          const int32_t* __restrict__ flag, const int64_t* __restrict__ offs,
+          const uint8_t* __restrict__ flag, const int64_t* __restrict__ offs,
           const float* __restrict__ raw, int64_t raw_count, float* __restrict__ u,
           float* __restrict__ v, float* __restrict__ w, float* __restrict__ th,
           int32_t* __restrict__ status) {
@@ -651,7 +631,7 @@ __global__ void __launch_bounds__(kT)
 modal_k(const float* __restrict__ u, const float* __restrict__ v, const float* __restrict__ w,
         const float* __restrict__ th, Gll7 g, const uint32_t* __restrict__ gmax_bits,
         const float* __restrict__ scale, uint16_t* __restrict__ coef,
-        int32_t* __restrict__ flag, float* __restrict__ ru, float* __restrict__ rv,
+        uint8_t* __restrict__ flag, float* __restrict__ ru, float* __restrict__ rv,
         float* __restrict__ rw, float* __restrict__ rth) {
   __shared__ float red[kT / 64];
   __shared__ float part[kT / 64][8];
@@ -727,342 +707,488 @@ modal_k(const float* __restrict__ u, const float* __restrict__ v, const float* _
 //   b01[o] = b1[o] + sum_{d1, j} W1[(d1 32 + j) 64 + o] b0[j]
 //   W45[i 256 + d4 32 + d5 4 + c] = sum_j W4[(i 8 + d4) 32 + j] W5[(j 8 + d5) 4 + c]
 //   b45[d4 32 + d5 4 + c] = b5[c] + sum_j b4[j] W5[(j 8 + d5) 4 + c]
-// (the same function, rounded differently).  The encoder kernel then takes
-// four elements per workgroup from the GLL fields to their binary16
-// latents, computing the element maxima on the way, and the decoder kernel
-// from the latents to the error check (compression) or to the fields
-// (decompression); neither writes an activation to memory.
+// (the same function, rounded differently).
+//
+// ae_encode takes elements from the GLL fields to their binary16 latents,
+// ae_decode from the latents to the error check (compression) or the fields
+// (decompression); no activation goes to memory.  A wave owns whole elements
+// from start to end (rows (element, octant) of the matrix-core tiles), so
+// after the weights are in LDS no barrier follows.  The weights (64 KB of the
+// folded map, 64 KB of the 512 x 32 one) stay in LDS while a persistent
+// workgroup walks the elements, laid out so that every lane's operands of
+// four column tiles are one conflict-free 16-byte read.
+//
+// Operands without staging: v_mfma_f32_16x16x4f32 computes D(m, n) with lane
+// l holding A(m = l % 16, k = l / 16), B(k = l / 16, n = l % 16) and outputs
+// m = 4 (l / 16) + r, n = l % 16.  Weights are the A side, so a lane's column
+// n is its own row (element, octant).  Encoder: input k = 4 s + c (s the
+// Morton node of the octant, c the channel) is in lane group c for step s, so
+// lane (row, c) needs exactly the 4 x 4 x 4 nodes of its octant in channel c:
+// 16 direct 16-byte loads, no transposition.  Decoder: output column
+// 32 d4 + 4 d5 + c is m = 4 (l / 16) + r with r = c: a lane holds all four
+// channels of its nodes.
+//
+// Bound: the FP32 matrix cores, 2 x 131,072 multiply-adds per element and
+// direction (0.11 ms for 65,536 elements at 157 TFLOP/s), with the 8 KB of
+// fields per element close behind (0.10 ms at 5.1 TB/s); the vector work
+// (layers 2 and 3: 16,384 multiply-adds per element each) hardly overlaps the
+// matrix instructions.  65,536 elements: encode 0.21, check 0.23, decode
+// 0.28 ms (with raw blocks for 72 % of them: 0.18 ms of traffic).  Four
+// elements per workgroup with the tiles transposed through LDS, every wave
+// reading every row and the weights coming from L2 took 0.30, 0.32 and
+// 0.35 ms.  Sixteen waves of two elements instead of eight of four were
+// slower (check 0.28 ms): every weight read then feeds one product.  The sums
+// keep their order, so latents, flags and fields are the same bits.
 
-constexpr int kFoldFloats = 256 * 64 + 64 + 64 * 256 + 256;
-constexpr int kEncE = 4;        // elements per workgroup
-constexpr int kRowPad = 49;     // k-major LDS rows for the 32 GEMM rows: an odd pitch
-                                // spreads the transposing stores over the banks
+constexpr int kFoldW01 = 0;                        // [step][lane][4 column tiles]
+constexpr int kFoldB01 = kFoldW01 + 256 * 64;
+constexpr int kFoldW45 = kFoldB01 + 64;            // [4 tile groups][step][lane][4 tiles]
+constexpr int kFoldB45 = kFoldW45 + 64 * 256;
+constexpr int kFoldW2 = kFoldB45 + 256;            // [k % 64][octant][32]
+constexpr int kFoldW3 = kFoldW2 + 512 * 32;        // [i][2][lane][4] (ae_decode)
+constexpr int kFoldFloats = kFoldW3 + 32 * 512;
+constexpr int kCodecT = 512;                       // threads of a full workgroup
+constexpr int kH1Pitch = 36;                       // half a layer-1 output row, padded
 
 __global__ void __launch_bounds__(kT)
 ae_fold(const float* __restrict__ prm, int64_t ow0, int64_t ob0, int64_t ow1, int64_t ob1,
-        int64_t ow4, int64_t ob4, int64_t ow5, int64_t ob5, float* __restrict__ fold) {
+        int64_t ow2, int64_t ow3, int64_t ow4, int64_t ob4, int64_t ow5, int64_t ob5,
+        float* __restrict__ fold) {
   const int idx = blockIdx.x * kT + threadIdx.x;
-  float* w01 = fold;
-  float* b01 = w01 + 256 * 64;
-  float* w45 = b01 + 64;
-  float* b45 = w45 + 64 * 256;
-  if (idx < 256 * 64) {
-    const int o = idx % 64, r = idx / 64, d1 = r / 32, dc = r % 32;
+  if (idx < kFoldB01) {
+    const int j = idx & 3, lane = (idx >> 2) & 63, s = idx >> 8;
+    const int o = 16 * j + (lane & 15), r = 4 * s + (lane >> 4), d1 = r / 32, dc = r % 32;
     float acc = 0.f;
-    for (int j = 0; j < 32; ++j)
-      acc = fmaf(prm[ow1 + (d1 * 32 + j) * 64 + o], prm[ow0 + dc * 32 + j], acc);
-    w01[idx] = acc;
-  } else if (idx < 256 * 64 + 64) {
-    const int o = idx - 256 * 64;
+    for (int q = 0; q < 32; ++q)
+      acc = fmaf(prm[ow1 + (d1 * 32 + q) * 64 + o], prm[ow0 + dc * 32 + q], acc);
+    fold[idx] = acc;
+  } else if (idx < kFoldW45) {
+    const int o = idx - kFoldB01;
     float acc = prm[ob1 + o];
     for (int d1 = 0; d1 < 8; ++d1)
-      for (int j = 0; j < 32; ++j)
-        acc = fmaf(prm[ow1 + (d1 * 32 + j) * 64 + o], prm[ob0 + j], acc);
-    b01[o] = acc;
-  } else if (idx < 256 * 64 + 64 + 64 * 256) {
-    const int q = idx - (256 * 64 + 64);
-    const int i = q / 256, col = q % 256, d4 = col / 32, d5 = (col / 4) % 8, c = col % 4;
+      for (int q = 0; q < 32; ++q)
+        acc = fmaf(prm[ow1 + (d1 * 32 + q) * 64 + o], prm[ob0 + q], acc);
+    fold[idx] = acc;
+  } else if (idx < kFoldB45) {
+    const int p = idx - kFoldW45, jj = p & 3, lane = (p >> 2) & 63, s = (p >> 8) & 15;
+    const int i = 4 * s + (lane >> 4), col = 64 * (p >> 12) + 16 * jj + (lane & 15);
+    const int d4 = col / 32, d5 = (col / 4) % 8, c = col % 4;
     float acc = 0.f;
-    for (int j = 0; j < 32; ++j)
-      acc = fmaf(prm[ow4 + (i * 8 + d4) * 32 + j], prm[ow5 + (j * 8 + d5) * 4 + c], acc);
-    w45[q] = acc;
-  } else if (idx < kFoldFloats) {
-    const int col = idx - (256 * 64 + 64 + 64 * 256), d5 = (col / 4) % 8, c = col % 4;
+    for (int q = 0; q < 32; ++q)
+      acc = fmaf(prm[ow4 + (i * 8 + d4) * 32 + q], prm[ow5 + (q * 8 + d5) * 4 + c], acc);
+    fold[idx] = acc;
+  } else if (idx < kFoldW2) {
+    const int col = idx - kFoldB45, d5 = (col / 4) % 8, c = col % 4;
     float acc = prm[ob5 + c];
-    for (int j = 0; j < 32; ++j) acc = fmaf(prm[ob4 + j], prm[ow5 + (j * 8 + d5) * 4 + c], acc);
-    b45[col] = acc;
+    for (int q = 0; q < 32; ++q) acc = fmaf(prm[ob4 + q], prm[ow5 + (q * 8 + d5) * 4 + c], acc);
+    fold[idx] = acc;
+  } else if (idx < kFoldW3) {
+    const int p = idx - kFoldW2, o = p & 31, oct = (p >> 5) & 7, k = p >> 8;
+    fold[idx] = prm[ow2 + (64 * oct + k) * 32 + o];
+  } else if (idx < kFoldFloats) {
+    const int p = idx - kFoldW3, lane = (p >> 2) & 63, i = p >> 9;
+    const int s = 8 * ((lane >> 3) & 1) + 4 * ((p >> 8) & 1) + (p & 3);
+    fold[idx] = prm[ow3 + i * 512 + (lane & 7) * 64 + 4 * s + (lane >> 4)];
   }
 }
 
-__device__ __forceinline__ int morton_node(int m) {
-  // inverse of morton8: bits (i0 j0 k0 i1 j1 k1 i2 j2 k2) -> node i + 8 j + 64 k
-  const int i = (m & 1) | ((m >> 2) & 2) | ((m >> 4) & 4);
-  const int j = ((m >> 1) & 1) | ((m >> 3) & 2) | ((m >> 5) & 4);
-  const int k = ((m >> 2) & 1) | ((m >> 4) & 2) | ((m >> 6) & 4);
-  return i + 8 * j + 64 * k;
+// A workgroup's copy of `n` weights (a multiple of 4) into LDS.
+__device__ __forceinline__ void weights_lds(const float* __restrict__ src, float* dst, int n) {
+#pragma unroll 8
+  for (int q = threadIdx.x; q < n / 4; q += kCodecT)
+    reinterpret_cast<f32x4*>(dst)[q] = reinterpret_cast<const f32x4*>(src)[q];
 }
 
-// Fields -> element maxima (scale), per-workgroup channel maxima (gpart)
-// and binary16 latents.  Wave w loads element 4 b + w; the normalised
-// values go k-major into LDS (k = the octant's Morton input index, row =
-// element x 8 + octant) for the folded layers 0-1 on the matrix cores; their
-// outputs (32 rows x 64) are layer 2's input rows, one per element.
-__global__ void __launch_bounds__(kT)
-ae_encode(int64_t n_elem, const float* __restrict__ u, const float* __restrict__ v,
+// Orders a wave's own LDS accesses (its lanes exchange data without a
+// barrier: LDS operations of one wave complete in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// m = max(m, |a|, |b|), one instruction (a NaN counts as smaller; fmaxf on
+// loaded values adds one instruction each to quiet signalling NaNs).
+__device__ __forceinline__ void max_abs(float& m, float a, float b) {
+  asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void max_abs8(float& m, const float* x) {
+  asm("v_max3_f32 %0, %0, |%1|, |%2|\n\tv_max3_f32 %0, %0, |%3|, |%4|\n\t"
+      "v_max3_f32 %0, %0, |%5|, |%6|\n\tv_max3_f32 %0, %0, |%7|, |%8|"
+      : "+v"(m)
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+}
+
+// Node 0 of the lane's octant: octant bits (i2, j2, k2).
+__device__ __forceinline__ int octant_node(int oct) {
+  return 4 * (oct & 1) + 32 * ((oct >> 1) & 1) + 256 * (oct >> 2);
+}
+
+// Fields -> element maxima (scale), per-workgroup channel maxima (gpart) and
+// binary16 latents, two elements per wave and pass.
+__global__ void __launch_bounds__(kCodecT)
+ae_encode(int64_t n_elem, int nw, const float* __restrict__ u, const float* __restrict__ v,
           const float* __restrict__ w, const float* __restrict__ th,
-          const float* __restrict__ fold, const float* __restrict__ w2,
-          const float* __restrict__ b2, float* __restrict__ scale, float* __restrict__ gpart,
-          uint16_t* __restrict__ latent) {
-  __shared__ float xs[256 * kRowPad];   // xT[k][row], then h1[element][512]
-  __shared__ float smax[kEncE][4];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t e0 = (int64_t)blockIdx.x * kEncE;
-  // this lane's 64 weights of the folded layers 0-1 (rows k = 4 i + lk,
-  // column 16 wv + lr), requested with the field loads: the matrix-core
-  // loop below then waits on LDS only
+          const float* __restrict__ fold, const float* __restrict__ b2,
+          float* __restrict__ scale, float* __restrict__ gpart, uint16_t* __restrict__ latent) {
+  __shared__ __align__(16) float s_w01[256 * 64];
+  __shared__ __align__(16) float s_w2[512 * 32];
+  __shared__ __align__(16) float s_h1[kCodecT / 64][16 * kH1Pitch];   // per wave
+  __shared__ float s_max[kCodecT / 64][4];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  const int c0 = 16 * wv;
-  float wb[64];
+  const int el = lr >> 3, oct = lr & 7;
+  const float* f = lk == 0 ? u : lk == 1 ? v : lk == 2 ? w : th;   // the lane's channel
+  const int64_t step = (int64_t)gridDim.x * nw * 2;
+  const int64_t first = ((int64_t)blockIdx.x * nw + wv) * 2;
+  // the octant's values in Morton order (bits i0 j0 k0 i1 j1 k1)
+  auto load = [&](float(&x)[64], int64_t e0) {
+    const int64_t e = e0 + el < n_elem ? e0 + el : n_elem - 1;
+    const float* src = f + e * 512 + octant_node(oct);
 #pragma unroll
-  for (int i = 0; i < 64; ++i) wb[i] = fold[(4 * i + lk) * 64 + c0 + lr];
-  {
-    // wave wv: element e0 + wv, every value of its four channels by 16-byte
-    // loads, all issued before the first use (elements past the end read
-    // element 0 and are zeroed)
-    const int64_t e = e0 + wv;
-    const bool ok = e < n_elem;
-    const int64_t eb = (ok ? e : 0) * 512;
-    const float* f[4] = {u, v, w, th};
-    float4 val[4][2];
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        val[c][q] = reinterpret_cast<const float4*>(f[c] + eb)[lane + 64 * q];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float* vv = reinterpret_cast<float*>(val[c]);
-      float mx = 0.f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (!ok) vv[q] = 0.f;
-        const float a = fabsf(vv[q]);
-        mx = a > mx ? a : mx;
+      for (int j = 0; j < 4; ++j) {
+        const float4 r = *reinterpret_cast<const float4*>(src + 8 * j + 64 * k);
+        const int s = 2 * (j & 1) + 4 * (k & 1) + 16 * (j >> 1) + 32 * (k >> 1);
+        x[s] = r.x;
+        x[s + 1] = r.y;
+        x[s + 8] = r.z;
+        x[s + 9] = r.w;
       }
-      mx = wave_max_pos(mx);
-      if (lane == 0) {
-        smax[wv][c] = mx;
-        if (ok) scale[e * 4 + c] = mx;
-      }
-      // normalised by one reciprocal per channel (the latent is checked
-      // against the exact encoder to within its binary16 step, and the
-      // error check compares the fields with s x_hat, not with x)
-      const float inv = mx > 0.f ? 1.f / mx : 0.f;
+  };
+  float xa[64], xb[64];
+  load(xa, first);
+  weights_lds(fold + kFoldW01, s_w01, 256 * 64);
+  weights_lds(fold + kFoldW2, s_w2, 512 * 32);
+  __syncthreads();
+  float* h1 = s_h1[wv];
+  const int p = lane >> 3, oq = lane & 7;   // layer 2: octant, output quad
+  float top = 0.f;                          // largest value of the lane's channel
+  // biases held in registers: a load inside the pass would wait for the
+  // fields requested before it
+  f32x4 bias[4];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int n = 4 * (lane + 64 * (q >> 2)) + (q & 3);   // node of value q
-        const int m = morton8(n & 7, (n >> 3) & 7, n >> 6);
-        xs[(4 * (m & 63) + c) * kRowPad + wv * 8 + (m >> 6)] = vv[q] * inv;
+  for (int j = 0; j < 4; ++j) {
+    bias[j] = *reinterpret_cast<const f32x4*>(fold + kFoldB01 + 16 * j + 4 * lk);
+    asm volatile("" : "+v"(bias[j]));
+  }
+  float bias2 = b2[lane & 31];
+  asm volatile("" : "+v"(bias2));
+  auto pass = [&](float(&x)[64], int64_t e0) {
+    // the weights' offsets anew in every pass: the reads stay in it
+    int lane_now = lane;
+    asm volatile("" : "+v"(lane_now));
+    const int lane4 = lane_now * 4;
+    float mx = 0.f;
+#pragma unroll
+    for (int s = 0; s < 64; s += 8) max_abs8(mx, x + s);
+    // over the element's octants (lanes of eight): quads, then half rows
+    mx = fmaxf(mx, dpp_or_zero<0xb1, 0xf>(mx));
+    mx = fmaxf(mx, dpp_or_zero<0x4e, 0xf>(mx));
+    mx = fmaxf(mx, dpp_or_zero<0x141, 0xf>(mx));
+    top = mx > top ? mx : top;
+    if (oct == 0 && e0 + el < n_elem) scale[(e0 + el) * 4 + lk] = mx;
+    // normalised by one reciprocal per channel (the latent is checked
+    // against the exact encoder to within its binary16 step, and the error
+    // check compares the fields with s x_hat, not with x)
+    const float inv = mx > 0.f ? 1.f / mx : 0.f;
+#pragma unroll
+    for (int s = 0; s < 64; ++s) x[s] *= inv;
+    // layers 0-1: outputs o = 16 j + 4 lk + r of the lane's row
+    f32x4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 64; ++s) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(&s_w01[s * 256 + lane4]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], x[s], acc[j], 0, 0, 0);
+    }
+    // layer 2: z[o] = b2[o] + sum_k h1[k] W2[k 32 + o]; lane (p, oq) sums the
+    // 64 inputs of octant p for four outputs of both elements, 32 inputs at a
+    // time through LDS
+    float z[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      wave_lds_fence();
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        *reinterpret_cast<f32x4*>(&h1[lr * kH1Pitch + 16 * j + 4 * lk]) =
+            acc[2 * h + j] + bias[2 * h + j];
+      wave_lds_fence();
+#pragma unroll
+      for (int k4 = 0; k4 < 8; ++k4) {
+        f32x4 hv[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          hv[q] = *reinterpret_cast<const f32x4*>(&h1[(8 * q + p) * kH1Pitch + 4 * k4]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const f32x4 wk = *reinterpret_cast<const f32x4*>(
+              &s_w2[(32 * h + 4 * k4 + k) * 256 + lane4]);
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int o = 0; o < 4; ++o) z[q][o] = fmaf(hv[q][k], wk[o], z[q][o]);
+        }
       }
     }
+    wave_lds_fence();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      *reinterpret_cast<f32x4*>(&h1[(8 * q + p) * 32 + 4 * oq]) =
+          f32x4{z[q][0], z[q][1], z[q][2], z[q][3]};
+    wave_lds_fence();
+    const int q = lane >> 5, o = lane & 31;
+    float sum = bias2;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) sum += h1[(8 * q + s) * 32 + o];
+    if (e0 + q < n_elem) latent[(e0 + q) * 32 + o] = __half_as_ushort(__float2half_rn(sum));
+  };
+  // two passes a round, each with the next one's fields in flight (requested
+  // without a branch, past the end the last element's again: behind a branch
+  // the compiler would wait for them with the current ones)
+  // (a small snapshot gives elements to the first nw waves only)
+  for (int64_t e0 = wv < nw ? first : n_elem; e0 < n_elem; e0 += 2 * step) {
+    load(xb, e0 + step);
+    pass(xa, e0);
+    if (e0 + step >= n_elem) break;
+    load(xa, e0 + 2 * step);
+    pass(xb, e0 + step);
   }
+  // channel maxima of the workgroup (both elements' lanes of a channel)
+  top = fmaxf(top, dpp_or_zero<0x140, 0xf>(top));
+  if (lr == 0) s_max[wv][lk] = top;
   __syncthreads();
   if (t < 4) {
     float g = 0.f;
-#pragma unroll
-    for (int q = 0; q < kEncE; ++q) g = smax[q][t] > g ? smax[q][t] : g;
+    for (int q = 0; q < kCodecT / 64; ++q) g = s_max[q][t] > g ? s_max[q][t] : g;
     gpart[blockIdx.x * 4 + t] = g;
-  }
-  // layers 0-1 folded: [32 rows x 256] x W01 [256 x 64]; wave w: both row
-  // tiles, columns 16 w .. 16 w + 15 (one weight feeds two MFMAs)
-  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < 64; ++i) {
-    const int k = 4 * i;
-    const float a0 = xs[(k + lk) * kRowPad + lr];
-    const float a1 = xs[(k + lk) * kRowPad + 16 + lr];
-    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, wb[i], acc0, 0, 0, 0);
-    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, wb[i], acc1, 0, 0, 0);
-  }
-  __syncthreads();                          // every read of xs is done
-  float* h1 = xs;                           // h1[el][p1 64 + o]
-  const float bias = fold[256 * 64 + c0 + lr];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row0 = 4 * lk + r, row1 = 16 + 4 * lk + r;
-    h1[(row0 >> 3) * 512 + (row0 & 7) * 64 + c0 + lr] = acc0[r] + bias;
-    h1[(row1 >> 3) * 512 + (row1 & 7) * 64 + c0 + lr] = acc1[r] + bias;
-  }
-  __syncthreads();
-  // layer 2: z[el][o] = b2[o] + sum_k h1[el][k] W2[k 32 + o]; thread: output o =
-  // t % 32 of all four elements over the k slice 64 (t / 32) .. + 63 (each
-  // weight read once per workgroup), slices summed in LDS in order
-  const int o2 = t & 31, ks = t >> 5;
-  float z[kEncE] = {0.f, 0.f, 0.f, 0.f};
-  const float* wr = w2 + (int64_t)(64 * ks) * 32 + o2;
-#pragma unroll 8
-  for (int k = 0; k < 64; ++k) {
-    const float wk = wr[k * 32];
-#pragma unroll
-    for (int el = 0; el < kEncE; ++el) z[el] = fmaf(h1[el * 512 + 64 * ks + k], wk, z[el]);
-  }
-  __syncthreads();                          // h1 reads done: reuse for the slice sums
-  float* zp = xs + kEncE * 512;             // [8 slices][4 elements][32]
-#pragma unroll
-  for (int el = 0; el < kEncE; ++el) zp[(ks * kEncE + el) * 32 + o2] = z[el];
-  __syncthreads();
-  if (t < kEncE * 32) {
-    const int el = t >> 5, o = t & 31;
-    float sum = b2[o];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) sum += zp[(q * kEncE + el) * 32 + o];
-    const int64_t e = e0 + el;
-    if (e < n_elem) latent[e * 32 + o] = __half_as_ushort(__float2half_rn(sum));
   }
 }
 
-// Latents -> reconstruction, four elements per workgroup: layer 3 on the
-// vector units, folded layers 4-5 on the matrix cores, the reconstruction
-// s x_hat placed in LDS at the GLL positions.  CHECK: compared with the
-// fields (flag[e] = some channel exceeds the fallback bound); else written
-// to the fields, raw blocks copied for flagged elements.
-template <bool CHECK>
-__global__ void __launch_bounds__(kT)
-ae_decode(int64_t n_elem, const uint16_t* __restrict__ latent, const float* __restrict__ scale,
-          const uint32_t* __restrict__ gmax_bits, const float* __restrict__ fold,
-          const float* __restrict__ w3, const float* __restrict__ b3,
-          const float* __restrict__ iu, const float* __restrict__ iv,
-          const float* __restrict__ iw, const float* __restrict__ ith,
-          float* __restrict__ ou, float* __restrict__ ov, float* __restrict__ ow,
-          float* __restrict__ oth, const int32_t* __restrict__ flag,
+// Exchange between lanes 16 apart (odd rows of a with even rows of b).
+__device__ __forceinline__ void swap_rows16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+// Latents -> reconstruction, 2 RT elements per wave and pass.  CHECK: compared
+// with the fields (flag_out[e] = some channel exceeds the fallback bound);
+// else written to the fields, raw blocks copied for flagged elements.
+template <bool CHECK, int RT>
+__global__ void __launch_bounds__(kCodecT)
+ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
+          const float* __restrict__ scale, const float* __restrict__ gpart, int n_gpart,
+          const float* __restrict__ fold,
+          const float* __restrict__ b3, const float* __restrict__ iu,
+          const float* __restrict__ iv, const float* __restrict__ iw,
+          const float* __restrict__ ith, float* __restrict__ ou, float* __restrict__ ov,
+          float* __restrict__ ow, float* __restrict__ oth, const uint8_t* __restrict__ flag,
           const int64_t* __restrict__ offs, const float* __restrict__ raw, int64_t raw_count,
-          int32_t* __restrict__ flag_out, int32_t* __restrict__ status) {
-  __shared__ float fl[kEncE][4][512];       // fields (CHECK) or reconstruction
-  __shared__ float h3[64 * kRowPad];        // layer 3 output, k-major: [o][el 8 + d]
-  __shared__ float zs[kEncE][32];
-  __shared__ uint32_t emax[kEncE][4];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t e0 = (int64_t)blockIdx.x * kEncE;
-  // this lane's 64 weights of the folded layers 4-5 (rows k = 4 i + lk,
-  // columns 64 wv + 16 j + lr), requested first: the matrix-core loop below
-  // then waits on LDS only
+          uint8_t* __restrict__ flag_out, int32_t* __restrict__ status) {
+  __shared__ __align__(16) float s_w3[32 * 512];
+  __shared__ __align__(16) float s_w45[64 * 256];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  const int c0 = 64 * wv;
-  const float* w45 = fold + 256 * 64 + 64;
-  const float* b45 = w45 + 64 * 256;
-  float wd[16][4];
-#pragma unroll
-  for (int i = 0; i < 16; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) wd[i][j] = w45[(4 * i + lk) * 256 + c0 + 16 * j + lr];
-  if (t < kEncE * 32) {
-    const int64_t e = e0 + t / 32;
-    zs[t / 32][t % 32] = e < n_elem ? __half2float(__ushort_as_half(latent[e * 32 + t % 32])) : 0.f;
-  }
-  if (t < kEncE * 4) emax[t / 4][t % 4] = 0u;
-  if (CHECK) {
-    const int64_t e = e0 + wv;
-    const int64_t eb = (e < n_elem ? e : 0) * 512;
-    const float4* g0 = reinterpret_cast<const float4*>(iu + eb);
-    const float4* g1 = reinterpret_cast<const float4*>(iv + eb);
-    const float4* g2 = reinterpret_cast<const float4*>(iw + eb);
-    const float4* g3 = reinterpret_cast<const float4*>(ith + eb);
-    const float4 v00 = g0[lane], v01 = g0[lane + 64], v10 = g1[lane], v11 = g1[lane + 64];
-    const float4 v20 = g2[lane], v21 = g2[lane + 64], v30 = g3[lane], v31 = g3[lane + 64];
-    float4* l0 = reinterpret_cast<float4*>(fl[wv][0]);
-    float4* l1 = reinterpret_cast<float4*>(fl[wv][1]);
-    float4* l2 = reinterpret_cast<float4*>(fl[wv][2]);
-    float4* l3 = reinterpret_cast<float4*>(fl[wv][3]);
-    l0[lane] = v00;
-    l0[lane + 64] = v01;
-    l1[lane] = v10;
-    l1[lane + 64] = v11;
-    l2[lane] = v20;
-    l2[lane + 64] = v21;
-    l3[lane] = v30;
-    l3[lane + 64] = v31;
+  const int el = lr >> 3, oct = lr & 7;
+  __shared__ float s_gmax[CHECK ? kCodecT / 64 : 1][4];
+  weights_lds(fold + kFoldW3, s_w3, 32 * 512);
+  weights_lds(fold + kFoldW45, s_w45, 64 * 256);
+  if constexpr (CHECK) {
+    // the channels' global maxima from the encoder's workgroups (<= kCodecT)
+    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (t < n_gpart) g = reinterpret_cast<const float4*>(gpart)[t];
+    g.x = wave_max_pos(g.x);
+    g.y = wave_max_pos(g.y);
+    g.z = wave_max_pos(g.z);
+    g.w = wave_max_pos(g.w);
+    if (lane == 0) *reinterpret_cast<float4*>(s_gmax[wv]) = g;
   }
   __syncthreads();
-  // layer 3: h3[el][d 64 + o] = b3[o] + sum_i z[el][i] W3[i 512 + d 64 + o]
+  // the lane's nodes: i pair from its octant and (after the exchange) the
+  // parity of lk, j0 from lk; the tile index gives j1, k0 and k1
+  const int node0 = octant_node(oct) + 2 * (lk & 1) + 8 * (lk >> 1);
+  const int64_t step = (int64_t)gridDim.x * nw * (2 * RT);
+  // (a small snapshot gives elements to the first nw waves only)
+  for (int64_t e0 = wv < nw ? ((int64_t)blockIdx.x * nw + wv) * (2 * RT) : n_elem; e0 < n_elem;
+       e0 += step) {
+    int64_t e[RT];      // the lane's elements e0 + 2 q + el
+    bool ok[RT];
+    float4 sc[RT];
+    uint4 zw[2 * RT][4];   // every element's latents, two halves a word
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int col = t + 256 * h;
-    float a[kEncE];
+    for (int q = 0; q < RT; ++q) {
+      e[q] = e0 + 2 * q + el;
+      ok[q] = e[q] < n_elem;
+      if (!ok[q]) e[q] = n_elem - 1;
+      // elements with a raw block are not written from their latents
+      if constexpr (!CHECK) ok[q] = ok[q] & !((flag[e[q]] != 0) & (offs[e[q]] < raw_count));
+      sc[q] = *reinterpret_cast<const float4*>(scale + e[q] * 4);
+    }
 #pragma unroll
-    for (int el = 0; el < kEncE; ++el) a[el] = b3[col & 63];
-#pragma unroll 8
+    for (int x = 0; x < 2 * RT; ++x) {
+      const int64_t ex = e0 + x < n_elem ? e0 + x : n_elem - 1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        zw[x][i] = reinterpret_cast<const uint4*>(latent + ex * 32)[i];
+    }
+    // the weights' offsets anew in every pass: the reads stay in it
+    int lane_now = lane;
+    asm volatile("" : "+v"(lane_now));
+    const int lane4 = lane_now * 4;
+    // layer 3: of the outputs 4 s + lk (s < 16) of octant oct, this lane sums
+    // s = 8 el .. 8 el + 7 for every element (64 lanes, 64 different weights)
+    float a[2 * RT][8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float b = b3[4 * (8 * el + s) + lk];
+#pragma unroll
+      for (int x = 0; x < 2 * RT; ++x) a[x][s] = b;
+    }
+#pragma unroll
     for (int i = 0; i < 32; ++i) {
-      const float wi = w3[i * 512 + col];
+      if (i % 4 == 0) asm volatile("" ::: "memory");   // at most eight reads in flight
+      float z[2 * RT];
 #pragma unroll
-      for (int el = 0; el < kEncE; ++el) a[el] = fmaf(zs[el][i], wi, a[el]);
-    }
+      for (int x = 0; x < 2 * RT; ++x) {
+        const uint4& b = zw[x][i >> 3];
+        const uint32_t word = (i & 6) == 0 ? b.x : (i & 6) == 2 ? b.y : (i & 6) == 4 ? b.z : b.w;
+        z[x] = __half2float(__ushort_as_half((uint16_t)(i & 1 ? word >> 16 : word & 0xffffu)));
+      }
 #pragma unroll
-    for (int el = 0; el < kEncE; ++el) h3[(col & 63) * kRowPad + el * 8 + (col >> 6)] = a[el];
-  }
-  __syncthreads();
-  // layers 4-5 folded: [32 rows x 64] x W45 [64 x 256]; wave w: both row
-  // tiles, columns 64 w .. 64 w + 63 (one weight feeds two MFMAs)
-  f32x4 acc[2][4];
+      for (int s4 = 0; s4 < 2; ++s4) {
+        const f32x4 wi = *reinterpret_cast<const f32x4*>(&s_w3[(i * 2 + s4) * 256 + lane4]);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+        for (int x = 0; x < 2 * RT; ++x)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int k = 4 * i;
-    const float a0 = h3[(k + lk) * kRowPad + lr];
-    const float a1 = h3[(k + lk) * kRowPad + 16 + lr];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, wd[i][j], acc[0][j], 0, 0, 0);
-      acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, wd[i][j], acc[1][j], 0, 0, 0);
-    }
-  }
-  // A lane's values: rows 16 rt + 4 lk + r (element 2 rt + lk / 2, octant
-  // (4 lk + r) & 7), columns c0 + 16 j + lr (channel lr & 3 for every j).
-  // The Morton bits of octant, d4 and d5 do not overlap, so a node index is
-  // the sum of the three parts' indices.
-  const int c = lr & 3;
-  int node_row[4], node_col[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) node_row[r] = morton_node(64 * ((4 * lk + r) & 7));
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int col = c0 + 16 * j + lr;
-    node_col[j] = morton_node(8 * (col >> 5) + ((col >> 2) & 7));
-  }
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    const int el = 2 * rt + (lk >> 1);
-    const int64_t e = e0 + el;
-    const float sc = e < n_elem ? scale[e * 4 + c] : 0.f;
-    float worst = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float bias = b45[c0 + 16 * j + lr];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int node = node_row[r] + node_col[j];
-        const float rec = sc * (acc[rt][j][r] + bias);
-        if (CHECK) {
-          const float d = fabsf(fl[el][c][node] - rec);
-          worst = d > worst ? d : worst;
-        } else {
-          fl[el][c][node] = rec;
-        }
+          for (int s = 0; s < 4; ++s) a[x][4 * s4 + s] = fmaf(z[x], wi[s], a[x][4 * s4 + s]);
       }
     }
-    if (CHECK) atomicMax(&emax[el][c], __float_as_uint(worst));
-  }
-  __syncthreads();
-  if (CHECK) {
-    if (t < kEncE) {
-      const int64_t e = e0 + t;
-      if (e < n_elem) {
+    // the lane eight on in the row (row_ror:8) has the other half of this
+    // lane's element
+    float h3[RT][16];
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const float other = dpp_or_zero<0x128, 0xf>(el ? a[2 * q][s] : a[2 * q + 1][s]);
+        h3[q][s] = el ? other : a[2 * q][s];
+        h3[q][8 + s] = el ? a[2 * q + 1][s] : other;
+      }
+    float worst[RT][4];
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) worst[q][c] = 0.f;
+    // layers 4-5, four column tiles at a time: tiles 4 g + jj, whose nodes
+    // differ in i1 (jj / 2) and k0 (jj % 2); g gives j1 and k1
+#pragma unroll 1
+    for (int g = 0; g < 4; ++g) {
+      const int node = node0 + 16 * (g & 1) + 128 * (g >> 1);
+      float2 ref[RT][2][4];
+      if constexpr (CHECK) {
+#pragma unroll
+        for (int q = 0; q < RT; ++q)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const int64_t at = e[q] * 512 + node + 64 * b;
+            ref[q][b][0] = *reinterpret_cast<const float2*>(iu + at);
+            ref[q][b][1] = *reinterpret_cast<const float2*>(iv + at);
+            ref[q][b][2] = *reinterpret_cast<const float2*>(iw + at);
+            ref[q][b][3] = *reinterpret_cast<const float2*>(ith + at);
+          }
+      }
+      f32x4 acc[RT][4];
+#pragma unroll
+      for (int q = 0; q < RT; ++q)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) acc[q][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const f32x4 wv4 = *reinterpret_cast<const f32x4*>(&s_w45[(g * 16 + s) * 256 + lane4]);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+          for (int q = 0; q < RT; ++q)
+            acc[q][jj] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(wv4[jj], h3[q][s], acc[q][jj], 0, 0, 0);
+      }
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const f32x4 b =
+            *reinterpret_cast<const f32x4*>(fold + kFoldB45 + 64 * g + 16 * jj + 4 * lk);
+#pragma unroll
+        for (int q = 0; q < RT; ++q) {
+          acc[q][jj][0] = sc[q].x * (acc[q][jj][0] + b[0]);
+          acc[q][jj][1] = sc[q].y * (acc[q][jj][1] + b[1]);
+          acc[q][jj][2] = sc[q].z * (acc[q][jj][2] + b[2]);
+          acc[q][jj][3] = sc[q].w * (acc[q][jj][3] + b[3]);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < RT; ++q)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            // values at i1 = 0 and 1 of this lane's i0 -> neighbours i, i + 1
+            float lo = acc[q][b][c], hi = acc[q][2 + b][c];
+            swap_rows16(lo, hi);
+            if constexpr (CHECK) {
+              max_abs(worst[q][c], ref[q][b][c].x - lo, ref[q][b][c].y - hi);
+            } else if (ok[q]) {
+              float* out = c == 0 ? ou : c == 1 ? ov : c == 2 ? ow : oth;
+              *reinterpret_cast<float2*>(out + e[q] * 512 + node + 64 * b) = make_float2(lo, hi);
+            }
+          }
+    }
+    if constexpr (CHECK) {
+#pragma unroll
+      for (int q = 0; q < RT; ++q) {
         int bad = 0;
+        const float s4[4] = {sc[q].x, sc[q].y, sc[q].z, sc[q].w};
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          bad |= __uint_as_float(emax[t][c]) > fallback_bound(scale[e * 4 + c], gmax_bits[c]);
-        flag_out[e] = bad;
-      }
-    }
-  } else {
-    const int64_t e = e0 + wv;
-    if (e < n_elem) {
-      const bool flagged = flag && flag[e];
-      const int64_t o = flagged ? offs[e] : 0;
-      const bool is_raw = flagged && raw && o < raw_count;
-      if (flagged && !is_raw && lane == 0 && status) atomicOr(status, SEM_FLAG_RAW_OVERFLOW);
-      float* f[4] = {ou, ov, ow, oth};
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int n4 = lane + 64 * q;
-          reinterpret_cast<float4*>(f[c] + e * 512)[n4] =
-              is_raw ? reinterpret_cast<const float4*>(raw + (o * 4 + c) * 512)[n4]
-                     : reinterpret_cast<const float4*>(fl[wv][c])[n4];
+        for (int c = 0; c < 4; ++c) {
+          // over the element's lanes: octants, then lk
+          float m = worst[q][c];
+          m = fmaxf(m, dpp_or_zero<0xb1, 0xf>(m));
+          m = fmaxf(m, dpp_or_zero<0x4e, 0xf>(m));
+          m = fmaxf(m, dpp_or_zero<0x141, 0xf>(m));
+          m = fmaxf(m, __shfl_xor(m, 16));
+          m = fmaxf(m, __shfl_xor(m, 32));
+          float gm = 0.f;
+          for (int w = 0; w < kCodecT / 64; ++w) gm = fmaxf(gm, s_gmax[w][c]);
+          bad |= m > fallback_bound(s4[c], __float_as_uint(gm));
         }
+        if (ok[q] && oct == 0 && lk == 0) flag_out[e[q]] = (uint8_t)bad;
+      }
+    } else {
+      // flagged elements: their raw blocks, by the whole wave
+      for (int x = 0; x < 2 * RT; ++x) {
+        const int64_t ex = e0 + x;
+        if (ex >= n_elem || !flag[ex]) continue;
+        const int64_t o = offs[ex];
+        if (o >= raw_count) {
+          // beyond the raw blocks given: decoded from its latent
+          if (lane == 0 && status) atomicOr(status, SEM_FLAG_RAW_OVERFLOW);
+          continue;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float* out = (c == 0 ? ou : c == 1 ? ov : c == 2 ? ow : oth) + ex * 512;
+          const float* src = raw + (o * 4 + c) * 512;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            reinterpret_cast<float4*>(out)[lane + 64 * h] =
+                reinterpret_cast<const float4*>(src)[lane + 64 * h];
+        }
+      }
     }
   }
 }
@@ -1352,10 +1478,11 @@ hipError_t launch_ae_pca_init(int64_t n_pool, const float* pool, float* params, 
 
 // Compression in chunks of kChunk elements.
 constexpr int64_t kChunk = 16384;
+// Workgroups of a codec kernel at most (one per CU).
+constexpr int kCodecGroups = 256;
 
 struct CompressWs {
   AeWs ae;
-  int32_t* flag;
   int64_t* offs;
   int64_t* partial;
   uint32_t* gmax;
@@ -1375,12 +1502,11 @@ CompressWs compress_layout(void* base, int64_t n_elem) {
     off += align256(b);
     return q;
   };
-  c.flag = reinterpret_cast<int32_t*>(take((size_t)(n_elem + 1) * 4));
   c.offs = reinterpret_cast<int64_t*>(take((size_t)(n_elem + 1) * 8));
   c.partial = reinterpret_cast<int64_t*>(take((size_t)(scan_partials_capacity(n_elem) + 1) * 8));
   c.gmax = reinterpret_cast<uint32_t*>(take(16));
   c.fold = reinterpret_cast<float*>(take((size_t)kFoldFloats * 4));
-  c.gpart = reinterpret_cast<float*>(take((size_t)(cdiv(n_elem, kEncE) + 1) * 4 * 4));
+  c.gpart = reinterpret_cast<float*>(take((size_t)kCodecGroups * 4 * 4));
   c.bytes = off;
   return c;
 }
@@ -1388,8 +1514,42 @@ CompressWs compress_layout(void* base, int64_t n_elem) {
 hipError_t launch_fold(const float* params, float* fold, hipStream_t s) {
   const Layer* L = layers();
   hipLaunchKernelGGL(ae_fold, dim3((unsigned)cdiv(kFoldFloats, kT)), dim3(kT), 0, s, params,
-                     L[0].w_off, L[0].b_off, L[1].w_off, L[1].b_off, L[4].w_off, L[4].b_off,
-                     L[5].w_off, L[5].b_off, fold);
+                     L[0].w_off, L[0].b_off, L[1].w_off, L[1].b_off, L[2].w_off, L[3].w_off,
+                     L[4].w_off, L[4].b_off, L[5].w_off, L[5].b_off, fold);
+  return hipGetLastError();
+}
+
+// Waves per workgroup that take elements, `per` a wave and pass (the weights
+// fill the CU's LDS: one workgroup per CU): as few as take the elements in
+// one pass, so that a small snapshot spreads over the chip, at most all.
+int codec_waves(int64_t n_elem, int per) {
+  int w = 1;
+  while (w < kCodecT / 64 && n_elem > (int64_t)kCodecGroups * w * per) w *= 2;
+  return w;
+}
+unsigned codec_groups(int64_t n_elem, int per) {
+  const int64_t g = cdiv(n_elem, codec_waves(n_elem, per) * per);
+  return (unsigned)(g < kCodecGroups ? g : kCodecGroups);
+}
+
+// Four elements a wave and pass (every weight read feeds two products) where
+// that still fills the chip, else two.
+template <bool CHECK>
+hipError_t launch_decode(int64_t n_elem, const uint16_t* latent, const float* scale,
+                         const CompressWs& c, const float* params, const float* const* in,
+                         float* const* out, const uint8_t* flag, const float* raw,
+                         int64_t raw_count, uint8_t* flag_out, int32_t* status, hipStream_t s) {
+  const int per = n_elem >= (int64_t)kCodecGroups * (kCodecT / 64) * 4 ? 4 : 2;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(codec_groups(n_elem, per)), dim3(kCodecT), 0, s, n_elem,
+                       codec_waves(n_elem, per), latent, scale, (const float*)c.gpart,
+                       (int)codec_groups(n_elem, 2), (const float*)c.fold,
+                       params + layers()[3].b_off, in[0], in[1], in[2], in[3], out[0], out[1],
+                       out[2], out[3], flag, (const int64_t*)c.offs, raw, raw ? raw_count : 0,
+                       flag_out, status);
+  };
+  if (per == 4) go(ae_decode<CHECK, 2>);
+  else go(ae_decode<CHECK, 1>);
   return hipGetLastError();
 }
 
@@ -1403,19 +1563,16 @@ hipError_t launch_ae_compress(int64_t n_elem, const float* const* f, const float
   hipError_t e;
   if (tanh_mask == 0 && n_elem > 0) {
     // linear network: fused encoder and decoder-check
-    const Layer* L = layers();
-    const unsigned grid = (unsigned)cdiv(n_elem, kEncE);
+    const unsigned grid = codec_groups(n_elem, 2);
     e = launch_fold(params, c.fold, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ae_encode, dim3(grid), dim3(kT), 0, s, n_elem, f[0], f[1], f[2], f[3],
-                       c.fold, params + L[2].w_off, params + L[2].b_off, scale, c.gpart, latent);
-    hipLaunchKernelGGL(fill_u32, dim3(1), dim3(kT), 0, s, c.gmax, 4, 0u);
-    hipLaunchKernelGGL(gmax_k, dim3(grid < 1024 * kT ? (unsigned)cdiv(grid, kT) : 1024u),
-                       dim3(kT), 0, s, c.gpart, (int64_t)grid, c.gmax);
-    hipLaunchKernelGGL((ae_decode<true>), dim3(grid), dim3(kT), 0, s, n_elem, latent, scale,
-                       c.gmax, c.fold, params + L[3].w_off, params + L[3].b_off, f[0], f[1],
-                       f[2], f[3], nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       (int64_t)0, c.flag, status);
+    hipLaunchKernelGGL(ae_encode, dim3(grid), dim3(kCodecT), 0, s, n_elem,
+                       codec_waves(n_elem, 2), f[0], f[1], f[2], f[3], c.fold,
+                       params + layers()[2].b_off, scale, c.gpart, latent);
+    float* const none[4] = {nullptr, nullptr, nullptr, nullptr};
+    e = launch_decode<true>(n_elem, latent, scale, c, params, f, none, nullptr, nullptr, 0, flags,
+                            status, s);
+    if (e != hipSuccess) return e;
   } else {
     e = launch_ae_scales(n_elem, f, scale, c.gmax, s);
     if (e != hipSuccess) return e;
@@ -1428,18 +1585,17 @@ hipError_t launch_ae_compress(int64_t n_elem, const float* const* f, const float
                            latent + b * 32, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(ae_check, dim3((unsigned)n), dim3(kT), 0, s, b, f[0], f[1], f[2], f[3],
-                       scale, c.gmax, c.ae.act[kLayers], c.flag);
+                       scale, c.gmax, c.ae.act[kLayers], flags);
   }
-  e = launch_exclusive_scan(c.flag, n_elem, c.partial, c.offs, s);
+  e = launch_flag_scan(flags, n_elem, c.partial, c.offs, s);
   if (e != hipSuccess) return e;
-  if (n_raw) {
-    e = hipMemcpyAsync(n_raw, c.offs + n_elem, 8, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-  }
-  if (n_elem > 0)
-    hipLaunchKernelGGL(pack_raw, dim3((unsigned)cdiv(n_elem, kPackE)), dim3(kT), 0, s, n_elem,
-                       f[0], f[1], f[2], f[3],
-                       c.flag, c.offs, raw_cap, raw, flags, status);
+  // elements per workgroup: one a wave up to some 8,192 elements (the copies
+  // of a wave follow one another), 16 a wave for large snapshots
+  const int64_t four = cdiv(cdiv(n_elem, 2048), 4);
+  const int per = 4 * (int)(four < 1 ? 1 : four > 16 ? 16 : four);
+  hipLaunchKernelGGL(pack_raw, dim3((unsigned)(n_elem > 0 ? cdiv(n_elem, per) : 1)), dim3(kT), 0,
+                     s, n_elem, per, f[0], f[1], f[2], f[3], (const uint8_t*)flags,
+                     (const int64_t*)c.offs, raw_cap, raw, n_raw, status);
   return hipGetLastError();
 }
 
@@ -1449,19 +1605,14 @@ hipError_t launch_ae_decompress(int64_t n_elem, const uint16_t* latent, const fl
                                 int32_t* status, hipStream_t s) {
   CompressWs c = compress_layout(ws, n_elem);
   if (n_elem <= 0) return hipSuccess;
-  hipLaunchKernelGGL(flags_u8_to_i32, dim3((unsigned)cdiv(n_elem, kT)), dim3(kT), 0, s, flags,
-                     n_elem, c.flag);
-  hipError_t e = launch_exclusive_scan(c.flag, n_elem, c.partial, c.offs, s);
+  hipError_t e = launch_flag_scan(flags, n_elem, c.partial, c.offs, s);
   if (e != hipSuccess) return e;
   if (tanh_mask == 0) {
-    const Layer* L = layers();
     e = launch_fold(params, c.fold, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((ae_decode<false>), dim3((unsigned)cdiv(n_elem, kEncE)), dim3(kT), 0, s,
-                       n_elem, latent, scale, nullptr, c.fold, params + L[3].w_off,
-                       params + L[3].b_off, nullptr, nullptr, nullptr, nullptr, f[0], f[1], f[2],
-                       f[3], c.flag, c.offs, raw, raw_count, nullptr, status);
-    return hipGetLastError();
+    const float* const none[4] = {nullptr, nullptr, nullptr, nullptr};
+    return launch_decode<false>(n_elem, latent, scale, c, params, none, f, flags, raw, raw_count,
+                                nullptr, status, s);
   }
   for (int64_t b = 0; b < n_elem; b += kChunk) {
     const int64_t n = n_elem - b < kChunk ? n_elem - b : kChunk;
@@ -1472,7 +1623,7 @@ hipError_t launch_ae_decompress(int64_t n_elem, const uint16_t* latent, const fl
       if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(ae_unpack, dim3((unsigned)n), dim3(kT), 0, s, b, c.ae.act[kLayers], scale,
-                       c.flag, c.offs, raw, raw_count, f[0], f[1], f[2], f[3], status);
+                       flags, c.offs, raw, raw_count, f[0], f[1], f[2], f[3], status);
   }
   return hipGetLastError();
 }
@@ -1493,9 +1644,7 @@ hipError_t launch_modal(int64_t n_elem, const float* const* f, const double* xi,
   if (recon)
     for (int k = 0; k < 4; ++k) r[k] = recon[k];
   hipLaunchKernelGGL(modal_k, dim3((unsigned)n_elem), dim3(kT), 0, s, f[0], f[1], f[2], f[3], g,
-                     c.gmax, scale, coef, c.flag, r[0], r[1], r[2], r[3]);
-  hipLaunchKernelGGL(flags_i32_to_u8_k, dim3((unsigned)cdiv(n_elem, kT)), dim3(kT), 0, s, c.flag,
-                     n_elem, flags);
+                     c.gmax, scale, coef, flags, r[0], r[1], r[2], r[3]);
   return hipGetLastError();
 }
 

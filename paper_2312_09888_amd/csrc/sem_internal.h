@@ -89,6 +89,10 @@ constexpr int64_t scan_partials_capacity(int64_t count) {
 hipError_t launch_exclusive_scan(const int32_t* cnt, int64_t count, int64_t* partial,
                                  int64_t* offs, hipStream_t s);
 
+// The same of count flags (nonzero counts as 1).
+hipError_t launch_flag_scan(const uint8_t* flag, int64_t count, int64_t* partial, int64_t* offs,
+                            hipStream_t s);
+
 // Batched snapshots: a plan (device) holds a header and one descriptor per
 // snapshot; one persistent kernel walks the work items (chunks of `chunk`
 // elements of one snapshot) of all snapshots.

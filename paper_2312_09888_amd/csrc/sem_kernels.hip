@@ -783,9 +783,15 @@ constexpr int kScanThreads = 256;
 // Tile sums; a tile is kScanThreads x ITEMS counts (scan_tile).  PACKED: the
 // counts are slots of triangles and active cells; the active cells of the
 // isovalues that the tile holds (n_elem slots each) are added to `active`.
-template <int ITEMS, bool PACKED>
+// CT: int32_t counts, or uint8_t flags (nonzero counts as 1).
+template <typename CT>
+__device__ __forceinline__ int32_t scan_value(CT v) {
+  if constexpr (sizeof(CT) == 1) return v != 0;
+  else return v;
+}
+template <int ITEMS, bool PACKED, typename CT>
 __global__ void __launch_bounds__(kScanThreads)
-scan_reduce(const int32_t* __restrict__ cnt, int64_t count, int64_t* __restrict__ partial,
+scan_reduce(const CT* __restrict__ cnt, int64_t count, int64_t* __restrict__ partial,
             int64_t* __restrict__ active, int64_t n_elem) {
   __shared__ int64_t sred[kScanThreads / 64];
   const int64_t start = (int64_t)blockIdx.x * (kScanThreads * ITEMS);
@@ -794,7 +800,7 @@ scan_reduce(const int32_t* __restrict__ cnt, int64_t count, int64_t* __restrict_
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     const int64_t idx = start + r * kScanThreads + threadIdx.x;
-    v[r] = idx < count ? cnt[idx] : 0;
+    v[r] = idx < count ? scan_value(cnt[idx]) : 0;
     // packed: both sums at once (a tile's stay below 2^24)
     if constexpr (PACKED) s += (int64_t)slot_tris(v[r]) | ((int64_t)slot_active(v[r]) << 32);
     else s += v[r];
@@ -841,9 +847,9 @@ scan_partials(int64_t* __restrict__ partial, int64_t nb) {
 // scanned (nb <= kScanFold), and each workgroup adds up the sums of the
 // tiles before it, which saves the one-workgroup scan of the partials.
 constexpr int64_t kScanFold = 1024;
-template <bool FOLD, int ITEMS, bool PACKED>
+template <bool FOLD, int ITEMS, bool PACKED, typename CT>
 __global__ void __launch_bounds__(kScanThreads)
-scan_apply(const int32_t* __restrict__ cnt, int64_t count, const int64_t* __restrict__ partial,
+scan_apply(const CT* __restrict__ cnt, int64_t count, const int64_t* __restrict__ partial,
            int64_t nb, int64_t* __restrict__ offs) {
   __shared__ int64_t sred[kScanThreads / 64];
   const int64_t start =
@@ -852,7 +858,7 @@ scan_apply(const int32_t* __restrict__ cnt, int64_t count, const int64_t* __rest
   int64_t s = 0;
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
-    v[r] = (start + r < count) ? cnt[start + r] : 0;
+    v[r] = (start + r < count) ? scan_value(cnt[start + r]) : 0;
     if constexpr (PACKED) v[r] = slot_tris(v[r]);
     s += v[r];
   }
@@ -1953,29 +1959,29 @@ IsoList<T> make_isolist(int n_iso, const double* iso_host) {
 // Tiles of 1,024 counts up to kScanSmall counts (always folded), else of
 // 4,096 (scan_tile).  `start` and `stop` (may be null) stamp the first and
 // the last kernel.
-template <int ITEMS, bool PACKED>
-void scan_kernels_t(const int32_t* cnt, int64_t count, int64_t* partial, int64_t* offs,
+template <int ITEMS, bool PACKED, typename CT>
+void scan_kernels_t(const CT* cnt, int64_t count, int64_t* partial, int64_t* offs,
                     int64_t* active, int64_t n_elem, hipStream_t s, hipEvent_t start,
                     hipEvent_t stop) {
   static_assert(kScanThreads * ITEMS == 1024 || kScanThreads * ITEMS == 4096, "scan_tile");
   const int64_t nb = scan_blocks(count);
-  hipExtLaunchKernelGGL((scan_reduce<ITEMS, PACKED>), dim3((unsigned)nb), dim3(kScanThreads), 0, s,
+  hipExtLaunchKernelGGL((scan_reduce<ITEMS, PACKED, CT>), dim3((unsigned)nb), dim3(kScanThreads), 0, s,
                         start, nullptr, 0, cnt, count, partial, active, n_elem);
   if (nb <= kScanFold) {
-    hipExtLaunchKernelGGL((scan_apply<true, ITEMS, PACKED>), dim3((unsigned)nb),
+    hipExtLaunchKernelGGL((scan_apply<true, ITEMS, PACKED, CT>), dim3((unsigned)nb),
                           dim3(kScanThreads), 0, s, nullptr, stop, 0, cnt, count,
                           (const int64_t*)partial, nb, offs);
   } else {
     hipLaunchKernelGGL(scan_partials, dim3(1), dim3(1024), 0, s, partial, nb);
-    hipExtLaunchKernelGGL((scan_apply<false, ITEMS, PACKED>), dim3((unsigned)nb),
+    hipExtLaunchKernelGGL((scan_apply<false, ITEMS, PACKED, CT>), dim3((unsigned)nb),
                           dim3(kScanThreads), 0, s, nullptr, stop, 0, cnt, count,
                           (const int64_t*)partial, nb, offs);
   }
 }
 // PACKED: count slots (active, if not NULL, receives the n_iso totals of the
 // active cells, n_elem slots each); otherwise plain counts.
-template <bool PACKED>
-void scan_kernels(const int32_t* cnt, int64_t count, int64_t* partial, int64_t* offs,
+template <bool PACKED, typename CT>
+void scan_kernels(const CT* cnt, int64_t count, int64_t* partial, int64_t* offs,
                   int64_t* active, int64_t n_elem, hipStream_t s, hipEvent_t start,
                   hipEvent_t stop) {
   if (scan_tile(count) == 1024)
@@ -2324,6 +2330,12 @@ hipError_t launch_tune_fill(sem_dtype dt, int order, int64_t n_elem, void* const
     hipLaunchKernelGGL(tune_fill<float>, dim3(blocks), dim3(256), 0, s, order, n_elem,
                        (float*)f[0], (float*)f[1], (float*)f[2], (float*)f[3], (float*)f[4],
                        (float*)f[5]);
+  return hipGetLastError();
+}
+
+hipError_t launch_flag_scan(const uint8_t* flag, int64_t count, int64_t* partial, int64_t* offs,
+                            hipStream_t s) {
+  scan_kernels<false>(flag, count, partial, offs, nullptr, 1, s, nullptr, nullptr);
   return hipGetLastError();
 }
 

@@ -219,6 +219,37 @@ def test_symmetric_eigensolver_matches_numpy(n):
     assert 1 <= int(sweeps.item()) < 40
 
 
+def test_codec_is_the_same_for_any_number_of_elements():
+    """Prefixes of one snapshot, element 0 holding every channel's maximum:
+    an element's packet and reconstruction do not depend on how many
+    elements a wave takes (two, or four from 8,192 on), how many waves have
+    any, or where the last pass ends."""
+    e = 8201
+    r = np.random.default_rng(33)
+    base = W.ae_fields(20, DEV, elements=np.arange(e), dtype=torch.float32)
+    params, _ = sem.ae_pca_init(sem.ae_blocks(base)[0])
+    # noise on a third of the elements: both outcomes occur
+    noise = torch.from_numpy((r.random(size=(e, 1, 1, 1)) < 0.3).astype(np.float32)).to(DEV)
+    f = []
+    for b in base:
+        t = b + 0.05 * noise * torch.from_numpy(
+            r.normal(size=(e, 8, 8, 8)).astype(np.float32)).to(DEV)
+        t[0] *= 50.0
+        f.append(t.contiguous())
+    full = sem.ae_compress(f, params)
+    rec = sem.ae_decompress(full, params)
+    assert 0.05 < float(full["flags"].float().mean()) < 0.95
+    raw_at = torch.cumsum(full["flags"].long(), 0)
+    for k in (1, 2, 3, 511, 513, 1024, 2050, 4097, 8192, 8193):
+        part = sem.ae_compress([t[:k].contiguous() for t in f], params)
+        for key in ("latent", "scale", "flags"):
+            assert torch.equal(part[key], full[key][:k]), (k, key)
+        assert part["n_raw"] == int(raw_at[k - 1])
+        assert torch.equal(part["raw"], full["raw"][:part["n_raw"]]), k
+        for a, b in zip(sem.ae_decompress(part, params), rec):
+            assert torch.equal(a, b[:k]), k
+
+
 def _octant_low_rank(b, seed):
     import test_oracle_ae as T
     return T._low_rank_blocks(b, 24, seed, noise=1e-4).astype(np.float32)
