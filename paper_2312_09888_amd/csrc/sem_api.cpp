@@ -714,7 +714,7 @@ int sem_dsavg(int64_t n_elem, int order, sem_dtype dt, const void* gs, int64_t n
   if (!current_tables()) return SEM_ERR_NOT_INIT;
   const int64_t p = order + 1;
   const GsLayout l = gs_layout(const_cast<void*>(gs), n_elem * p * p * p, n_global);
-  const hipError_t e = launch_dsavg(dt == SEM_F64 ? SEM_F64 : SEM_F32, n_global, l, field, out,
+  const hipError_t e = launch_dsavg(dt == SEM_F64 ? SEM_F64 : SEM_F32, l, field, out,
                                     static_cast<hipStream_t>(stream));
   return e == hipSuccess ? SEM_OK : SEM_ERR_HIP;
 }

@@ -7,12 +7,16 @@
 // over all copies of its node, which makes per-element derived fields
 // continuous and their isosurfaces closed across element faces.
 //
-// sem_gs_setup turns the ids into a compressed row structure (copies of a
-// global node listed in increasing storage order), so every average is
-// summed in one fixed order and the result does not depend on scheduling.
+// sem_gs_setup lists the copies of every shared node in increasing storage
+// order, so every average is summed in one fixed order and the result does
+// not depend on scheduling.  The structure follows the storage: 64 stored
+// nodes have one word of flags that says which of them are the first copy of
+// their node and which of those have other copies; only the other copies are
+// listed by index, in 32 bits (a launch covers fewer than 2^32 work-items, so
+// there are never more nodes).
 // Welding numbers the distinct global edge keys of a triangle soup in order
-// of first occurrence: a hash table records each key's first corner, a flag
-// marks those corners, and their exclusive prefix gives the vertex index.
+// of first occurrence: a hash table records each key's first corner, flags
+// mark those corners, and their exclusive prefix gives the vertex index.
 #include <hip/hip_runtime.h>
 
 #include "sem_internal.h"
@@ -22,24 +26,60 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr uint64_t kEmpty = ~0ull;
+constexpr int kGsWords = 4;              // flag words (64 nodes each) a wave averages at once
+constexpr int kGsExt = 2048;             // listed copies a workgroup holds in LDS
+constexpr int kWeldT = 512;              // threads of weld_insert
+constexpr int kWeldPer = 4;              // corners of each of them
+constexpr int kWeldRefs = kWeldT * kWeldPer;
 
 inline unsigned blocks_for(int64_t n) {
   return (unsigned)((n + kThreads - 1) / kThreads > 0 ? (n + kThreads - 1) / kThreads : 1);
 }
 
-__global__ void fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) p[i] = v;
+__host__ __device__ constexpr size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
+
+// the listed copies follow the flag words
+__device__ __forceinline__ const uint32_t* gs_col(const GsWord* words, int64_t n_words) {
+  return reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(words) +
+                                           al256((size_t)(n_words + 1) * sizeof(GsWord)));
 }
 
-__global__ void fill_u64(uint64_t* __restrict__ p, int64_t n, uint64_t v) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) p[i] = v;
+// Workgroups go to the eight XCDs in turn; this gives each XCD runs of 64
+// neighbouring ones, so that most copies of a node meet in one L2 while the
+// XCDs stay close enough in the mesh to meet in the shared cache (32,768
+// elements of order 7 in FP64: 100 us without, 98 with an eighth of the mesh
+// per XCD, 92 with runs of 64).
+__device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned n) {
+  constexpr unsigned kRun = 64, kRound = 8 * kRun;
+  if (b >= n / kRound * kRound) return b;
+  const unsigned z = b % kRound;
+  return b - z + (z % 8) * kRun + z / 8;
 }
 
-// copies per global node
+// all ones in n pairs of words
+__global__ void fill_ones(uint64_t* __restrict__ p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i < n) p[2 * i] = p[2 * i + 1] = ~0ull;
+}
+
+__device__ __forceinline__ int below(uint64_t mask, int lane) {
+  return __popcll(mask & ((1ull << lane) - 1));
+}
+
+__global__ void gs_clear(int64_t n_global, uint32_t* __restrict__ cnt,
+                         uint32_t* __restrict__ first, GsHead* __restrict__ head,
+                         int64_t n_words) {
+  const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (g == 0) head->n_words = n_words;
+  if (g >= n_global) return;
+  cnt[g] = 0;
+  first[g] = ~0u;
+}
+
+// copies of each global node, and the first of them
 __global__ void gs_count(int64_t n_nodes, const int64_t* __restrict__ gid, int64_t n_global,
-                         int32_t* __restrict__ cnt, int32_t* __restrict__ status) {
+                         uint32_t* __restrict__ cnt, uint32_t* __restrict__ first,
+                         int32_t* __restrict__ status) {
   const int64_t n = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (n >= n_nodes) return;
   const int64_t g = gid[n];
@@ -47,28 +87,83 @@ __global__ void gs_count(int64_t n_nodes, const int64_t* __restrict__ gid, int64
     if (status) atomicOr(status, SEM_FLAG_BAD_ID);
     return;
   }
-  atomicAdd(&cnt[g], 1);
+  atomicAdd(&cnt[g], 1u);
+  atomicMin(&first[g], (uint32_t)n);
 }
 
-// place every copy in its node's row (arbitrary order within the row)
+// flags of 64 stored nodes a wave, and how many rows and listed copies they start
+__global__ void gs_words(int64_t n_nodes, const int64_t* __restrict__ gid, int64_t n_global,
+                         const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ first,
+                         GsWord* __restrict__ words, int32_t* __restrict__ rows,
+                         int32_t* __restrict__ copies) {
+  const int64_t n = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t g = n < n_nodes ? gid[n] : -1;
+  const bool own = g >= 0 && g < n_global && first[g] == (uint32_t)n;
+  const int others = own ? (int)cnt[g] - 1 : 0;
+  const uint64_t mo = __ballot(own), ms = __ballot(others > 0);
+  int sum = others;
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+  if ((threadIdx.x & 63) == 0 && n < n_nodes) {
+    words[n >> 6].own = mo;
+    words[n >> 6].shared = ms;
+    rows[n >> 6] = __popcll(ms);
+    copies[n >> 6] = sum;
+  }
+}
+
+// where the row of each shared node starts (first[] of its node then holds
+// that too, and cnt[] the cursor of the copies that gs_fill places)
+__global__ void gs_rows(int64_t n_nodes, const int64_t* __restrict__ gid, int64_t n_words,
+                        const int64_t* __restrict__ row0, const int64_t* __restrict__ copy0,
+                        GsWord* __restrict__ words, uint32_t* __restrict__ cnt,
+                        uint32_t* __restrict__ first, uint32_t* __restrict__ rowptr) {
+  const int64_t n = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t w = n >> 6;
+  const int lane = threadIdx.x & 63;
+  if (n == 0) {
+    rowptr[row0[n_words]] = (uint32_t)copy0[n_words];
+    words[n_words].copy = (uint32_t)copy0[n_words];
+  }
+  if (w >= n_words) return;
+  const uint64_t ms = words[w].shared;
+  const bool sh = (ms >> lane) & 1;
+  const int64_t g = sh ? gid[n] : 0;
+  const int others = sh ? (int)cnt[g] - 1 : 0;
+  int pre = others;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int up = __shfl_up(pre, d);
+    if (lane >= d) pre += up;
+  }
+  if (lane == 0) {
+    words[w].rank = (uint32_t)row0[w];
+    words[w].copy = (uint32_t)copy0[w];
+  }
+  if (!sh) return;
+  const uint32_t start = (uint32_t)(copy0[w] + pre - others);
+  rowptr[row0[w] + below(ms, lane)] = start;
+  first[g] = start;
+  cnt[g] = 0;
+}
+
+// place every later copy in its node's row (arbitrary order within the row)
 __global__ void gs_fill(int64_t n_nodes, const int64_t* __restrict__ gid, int64_t n_global,
-                        const int64_t* __restrict__ rowptr, int32_t* __restrict__ cursor,
-                        int64_t* __restrict__ col) {
+                        const GsWord* __restrict__ words, const uint32_t* __restrict__ start,
+                        uint32_t* __restrict__ cursor, uint32_t* __restrict__ col) {
   const int64_t n = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (n >= n_nodes) return;
   const int64_t g = gid[n];
-  if (g < 0 || g >= n_global) return;
-  col[rowptr[g] + atomicAdd(&cursor[g], 1)] = n;
+  if (g < 0 || g >= n_global || ((words[n >> 6].own >> (n & 63)) & 1)) return;
+  col[start[g] + atomicAdd(&cursor[g], 1u)] = (uint32_t)n;
 }
 
 // order each row by storage index (rows are short: the copies of one node)
-__global__ void gs_sort(int64_t n_global, const int64_t* __restrict__ rowptr,
-                        int64_t* __restrict__ col) {
-  const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (g >= n_global) return;
-  const int64_t a = rowptr[g], b = rowptr[g + 1];
+__global__ void gs_sort(const int64_t* __restrict__ n_rows, const uint32_t* __restrict__ rowptr,
+                        uint32_t* __restrict__ col) {
+  const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (r >= *n_rows) return;
+  const int64_t a = rowptr[r], b = rowptr[r + 1];
   for (int64_t i = a + 1; i < b; ++i) {
-    const int64_t v = col[i];
+    const uint32_t v = col[i];
     int64_t j = i - 1;
     while (j >= a && col[j] > v) {
       col[j + 1] = col[j];
@@ -78,19 +173,83 @@ __global__ void gs_sort(int64_t n_global, const int64_t* __restrict__ rowptr,
   }
 }
 
-// mean over the copies of each global node, summed in storage order, then
-// written back to every copy (in may equal out)
+// Mean over the copies of each global node, summed in storage order, then
+// written back to every copy (in may equal out: a node's copies are read and
+// written by one workgroup, that of its first copy).  The listed copies of a
+// workgroup's rows are contiguous, so they are read and written as one flat
+// list through LDS: a lane that walks its own row instead waits for up to
+// seven loads one after the other, and the wave for its longest row.  Only a
+// list that does not fit is walked by row.  Bound by the field once in and
+// once out plus 2.6 bytes a node of structure (62 us at copy rate for 32,768
+// elements of order 7 in FP64).  Measured there: 162 us with 64-bit rows for
+// all global nodes, 195 with words and per-lane walks, 92 so; the rest is
+// the chain flags -> list -> copies -> average -> copies of each workgroup
+// (8 words a wave: 121 us, too few waves; 2 words: 107).
 template <typename T>
-__global__ void dsavg_k(int64_t n_global, const int64_t* __restrict__ rowptr,
-                        const int64_t* __restrict__ col, const T* in, T* out) {
-  const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (g >= n_global) return;
-  const int64_t a = rowptr[g], b = rowptr[g + 1];
-  if (a == b) return;
-  T s = T(0);
-  for (int64_t i = a; i < b; ++i) s += in[col[i]];
-  const T avg = s / (T)(b - a);
-  for (int64_t i = a; i < b; ++i) out[col[i]] = avg;
+__global__ void __launch_bounds__(kThreads)
+    dsavg_k(const GsHead* __restrict__ head, const uint32_t* __restrict__ rowptr,
+            const GsWord* __restrict__ words, const T* in, T* out) {
+  __shared__ T ext[kGsExt];
+  const int64_t n_words = head->n_words;
+  const uint32_t* __restrict__ col = gs_col(words, n_words);
+  const int t = threadIdx.x, lane = t & 63;
+  constexpr int kBlockWords = kGsWords * (kThreads / 64);
+  for (int64_t b0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kBlockWords; b0 < n_words;
+       b0 += (int64_t)gridDim.x * kBlockWords) {
+    const int64_t w0 = b0 + __builtin_amdgcn_readfirstlane(t >> 6) * kGsWords;
+    const uint32_t c0 = words[b0].copy;
+    const uint32_t n_ext = words[b0 + kBlockWords <= n_words ? b0 + kBlockWords : n_words].copy - c0;
+    const bool flat = n_ext <= kGsExt;
+    GsWord g[kGsWords];
+    T v[kGsWords];
+    uint32_t a[kGsWords], b[kGsWords];
+#pragma unroll
+    for (int k = 0; k < kGsWords; ++k) {
+      g[k].own = g[k].shared = 0;
+      g[k].rank = 0;
+      if (w0 + k < n_words) g[k] = words[w0 + k];
+      if ((g[k].own >> lane) & 1) v[k] = in[(w0 + k) * 64 + lane];
+      if ((g[k].shared >> lane) & 1) {
+        const uint32_t r = g[k].rank + below(g[k].shared, lane);
+        a[k] = rowptr[r] - c0;
+        b[k] = rowptr[r + 1] - c0;
+      }
+    }
+    uint32_t c[kGsExt / kThreads];
+    if (flat) {
+#pragma unroll
+      for (int j = 0; j < kGsExt / kThreads; ++j)
+        if (t + j * kThreads < n_ext) c[j] = col[c0 + t + j * kThreads];
+#pragma unroll
+      for (int j = 0; j < kGsExt / kThreads; ++j)
+        if (t + j * kThreads < n_ext) ext[t + j * kThreads] = in[c[j]];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kGsWords; ++k) {
+      if (!((g[k].own >> lane) & 1)) continue;
+      T s = T(0) + v[k];
+      if ((g[k].shared >> lane) & 1) {
+        if (flat) {
+          for (uint32_t i = a[k]; i < b[k]; ++i) s += ext[i];
+          s = s / (T)(b[k] - a[k] + 1);
+          for (uint32_t i = a[k]; i < b[k]; ++i) ext[i] = s;
+        } else {
+          for (uint32_t i = a[k]; i < b[k]; ++i) s += in[col[c0 + i]];
+          s = s / (T)(b[k] - a[k] + 1);
+          for (uint32_t i = a[k]; i < b[k]; ++i) out[col[c0 + i]] = s;
+        }
+      }
+      out[(w0 + k) * 64 + lane] = s;
+    }
+    __syncthreads();
+    if (flat) {
+#pragma unroll
+      for (int j = 0; j < kGsExt / kThreads; ++j)
+        if (t + j * kThreads < n_ext) out[c[j]] = ext[t + j * kThreads];
+    }
+    __syncthreads();
+  }
 }
 
 // element-local key (e P^3 + n_lo) * 3 + axis  ->  (min gid << 32) | max gid
@@ -129,121 +288,206 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-// table slot of every corner's key (linear probing; the table is at least
-// twice the number of corners, so a free slot is always reached), and the
-// smallest corner index per key
-__global__ void weld_insert(int64_t n_ref, const uint64_t* __restrict__ keys,
-                            uint64_t* __restrict__ tkey, uint64_t* __restrict__ tpos,
-                            int32_t* __restrict__ slot, int64_t cap,
-                            int32_t* __restrict__ status) {
-  const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (r >= n_ref) return;
-  const uint64_t k = keys[r];
-  if (k == kEmpty) {
-    if (status) atomicOr(status, SEM_FLAG_BAD_ID);
-    slot[r] = -1;
-    return;
+// Table slot of every corner's key (linear probing; the table is at least
+// twice the number of corners, so a free slot is always reached).  A slot
+// holds the smallest corner of its key, and the key is looked up there: one
+// atomic claims a slot and records the corner, and an entry is 4 bytes.  A
+// workgroup finds the distinct keys of its kWeldRefs consecutive corners in
+// LDS first, in the same way (also at most half full), and only the first
+// corner of each goes to the table in memory; local[] marks these corners,
+// 64 to a word.  535,000 triangles of two isovalues: 165 us with an atomic
+// each for key and corner of every corner, 48 with the distinct keys of a
+// workgroup only, 26 with the key looked up at the corner.
+__global__ void __launch_bounds__(kWeldT)
+    weld_insert(int64_t n_ref, const uint64_t* __restrict__ keys, uint32_t* __restrict__ table,
+                int32_t* __restrict__ slot, uint64_t* __restrict__ local, int64_t cap,
+                int32_t* __restrict__ status) {
+  __shared__ uint64_t lkey[kWeldRefs];
+  __shared__ uint32_t lpos[2 * kWeldRefs];
+  const int t = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * kWeldRefs;
+  uint64_t k[kWeldPer], hash[kWeldPer];
+  uint32_t ls[kWeldPer];
+  bool own[kWeldPer], bad = false;
+#pragma unroll
+  for (int j = 0; j < kWeldPer; ++j) {
+    const int64_t r = base + j * kWeldT + t;
+    k[j] = r < n_ref ? keys[r] : kEmpty;
+    bad |= r < n_ref && k[j] == kEmpty;
+    hash[j] = mix64(k[j]);
+    lkey[j * kWeldT + t] = k[j];
+    lpos[2 * j * kWeldT + t] = lpos[(2 * j + 1) * kWeldT + t] = ~0u;
   }
-  const uint64_t mask = (uint64_t)cap - 1;
-  uint64_t h = mix64(k) & mask;
-  for (int64_t probe = 0; probe < cap; ++probe) {
-    const uint64_t prev = atomicCAS((unsigned long long*)&tkey[h], (unsigned long long)kEmpty,
-                                    (unsigned long long)k);
-    if (prev == kEmpty || prev == k) {
-      atomicMin((unsigned long long*)&tpos[h], (unsigned long long)r);
-      slot[r] = (int32_t)h;
-      return;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kWeldPer; ++j) {
+    if (k[j] == kEmpty) continue;
+    const uint32_t me = j * kWeldT + t;
+    uint32_t h = (uint32_t)(hash[j] >> 40) & (2 * kWeldRefs - 1);
+    for (;;) {   // ends: at most kWeldRefs of the 2 kWeldRefs entries are taken
+      const uint32_t prev = atomicCAS(&lpos[h], ~0u, me);
+      if (prev == ~0u) break;
+      if (lkey[prev] == k[j]) {
+        if (me < prev) atomicMin(&lpos[h], me);
+        break;
+      }
+      h = (h + 1) & (2 * kWeldRefs - 1);
     }
-    h = (h + 1) & mask;
+    ls[j] = h;
   }
-  slot[r] = -1;   // unreachable with a half-empty table
-  if (status) atomicOr(status, SEM_FLAG_BAD_ID);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kWeldPer; ++j)
+    own[j] = k[j] != kEmpty && lpos[ls[j]] == (uint32_t)(j * kWeldT + t);
+  __syncthreads();
+  const uint64_t mask = (uint64_t)cap - 1;
+  uint32_t prev[kWeldPer];
+#pragma unroll
+  for (int j = 0; j < kWeldPer; ++j)
+    if (own[j])
+      prev[j] = atomicCAS(&table[hash[j] & mask], ~0u, (uint32_t)(base + j * kWeldT + t));
+#pragma unroll
+  for (int j = 0; j < kWeldPer; ++j) {
+    const int64_t r = base + j * kWeldT + t;
+    const uint64_t marks = __ballot(own[j]);
+    if ((t & 63) == 0 && r < n_ref) local[r >> 6] = marks;
+    if (!own[j]) continue;
+    uint64_t h = hash[j] & mask;
+    for (int64_t probe = 1; prev[j] != ~0u; ++probe) {
+      if (keys[prev[j]] == k[j]) {
+        if ((uint32_t)r < prev[j]) atomicMin(&table[h], (uint32_t)r);
+        break;
+      }
+      if (probe == cap) break;   // not reached in a half-empty table
+      h = (h + 1) & mask;
+      prev[j] = atomicCAS(&table[h], ~0u, (uint32_t)r);
+    }
+    lpos[ls[j]] = (uint32_t)h;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kWeldPer; ++j) {
+    const int64_t r = base + j * kWeldT + t;
+    if (r < n_ref) slot[r] = k[j] != kEmpty ? (int32_t)lpos[ls[j]] : -1;
+  }
+  if (bad && status) atomicOr(status, SEM_FLAG_BAD_ID);
 }
 
-__global__ void weld_flag(int64_t n_ref, const int32_t* __restrict__ slot,
-                          const uint64_t* __restrict__ tpos, int32_t* __restrict__ flag) {
+// first corners of the keys, 64 corners a wave
+__global__ void weld_flag(int64_t n_words, const int32_t* __restrict__ slot,
+                          const uint32_t* __restrict__ table, uint64_t* __restrict__ marks,
+                          int32_t* __restrict__ count) {
   const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (r >= n_ref) return;
-  const int32_t h = slot[r];
-  flag[r] = (h >= 0 && tpos[h] == (uint64_t)r) ? 1 : 0;
+  const int64_t w = r >> 6;
+  if (w >= n_words) return;
+  bool first = false;
+  if ((marks[w] >> (r & 63)) & 1) first = table[slot[r]] == (uint32_t)r;
+  const uint64_t m = __ballot(first);
+  if ((r & 63) == 0) {
+    marks[w] = m;
+    count[w] = __popcll(m);
+  }
 }
 
+// number the vertices (in the table, in place of their corners) and write their coordinates
 template <typename T>
-__global__ void weld_emit(int64_t n_ref, const int32_t* __restrict__ slot,
-                          const uint64_t* __restrict__ tpos, const int64_t* __restrict__ offs,
-                          const T* __restrict__ tri_xyz, int64_t* __restrict__ tri_index,
-                          T* __restrict__ vert_xyz, int64_t vert_cap) {
+__global__ void weld_emit(int64_t n_words, const int32_t* __restrict__ slot,
+                          const uint64_t* __restrict__ marks, const int64_t* __restrict__ offs,
+                          const T* __restrict__ tri_xyz, uint32_t* __restrict__ table,
+                          T* __restrict__ vert_xyz, int64_t vert_cap,
+                          int64_t* __restrict__ n_vert, int32_t* __restrict__ status) {
   const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (r >= n_ref) return;
-  const int32_t h = slot[r];
-  if (h < 0) {
-    tri_index[r] = -1;
-    return;
+  if (r == 0) {
+    const int64_t total = offs[n_words];
+    *n_vert = total;
+    if (status && total > vert_cap) atomicOr(status, SEM_FLAG_VERT_OVERFLOW);
   }
-  const int64_t first = (int64_t)tpos[h];
-  const int64_t v = offs[first];
-  tri_index[r] = v;
-  if (first == r && v < vert_cap) {
+  const int64_t w = r >> 6;
+  if (w >= n_words) return;
+  const uint64_t m = marks[w];
+  if (!((m >> (r & 63)) & 1)) return;
+  const int64_t v = offs[w] + below(m, (int)(r & 63));
+  table[slot[r]] = (uint32_t)v;
+  if (v < vert_cap) {
     vert_xyz[3 * v] = tri_xyz[3 * r];
     vert_xyz[3 * v + 1] = tri_xyz[3 * r + 1];
     vert_xyz[3 * v + 2] = tri_xyz[3 * r + 2];
   }
 }
 
-__global__ void weld_total(const int64_t* __restrict__ offs, int64_t n_ref,
-                           int64_t* __restrict__ n_vert, int64_t vert_cap,
-                           int32_t* __restrict__ status) {
-  const int64_t total = offs[n_ref];
-  *n_vert = total;
-  if (status && total > vert_cap) atomicOr(status, SEM_FLAG_VERT_OVERFLOW);
+__global__ void weld_index(int64_t n_ref, const int32_t* __restrict__ slot,
+                           const uint32_t* __restrict__ table, int64_t* __restrict__ tri_index) {
+  const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (r >= n_ref) return;
+  const int32_t h = slot[r];
+  tri_index[r] = h < 0 ? -1 : (int64_t)table[h];
 }
-
-size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
 }  // namespace
 
 GsLayout gs_layout(void* base, int64_t n_nodes, int64_t n_global) {
   GsLayout l;
-  const size_t b_cnt = al256((size_t)n_global * sizeof(int32_t));
-  const size_t b_row = al256((size_t)(n_global + 1) * sizeof(int64_t));
-  const size_t b_par = al256((size_t)(scan_partials_capacity(n_global) + 1) * sizeof(int64_t));
-  const size_t b_col = al256((size_t)n_nodes * sizeof(int64_t));
   char* p = static_cast<char*>(base);
-  l.cnt = reinterpret_cast<int32_t*>(p);
-  l.rowptr = reinterpret_cast<int64_t*>(p ? p + b_cnt : nullptr);
-  l.partial = reinterpret_cast<int64_t*>(p ? p + b_cnt + b_row : nullptr);
-  l.col = reinterpret_cast<int64_t*>(p ? p + b_cnt + b_row + b_par : nullptr);
-  l.bytes = b_cnt + b_row + b_par + b_col;
+  size_t o = 0;
+  auto take = [&](size_t bytes) {
+    char* q = p ? p + o : nullptr;
+    o += al256(bytes);
+    return q;
+  };
+  const int64_t nw = (n_nodes + 63) / 64;
+  l.n_words = nw;
+  l.head = reinterpret_cast<GsHead*>(take(sizeof(GsHead)));
+  l.cnt = reinterpret_cast<uint32_t*>(take((size_t)n_global * 4));
+  l.first = reinterpret_cast<uint32_t*>(take((size_t)n_global * 4));
+  l.rowptr = reinterpret_cast<uint32_t*>(take((size_t)(n_global + 1) * 4));
+  l.words = reinterpret_cast<GsWord*>(take((size_t)(nw + 1) * sizeof(GsWord)));
+  l.col = reinterpret_cast<uint32_t*>(take((size_t)n_nodes * 4));
+  l.rows = reinterpret_cast<int32_t*>(take((size_t)nw * 4));
+  l.copies = reinterpret_cast<int32_t*>(take((size_t)nw * 4));
+  l.row0 = reinterpret_cast<int64_t*>(take((size_t)(nw + 1) * 8));
+  l.copy0 = reinterpret_cast<int64_t*>(take((size_t)(nw + 1) * 8));
+  l.partial = reinterpret_cast<int64_t*>(take((size_t)(scan_partials_capacity(nw) + 1) * 8));
+  l.bytes = o;
   return l;
 }
 
 hipError_t launch_gs_setup(int64_t n_nodes, const int64_t* gid, int64_t n_global,
                            const GsLayout& gs, int32_t* status, hipStream_t s) {
-  hipLaunchKernelGGL(fill_i32, dim3(blocks_for(n_global)), dim3(kThreads), 0, s, gs.cnt,
-                     n_global, 0);
-  hipLaunchKernelGGL(gs_count, dim3(blocks_for(n_nodes)), dim3(kThreads), 0, s, n_nodes, gid,
-                     n_global, gs.cnt, status);
-  hipError_t e = launch_exclusive_scan(gs.cnt, n_global, gs.partial, gs.rowptr, s);
+  if (n_nodes > (int64_t)0xffffff00) return hipErrorInvalidConfiguration;
+  const unsigned nb = blocks_for(n_nodes);
+  hipLaunchKernelGGL(gs_clear, dim3(blocks_for(n_global)), dim3(kThreads), 0, s, n_global,
+                     gs.cnt, gs.first, gs.head, gs.n_words);
+  if (n_nodes == 0) return hipGetLastError();
+  hipLaunchKernelGGL(gs_count, dim3(nb), dim3(kThreads), 0, s, n_nodes, gid, n_global, gs.cnt,
+                     gs.first, status);
+  hipLaunchKernelGGL(gs_words, dim3(nb), dim3(kThreads), 0, s, n_nodes, gid, n_global,
+                     (const uint32_t*)gs.cnt, (const uint32_t*)gs.first, gs.words, gs.rows,
+                     gs.copies);
+  hipError_t e = launch_exclusive_scan(gs.rows, gs.n_words, gs.partial, gs.row0, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fill_i32, dim3(blocks_for(n_global)), dim3(kThreads), 0, s, gs.cnt,
-                     n_global, 0);
-  hipLaunchKernelGGL(gs_fill, dim3(blocks_for(n_nodes)), dim3(kThreads), 0, s, n_nodes, gid,
-                     n_global, gs.rowptr, gs.cnt, gs.col);
-  hipLaunchKernelGGL(gs_sort, dim3(blocks_for(n_global)), dim3(kThreads), 0, s, n_global,
-                     gs.rowptr, gs.col);
+  e = launch_exclusive_scan(gs.copies, gs.n_words, gs.partial, gs.copy0, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gs_rows, dim3(nb), dim3(kThreads), 0, s, n_nodes, gid, gs.n_words,
+                     (const int64_t*)gs.row0, (const int64_t*)gs.copy0, gs.words, gs.cnt,
+                     gs.first, gs.rowptr);
+  hipLaunchKernelGGL(gs_fill, dim3(nb), dim3(kThreads), 0, s, n_nodes, gid, n_global,
+                     (const GsWord*)gs.words, (const uint32_t*)gs.first, gs.cnt, gs.col);
+  hipLaunchKernelGGL(gs_sort, dim3(blocks_for(n_global)), dim3(kThreads), 0, s,
+                     (const int64_t*)gs.row0 + gs.n_words, (const uint32_t*)gs.rowptr, gs.col);
   return hipGetLastError();
 }
 
-hipError_t launch_dsavg(sem_dtype dt, int64_t n_global, const GsLayout& gs, const void* in,
-                        void* out, hipStream_t s) {
+hipError_t launch_dsavg(sem_dtype dt, const GsLayout& gs, const void* in, void* out,
+                        hipStream_t s) {
+  const unsigned nb = blocks_for((gs.n_words * 64 + kGsWords - 1) / kGsWords);
   if (dt == SEM_F64)
-    hipLaunchKernelGGL(dsavg_k<double>, dim3(blocks_for(n_global)), dim3(kThreads), 0, s,
-                       n_global, (const int64_t*)gs.rowptr, (const int64_t*)gs.col,
-                       (const double*)in, (double*)out);
+    hipLaunchKernelGGL(dsavg_k<double>, dim3(nb), dim3(kThreads), 0, s, (const GsHead*)gs.head,
+                       (const uint32_t*)gs.rowptr, (const GsWord*)gs.words, (const double*)in,
+                       (double*)out);
   else
-    hipLaunchKernelGGL(dsavg_k<float>, dim3(blocks_for(n_global)), dim3(kThreads), 0, s,
-                       n_global, (const int64_t*)gs.rowptr, (const int64_t*)gs.col,
-                       (const float*)in, (float*)out);
+    hipLaunchKernelGGL(dsavg_k<float>, dim3(nb), dim3(kThreads), 0, s, (const GsHead*)gs.head,
+                       (const uint32_t*)gs.rowptr, (const GsWord*)gs.words, (const float*)in,
+                       (float*)out);
   return hipGetLastError();
 }
 
@@ -260,58 +504,62 @@ WeldLayout weld_layout(void* base, int64_t n_ref) {
   int64_t cap = 64;
   while (cap < 2 * n_ref) cap <<= 1;
   w.cap = cap;
-  const size_t b_key = al256((size_t)cap * sizeof(uint64_t));
-  const size_t b_slot = al256((size_t)n_ref * sizeof(int32_t));
-  const size_t b_offs = al256((size_t)(n_ref + 1) * sizeof(int64_t));
-  const size_t b_par = al256((size_t)(scan_partials_capacity(n_ref) + 1) * sizeof(int64_t));
+  w.n_words = (n_ref + 63) / 64;
   char* p = static_cast<char*>(base);
   size_t o = 0;
-  w.key = reinterpret_cast<uint64_t*>(p ? p + o : nullptr);
-  o += b_key;
-  w.pos = reinterpret_cast<uint64_t*>(p ? p + o : nullptr);
-  o += b_key;
-  w.slot = reinterpret_cast<int32_t*>(p ? p + o : nullptr);
-  o += b_slot;
-  w.flag = reinterpret_cast<int32_t*>(p ? p + o : nullptr);
-  o += b_slot;
-  w.offs = reinterpret_cast<int64_t*>(p ? p + o : nullptr);
-  o += b_offs;
-  w.partial = reinterpret_cast<int64_t*>(p ? p + o : nullptr);
-  o += b_par;
-  w.bytes = o;
+  auto take = [&](size_t bytes) {
+    char* q = p ? p + o : nullptr;
+    o += al256(bytes);
+    return q;
+  };
+  w.table = reinterpret_cast<uint32_t*>(take((size_t)cap * 4));
+  w.slot = reinterpret_cast<int32_t*>(take((size_t)n_ref * 4));
+  w.marks = reinterpret_cast<uint64_t*>(take((size_t)w.n_words * 8));
+  w.count = reinterpret_cast<int32_t*>(take((size_t)w.n_words * 4));
+  w.offs = reinterpret_cast<int64_t*>(take((size_t)(w.n_words + 1) * 8));
+  w.partial =
+      reinterpret_cast<int64_t*>(take((size_t)(scan_partials_capacity(w.n_words) + 1) * 8));
+  // callers may count on 16 bytes a corner and as many a table slot
+  const size_t told = (size_t)n_ref * 16 + (size_t)cap * 16;
+  w.bytes = o > told ? o : told;
   return w;
 }
+
+namespace {
+template <typename T>
+hipError_t weld_t(int64_t n_ref, const T* tri_xyz, const uint64_t* keys, int64_t* tri_index,
+                  T* vert_xyz, int64_t vert_cap, int64_t* n_vert, const WeldLayout& w,
+                  int32_t* status, hipStream_t s) {
+  if (n_ref > 0) {
+    hipLaunchKernelGGL(fill_ones, dim3(blocks_for(w.cap / 4)), dim3(kThreads), 0, s,
+                       reinterpret_cast<uint64_t*>(w.table), w.cap / 4);
+    hipLaunchKernelGGL(weld_insert, dim3((unsigned)((n_ref + kWeldRefs - 1) / kWeldRefs)),
+                       dim3(kWeldT), 0, s, n_ref, keys, w.table, w.slot, w.marks, w.cap, status);
+    hipLaunchKernelGGL(weld_flag, dim3(blocks_for(w.n_words * 64)), dim3(kThreads), 0, s,
+                       w.n_words, (const int32_t*)w.slot, (const uint32_t*)w.table, w.marks,
+                       w.count);
+  }
+  const hipError_t e = launch_exclusive_scan(w.count, w.n_words, w.partial, w.offs, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(weld_emit<T>, dim3(blocks_for(w.n_words * 64)), dim3(kThreads), 0, s,
+                     w.n_words, (const int32_t*)w.slot, (const uint64_t*)w.marks,
+                     (const int64_t*)w.offs, tri_xyz, w.table, vert_xyz, vert_cap, n_vert,
+                     status);
+  if (n_ref > 0)
+    hipLaunchKernelGGL(weld_index, dim3(blocks_for(n_ref)), dim3(kThreads), 0, s, n_ref,
+                       (const int32_t*)w.slot, (const uint32_t*)w.table, tri_index);
+  return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_weld(int64_t n_ref, sem_dtype dt, const void* tri_xyz, const uint64_t* keys,
                        int64_t* tri_index, void* vert_xyz, int64_t vert_cap, int64_t* n_vert,
                        const WeldLayout& w, int32_t* status, hipStream_t s) {
-  hipLaunchKernelGGL(fill_u64, dim3(blocks_for(w.cap)), dim3(kThreads), 0, s, w.key, w.cap,
-                     kEmpty);
-  hipLaunchKernelGGL(fill_u64, dim3(blocks_for(w.cap)), dim3(kThreads), 0, s, w.pos, w.cap,
-                     kEmpty);
-  if (n_ref > 0) {
-    hipLaunchKernelGGL(weld_insert, dim3(blocks_for(n_ref)), dim3(kThreads), 0, s, n_ref, keys,
-                       w.key, w.pos, w.slot, w.cap, status);
-    hipLaunchKernelGGL(weld_flag, dim3(blocks_for(n_ref)), dim3(kThreads), 0, s, n_ref,
-                       (const int32_t*)w.slot, (const uint64_t*)w.pos, w.flag);
-  }
-  hipError_t e = launch_exclusive_scan(w.flag, n_ref, w.partial, w.offs, s);
-  if (e != hipSuccess) return e;
-  if (n_ref > 0) {
-    if (dt == SEM_F64)
-      hipLaunchKernelGGL(weld_emit<double>, dim3(blocks_for(n_ref)), dim3(kThreads), 0, s,
-                         n_ref, (const int32_t*)w.slot, (const uint64_t*)w.pos,
-                         (const int64_t*)w.offs, (const double*)tri_xyz, tri_index,
-                         (double*)vert_xyz, vert_cap);
-    else
-      hipLaunchKernelGGL(weld_emit<float>, dim3(blocks_for(n_ref)), dim3(kThreads), 0, s,
-                         n_ref, (const int32_t*)w.slot, (const uint64_t*)w.pos,
-                         (const int64_t*)w.offs, (const float*)tri_xyz, tri_index,
-                         (float*)vert_xyz, vert_cap);
-  }
-  hipLaunchKernelGGL(weld_total, dim3(1), dim3(1), 0, s, (const int64_t*)w.offs, n_ref, n_vert,
-                     vert_cap, status);
-  return hipGetLastError();
+  if (dt == SEM_F64)
+    return weld_t(n_ref, (const double*)tri_xyz, keys, tri_index, (double*)vert_xyz, vert_cap,
+                  n_vert, w, status, s);
+  return weld_t(n_ref, (const float*)tri_xyz, keys, tri_index, (float*)vert_xyz, vert_cap,
+                n_vert, w, status, s);
 }
 
 }  // namespace sem

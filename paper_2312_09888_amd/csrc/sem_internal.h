@@ -175,28 +175,44 @@ hipError_t launch_tune_fill(sem_dtype dt, int order, int64_t n_elem, void* const
 
 // sem_c0.hip: gather-scatter structure built by sem_gs_setup in the
 // caller's buffer, C0 averaging, global edge keys, welding.
+struct GsHead {
+  int64_t n_words;
+};
+// flags of 64 stored nodes: first copies of their nodes, those of them that
+// have other copies, and the row and the first listed copy of the first of these
+struct GsWord {
+  uint64_t own, shared;
+  uint32_t rank, copy;
+};
 struct GsLayout {
-  int32_t* cnt;       // [n_global] copies per global node (then a fill cursor)
-  int64_t* rowptr;    // [n_global + 1] first copy of each global node
+  GsHead* head;       // what sem_dsavg needs to know of the mesh
+  uint32_t* cnt;      // [n_global] copies per global node (then a fill cursor)
+  uint32_t* first;    // [n_global] first copy per global node (then its row's start)
+  uint32_t* rowptr;   // [n_global + 1] rows of shared nodes, by their first copy
+  GsWord* words;      // [n_words + 1], of the last only `copy`
+  uint32_t* col;      // [n_nodes] storage index of the later copies, by row, ascending
+  int32_t *rows, *copies;   // [n_words] rows and listed copies of each word
+  int64_t *row0, *copy0;    // [n_words + 1] their exclusive prefixes
   int64_t* partial;   // scan partials
-  int64_t* col;       // [n_nodes] storage index of each copy, by node, ascending
+  int64_t n_words;
   size_t bytes;
 };
 GsLayout gs_layout(void* base, int64_t n_nodes, int64_t n_global);
 hipError_t launch_gs_setup(int64_t n_nodes, const int64_t* gid, int64_t n_global,
                            const GsLayout& gs, int32_t* status, hipStream_t s);
-hipError_t launch_dsavg(sem_dtype dt, int64_t n_global, const GsLayout& gs, const void* in,
-                        void* out, hipStream_t s);
+hipError_t launch_dsavg(sem_dtype dt, const GsLayout& gs, const void* in, void* out,
+                        hipStream_t s);
 hipError_t launch_global_keys(int64_t n_ref, int order, int64_t n_elem, const uint64_t* local,
                               const int64_t* gid, uint64_t* global, int32_t* status,
                               hipStream_t s);
 struct WeldLayout {
-  uint64_t* key;      // [cap] hash table keys (all ones = empty)
-  uint64_t* pos;      // [cap] first corner holding the key
+  uint32_t* table;    // [cap] first corner of a key (all ones = empty), then its vertex
   int32_t* slot;      // [n_ref] table slot of each corner
-  int32_t* flag;      // [n_ref] 1 at a key's first corner
-  int64_t* offs;      // [n_ref + 1] exclusive prefix of flag
+  uint64_t* marks;    // [n_words] keys' first corners (in a workgroup, then in all)
+  int32_t* count;     // [n_words] marks in each word
+  int64_t* offs;      // [n_words + 1] exclusive prefix of count
   int64_t* partial;
+  int64_t n_words;
   int64_t cap;
   size_t bytes;
 };

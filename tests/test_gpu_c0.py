@@ -147,3 +147,52 @@ def test_averaged_q_isosurface_end_to_end():
     ov, oi = c0.weld(o["tri_xyz"], okeys)
     np.testing.assert_array_equal(host(idx), oi)
     assert np.abs(host(verts) - ov).max() <= 1e-12 * np.abs(ov).max()
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+@pytest.mark.parametrize("n,e,pool", [(1, 1, 3), (2, 5, 40), (3, 16, 1), (4, 700, 30000),
+                                      (4, 2100, 500000)])
+def test_dsavg_of_any_numbering(dt, n, e, pool):
+    """Partial words, one node for all, ids without copies, nodes with bad ids
+    (left alone), in place and not."""
+    rng = np.random.default_rng(e)
+    gid = rng.integers(0, pool, size=(e,) + (n + 1,) * 3)
+    f = rng.normal(size=gid.shape).astype(dt)
+    bad = rng.random(gid.shape) < 0.05
+    ids = np.where(bad, rng.choice([-1, pool + 9, 1 << 40], size=gid.shape), gid)
+    want = np.full_like(f, -7)
+    want[~bad] = c0.dsavg(f[~bad], ids[~bad])
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    gs = sem.GatherScatter(dev(ids), n_global=pool + 9, status=st)
+    out = sem.dsavg(dev(f), gs, out=torch.full_like(dev(f), -7))
+    np.testing.assert_array_equal(host(out), want)
+    assert bool(int(st.item()) & sem.SEM_FLAG_BAD_ID) == bool(bad.any())
+    t = dev(f)
+    sem.dsavg(t, gs, out=t)
+    np.testing.assert_array_equal(host(t), np.where(bad, f, want))
+
+
+@pytest.mark.parametrize("n_tri", [1, 682, 683, 2048, 100001])
+@pytest.mark.parametrize("share", [1, 6, 500])
+def test_weld_of_any_keys(n_tri, share):
+    """Corners around the workgroup's number of them, from all distinct keys
+    to a few that every workgroup holds; some bad keys."""
+    n_ref = 3 * n_tri
+    rng = np.random.default_rng(n_tri + share)
+    pool = rng.integers(0, 2 ** 63, size=max(1, n_ref // share))
+    keys = pool[rng.integers(0, pool.size, size=n_ref)] if share > 1 else \
+        rng.permutation(n_ref).astype(np.int64) * 65536
+    keys[rng.random(n_ref) < 0.01] = -1
+    xyz = rng.normal(size=(n_tri, 3, 3))
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    verts, idx = sem.weld(dev(xyz), dev(keys), status=st)
+    good = np.flatnonzero(keys != -1)
+    _, at, inv = np.unique(keys[good], return_index=True, return_inverse=True)
+    order = np.argsort(at)
+    number = np.empty_like(order)
+    number[order] = np.arange(order.size)
+    want = np.full(n_ref, -1)
+    want[good] = number[inv]
+    np.testing.assert_array_equal(host(idx).ravel(), want)
+    np.testing.assert_array_equal(host(verts), xyz.reshape(-1, 3)[good[at[order]]])
+    assert bool(int(st.item()) & sem.SEM_FLAG_BAD_ID) == (good.size < n_ref)
