@@ -26,14 +26,6 @@
 namespace sem {
 namespace {
 
-template <int N>
-struct Shape {
-  static constexpr int P = N + 1;
-  static constexpr int NP = P * P * P;                // nodes per element
-  static constexpr int NC = N * N * N;                // cells per element
-  static constexpr int kCellThreads = ((NC + 63) / 64) * 64;
-};
-
 // ---------------------------------------------------------------------------
 // small device helpers
 // ---------------------------------------------------------------------------
@@ -526,29 +518,6 @@ __device__ __forceinline__ void barrier_after_wait() {
 constexpr uint64_t kEdgeLoPacked = 0x321054106420ull;
 __device__ __forceinline__ int edge_lo(int e) { return (int)((kEdgeLoPacked >> (4 * e)) & 15); }
 
-// Node offset of cube corner v in a tile with row stride RS and slab stride SS.
-template <int RS, int SS>
-__device__ __forceinline__ int corner_offset(int v) {
-  return (v & 1) + RS * ((v >> 1) & 1) + SS * ((v >> 2) & 1);
-}
-template <int P>
-__device__ __forceinline__ int corner_offset(int v) {
-  return corner_offset<P, P * P>(v);
-}
-
-// Case index of the cell whose lowest node sits at tile offset n0.
-template <int RS, int SS, typename T>
-__device__ __forceinline__ int cell_case_strided(const T* __restrict__ sf, int n0, T c) {
-  int cs = 0;
-#pragma unroll
-  for (int vtx = 0; vtx < 8; ++vtx) cs |= (sf[n0 + corner_offset<RS, SS>(vtx)] > c) << vtx;
-  return cs;
-}
-template <int N, typename T>
-__device__ __forceinline__ int cell_case(const T* __restrict__ sf, int n0, T c) {
-  return cell_case_strided<N + 1, (N + 1) * (N + 1)>(sf, n0, c);
-}
-
 // Exclusive prefix over the cells of a block of the per-cell triangle counts
 // nt (0..7): one ballot per bit gives the wave prefix; wave totals go through
 // LDS.  Returns the thread's offset; *block_total receives the block total.
@@ -651,128 +620,6 @@ struct StridedNode {
     return i + RS * j + SS * k;
   }
 };
-
-// Per (isovalue, element): triangle and active-cell counts; optional case dump.
-template <int N, typename T>
-__global__ void __launch_bounds__(Shape<N>::kCellThreads)
-iso_count(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ mm, int n_iso,
-          IsoList<T> iso, const uint8_t* __restrict__ ntri_tab, int32_t* __restrict__ cnt,
-          int64_t* __restrict__ active_total, uint8_t* __restrict__ case_idx) {
-  using S = Shape<N>;
-  constexpr int TH = S::kCellThreads;
-  __shared__ T sf[S::NP];
-  __shared__ uint32_t s_ntri4[64];
-  __shared__ T red[2 * (TH / 64)];
-  __shared__ int32_t sred[TH / 64];
-  clear_active(active_total, n_iso);
-  const int t = threadIdx.x;
-  const int64_t e = blockIdx.x;
-  const int64_t base = e * S::NP;
-  const uint8_t* s_ntri = reinterpret_cast<const uint8_t*>(s_ntri4);
-  if (t < 64) s_ntri4[t] = reinterpret_cast<const uint32_t*>(ntri_tab)[t];
-  T mn, mx;
-  bool need = true;
-  if (mm) {
-    mn = mm[2 * e];
-    mx = mm[2 * e + 1];
-    need = false;
-    for (int s = 0; s < n_iso; ++s) need = need || ((mx > iso.v[s]) && !(mn > iso.v[s]));
-  }
-  if (need)
-    for (int q = t; q < S::NP; q += TH) sf[q] = field[base + q];
-  __syncthreads();
-  if (!mm) {
-    T a = pos_inf<T>(), b = neg_inf<T>();
-    for (int q = t; q < S::NP; q += TH) {
-      T val = sf[q];
-      if (val != val) val = neg_inf<T>();
-      a = val < a ? val : a;
-      b = val > b ? val : b;
-    }
-    block_minmax<T, TH>(a, b, red);
-    mn = a;
-    mx = b;
-  }
-  const int i = t % N, j = (t / N) % N, k = t / (N * N);
-  const int n0 = i + S::P * (j + S::P * k);
-  for (int s = 0; s < n_iso; ++s) {
-    const T c = iso.v[s];
-    const bool straddle = (mx > c) && !(mn > c);
-    uint8_t* cdump = case_idx ? case_idx + ((int64_t)s * n_elem + e) * S::NC : nullptr;
-    if (!straddle) {
-      if (t == 0) cnt[(int64_t)s * n_elem + e] = 0;
-      if (cdump && t < S::NC) cdump[t] = (mx > c) ? 255 : 0;
-      continue;
-    }
-    // triangles in the low 16 bits, active cells above: one block sum
-    int packed = 0;
-    if (t < S::NC) {
-      const int cs = cell_case<N>(sf, n0, c);
-      packed = s_ntri[cs] + ((cs != 0 && cs != 255) << 16);
-      if (cdump) cdump[t] = (uint8_t)cs;
-    }
-    packed = (int)wave_sum_to63((uint32_t)packed);
-    if ((t & 63) == 63) sred[t >> 6] = packed;
-    __syncthreads();
-    if (t == 0) {
-      int sum = 0;
-#pragma unroll
-      for (int q = 0; q < TH / 64; ++q) sum += sred[q];
-      cnt[(int64_t)s * n_elem + e] = sum;
-    }
-    __syncthreads();
-  }
-}
-
-// Emit triangles of every (isovalue, element) with a nonzero count.
-template <int N, typename T>
-__global__ void __launch_bounds__(Shape<N>::kCellThreads)
-iso_emit(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
-         const T* __restrict__ z, const T* __restrict__ field, int n_iso, IsoList<T> iso,
-         const uint8_t* __restrict__ ntri_tab, const int8_t* __restrict__ tri_tab,
-         const int32_t* __restrict__ cnt, const int64_t* __restrict__ offs, IsoOut<T> out,
-         uint64_t* __restrict__ keys) {
-  using S = Shape<N>;
-  constexpr int TH = S::kCellThreads;
-  constexpr int P = S::P;
-  __shared__ T sf[S::NP], sx[S::NP], sy[S::NP], sz[S::NP];
-  __shared__ uint8_t s_ntri[256];
-  __shared__ int8_t s_tri[256 * kMcMaxTri * 3];
-  __shared__ uint8_t s_case[S::NC];
-  __shared__ uint16_t s_desc[S::NC * kMcMaxTri];
-  __shared__ int32_t s_wave[TH / 64];
-  const int t = threadIdx.x;
-  const int64_t e = blockIdx.x;
-  bool any = false;
-  for (int s = 0; s < n_iso; ++s) any = any || slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
-  if (!any) return;
-  const int64_t base = e * S::NP;
-  for (int q = t; q < 256; q += TH) s_ntri[q] = ntri_tab[q];
-  for (int q = t; q < 256 * kMcMaxTri * 3; q += TH) s_tri[q] = tri_tab[q];
-  for (int q = t; q < S::NP; q += TH) {
-    sf[q] = field[base + q];
-    sx[q] = x[base + q];
-    sy[q] = y[base + q];
-    sz[q] = z[base + q];
-  }
-  __syncthreads();
-  for (int s = 0; s < n_iso; ++s) {
-    const int64_t flat = (int64_t)s * n_elem + e;
-    if (slot_tris(cnt[flat]) == 0) continue;
-    int64_t g = offs[flat];
-    T* dst = out.ptr[0];
-    int64_t cap = out.cap[0];
-    if (out.per_iso) {
-      g -= offs[(int64_t)s * n_elem];
-      dst = out.ptr[s];
-      cap = out.cap[s];
-    }
-    emit_element<N, TH>(iso.v[s], StridedNode<P, P * P>{}, StridedNode<P, P * P>{}, sf, sx, sy,
-                        sz, s_ntri, s_tri,
-                        s_case, s_desc, s_wave, dst, g, cap, out.per_iso ? nullptr : keys,
-                        base);
-  }
-}
 
 // ---------------------------------------------------------------------------
 // device-wide exclusive scan of int32 counts into int64 offsets
@@ -932,8 +779,6 @@ __device__ __forceinline__ void dma_tile_natural(const T* __restrict__ src, T* r
   }
 }
 
-// emit_direct<N, T>: the element's tiles and the case tables by direct loads,
-// two waves per element (odd N; N = 7 FP64 uses the swizzled tile).
 // Element tile of any order into LDS for two waves: direct loads where the
 // tile is a whole number of 16-byte chunks at a 16-byte aligned address
 // (odd N), plain loads otherwise.  Consumers wait with
@@ -948,7 +793,7 @@ __device__ __forceinline__ void tile2_lds(const T* __restrict__ src, T* dst, int
   }
 }
 
-// Emission of element e (two waves): every isovalue with a nonzero count
+// Emission of element e, which has triangles (two waves): every isovalue with a nonzero count
 // writes its triangles at offs[s * n_elem + e] of out (or of out.ptr[s],
 // relative to the isovalue's first offset, when out.per_iso).
 template <int N, typename T, class IL = IsoList<T>, class OUT = IsoOut<T>>
@@ -983,9 +828,6 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
   __builtin_assume(t >= 0 && t < 128);
   const int h = __builtin_amdgcn_readfirstlane(t >> 6);
   const int p = t & 63;
-  bool any = false;
-  for (int s = 0; s < n_iso; ++s) any = any || slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
-  if (!any) return;
   const int64_t base = e * NP;
   // the triangle counts (256 B) and the tiles arrive by direct loads before
   // the one wait below; the case table (3.75 KiB) is read through the caches
@@ -1035,6 +877,11 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
   }
 }
 
+// A workgroup per element, at every order.  Most leave at once (of 65,536
+// elements of order 7, 26 % have triangles; 31 of 124 us if none has), but
+// workgroups that take several elements and look them up together are
+// slower, 133 against 120 us: the triangles of one element must be written
+// before the tiles of the next are known to be there.
 template <int N, typename T>
 __global__ void __launch_bounds__(128)
 emit_direct(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
@@ -1046,119 +893,106 @@ emit_direct(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
   // the last workgroup also writes the totals (in place of a kernel of its own)
   if (blockIdx.x == gridDim.x - 1)
     write_totals<T>(threadIdx.x, offs, n_elem, n_iso, tri_count, out, status);
-  emit_elem<N, T>(blockIdx.x, threadIdx.x, n_elem, x, y, z, field, n_iso, iso, out, ntri_tab,
-                  cnt, offs, keys);
+  const int64_t e = blockIdx.x;
+  bool any = false;
+  for (int s = 0; s < n_iso; ++s) any |= slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
+  if (any)
+    emit_elem<N, T>(e, threadIdx.x, n_elem, x, y, z, field, n_iso, iso, out, ntri_tab, cnt, offs,
+                    keys);
 }
 
-// count_direct<N, T>: the count pass of the two-pass isosurface for odd N:
-// the field tile (and the triangle-count table) by direct loads, two waves
-// per element, one packed block sum (triangles | active cells << 16) per
-// isovalue; elements the range excludes write zero counts without loading.
-template <int N, typename T, class IL = IsoList<T>>
-__device__ __forceinline__ void count_elem(int64_t e, int t, int64_t n_elem,
-                                           const T* __restrict__ field, const T* __restrict__ mm,
-                                           int n_iso, const IL& iso,
-                                           const uint8_t* __restrict__ ntri_tab,
-                                           int32_t* __restrict__ cnt,
-                                           uint8_t* __restrict__ case_idx) {
-  constexpr int P = N + 1, NP = P * P * P, NC = N * N * N, R = (NC + 127) / 128;
-  __shared__ __attribute__((aligned(16))) T sf[NP];
-  __shared__ __attribute__((aligned(16))) uint8_t s_ntri[256];
-  __shared__ T red[4];
-  __shared__ int32_t s_sum[2];
-  __builtin_assume(t >= 0 && t < 128);
-  const int h = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int lane = t & 63;
-  T mn = pos_inf<T>(), mx = neg_inf<T>();
-  bool need = true;
-  if (mm) {
-    mn = mm[2 * e];
-    mx = mm[2 * e + 1];
-    need = false;
-    for (int s = 0; s < n_iso; ++s) need = need || ((mx > iso.v[s]) && !(mn > iso.v[s]));
+// Counts of the elements `mine` of a wave's lanes (in == false: none) at
+// every isovalue, and their cells' cases if case_idx.  The lanes look their
+// elements' ranges up at once; elements that no isovalue crosses get zero
+// counts without being read, the others are counted one after the other from
+// bit rows (count_rows).  mm == NULL: every element is read (a value that is
+// not above an isovalue, NaN included, is below it).  bits: the wave's own
+// LDS.
+template <int N, typename T, class IL>
+__device__ __forceinline__ void count_lanes(int64_t mine, bool in, int lane, int64_t n_elem,
+                                            const T* __restrict__ field,
+                                            const T* __restrict__ mm, int n_iso, const IL& iso,
+                                            const uint8_t* tab, uint64_t* bits,
+                                            int32_t* __restrict__ cnt,
+                                            uint8_t* __restrict__ case_idx) {
+  constexpr int P = N + 1, NP = P * P * P, NC = N * N * N, R = (NP + 63) / 64;
+  T lo = neg_inf<T>(), hi = pos_inf<T>();
+  if (mm && in) {
+    lo = mm[2 * mine];
+    hi = mm[2 * mine + 1];
   }
-  if (!need) {
-    // no isovalue inside the element's range: zero counts, uniform cases
-    for (int s = 0; s < n_iso; ++s) {
-      if (t == 0) cnt[(int64_t)s * n_elem + e] = 0;
-      if (case_idx) {
-        uint8_t* cd = case_idx + ((int64_t)s * n_elem + e) * NC;
-        const uint8_t v = (mx > iso.v[s]) ? 255 : 0;
-        for (int q = t; q < NC; q += 128) cd[q] = v;
-      }
-    }
-    return;
-  }
-  if (h == 0 && lane < 16)
-    lds_load16(reinterpret_cast<const double*>(ntri_tab) + 2 * lane,
-               reinterpret_cast<double*>(s_ntri));
-  tile2_lds<N>(field + e * NP, sf, h, lane);
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
-  barrier_after_wait();
-  if (!mm) {
-    T a = pos_inf<T>(), b = neg_inf<T>();
-    for (int q = t; q < NP; q += 128) {
-      T val = sf[q];
-      if (val != val) val = neg_inf<T>();
-      a = val < a ? val : a;
-      b = val > b ? val : b;
-    }
-    block_minmax<T, 128>(a, b, red);
-    mn = a;
-    mx = b;
-  }
-  // corners of this thread's cells, loaded once
-  T cv[R][8];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int cc = t + 128 * r < NC ? t + 128 * r : 0;
-    const int n0 = cc % N + P * ((cc / N) % N) + P * P * (cc / (N * N));
-#pragma unroll
-    for (int vtx = 0; vtx < 8; ++vtx)
-      cv[r][vtx] = sf[n0 + (vtx & 1) + P * ((vtx >> 1) & 1) + P * P * (vtx >> 2)];
-  }
+  bool need = false;
   for (int s = 0; s < n_iso; ++s) {
     const T c = iso.v[s];
-    const bool straddle = (mx > c) && !(mn > c);
-    uint8_t* cd = case_idx ? case_idx + ((int64_t)s * n_elem + e) * NC : nullptr;
-    int packed = 0;
+    const bool crossed = in && (!mm || (hi > c && !(lo > c)));
+    need |= crossed;
+    if (in && !crossed) cnt[(int64_t)s * n_elem + mine] = 0;
+    if (case_idx) {   // uniform cases
+      const uint64_t above = __ballot(hi > c);
+      for (uint64_t out = __ballot(in && !crossed); out != 0; out &= out - 1) {
+        const int from = __builtin_ctzll(out);
+        uint8_t* cd = case_idx + ((int64_t)s * n_elem + __shfl(mine, from)) * NC;
+        for (int q = lane; q < NC; q += 64) cd[q] = (above >> from) & 1 ? 255 : 0;
+      }
+    }
+  }
+  for (uint64_t live = __ballot(need); live != 0; live &= live - 1) {
+    const int from = __builtin_ctzll(live);
+    const int64_t e = __shfl(mine, from);
+    const T* src = field + e * NP;
+    T v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int cell = t + 128 * r;
-      if (cell >= NC) continue;
-      int cs = 0;
-      if (straddle) {
+      const int q = 64 * r + lane;
+      v[r] = src[q < NP ? q : NP - 1];
+    }
+    for (int s = 0; s < n_iso; ++s) {
+      const T c = iso.v[s];
+      if (__ballot(lane == from && (!mm || (hi > c && !(lo > c)))) == 0) continue;
+      uint64_t b[R];
 #pragma unroll
-        for (int vtx = 7; vtx >= 0; --vtx) cs = cs + cs + (cv[r][vtx] > c);
-        packed += s_ntri[cs] + ((cs != 0 && cs != 255) << 16);
-      } else {
-        cs = (mx > c) ? 255 : 0;
+      for (int r = 0; r < R; ++r) b[r] = __ballot(64 * r + lane < NP && v[r] > c);
+      if (lane == 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) bits[r] = b[r];
       }
-      if (cd) cd[cell] = (uint8_t)cs;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int64_t flat = (int64_t)s * n_elem + e;
+      const uint32_t sum = count_rows<N>(reinterpret_cast<const uint32_t*>(bits), 0, lane, tab,
+                                         case_idx ? case_idx + flat * NC : nullptr);
+      if (lane == 63) cnt[flat] = (int)sum;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    if (!straddle) {
-      if (t == 0) cnt[(int64_t)s * n_elem + e] = 0;
-      continue;
-    }
-    packed = (int)wave_sum_to63((uint32_t)packed);
-    if (lane == 63) s_sum[h] = packed;
-    __syncthreads();
-    if (t == 0) {
-      cnt[(int64_t)s * n_elem + e] = s_sum[0] + s_sum[1];
-    }
-    __syncthreads();
   }
 }
 
+// count_waves<N, T>: the count pass of the two-pass isosurface, four
+// independent waves a workgroup; wave w takes elements w, w + waves, ...
+// Bound by the field's elements that an isovalue crosses, read once.  A
+// workgroup per element spent its time on starting: 33 us for 24,389
+// elements of order 6 (FP32, four isovalues) with or without any to read.
+constexpr int kCountWaves = 4;
+template <int N>
+constexpr int kCountBits = ((N + 1) * (N + 1) * (N + 1) + 63) / 64 + 1;   // a word past the last row's
+
 template <int N, typename T>
-__global__ void __launch_bounds__(128)
-count_direct(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ mm,
-             int n_iso, IsoList<T> iso, const uint8_t* __restrict__ ntri_tab,
-             int32_t* __restrict__ cnt, int64_t* __restrict__ active_total,
-             uint8_t* __restrict__ case_idx) {
+__global__ void __launch_bounds__(64 * kCountWaves)
+count_waves(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ mm,
+            int n_iso, IsoList<T> iso, const uint8_t* __restrict__ ntri_tab,
+            int32_t* __restrict__ cnt, int64_t* __restrict__ active_total,
+            uint8_t* __restrict__ case_idx) {
+  __shared__ uint32_t s_tab[64];
+  __shared__ uint64_t s_bits[kCountWaves][kCountBits<N>];
   clear_active(active_total, n_iso);
-  count_elem<N, T>(blockIdx.x, threadIdx.x, n_elem, field, mm, n_iso, iso, ntri_tab, cnt,
-                   case_idx);
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  if (t < 64) s_tab[t] = reinterpret_cast<const uint32_t*>(ntri_tab)[t];
+  __syncthreads();
+  const int64_t step = (int64_t)gridDim.x * kCountWaves;
+  for (int64_t e0 = (int64_t)blockIdx.x * kCountWaves + wave; e0 < n_elem; e0 += 64 * step) {
+    const int64_t mine = e0 + lane * step;
+    count_lanes<N, T>(mine, mine < n_elem, lane, n_elem, field, mm, n_iso, iso,
+                      reinterpret_cast<const uint8_t*>(s_tab), s_bits[wave], cnt, case_idx);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1758,20 +1592,36 @@ struct JobCursor {
   }
 };
 
+// Waves take runs of consecutive items, a lane each (a run is cut where a job
+// ends), as long as one round of waves covers them all: on the batched
+// snapshots 109 us in all for the three orders, 127 with a run of one.
 template <int N, typename T>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(64 * kCountWaves)
 iso_batch_count(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __restrict__ jobs,
                 const uint8_t* __restrict__ ntri_tab, int32_t* __restrict__ cnt) {
+  __shared__ uint32_t s_tab[64];
+  __shared__ uint64_t s_bits[kCountWaves][kCountBits<N>];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  if (t < 64) s_tab[t] = reinterpret_cast<const uint32_t*>(ntri_tab)[t];
+  __syncthreads();
   const int j0 = hdr->job_begin[N], j1 = hdr->job_begin[N + 1];
   const int64_t total = hdr->items[N];
+  const int64_t waves = (int64_t)gridDim.x * kCountWaves;
+  const int64_t each = (total + waves - 1) / waves;
+  const int run = each > 64 ? 64 : (int)each;
   JobCursor<T> c;
-  for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-    c.seek(jobs, j0, j1, total, item);
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    count_elem<N, T>(item - c.begin, t, c.n_elem, c.field, c.mm, c.n_iso, IsoPtr<T>{c.iso},
-                     ntri_tab, cnt + c.slot, nullptr);
-    __syncthreads();                   // the next item reuses the LDS
+  for (int64_t i0 = ((int64_t)blockIdx.x * kCountWaves + wave) * run; i0 < total;
+       i0 += waves * run) {
+    const int64_t end = i0 + run < total ? i0 + run : total;
+    for (int64_t i = i0; i < end;) {
+      c.seek(jobs, j0, j1, total, i);
+      const int64_t stop = end < c.next_begin ? end : c.next_begin;
+      const int64_t mine = i - c.begin + lane;
+      count_lanes<N, T>(mine, i + lane < stop, lane, c.n_elem, c.field, c.mm, c.n_iso,
+                        IsoPtr<T>{c.iso}, reinterpret_cast<const uint8_t*>(s_tab),
+                        s_bits[wave], cnt + c.slot, nullptr);
+      i = stop;
+    }
   }
 }
 
@@ -1790,9 +1640,12 @@ iso_batch_emit(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __rest
     c.seek(jobs, j0, j1, total, item);
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
-    emit_elem<N, T>(item - c.begin, t, c.n_elem, c.x, c.y, c.z, c.field, c.n_iso,
-                    IsoPtr<T>{c.iso}, out, ntri_tab, cnt + c.slot, offs + c.slot, nullptr);
-    __syncthreads();
+    const int64_t e = item - c.begin;
+    bool any = false;
+    for (int s = 0; s < c.n_iso; ++s) any |= slot_tris(cnt[c.slot + s * c.n_elem + e]) > 0;
+    if (any)
+      emit_elem<N, T>(e, t, c.n_elem, c.x, c.y, c.z, c.field, c.n_iso, IsoPtr<T>{c.iso}, out,
+                      ntri_tab, cnt + c.slot, offs + c.slot, nullptr);
   }
 }
 
@@ -1992,6 +1845,13 @@ void scan_kernels(const CT* cnt, int64_t count, int64_t* partial, int64_t* offs,
                                                 start, stop);
 }
 
+// Workgroups of the count kernel: an element per wave while the chip has room
+// for more waves, then as many waves as it holds.
+unsigned count_grid(int64_t n_elem) {
+  const int64_t waves = n_elem < 8192 ? n_elem : 8192;
+  return (unsigned)((waves + kCountWaves - 1) / kCountWaves);
+}
+
 template <typename T>
 hipError_t iso_scan_emit(int order, const DeviceTables& tab, int64_t n_elem, const void* x,
                          const void* y, const void* z, const void* field, int n_iso,
@@ -2004,27 +1864,17 @@ hipError_t iso_scan_emit(int order, const DeviceTables& tab, int64_t n_elem, con
   phase_done(ps);
   bool any_cap = false;
   for (int q = 0; q < (out.per_iso ? n_iso : 1); ++q) any_cap = any_cap || out.cap[q] > 0;
-  // the totals: a kernel of their own, unless the emission kernel for odd
-  // orders writes them
-  if (!any_cap || order % 2 == 0)
+  if (!any_cap)   // otherwise the emission kernel writes the totals
     hipLaunchKernelGGL((iso_totals<T>), dim3(1), dim3(SEM_MAX_ISO), 0, s, (const int64_t*)ws.offs,
                        n_elem, n_iso, tri_count, out, status);
   if (!any_cap) return hipGetLastError();
   const PhaseTimer pe = phase_timer(SEM_PHASE_EMIT);
   SEM_ORDER_SWITCH(order, {
-    if constexpr (N % 2 == 1) {
-      hipExtLaunchKernelGGL((emit_direct<N, T>), dim3((unsigned)n_elem), dim3(128), 0, s,
-                            pe.start, pe.stop, 0, n_elem, (const T*)x, (const T*)y,
-                            (const T*)z, (const T*)field, n_iso, iso, out, tab.ntri,
-                            (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys, tri_count,
-                            status);
-    } else {
-      hipExtLaunchKernelGGL((iso_emit<N, T>), dim3((unsigned)n_elem),
-                            dim3(Shape<N>::kCellThreads), 0, s, pe.start, pe.stop, 0, n_elem,
-                            (const T*)x, (const T*)y, (const T*)z, (const T*)field, n_iso, iso,
-                            tab.ntri, tab.tri, (const int32_t*)ws.cnt, (const int64_t*)ws.offs,
-                            out, keys);
-    }
+    hipExtLaunchKernelGGL((emit_direct<N, T>), dim3((unsigned)n_elem), dim3(128), 0, s,
+                          pe.start, pe.stop, 0, n_elem, (const T*)x, (const T*)y,
+                          (const T*)z, (const T*)field, n_iso, iso, out, tab.ntri,
+                          (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys, tri_count,
+                          status);
   });
   phase_done(pe);
   return hipGetLastError();
@@ -2041,16 +1891,9 @@ hipError_t iso_pipeline(int order, const DeviceTables& tab, int64_t n_elem, cons
   const IsoList<T> iso = make_isolist<T>(n_iso, iso_host);
   const PhaseTimer pt = phase_timer(SEM_PHASE_COUNT);
   SEM_ORDER_SWITCH(order, {
-    if constexpr (N % 2 == 1) {
-      hipExtLaunchKernelGGL((count_direct<N, T>), dim3((unsigned)n_elem), dim3(128), 0, s,
-                            pt.start, pt.stop, 0, n_elem, (const T*)field, (const T*)mm, n_iso,
-                            iso, tab.ntri, ws.cnt, active, case_idx);
-    } else {
-      hipExtLaunchKernelGGL((iso_count<N, T>), dim3((unsigned)n_elem),
-                            dim3(Shape<N>::kCellThreads), 0, s, pt.start, pt.stop, 0, n_elem,
-                            (const T*)field, (const T*)mm, n_iso, iso, tab.ntri, ws.cnt, active,
-                            case_idx);
-    }
+    hipExtLaunchKernelGGL((count_waves<N, T>), dim3(count_grid(n_elem)), dim3(64 * kCountWaves), 0,
+                          s, pt.start, pt.stop, 0, n_elem, (const T*)field, (const T*)mm, n_iso,
+                          iso, tab.ntri, ws.cnt, active, case_idx);
   });
   phase_done(pt);
   return iso_scan_emit<T>(order, tab, n_elem, x, y, z, field, n_iso, iso, out, keys, tri_count,
@@ -2252,14 +2095,15 @@ hipError_t iso_batch_phase(bool f64, bool emit, const IsoBatchHeader* hdr,
   int64_t* offs = ws.offs;
   void* count_args[] = {&hdr, &jobs, &ntri, &cnt};
   void* emit_args[] = {&hdr, &jobs, &ntri, &cnt, &offs, &tri, &cap};
-  // Four times the workgroups the CUs hold at once: the cost of an element
+  // Emission with four times the workgroups the CUs hold at once: the cost of an element
   // varies with its triangles, and with a grid of exactly the resident
   // workgroups the unluckiest one sets the end (measured on the batched
   // benchmark snapshots: 4.54 ms at 1x, 3.58 at 4x, 3.60 at 16x, 3.84 at 64x;
   // 48 separate sem_isosurface calls: 4.4 ms).  Workgroups that start later
   // take the slots the early finishers free.
-  return hipExtLaunchKernel(fn, dim3(4 * batch_grid(fn, 128, tab.cu_count)), dim3(128),
-                            emit ? emit_args : count_args, 0, s, a, b, 0);
+  const int threads = emit ? 128 : 64 * kCountWaves;
+  return hipExtLaunchKernel(fn, dim3((emit ? 4 : 1) * batch_grid(fn, threads, tab.cu_count)),
+                            dim3(threads), emit ? emit_args : count_args, 0, s, a, b, 0);
 }
 }  // namespace
 

@@ -361,3 +361,34 @@ def test_stream_copy_copies_every_byte():
         sem.stream_copy(src, dst)
         torch.cuda.synchronize()
         assert torch.equal(src, dst), nbytes
+
+
+@pytest.mark.parametrize("n,e", [(1, 530001), (2, 8193), (3, 8191), (6, 100), (8, 33), (9, 37)])
+@pytest.mark.parametrize("ranges", [True, False])
+def test_counts_of_any_number_of_elements(n, e, ranges):
+    """Counts, active cells and cases where waves take several elements (and
+    several rounds of 64), with and without ranges, NaN and infinities in the
+    field, and isovalues that no element, few and most cross."""
+    rng = np.random.default_rng(100 * n + e)
+    f = rng.normal(size=(e, 1, 1, 1)) + 0.3 * rng.normal(size=(e,) + (n + 1,) * 3)
+    f[rng.random(f.shape) < 1e-3] = np.nan
+    f[rng.random(f.shape) < 1e-3] = np.inf
+    f[rng.random(f.shape) < 1e-3] = -np.inf
+    f = f.astype(np.float32)
+    isos = [0.0, 99.0, 2.5, -0.2, -1.0]
+    t = torch.from_numpy(f).to(DEV)
+    low = np.where(np.isnan(f), -np.inf, f).reshape(e, -1)
+    mm = torch.from_numpy(np.stack([low.min(1), low.max(1)], 1)).to(DEV) if ranges else None
+    dump = e < 10000
+    cnt, act = (torch.zeros(len(isos), dtype=torch.int64, device=DEV) for _ in range(2))
+    cid = torch.full((len(isos), e, n ** 3), 7, dtype=torch.uint8, device=DEV) if dump else None
+    ws = torch.empty(sem.workspace_bytes(e, n, len(isos)), dtype=torch.uint8, device=DEV)
+    sem.isosurface_into(t, t, t, t, isos, None, cnt, ws, minmax=mm, active=act,
+                        case_idx=cid)
+    ntri, _ = mc.case_table()
+    for s, c in enumerate(isos):
+        cs = mc.classify(f, c)
+        assert int(cnt[s]) == int(ntri[cs].astype(np.int64).sum())
+        assert int(act[s]) == int(((cs != 0) & (cs != 255)).sum())
+        if dump:
+            np.testing.assert_array_equal(host(cid[s]), cs.reshape(e, -1))
