@@ -321,28 +321,6 @@ __device__ __forceinline__ void line_deriv_all(const C* __restrict__ d, const T 
   }
 }
 
-// Counting four isovalues at a time. A node's word holds bit (q > c_s) at
-// bit 8s for the isovalues g .. g + 3 below n (a NaN compares below every
-// isovalue); the eight corner words of a cell, each shifted by its vertex
-// number (vertex bits x, y, z = 1, 2, 4) and summed, hold the cell's four
-// cases as bytes. A case maps to triangles + (1 << 16) when non-trivial, so
-// one sum per isovalue gives both the triangle and the active-cell count.
-template <typename T>
-__device__ __forceinline__ uint32_t iso_bits4(T q, const IsoList<T>& iso, int g, int n) {
-  uint32_t b = 0;
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-    if (g + s < n) b |= (uint32_t)(q > iso.v[g + s]) << (8 * s);
-  return b;
-}
-template <int RS, int SS>
-__device__ __forceinline__ uint32_t cell_word(const uint32_t* bits, int n0) {
-  uint32_t w = 0;
-#pragma unroll
-  for (int vtx = 0; vtx < 8; ++vtx)
-    w += bits[n0 + (vtx & 1) + RS * ((vtx >> 1) & 1) + SS * (vtx >> 2)] << vtx;
-  return w;
-}
 // Sum over the 16 lanes of each row of the wave, by DPP row shifts (lanes
 // shifted in from outside the row read 0): lane 15 of the row ends with the
 // row's sum (the others with partial sums).  Four VALU operations, no LDS.
@@ -365,47 +343,6 @@ __device__ __forceinline__ uint32_t wave_sum_to63(uint32_t v) {
   return v;
 }
 
-// Order-7 cell c = i + 7 j + 49 k has corner 0 at node i + 8 j + 64 k =
-// c + c / 7 + 8 (c / 49); the divisions by multiply and shift, exact for
-// c < 512 (the rounding errors stay below the gap to the next integer).
-__device__ __forceinline__ int cell_base7(int c) {
-  return c + ((c * 9363) >> 16) + 8 * ((c * 1338) >> 16);
-}
-
-// Case-table entry for packed counting: triangles + (1 << 8) for a
-// non-trivial case.
-__device__ __forceinline__ int case_count_entry8(int cs, uint8_t nt) {
-  return (int)nt + ((cs != 0 && cs != 255) << 8);
-}
-
-// Element counts of the isovalues g .. g + m - 1 (m <= 4) for a workgroup
-// of NW <= 4 waves with at most three cells per lane: pw[s >> 1] holds, in
-// its 16-bit half s & 1, the lane's triangles + (active cells << 8) of
-// isovalue s (at most 3 x 5 triangles per lane, so a row of 16 lanes stays
-// below 240 + (48 << 8)).  DPP row sums, the 4 NW row sums through s_rows
-// (8 NW words), one barrier, then wave 0 sums the rows of each isovalue.
-// s_rows must not be written again before a later barrier.
-template <int NW>
-__device__ __forceinline__ void publish_rows(uint32_t (&pw)[2], int m, int g, int t,
-                                             uint32_t* s_rows, int32_t* __restrict__ cnt,
-                                             int64_t n_elem, int64_t e) {
-  static_assert(NW >= 1 && NW <= 4, "at most 16 rows");
-  const int h = t >> 6, p = t & 63;
-  pw[0] = row_sum16(pw[0]);
-  if (m > 2) pw[1] = row_sum16(pw[1]);
-  if ((p & 15) == 15) {
-    s_rows[2 * (4 * h + (p >> 4))] = pw[0];
-    s_rows[2 * (4 * h + (p >> 4)) + 1] = pw[1];
-  }
-  __syncthreads();
-  if (h == 0) {
-    const int row = p & 15, s = p >> 4;   // lane: one row's field of isovalue s
-    const uint32_t f =
-        row < 4 * NW ? (s_rows[2 * row + (s >> 1)] >> (16 * (s & 1))) & 0xffffu : 0u;
-    const uint32_t sum = row_sum16((f & 255u) | ((f >> 8) << 16));
-    if (row == 15 && s < m) cnt[(int64_t)(g + s) * n_elem + e] = (int)sum;
-  }
-}
 // Where a Q kernel also counts each isovalue's triangles and active cells per
 // element (the count pass of the isosurface, fused).
 template <typename T>
@@ -1000,25 +937,41 @@ count_waves(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ m
 // ---------------------------------------------------------------------------
 //
 // The 1-D contractions run as v_mfma_f32_16x16x32_{bf16,f16}: low-precision
-// operands, FP32 accumulation.  One workgroup of four waves per element; for
-// each field and direction wave w differentiates the 16 lines 16w..16w+15:
-//   rows     i = output node along the line (rows 8..15 are zero),
-//   columns  the 16 lines,
+// operands, FP32 accumulation.  One workgroup of two waves per element; for
+// each field and direction wave w differentiates the 32 lines 32w..32w+31,
+// two sets of 16 at once through a block-diagonal D:
+//   rows     i = output node along the line, 0..7 of the first set's lines,
+//            8..15 of the second's,
+//   columns  the 16 lines of a set,
 //   depth    the 8 line values spread over the four lane groups (group g
-//            holds values m0 = 2g and m1 = 2g + 1), each with the products
-//            the mode needs:
+//            holds values m0 = 2g and m1 = 2g + 1 of both sets' lines), each
+//            with the products the mode needs:
 //   plain            D_hi (f - f_0)_hi
-//   split (x3)       D_hi f_hi + D_lo f_hi + D_hi f_lo   (Henry, Tang &
-//                    Heinecke 2019: the lo*lo term is dropped)
+//   split (x3)       D_hi f_hi, then D_lo f_hi + D_hi f_lo in a product of
+//                    its own (Henry, Tang & Heinecke 2019: the lo*lo term is
+//                    dropped)
 // where x_hi = round(x) to the operand format and x_lo = round(x - x_hi).
 // In the FP16 split the lo parts are scaled by 2^11 (out of FP16's subnormal
 // range; Ootomo & Yokota 2022) and accumulate separately, then scaled back.
 // Values enter line-shifted (f_m - f_0), which keeps the coordinates'
 // absolute offset out of the rounding.  The Jacobian is inverted in FP64;
 // the chain rule, Q and |omega| are FP32.
+//
+// A lane gets four neighbouring outputs of one line.  It owns those four
+// nodes of its t line, whose t derivatives therefore stay in registers; the
+// r and s derivatives reach their owners through LDS, in node order with a
+// pitch of 72 words a slab, which spreads the accesses of all three
+// directions over the banks.  Bound by the vector units and the wait for the
+// element's fields with six workgroups per CU (162 registers; with 128 and
+// eight workgroups the Jacobians spill: 475 us).  65,536 elements, FP16 split:
+// 450 us with four waves, one set of 16 lines a product (half its rows zero,
+// half the lanes without outputs) and all derivatives through LDS, 4,596
+// vector instructions an element; 340 so, with 2,460.  The fields once in and
+// Q and |omega| once out take 212 us at copy rate.
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 enum MixMode { kMixBF16 = 0, kMixFP16 = 1, kMixBF16x3 = 2, kMixFP16x3 = 3 };
@@ -1042,133 +995,141 @@ struct MixT<kMixFP16x3> {
 constexpr float kF16LoScale = 2048.0f;   // 2^11
 
 template <int M>
-__device__ __forceinline__ f32x4 mfma_line(typename MixT<M>::V a, typename MixT<M>::V b) {
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+__device__ __forceinline__ f32x4 mfma_line(typename MixT<M>::V a, typename MixT<M>::V b,
+                                           f32x4 c) {
   if constexpr (M == kMixBF16 || M == kMixBF16x3)
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, zero, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   else
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, zero, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
+
+template <int M>
+constexpr bool kMixSplit = M == kMixBF16x3 || M == kMixFP16x3;
+// scale of the lo parts
+template <int M>
+constexpr float kMixLo = M == kMixFP16x3 ? kF16LoScale : 1.0f;
 
 // A operands of one lane (row i = lane % 16, lane group g = lane / 16).
 template <int M>
 struct MixOps {
   typename MixT<M>::V a;    // main product
-  typename MixT<M>::V ac;   // scaled correction (FP16 split only)
+  typename MixT<M>::V ac;   // correction (splits only)
 };
 
 template <int M>
 __device__ __forceinline__ MixOps<M> mix_ops(const double* __restrict__ d, int lane) {
   using E = typename MixT<M>::E;
   MixOps<M> o;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    o.a[q] = E(0.f);
-    o.ac[q] = E(0.f);
-  }
   const int i = lane & 15, g = lane >> 4;
-  // rows 8..15 are zero: their values are selected to zero after an
-  // unconditional load (row i & 7), so that no branch holds the caller's
-  // later loads behind this load's wait
+  // an unconditional load (row i & 7): no branch holds the caller's later
+  // loads behind its wait
   const double r0 = d[(i & 7) * 8 + 2 * g], r1 = d[(i & 7) * 8 + 2 * g + 1];
-  const double d0 = i < 8 ? r0 : 0.0, d1 = i < 8 ? r1 : 0.0;
-  const E h0 = E((float)d0), h1 = E((float)d1);
-  if constexpr (M == kMixBF16x3) {
-    const E l0 = E((float)(d0 - (double)(float)h0));
-    const E l1 = E((float)(d1 - (double)(float)h1));
-    o.a[0] = h0; o.a[1] = l0; o.a[2] = h0;
-    o.a[3] = h1; o.a[4] = l1; o.a[5] = h1;
-  } else {
-    o.a[0] = h0;
-    o.a[1] = h1;
-    if constexpr (M == kMixFP16x3) {
-      o.ac[0] = E((float)((d0 - (double)(float)h0) * kF16LoScale));
-      o.ac[1] = h0;
-      o.ac[2] = E((float)((d1 - (double)(float)h1) * kF16LoScale));
-      o.ac[3] = h1;
-    }
+  const E zero = E(0.f), h0 = E((float)r0), h1 = E((float)r1);
+  const E l0 = E((float)((r0 - (double)(float)h0) * kMixLo<M>));
+  const E l1 = E((float)((r1 - (double)(float)h1) * kMixLo<M>));
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {   // the set whose rows these are
+    const bool on = (i >> 3) == q;
+    o.a[2 * q] = on ? h0 : zero;
+    o.a[2 * q + 1] = on ? h1 : zero;
+    o.a[4 + 2 * q] = o.a[5 + 2 * q] = zero;
+    o.ac[4 * q] = on ? l0 : zero;
+    o.ac[4 * q + 1] = on ? l1 : zero;
+    o.ac[4 * q + 2] = on ? h0 : zero;
+    o.ac[4 * q + 3] = on ? h1 : zero;
   }
   return o;
 }
 
-// Derivatives along one line set: v0, v1 are this lane's shifted values
-// f[m0] - f[0], f[m1] - f[0]; lanes 0..31 receive the outputs of rows
-// 4 (lane / 16) .. + 3 for line lane % 16.
+// Derivatives along two line sets: v[q] are this lane's shifted values
+// f[2g] - f[0], f[2g + 1] - f[0] of line lane % 16 of set q; lane group g
+// receives the outputs 4 (g & 1) .. + 3 of that line of set g >> 1.
 template <int M>
-__device__ __forceinline__ f32x4 mix_contract(const MixOps<M>& o, float v0, float v1) {
+__device__ __forceinline__ f32x4 mix_contract(const MixOps<M>& o, const f32x2 (&v)[2]) {
   using E = typename MixT<M>::E;
-  typename MixT<M>::V b;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  typename MixT<M>::V b, bc;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) b[q] = E(0.f);
-  const E h0 = E(v0), h1 = E(v1);
-  if constexpr (M == kMixBF16x3) {
-    const E l0 = E(v0 - (float)h0), l1 = E(v1 - (float)h1);
-    b[0] = h0; b[1] = h0; b[2] = l0;
-    b[3] = h1; b[4] = h1; b[5] = l1;
-    return mfma_line<M>(o.a, b);
-  } else {
-    b[0] = h0;
-    b[1] = h1;
-    f32x4 acc = mfma_line<M>(o.a, b);
-    if constexpr (M == kMixFP16x3) {
-      typename MixT<M>::V bc;
+  for (int q = 0; q < 2; ++q) {
+    // a pair at a time: one packed conversion, and its result is both
+    // products' operand
+    typedef E E2 __attribute__((ext_vector_type(2)));
+    const E2 h = __builtin_convertvector(v[q], E2);
+    b[2 * q] = bc[4 * q] = h[0];
+    b[2 * q + 1] = bc[4 * q + 1] = h[1];
+    b[4 + 2 * q] = b[5 + 2 * q] = E(0.f);
+    if constexpr (kMixSplit<M>) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) bc[q] = E(0.f);
-      bc[0] = h0;
-      bc[1] = E((v0 - (float)h0) * kF16LoScale);
-      bc[2] = h1;
-      bc[3] = E((v1 - (float)h1) * kF16LoScale);
-      const f32x4 c = mfma_line<M>(o.ac, bc);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r] = fmaf(c[r], 1.0f / kF16LoScale, acc[r]);
+      for (int m = 0; m < 2; ++m)   // (v - h) scaled, exact in one operation
+        bc[4 * q + 2 + m] = E(fmaf((float)h[m], -kMixLo<M>, v[q][m] * kMixLo<M>));
     }
-    return acc;
   }
+  f32x4 acc = mfma_line<M>(o.a, b, zero);
+  if constexpr (M == kMixBF16x3) acc = mfma_line<M>(o.ac, bc, acc);
+  if constexpr (M == kMixFP16x3) {
+    const f32x4 c = mfma_line<M>(o.ac, bc, zero);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[r] = fmaf(c[r], 1.0f / kF16LoScale, acc[r]);
+  }
+  return acc;
 }
 
-constexpr int kMixLS = 9;            // derivative tile: line stride (floats)
-constexpr int kMixDT = 64 * kMixLS;  // one derivative tile
+constexpr int kMixSlab = 72;             // words of a slab of 64 nodes in LDS
+constexpr int kMixTile = 8 * kMixSlab;
 
-// One field (tile `f`, natural layout i + 8j + 64k) -> its three derivative
-// tiles `dt` (line-major: dt[d * kMixDT + line * kMixLS + node along line]).
+// Where a lane finds things in a tile (words): node 0 and node 2g of its line
+// of the first set in each direction (the second set's lie kMixSet further),
+// its four outputs along r and along s, and its first own node.
+struct MixLane {
+  int line0[3], line2g[3], out_r, out_s, own;
+};
+constexpr int kMixSet[3] = {2 * kMixSlab, 2 * kMixSlab, 16};
+constexpr int kMixStride[3] = {1, 8, kMixSlab};
+__device__ __forceinline__ MixLane mix_lane(int wv, int lane) {
+  const int n = lane & 15, g = lane >> 4, lo = n & 7, hi = 4 * wv + (n >> 3);
+  MixLane m;
+  m.line0[0] = 8 * lo + kMixSlab * hi;
+  m.line0[1] = lo + kMixSlab * hi;
+  m.line0[2] = lo + 8 * hi;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) m.line2g[d] = m.line0[d] + 2 * g * kMixStride[d];
+  m.out_r = m.line0[0] + (g >> 1) * kMixSet[0] + 4 * (g & 1);
+  m.out_s = m.line0[1] + (g >> 1) * kMixSet[1] + 32 * (g & 1);
+  m.own = m.line0[2] + (g >> 1) * kMixSet[2] + 4 * kMixSlab * (g & 1);
+  return m;
+}
+
+// One field (tile f) -> its r and s derivatives (tiles dr, ds), and the t
+// derivatives of the lane's own nodes.
 template <int M>
-__device__ __forceinline__ void mix_field(const float* __restrict__ f, float* __restrict__ dt,
-                                          const MixOps<M>& o, int wv, int lane) {
-  const int n = lane & 15, g = lane >> 4;
-  const int L = 16 * wv + n;
-  const int lo = L & 7, hi = L >> 3;
-  // line base and stride of direction r, s, t
-  const int base[3] = {8 * L, lo + 64 * hi, L};
-  const int stride[3] = {1, 8, 64};
+__device__ __forceinline__ f32x4 mix_field(const float* __restrict__ f, float* __restrict__ dr,
+                                           float* __restrict__ ds, const MixOps<M>& o,
+                                           const MixLane& at) {
+  f32x4 acc[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const float* line = f + base[d];
-    const float f0 = line[0];
-    const float v0 = line[(2 * g) * stride[d]] - f0;
-    const float v1 = line[(2 * g + 1) * stride[d]] - f0;
-    const f32x4 acc = mix_contract<M>(o, v0, v1);
-    if (lane < 32) {
-      float* out = dt + d * kMixDT + L * kMixLS + 4 * g;
+    f32x2 v[2];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) out[r] = acc[r];
+    for (int q = 0; q < 2; ++q) {
+      const float f0 = f[at.line0[d] + q * kMixSet[d]];
+      const float* p = f + at.line2g[d] + q * kMixSet[d];
+      v[q][0] = p[0] - f0;
+      v[q][1] = p[kMixStride[d]] - f0;
     }
+    acc[d] = mix_contract<M>(o, v);
   }
-}
-
-// (f_r, f_s, f_t) of node (i, j, k) from its field's derivative tiles.
-__device__ __forceinline__ void mix_read(const float* __restrict__ dt, int i, int j, int k,
-                                         float& fr, float& fs, float& ft) {
-  fr = dt[(j + 8 * k) * kMixLS + i];
-  fs = dt[kMixDT + (i + 8 * k) * kMixLS + j];
-  ft = dt[2 * kMixDT + (i + 8 * j) * kMixLS + k];
+  *reinterpret_cast<f32x4*>(dr + at.out_r) = acc[0];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) ds[at.out_s + 8 * r] = acc[1][r];
+  return acc[2];
 }
 
 // QC: Q, |omega| and the element range of Q from (x, y, z, u, v, w);
 // otherwise the physical gradient of f = u into (o0, o1, o2).
 // COUNT (with QC): also the per-(isovalue, element) triangle and active-cell
-// counts from the element's Q tile.
+// counts from the element's Q, by bit rows.
 template <int M, bool QC, bool COUNT = false>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(128, 3)
 mixed7(const double* __restrict__ dmat, const float* __restrict__ x,
        const float* __restrict__ y, const float* __restrict__ z, const float* __restrict__ u,
        const float* __restrict__ v, const float* __restrict__ w, float* __restrict__ o0,
@@ -1176,150 +1137,135 @@ mixed7(const double* __restrict__ dmat, const float* __restrict__ x,
        int32_t* __restrict__ status, CountSink<float> sink) {
   static_assert(QC || !COUNT, "counting needs Q");
   constexpr int NF = QC ? 6 : 4;
-  __shared__ float s_in[NF][512];
-  __shared__ float s_d[2][3 * kMixDT];
-  __shared__ float s_red[8];
-  __shared__ int32_t s_tab[COUNT ? 256 : 1];
-  __shared__ uint32_t s_rows[COUNT ? 32 : 1];
+  __shared__ __align__(16) float s_in[NF][kMixTile];
+  __shared__ __align__(16) float s_d[2][2][kMixTile];
+  __shared__ float s_red[4];
+  __shared__ uint32_t s_tab[COUNT ? 64 : 1];
   if constexpr (COUNT) clear_active(sink.active, sink.n_iso);
   const int t = threadIdx.x, lane = t & 63;
-  __builtin_assume(t >= 0 && t < 256);
+  __builtin_assume(t >= 0 && t < 128);
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int64_t base = (int64_t)blockIdx.x * 512;
-  // the first 128 threads stage the 16-byte chunks of x, z, v, the others
-  // those of y, u, w; every load is requested before the first LDS write (a
-  // field picked by an index into a pointer list became a compare-and-select
-  // chain that serialised the loads)
   const MixOps<M> ops = mix_ops<M>(dmat, lane);   // its loads first: in flight with the tiles'
-  const bool hi = t >= 128;
-  const int64_t off = base + 4 * (t & 127);
-  const int slot = 4 * (t & 127);
-  const float4 c0 = *reinterpret_cast<const float4*>((hi ? y : x) + off);
-  const float4 c1 = *reinterpret_cast<const float4*>((hi ? u : z) + off);
-  float4 c2 = make_float4(0.f, 0.f, 0.f, 0.f);
-  if constexpr (NF == 6) c2 = *reinterpret_cast<const float4*>((hi ? w : v) + off);
-  uint8_t nt_own = 0;
-  if constexpr (COUNT) nt_own = sink.ntri[t];
-  *reinterpret_cast<float4*>((hi ? s_in[1] : s_in[0]) + slot) = c0;
-  *reinterpret_cast<float4*>((hi ? s_in[3] : s_in[2]) + slot) = c1;
-  if constexpr (NF == 6) *reinterpret_cast<float4*>((hi ? s_in[5] : s_in[4]) + slot) = c2;
-  if constexpr (COUNT) s_tab[t] = case_count_entry8(t, nt_own);
+  const int64_t off = base + 4 * t;
+  f32x4 in[NF];
+  in[0] = *reinterpret_cast<const f32x4*>(x + off);
+  in[1] = *reinterpret_cast<const f32x4*>(y + off);
+  in[2] = *reinterpret_cast<const f32x4*>(z + off);
+  in[3] = *reinterpret_cast<const f32x4*>(u + off);
+  if constexpr (NF == 6) {
+    in[4] = *reinterpret_cast<const f32x4*>(v + off);
+    in[5] = *reinterpret_cast<const f32x4*>(w + off);
+  }
+  if (COUNT && t < 64) s_tab[t] = reinterpret_cast<const uint32_t*>(sink.ntri)[t];
+#pragma unroll
+  for (int c = 0; c < NF; ++c)
+    *reinterpret_cast<f32x4*>(s_in[c] + kMixSlab * (t >> 4) + 4 * (t & 15)) = in[c];
   __syncthreads();
 
-  // owners: nodes t and t + 256
-  int ni[2], nj[2], nk[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int nd = t + 256 * h;
-    ni[h] = nd & 7;
-    nj[h] = (nd >> 3) & 7;
-    nk[h] = nd >> 6;
-  }
-  float gd[3][2][3];   // geometry: [coordinate][node][r, s, t]
+  const MixLane at = mix_lane(wv, lane);
+  float gd[3][4][3];   // geometry: [coordinate][node][r, s, t]
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    float* dt = s_d[c & 1];
-    mix_field<M>(s_in[c], dt, ops, wv, lane);
+    const f32x4 ft = mix_field<M>(s_in[c], s_d[c & 1][0], s_d[c & 1][1], ops, at);
     __syncthreads();
 #pragma unroll
-    for (int h = 0; h < 2; ++h) mix_read(dt, ni[h], nj[h], nk[h], gd[c][h][0], gd[c][h][1],
-                                         gd[c][h][2]);
+    for (int r = 0; r < 4; ++r) {
+      gd[c][r][0] = s_d[c & 1][0][at.own + kMixSlab * r];
+      gd[c][r][1] = s_d[c & 1][1][at.own + kMixSlab * r];
+      gd[c][r][2] = ft[r];
+    }
   }
   int bad = 0;
-  InvJac<float> kk[2];
+  InvJac<float> kk[4];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int r = 0; r < 4; ++r) {
     InvJac<double> k64;
-    bad |= !invert_jacobian<double>(gd[0][h][0], gd[0][h][1], gd[0][h][2], gd[1][h][0],
-                                    gd[1][h][1], gd[1][h][2], gd[2][h][0], gd[2][h][1],
-                                    gd[2][h][2], k64);
-    kk[h] = InvJac<float>{(float)k64.rx, (float)k64.ry, (float)k64.rz,
+    bad |= !invert_jacobian<double>(gd[0][r][0], gd[0][r][1], gd[0][r][2], gd[1][r][0],
+                                    gd[1][r][1], gd[1][r][2], gd[2][r][0], gd[2][r][1],
+                                    gd[2][r][2], k64);
+    kk[r] = InvJac<float>{(float)k64.rx, (float)k64.ry, (float)k64.rz,
                           (float)k64.sx, (float)k64.sy, (float)k64.sz,
                           (float)k64.tx, (float)k64.ty, (float)k64.tz};
-  }
-  float a[2][3][3];
-#pragma unroll
-  for (int c = 0; c < NF - 3; ++c) {
-    float* dt = s_d[(3 + c) & 1];
-    mix_field<M>(s_in[3 + c], dt, ops, wv, lane);
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float fr, fs, ft;
-      mix_read(dt, ni[h], nj[h], nk[h], fr, fs, ft);
-      const InvJac<float>& K = kk[h];
-      a[h][c][0] = fr * K.rx + fs * K.sx + ft * K.tx;
-      a[h][c][1] = fr * K.ry + fs * K.sy + ft * K.ty;
-      a[h][c][2] = fr * K.rz + fs * K.sz + ft * K.tz;
-    }
+    __builtin_amdgcn_sched_barrier(0);   // one node's FP64 values at a time
   }
   // an inverted element (rare) is flagged by its own lanes: no block vote
   if (bad && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);
-  __syncthreads();
+  float a[4][NF - 3][3];
+#pragma unroll
+  for (int c = 0; c < NF - 3; ++c) {
+    const int buf = (3 + c) & 1;
+    const f32x4 tt = mix_field<M>(s_in[3 + c], s_d[buf][0], s_d[buf][1], ops, at);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float fr = s_d[buf][0][at.own + kMixSlab * r];
+      const float fs = s_d[buf][1][at.own + kMixSlab * r];
+      const float ft = tt[r];
+      const InvJac<float>& K = kk[r];
+      a[r][c][0] = fr * K.rx + fs * K.sx + ft * K.tx;
+      a[r][c][1] = fr * K.ry + fs * K.sy + ft * K.ty;
+      a[r][c][2] = fr * K.rz + fs * K.sz + ft * K.tz;
+    }
+  }
+  // the lane's nodes: 4 (g & 1) + r along its t line
+  const int g = lane >> 4, k0 = 4 * (g & 1);
+  const int64_t own = base + 64 * k0 + 32 * wv + 16 * (g >> 1) + (lane & 15);
   if constexpr (!QC) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int64_t o = base + t + 256 * h;
-      o0[o] = a[h][0][0];
-      o1[o] = a[h][0][1];
-      o2[o] = a[h][0][2];
+    for (int r = 0; r < 4; ++r) {
+      o0[own + 64 * r] = a[r][0][0];
+      o1[own + 64 * r] = a[r][0][1];
+      o2[own + 64 * r] = a[r][0][2];
     }
   } else {
     float mn = pos_inf<float>(), mx = neg_inf<float>();
-    float qn[2];
-    uint32_t* bits = reinterpret_cast<uint32_t*>(s_in[0]);   // x was read in the first pass only
+    float qn[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const float(&A)[3][3] = a[h];
+    for (int r = 0; r < 4; ++r) {
+      const float(&A)[3][3] = a[r];
       const float tr2 = A[0][0] * A[0][0] + A[1][1] * A[1][1] + A[2][2] * A[2][2] +
                         2.f * (A[0][1] * A[1][0] + A[0][2] * A[2][0] + A[1][2] * A[2][1]);
       const float w1 = A[2][1] - A[1][2], w2 = A[0][2] - A[2][0], w3 = A[1][0] - A[0][1];
       const float qv = -0.5f * tr2;
-      const int64_t o = base + t + 256 * h;
-      if (o0) o0[o] = qv;
-      if (o1) o1[o] = vort_root(w1 * w1 + w2 * w2 + w3 * w3);
-      qn[h] = qv;
-      if constexpr (COUNT) bits[t + 256 * h] = iso_bits4<float>(qv, sink.iso, 0, sink.n_iso);
+      if (o0) o0[own + 64 * r] = qv;
+      if (o1) o1[own + 64 * r] = vort_root(w1 * w1 + w2 * w2 + w3 * w3);
+      qn[r] = qv;
       const float c = qv != qv ? neg_inf<float>() : qv;
       mn = c < mn ? c : mn;
       mx = c > mx ? c : mx;
     }
-    if (qmm || COUNT) {
-      block_minmax<float, 256>(mn, mx, s_red);   // its barriers publish the Q tile
-      if (qmm && t == 0) {
+    if (qmm) {
+      block_minmax<float, 128>(mn, mx, s_red);
+      if (t == 0) {
         qmm[2 * (int64_t)blockIdx.x] = mn;
         qmm[2 * (int64_t)blockIdx.x + 1] = mx;
       }
     }
     if constexpr (COUNT) {
-      // cells t and t + 256 (t < 87); node words in natural order
-      constexpr int NC = 343;
-      int n0[2];
+      // 16 lanes of a ballot are 16 consecutive nodes
+      __shared__ uint32_t s_bits[kBitGroup][18];
+      for (int i = 0; i < sink.n_iso; i += kBitGroup) {
+        const int m = sink.n_iso - i < kBitGroup ? sink.n_iso - i : kBitGroup;
+        if (i > 0) __syncthreads();   // both waves are done with the previous bits
 #pragma unroll
-      for (int r = 0; r < 2; ++r) n0[r] = cell_base7(t + 256 * r < NC ? t + 256 * r : t);
-      const int64_t e = blockIdx.x;
-      const int n_iso = sink.n_iso;
-      for (int g = 0; g < n_iso; g += 4) {
-        const int m = n_iso - g < 4 ? n_iso - g : 4;
-        if (g > 0) {   // every read of the previous words is behind the last barrier
+        for (int q = 0; q < kBitGroup; ++q) {
+          if (q >= m) break;
+          const float c = sink.iso.v[i + q];
 #pragma unroll
-          for (int h = 0; h < 2; ++h) bits[t + 256 * h] = iso_bits4<float>(qn[h], sink.iso, g, n_iso);
-          __syncthreads();
-        }
-        bool live = false;   // (NaN nodes count as below; mn is -inf then)
-        for (int s = 0; s < m; ++s) live |= (mx > sink.iso.v[g + s]) && !(mn > sink.iso.v[g + s]);
-        uint32_t pw[2] = {0u, 0u};
-        if (live) {
-#pragma unroll
-          for (int r = 0; r < 2; ++r) {
-            if (t + 256 * r >= NC) continue;
-            const uint32_t word = cell_word<8, 64>(bits, n0[r]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-              if (s < m) pw[s >> 1] += (uint32_t)s_tab[(word >> (8 * s)) & 255] << (16 * (s & 1));
+          for (int r = 0; r < 4; ++r) {
+            const uint64_t b = __ballot(qn[r] > c);
+            if ((lane & 15) == 0)
+              reinterpret_cast<uint16_t*>(s_bits[q])[4 * (k0 + r) + 2 * wv + (g >> 1)] =
+                  (uint16_t)(b >> (16 * g));
           }
         }
-        publish_rows<4>(pw, m, g, t, s_rows, sink.cnt, sink.n_elem, e);
+        __syncthreads();
+        for (int q = wv; q < m; q += 2) {
+          const uint32_t sum =
+              count_rows<7>(s_bits[q], 0, lane, reinterpret_cast<const uint8_t*>(s_tab));
+          if (lane == 63) sink.cnt[(int64_t)(i + q) * sink.n_elem + blockIdx.x] = (int)sum;
+        }
       }
     }
   }
@@ -1774,7 +1720,7 @@ hipError_t mixed_t(sem_dtype dt, const DeviceTables& tab, int64_t n_elem, const 
   const CountSink<float> none{};
   const CountSink<float>& sk = sink ? *sink : none;
   auto go = [&](auto kern) {
-    hipExtLaunchKernelGGL(kern, dim3((unsigned)n_elem), dim3(256), 0, s, pt.start, pt.stop, 0,
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)n_elem), dim3(128), 0, s, pt.start, pt.stop, 0,
                           tab.d64[7], (const float*)x, (const float*)y, (const float*)z,
                           (const float*)u, (const float*)v, (const float*)w, (float*)o0,
                           (float*)o1, (float*)o2, (float*)qmm, status, sk);

@@ -190,3 +190,24 @@ def test_mixed_rejects_other_orders_and_dtypes():
     xd = torch.zeros((2, 8, 8, 8), dtype=torch.float64, device=DEV)
     with pytest.raises(TypeError):
         sem.qcrit(xd, xd, xd, xd, xd, xd, precision="bf16")
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("shape,n_iso", [((1, 1, 1), 1), ((3, 1, 1), 4), ((5, 3, 1), 6)])
+def test_mixed_counts_of_a_few_elements_and_many_isovalues(mode, shape, n_iso):
+    """Counts and active cells of the fused call (bit rows, up to four
+    isovalues a round) against the count kernel on the same Q; Q at a NaN
+    velocity node is NaN and counts as below."""
+    x, y, z, u, v, w = (a.astype(np.float32) for a in W.tgv_config(7, shape=shape))
+    u = u.copy()
+    u[-1, 3, 2, 1] = np.nan
+    t = [torch.from_numpy(np.ascontiguousarray(a)).to(DEV) for a in (x, y, z, u, v, w)]
+    q, _, mm = sem.qcrit(*t, precision=mode)
+    isos = [0.01 * (i - 2) for i in range(n_iso)]
+    r = sem.isosurface(t[0], t[1], t[2], q, isos, minmax=mm)
+    e = q.shape[0]
+    ws = torch.empty(sem.extract_workspace_bytes(e, 7, n_iso), dtype=torch.uint8, device=DEV)
+    cnt, act = (torch.zeros(n_iso, dtype=torch.int64, device=DEV) for _ in range(2))
+    sem.extract_into(*t, isos, [None] * n_iso, cnt, ws, active=act, precision=mode)
+    assert torch.equal(cnt, r["tri_count"]) and torch.equal(act, r["active"])
+    assert int(cnt.sum()) > 0
