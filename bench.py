@@ -887,8 +887,9 @@ def c0_timing(args, sem, fields, q, isos, n):
     n_global = gs.n_global
     n_nodes = int(q.numel())
     del gid, gs, qa
-    # dsavg: row pointers, column list, field in and out (FP64)
-    dbytes = 8 * (n_global + 1) + 24 * n_nodes
+    # dsavg: field in and out (FP64), 24 bytes of flags per 64 nodes, and the
+    # 32-bit index of every copy after a node's first
+    dbytes = 16 * n_nodes + 24 * ((n_nodes + 63) // 64) + 4 * (n_nodes - n_global)
     return {"gs_setup_ms": round(setup_ms, 4), "gs_setup_first_ms": round(first_ms, 3),
             "dsavg_ms": round(avg_ms, 5),
             "keys_weld_ms": round(weld_ms, 5), "triangles": n_tri,
