@@ -230,7 +230,6 @@ int sem_init(int device) {
       st.tab.d32[n] = n ? reinterpret_cast<const float*>(b + off32[n]) : nullptr;
     }
     st.tab.ntri = reinterpret_cast<const uint8_t*>(b + off_ntri);
-    st.tab.tri = reinterpret_cast<const int8_t*>(b + off_tri);
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) !=
             hipSuccess || cus <= 0)

@@ -32,8 +32,7 @@ struct DeviceTables {
   // rounded to FP32
   const double* d64[kMaxOrder + 1];
   const float* d32[kMaxOrder + 1];
-  const uint8_t* ntri;                // [256]
-  const int8_t* tri;                  // [256][kMcMaxTri][3]
+  const uint8_t* ntri;                // [256], then the case table [256][kMcMaxTri][3]
   int cu_count;                       // compute units (persistent grids)
   void* scratch;                      // device address of this GPU's copy of the
                                       // fixed scratch array (sem_noalloc.hip)
