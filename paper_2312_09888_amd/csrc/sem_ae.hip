@@ -44,6 +44,10 @@ __device__ __forceinline__ int morton8(int i, int j, int k) {
   return m;
 }
 
+// Several floats of a caller's buffer at once; its alignment is a float's.
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ float half_round(float v) {
   return __half2float(__float2half_rn(v));
 }
@@ -577,17 +581,17 @@ pack_raw(int64_t n_elem, int per, const float* __restrict__ u, const float* __re
       if (lane == 0 && status) atomicOr(status, SEM_FLAG_RAW_OVERFLOW);
       continue;
     }
-    float4 val[4][2];
+    f32x4u val[4][2];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        val[c][h] = reinterpret_cast<const float4*>(f[c] + e * 512)[lane + 64 * h];
+        val[c][h] = reinterpret_cast<const f32x4u*>(f[c] + e * 512)[lane + 64 * h];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        reinterpret_cast<float4*>(raw + (o * 4 + c) * 512)[lane + 64 * h] = val[c][h];
+        reinterpret_cast<f32x4u*>(raw + (o * 4 + c) * 512)[lane + 64 * h] = val[c][h];
   }
 }
 
@@ -849,7 +853,7 @@ ae_encode(int64_t n_elem, int nw, const float* __restrict__ u, const float* __re
     for (int k = 0; k < 4; ++k)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float4 r = *reinterpret_cast<const float4*>(src + 8 * j + 64 * k);
+        const f32x4u r = *reinterpret_cast<const f32x4u*>(src + 8 * j + 64 * k);
         const int s = 2 * (j & 1) + 4 * (k & 1) + 16 * (j >> 1) + 32 * (k >> 1);
         x[s] = r.x;
         x[s + 1] = r.y;
@@ -977,12 +981,33 @@ __device__ __forceinline__ void swap_rows16(float& a, float& b) {
   b = __uint_as_float(r[1]);
 }
 
+// The 32 latents of element e as 16 words, two halves a word.  The address is
+// the same in every lane, so these become scalar loads, and those drop the two
+// low address bits: `words` is the caller's pointer rounded down to a multiple
+// of four, and latents that begin `shift` bits into it are moved into place.
+// (The rounding is done on the host: here it would hide from the compiler that
+// nothing writes to the latents, and the loads would be vector loads.)
+__device__ __forceinline__ void latent_words(const uint32_t* __restrict__ words, int shift,
+                                             int64_t e, uint32_t (&z)[16]) {
+  const uint32_t* w = words + e * 16;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = w[i];
+  if (shift != 0) {
+    const uint32_t last = w[16];   // the rest of the last latent
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint64_t pair = ((uint64_t)(i < 15 ? z[i + 1] : last) << 32) | z[i];
+      z[i] = (uint32_t)(pair >> shift);
+    }
+  }
+}
+
 // Latents -> reconstruction, 2 RT elements per wave and pass.  CHECK: compared
 // with the fields (flag_out[e] = some channel exceeds the fallback bound);
 // else written to the fields, raw blocks copied for flagged elements.
 template <bool CHECK, int RT>
 __global__ void __launch_bounds__(kCodecT)
-ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
+ae_decode(int64_t n_elem, int nw, const uint32_t* __restrict__ latent, int latent_shift,
           const float* __restrict__ scale, const float* __restrict__ gpart, int n_gpart,
           const float* __restrict__ fold,
           const float* __restrict__ b3, const float* __restrict__ iu,
@@ -1020,8 +1045,8 @@ ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
        e0 += step) {
     int64_t e[RT];      // the lane's elements e0 + 2 q + el
     bool ok[RT];
-    float4 sc[RT];
-    uint4 zw[2 * RT][4];   // every element's latents, two halves a word
+    f32x4u sc[RT];
+    uint32_t zw[2 * RT][16];   // every element's latents, two halves a word
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
       e[q] = e0 + 2 * q + el;
@@ -1029,15 +1054,11 @@ ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
       if (!ok[q]) e[q] = n_elem - 1;
       // elements with a raw block are not written from their latents
       if constexpr (!CHECK) ok[q] = ok[q] & !((flag[e[q]] != 0) & (offs[e[q]] < raw_count));
-      sc[q] = *reinterpret_cast<const float4*>(scale + e[q] * 4);
+      sc[q] = *reinterpret_cast<const f32x4u*>(scale + e[q] * 4);
     }
 #pragma unroll
-    for (int x = 0; x < 2 * RT; ++x) {
-      const int64_t ex = e0 + x < n_elem ? e0 + x : n_elem - 1;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        zw[x][i] = reinterpret_cast<const uint4*>(latent + ex * 32)[i];
-    }
+    for (int x = 0; x < 2 * RT; ++x)
+      latent_words(latent, latent_shift, e0 + x < n_elem ? e0 + x : n_elem - 1, zw[x]);
     // the weights' offsets anew in every pass: the reads stay in it
     int lane_now = lane;
     asm volatile("" : "+v"(lane_now));
@@ -1057,8 +1078,7 @@ ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
       float z[2 * RT];
 #pragma unroll
       for (int x = 0; x < 2 * RT; ++x) {
-        const uint4& b = zw[x][i >> 3];
-        const uint32_t word = (i & 6) == 0 ? b.x : (i & 6) == 2 ? b.y : (i & 6) == 4 ? b.z : b.w;
+        const uint32_t word = zw[x][i >> 1];
         z[x] = __half2float(__ushort_as_half((uint16_t)(i & 1 ? word >> 16 : word & 0xffffu)));
       }
 #pragma unroll
@@ -1091,17 +1111,17 @@ ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
 #pragma unroll 1
     for (int g = 0; g < 4; ++g) {
       const int node = node0 + 16 * (g & 1) + 128 * (g >> 1);
-      float2 ref[RT][2][4];
+      f32x2u ref[RT][2][4];
       if constexpr (CHECK) {
 #pragma unroll
         for (int q = 0; q < RT; ++q)
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
             const int64_t at = e[q] * 512 + node + 64 * b;
-            ref[q][b][0] = *reinterpret_cast<const float2*>(iu + at);
-            ref[q][b][1] = *reinterpret_cast<const float2*>(iv + at);
-            ref[q][b][2] = *reinterpret_cast<const float2*>(iw + at);
-            ref[q][b][3] = *reinterpret_cast<const float2*>(ith + at);
+            ref[q][b][0] = *reinterpret_cast<const f32x2u*>(iu + at);
+            ref[q][b][1] = *reinterpret_cast<const f32x2u*>(iv + at);
+            ref[q][b][2] = *reinterpret_cast<const f32x2u*>(iw + at);
+            ref[q][b][3] = *reinterpret_cast<const f32x2u*>(ith + at);
           }
       }
       f32x4 acc[RT][4];
@@ -1144,7 +1164,7 @@ ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
               max_abs(worst[q][c], ref[q][b][c].x - lo, ref[q][b][c].y - hi);
             } else if (ok[q]) {
               float* out = c == 0 ? ou : c == 1 ? ov : c == 2 ? ow : oth;
-              *reinterpret_cast<float2*>(out + e[q] * 512 + node + 64 * b) = make_float2(lo, hi);
+              *reinterpret_cast<f32x2u*>(out + e[q] * 512 + node + 64 * b) = f32x2u{lo, hi};
             }
           }
     }
@@ -1185,8 +1205,8 @@ ae_decode(int64_t n_elem, int nw, const uint16_t* __restrict__ latent,
           const float* src = raw + (o * 4 + c) * 512;
 #pragma unroll
           for (int h = 0; h < 2; ++h)
-            reinterpret_cast<float4*>(out)[lane + 64 * h] =
-                reinterpret_cast<const float4*>(src)[lane + 64 * h];
+            reinterpret_cast<f32x4u*>(out)[lane + 64 * h] =
+                reinterpret_cast<const f32x4u*>(src)[lane + 64 * h];
         }
       }
     }
@@ -1540,9 +1560,12 @@ hipError_t launch_decode(int64_t n_elem, const uint16_t* latent, const float* sc
                          float* const* out, const uint8_t* flag, const float* raw,
                          int64_t raw_count, uint8_t* flag_out, int32_t* status, hipStream_t s) {
   const int per = n_elem >= (int64_t)kCodecGroups * (kCodecT / 64) * 4 ? 4 : 2;
+  const uintptr_t at = reinterpret_cast<uintptr_t>(latent);
+  const uint32_t* words = reinterpret_cast<const uint32_t*>(at & ~uintptr_t(3));
+  const int shift = 8 * (int)(at & 3);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(codec_groups(n_elem, per)), dim3(kCodecT), 0, s, n_elem,
-                       codec_waves(n_elem, per), latent, scale, (const float*)c.gpart,
+                       codec_waves(n_elem, per), words, shift, scale, (const float*)c.gpart,
                        (int)codec_groups(n_elem, 2), (const float*)c.fold,
                        params + layers()[3].b_off, in[0], in[1], in[2], in[3], out[0], out[1],
                        out[2], out[3], flag, (const int64_t*)c.offs, raw, raw ? raw_count : 0,

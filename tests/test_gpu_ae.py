@@ -250,6 +250,49 @@ def test_codec_is_the_same_for_any_number_of_elements():
             assert torch.equal(a, b[:k]), k
 
 
+@pytest.mark.parametrize("e", [5, 8195])
+def test_codec_buffers_at_every_alignment(e):
+    """A packet cut out of one received buffer: latent, scale, flags, raw
+    blocks and fields at every offset that their types allow give the bits of
+    the aligned call (two elements a wave, and four)."""
+    L = sem.lib()
+    r = np.random.default_rng(34)
+    params, _ = sem.ae_pca_init(sem.ae_blocks(
+        list(W.ae_fields(20, DEV, elements=np.arange(1024), dtype=torch.float32)))[0])
+    # noise on every third element: both outcomes occur
+    noise = 0.05 * (np.arange(e).reshape(e, 1, 1, 1) % 3 == 1)
+    f = [(b + torch.from_numpy(noise * r.normal(size=(e, 8, 8, 8))).to(DEV, torch.float32))
+         .contiguous() for b in W.ae_fields(20, DEV, elements=np.arange(e), dtype=torch.float32)]
+    want = sem.ae_compress(f, params)
+    want_f = sem.ae_decompress(want, params)
+    k = want["n_raw"]
+    assert 0 < k < e
+    ws = torch.empty(int(L.sem_ae_compress_workspace_bytes(e)), dtype=torch.uint8, device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def cut(n, dtype, o):                     # n values, o of them into an allocation
+        return torch.full((n + 16,), 99, dtype=dtype, device=DEV)[o:o + n]
+
+    for o in range(1, 9):
+        fields = [cut(e * 512, torch.float32, o % 4).copy_(t.flatten()) for t in f]
+        z, s = cut(e * 32, torch.float16, o), cut(e * 4, torch.float32, o % 4)
+        fl, raw = cut(e, torch.uint8, o), cut(k * 2048, torch.float32, o % 4)
+        n_raw = torch.zeros(1, dtype=torch.int64, device=DEV)
+        rc = L.sem_ae_compress(e, *(t.data_ptr() for t in fields), params.data_ptr(), 0,
+                               z.data_ptr(), s.data_ptr(), fl.data_ptr(), raw.data_ptr(), k,
+                               n_raw.data_ptr(), ws.data_ptr(), ws.numel(), None, stream)
+        assert rc == 0 and int(n_raw.item()) == k
+        for key, t in (("latent", z), ("scale", s), ("flags", fl), ("raw", raw)):
+            assert torch.equal(t, want[key].flatten()), (o, key)
+        out = [cut(e * 512, torch.float32, o % 4) for _ in range(4)]
+        rc = L.sem_ae_decompress(e, z.data_ptr(), s.data_ptr(), fl.data_ptr(), raw.data_ptr(), k,
+                                 params.data_ptr(), 0, *(t.data_ptr() for t in out),
+                                 ws.data_ptr(), ws.numel(), None, stream)
+        assert rc == 0
+        for a, b in zip(out, want_f):
+            assert torch.equal(a, b.flatten()), o
+
+
 def _octant_low_rank(b, seed):
     import test_oracle_ae as T
     return T._low_rank_blocks(b, 24, seed, noise=1e-4).astype(np.float32)
