@@ -810,16 +810,11 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// m = max(m, |a|, |b|), one instruction (a NaN counts as smaller; fmaxf on
-// loaded values adds one instruction each to quiet signalling NaNs).
+// m = max(m, |a|, |b|) in one instruction, for m that is no NaN: a quiet NaN
+// counts as smaller.  A signalling one would replace m, so a and b are results
+// of arithmetic (loaded values are quieted first).
 __device__ __forceinline__ void max_abs(float& m, float a, float b) {
   asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void max_abs8(float& m, const float* x) {
-  asm("v_max3_f32 %0, %0, |%1|, |%2|\n\tv_max3_f32 %0, %0, |%3|, |%4|\n\t"
-      "v_max3_f32 %0, %0, |%5|, |%6|\n\tv_max3_f32 %0, %0, |%7|, |%8|"
-      : "+v"(m)
-      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
 }
 
 // Node 0 of the lane's octant: octant bits (i2, j2, k2).
@@ -884,9 +879,10 @@ ae_encode(int64_t n_elem, int nw, const float* __restrict__ u, const float* __re
     int lane_now = lane;
     asm volatile("" : "+v"(lane_now));
     const int lane4 = lane_now * 4;
-    float mx = 0.f;
+    float mx = 0.f;   // a NaN counts as smaller
 #pragma unroll
-    for (int s = 0; s < 64; s += 8) max_abs8(mx, x + s);
+    for (int s = 0; s < 64; s += 2)
+      max_abs(mx, __builtin_canonicalizef(x[s]), __builtin_canonicalizef(x[s + 1]));
     // over the element's octants (lanes of eight): quads, then half rows
     mx = fmaxf(mx, dpp_or_zero<0xb1, 0xf>(mx));
     mx = fmaxf(mx, dpp_or_zero<0x4e, 0xf>(mx));

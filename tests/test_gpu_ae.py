@@ -293,6 +293,26 @@ def test_codec_buffers_at_every_alignment(e):
             assert torch.equal(a, b.flatten()), o
 
 
+def test_scale_of_fields_with_nan_and_infinity():
+    """A NaN counts as smaller than any value, quiet or signalling, wherever
+    it stands; an infinity is the maximum; other elements do not notice."""
+    r = np.random.default_rng(35)
+    clean = [r.normal(size=(40, 512)).astype(np.float32) for _ in range(4)]
+    params = dev(ae.init_params(36))
+    f = [a.copy() for a in clean]
+    bits = [0x7fc00001, 0x7fa00000, 0xffa00000, 0xffc00000]
+    for e in range(20):                       # element e: NaN of one kind, at 1 to 512 nodes
+        at = r.permutation(512)[:[1, 2, 64, 511, 512][e % 5]]
+        f[e % 4].view(np.uint32)[e, at] = bits[(e // 4) % 4]
+    f[1][7, 100], f[2][13, 5] = np.inf, -np.inf
+    shape = (-1, 8, 8, 8)
+    got = sem.ae_compress([dev(a.reshape(shape)) for a in f], params)
+    want = np.stack([np.where(np.isnan(a), 0, np.abs(a)).max(axis=1) for a in f], 1)
+    np.testing.assert_array_equal(got["scale"].cpu().numpy(), want)
+    ref = sem.ae_compress([dev(a.reshape(shape)) for a in clean], params)
+    assert torch.equal(got["latent"][20:], ref["latent"][20:])
+
+
 def _octant_low_rank(b, seed):
     import test_oracle_ae as T
     return T._low_rank_blocks(b, 24, seed, noise=1e-4).astype(np.float32)
