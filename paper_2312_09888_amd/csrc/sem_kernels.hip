@@ -821,16 +821,16 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
 // before the tiles of the next are known to be there.
 template <int N, typename T>
 __global__ void __launch_bounds__(128)
-emit_direct(int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
+emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
             const T* __restrict__ z, const T* __restrict__ field, int n_iso,
             IsoList<T> iso, IsoOut<T> out, const uint8_t* __restrict__ ntri_tab,
             const int32_t* __restrict__ cnt, const int64_t* __restrict__ offs,
             uint64_t* __restrict__ keys, int64_t* __restrict__ tri_count,
             int32_t* __restrict__ status) {
+  const int64_t e = e_begin + blockIdx.x;
   // the last workgroup also writes the totals (in place of a kernel of its own)
-  if (blockIdx.x == gridDim.x - 1)
+  if (e == n_elem - 1)
     write_totals<T>(threadIdx.x, offs, n_elem, n_iso, tri_count, out, status);
-  const int64_t e = blockIdx.x;
   bool any = false;
   for (int s = 0; s < n_iso; ++s) any |= slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
   if (any)
@@ -1676,15 +1676,32 @@ const coef_t<N, T>* dmat_of(const DeviceTables& tab) {
   else return tab.d64[N];
 }
 
+// A launch holds fewer than 2^32 work-items: more elements than that (at
+// `threads` for every `per` of them) take several.  go(first element, element
+// past the last one, workgroups, start event, stop event).
+template <class Go>
+void launch_parts(int64_t n_elem, int per, int threads, hipEvent_t start, hipEvent_t stop,
+                  const Go& go) {
+  const int64_t most = 0xffffffffll / threads * per;
+  for (int64_t b = 0; b < n_elem; b += most) {
+    const int64_t end = n_elem - b < most ? n_elem : b + most;
+    go(b, end, dim3((unsigned)((end - b + per - 1) / per)), b == 0 ? start : nullptr,
+       end == n_elem ? stop : nullptr);
+  }
+}
+
 template <typename T>
 hipError_t derivs_t(int order, const DeviceTables& tab, int64_t n_elem, const void* x,
                     const void* y, const void* z, const void* f, void* gx, void* gy, void* gz,
                     int32_t* status, hipStream_t s) {
   SEM_ORDER_SWITCH(order, {
     using C = LineOf<N, T>;
-    hipLaunchKernelGGL((derivs_lines<N, T>), dim3((unsigned)((n_elem + C::E - 1) / C::E)),
-                       dim3(C::TH), 0, s, dmat_of<N, T>(tab), (const T*)x, (const T*)y,
-                       (const T*)z, (const T*)f, (T*)gx, (T*)gy, (T*)gz, status, n_elem);
+    launch_parts(n_elem, C::E, C::TH, nullptr, nullptr,
+                 [&](int64_t b, int64_t end, dim3 grid, hipEvent_t, hipEvent_t) {
+                   hipLaunchKernelGGL((derivs_lines<N, T>), grid, dim3(C::TH), 0, s,
+                                      dmat_of<N, T>(tab), (const T*)x, (const T*)y, (const T*)z,
+                                      (const T*)f, (T*)gx, (T*)gy, (T*)gz, status, b, end);
+                 });
   });
   return hipGetLastError();
 }
@@ -1696,10 +1713,13 @@ hipError_t qcrit_t(int order, const DeviceTables& tab, int64_t n_elem, const voi
   const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
   SEM_ORDER_SWITCH(order, {
     using C = LineOf<N, T>;
-    hipExtLaunchKernelGGL((qcrit_lines<N, T>), dim3((unsigned)((n_elem + C::E - 1) / C::E)),
-                          dim3(C::TH), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
-                          (const T*)x, (const T*)y, (const T*)z, (const T*)u, (const T*)v,
-                          (const T*)w, (T*)q, (T*)om, (T*)qmm, status, n_elem);
+    launch_parts(n_elem, C::E, C::TH, pt.start, pt.stop,
+                 [&](int64_t b, int64_t end, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
+                   hipExtLaunchKernelGGL((qcrit_lines<N, T>), grid, dim3(C::TH), 0, s, e0, e1, 0,
+                                         dmat_of<N, T>(tab), (const T*)x, (const T*)y,
+                                         (const T*)z, (const T*)u, (const T*)v, (const T*)w,
+                                         (T*)q, (T*)om, (T*)qmm, status, b, end);
+                 });
   });
   phase_done(pt);
   return hipGetLastError();
@@ -1816,11 +1836,14 @@ hipError_t iso_scan_emit(int order, const DeviceTables& tab, int64_t n_elem, con
   if (!any_cap) return hipGetLastError();
   const PhaseTimer pe = phase_timer(SEM_PHASE_EMIT);
   SEM_ORDER_SWITCH(order, {
-    hipExtLaunchKernelGGL((emit_direct<N, T>), dim3((unsigned)n_elem), dim3(128), 0, s,
-                          pe.start, pe.stop, 0, n_elem, (const T*)x, (const T*)y,
-                          (const T*)z, (const T*)field, n_iso, iso, out, tab.ntri,
-                          (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys, tri_count,
-                          status);
+    launch_parts(n_elem, 1, 128, pe.start, pe.stop,
+                 [&](int64_t b, int64_t, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
+                   hipExtLaunchKernelGGL((emit_direct<N, T>), grid, dim3(128), 0, s, e0, e1, 0, b,
+                                         n_elem, (const T*)x, (const T*)y, (const T*)z,
+                                         (const T*)field, n_iso, iso, out, tab.ntri,
+                                         (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys,
+                                         tri_count, status);
+                 });
   });
   phase_done(pe);
   return hipGetLastError();
@@ -1896,10 +1919,13 @@ hipError_t extract_t(int order, sem_dtype dt, const DeviceTables& tab, int64_t n
   if (!done) {
     SEM_ORDER_SWITCH(order, {
       using C = LineOf<N, T>;
-      hipExtLaunchKernelGGL((qcount_lines<N, T>), dim3((unsigned)((n_elem + C::E - 1) / C::E)),
-                            dim3(C::TH), 0, s, pt.start, pt.stop, 0, dmat_of<N, T>(tab),
-                            (const T*)x, (const T*)y, (const T*)z, (const T*)u, (const T*)v,
-                            (const T*)w, (T*)q, (T*)om, (T*)qmm, status, sink);
+      launch_parts(n_elem, C::E, C::TH, pt.start, pt.stop,
+                   [&](int64_t b, int64_t, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
+                     hipExtLaunchKernelGGL((qcount_lines<N, T>), grid, dim3(C::TH), 0, s, e0, e1,
+                                           0, dmat_of<N, T>(tab), (const T*)x, (const T*)y,
+                                           (const T*)z, (const T*)u, (const T*)v, (const T*)w,
+                                           (T*)q, (T*)om, (T*)qmm, status, b, sink);
+                   });
     });
   }
   phase_done(pt);

@@ -440,9 +440,9 @@ qcrit_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
             const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
             const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
             T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
-            int64_t n_elem) {
+            int64_t e_begin, int64_t n_elem) {
   constexpr int E = LineOf<N, T>::E;
-  const int64_t e0 = (int64_t)blockIdx.x * E;
+  const int64_t e0 = e_begin + (int64_t)blockIdx.x * E;
   const int ne = n_elem - e0 < E ? (int)(n_elem - e0) : E;
   qcrit_lines_elem<N, T, false>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status);
 }
@@ -454,9 +454,9 @@ qcount_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
              const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
              const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
              T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
-             CountSink<T> sink) {
+             int64_t e_begin, CountSink<T> sink) {
   constexpr int E = LineOf<N, T>::E;
-  const int64_t e0 = (int64_t)blockIdx.x * E;
+  const int64_t e0 = e_begin + (int64_t)blockIdx.x * E;
   const int ne = sink.n_elem - e0 < E ? (int)(sink.n_elem - e0) : E;
   qcrit_lines_elem<N, T, true>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status,
                                &sink);
@@ -468,12 +468,12 @@ __global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) =
 derivs_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
              const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ f,
              T* __restrict__ gx, T* __restrict__ gy, T* __restrict__ gz,
-             int32_t* __restrict__ status, int64_t n_elem) {
+             int32_t* __restrict__ status, int64_t e_begin, int64_t n_elem) {
   using C = LineOf<N, T>;
   constexpr int R = C::R;
   __shared__ __align__(16) T tile[C::NF * C::SZ];
   const int t = threadIdx.x;
-  const int64_t e0 = (int64_t)blockIdx.x * C::E, base = e0 * C::NP;
+  const int64_t e0 = e_begin + (int64_t)blockIdx.x * C::E, base = e0 * C::NP;
   const int ne = C::E == 1 || n_elem - e0 >= C::E ? C::E : (int)(n_elem - e0);
   const int nn = C::E == 1 ? C::NN : ne * C::NP, nl = C::E == 1 ? C::NL : ne * C::LN;
   const LineOwner<C> own(t);

@@ -392,3 +392,68 @@ def test_counts_of_any_number_of_elements(n, e, ranges):
         assert int(act[s]) == int(((cs != 0) & (cs != 255)).sum())
         if dump:
             np.testing.assert_array_equal(host(cid[s]), cs.reshape(e, -1))
+
+
+def test_emission_over_more_elements_than_one_launch_holds():
+    """2^25 + 3 elements at 128 work-items each: past what one launch may
+    have.  The crossed elements, on both sides of the cut and at the ends,
+    give the triangles of a call on them alone."""
+    n, e = 2, (1 << 25) + 3
+    at = torch.tensor([0, 5, (1 << 25) - 2, (1 << 25) - 1, 1 << 25, e - 1], device=DEV)
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.rand((e, 3, 3, 3), device=DEV, generator=gen)
+    f = torch.zeros((e, 3, 3, 3), device=DEV)
+    f[at] = torch.rand((len(at), 3, 3, 3), device=DEV, generator=gen)
+    sub = x[at].contiguous()
+    want = sem.isosurface(sub, sub, sub, f[at].contiguous(), [0.4, 0.7])
+    got = sem.isosurface(x, x, x, f, [0.4, 0.7])
+    assert torch.equal(got["tri_count"], want["tri_count"]) and int(got["tri_count"][1]) > 20
+    assert torch.equal(got["active"], want["active"])
+    assert torch.equal(got["tri_xyz"], want["tri_xyz"])
+
+
+def test_q_and_counts_over_more_elements_than_one_launch_holds():
+    """2^26 + 3 order-3 elements in FP32 (64 work-items each): Q and ranges
+    of every element, and the fused counts, equal those of a few."""
+    n, e = 3, (1 << 26) + 3
+    rng = np.random.default_rng(4)
+    g = W.gll_points(n)
+    k, j, i = np.meshgrid(g, g, g, indexing="ij")
+    base = [c + 0.05 * rng.normal(size=c.shape) for c in (i, j, k)] + [rng.normal(size=(4, 4, 4))]
+    few = [torch.from_numpy(np.stack([b] * 8).astype(np.float32)).to(DEV) for b in base]
+    few[3][4:] *= 2.0
+    full = []
+    for t in few:
+        big = torch.empty((e, 4, 4, 4), device=DEV)
+        big[:] = t[0]
+        big[-4:] = t[4:]
+        full.append(big)
+    args = lambda t: (t[0], t[1], t[2], t[3], t[0], t[3])   # noqa: E731
+    wq, _, wmm = sem.qcrit(*args(few), want=("q", "minmax"))
+    q = torch.full((e, 4, 4, 4), float("nan"), device=DEV)
+    mm = torch.full((e, 2), float("nan"), device=DEV)
+    sem.qcrit(*args(full), q=q, minmax=mm, want=())
+    assert not torch.equal(wq[0], wq[4])
+
+    def same(q, mm):
+        ok = torch.equal(q[-4:], wq[4:]) and torch.equal(mm[-4:], wmm[4:])
+        for b in range(0, e - 4, 1 << 22):
+            s = slice(b, min(b + (1 << 22), e - 4))
+            ok = ok and bool((q[s] == wq[0]).all()) and bool((mm[s] == wmm[0]).all())
+        return ok
+
+    assert same(q, mm)
+    q.fill_(float("nan"))
+    mm.fill_(float("nan"))
+    iso = [float(wq[0].median())]
+    cnt, act = (torch.zeros(1, dtype=torch.int64, device=DEV) for _ in range(2))
+    ws = torch.empty(sem.extract_workspace_bytes(e, n, 1, sem.SEM_F32), dtype=torch.uint8,
+                     device=DEV)
+    sem.extract_into(*args(full), iso, [None], cnt, ws, q=q, minmax=mm, active=act)
+    assert same(q, mm)
+    ref = sem.isosurface(few[0], few[1], few[2], wq, iso, cases=True)
+    ntri, _ = mc.case_table()
+    cs = host(ref["cases"][0])
+    t, a = ntri[cs].astype(np.int64).sum(1), ((cs != 0) & (cs != 255)).sum(1)
+    assert int(cnt[0]) == (e - 4) * int(t[0]) + int(t[4:].sum()) and t[0] > 0
+    assert int(act[0]) == (e - 4) * int(a[0]) + int(a[4:].sum())
