@@ -720,48 +720,54 @@ __global__ void fill_i64(int64_t* __restrict__ p, int n, int64_t value) {
 
 // Odd N (an even number of nodes per edge: every tile is a whole number of
 // 16-byte chunks and starts 16-byte aligned): a tile arrives in natural
-// node order, wave h issuing the 1 KiB instructions h, h + 2, ... (lanes
+// node order, wave h of W issuing the 1 KiB instructions h, h + W, ... (lanes
 // past the tile's end load nothing).
-template <int N, typename T>
+template <int N, int W, typename T>
 __device__ __forceinline__ void dma_tile_natural(const T* __restrict__ src, T* raw, int h,
                                                  int lane) {
   constexpr int CH = (N + 1) * (N + 1) * (N + 1) * (int)sizeof(T) / 16;   // 16-byte chunks
   static_assert((N + 1) * (N + 1) * (N + 1) * sizeof(T) % 16 == 0, "whole chunks");
 #pragma unroll
-  for (int q = h; q * 64 < CH; q += 2) {
+  for (int q = h; q * 64 < CH; q += W) {
     if (q * 64 + lane < CH)
       lds_load16(reinterpret_cast<const double*>(src) + 2 * (q * 64 + lane),
                  reinterpret_cast<double*>(raw) + 128 * q);
   }
 }
 
-// Element tile of any order into LDS for two waves: direct loads where the
+// Element tile of any order into LDS by W waves: direct loads where the
 // tile is a whole number of 16-byte chunks at a 16-byte aligned address
 // (odd N), plain loads otherwise.  Consumers wait with
 // s_waitcnt(vm, lgkm = 0) and a barrier.
-template <int N, typename T>
-__device__ __forceinline__ void tile2_lds(const T* __restrict__ src, T* dst, int h, int lane) {
+template <int N, int W, typename T>
+__device__ __forceinline__ void tile_lds(const T* __restrict__ src, T* dst, int h, int lane) {
   constexpr int NP = (N + 1) * (N + 1) * (N + 1);
   if constexpr (N % 2 == 1) {
-    dma_tile_natural<N>(src, dst, h, lane);
+    dma_tile_natural<N, W>(src, dst, h, lane);
   } else {
-    for (int q = 64 * h + lane; q < NP; q += 128) dst[q] = src[q];
+    for (int q = 64 * h + lane; q < NP; q += 64 * W) dst[q] = src[q];
   }
 }
 
-// Emission of element e, which has triangles (two waves): every isovalue with a nonzero count
-// writes its triangles at offs[s * n_elem + e] of out (or of out.ptr[s],
-// relative to the isovalue's first offset, when out.per_iso).
+// Threads of an emission workgroup: one wave where it has a lane for every cell
+// (155,344 order-2 elements at four isovalues, FP32: the extraction 293 us with
+// two waves, 216 with one; 524,288 order-1 elements 781 and 560).
+constexpr int emit_threads(int n) { return n <= 4 ? 64 : 128; }
+
+// Emission of element e, which has triangles: the isovalues s0, s0 + ds, ...
+// with a nonzero count write their triangles at offs[s * n_elem + e] of out (or
+// of out.ptr[s], relative to the isovalue's first offset, when out.per_iso).
 template <int N, typename T, class IL = IsoList<T>, class OUT = IsoOut<T>>
 __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
                                           const T* __restrict__ x, const T* __restrict__ y,
                                           const T* __restrict__ z, const T* __restrict__ field,
-                                          int n_iso, const IL& iso, const OUT& out,
+                                          int s0, int ds, int n_iso, const IL& iso,
+                                          const OUT& out,
                                           const uint8_t* __restrict__ ntri_tab,
                                           const int32_t* __restrict__ cnt,
                                           const int64_t* __restrict__ offs,
                                           uint64_t* __restrict__ keys) {
-  constexpr int P = N + 1, NP = P * P * P, NC = N * N * N;
+  constexpr int P = N + 1, NP = P * P * P, NC = N * N * N, TH = emit_threads(N), W = TH / 64;
   constexpr bool SWZ = N == 7 && std::is_same<T, double>::value;
   // The coordinate tiles are staged in LDS too, except for FP32 at N = 9,
   // which reads the coordinates where the vertices need them (edge
@@ -778,10 +784,10 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
   __shared__ uint4 s_tab[16];      // triangle counts (256 B)
   __shared__ uint8_t s_case[NC];
   __shared__ uint16_t s_desc[NC * kMcMaxTri];
-  __shared__ int32_t s_wave[2];
+  __shared__ int32_t s_wave[W];
   const uint8_t* s_ntri = reinterpret_cast<const uint8_t*>(s_tab);
   const int8_t* s_tri = reinterpret_cast<const int8_t*>(ntri_tab) + 256;   // through the caches
-  __builtin_assume(t >= 0 && t < 128);
+  __builtin_assume(t >= 0 && t < TH);
   const int h = __builtin_amdgcn_readfirstlane(t >> 6);
   const int p = t & 63;
   const int64_t base = e * NP;
@@ -799,11 +805,11 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
     dma_tile(y + base, s_y, h, p);
     dma_tile(z + base, s_z, h, p);
   } else {
-    tile2_lds<N>(field + base, s_f, h, p);
+    tile_lds<N, W>(field + base, s_f, h, p);
     if constexpr (XYZ) {
-      tile2_lds<N>(x + base, s_x, h, p);
-      tile2_lds<N>(y + base, s_y, h, p);
-      tile2_lds<N>(z + base, s_z, h, p);
+      tile_lds<N, W>(x + base, s_x, h, p);
+      tile_lds<N, W>(y + base, s_y, h, p);
+      tile_lds<N, W>(z + base, s_z, h, p);
     }
   }
   const T* gx = XYZ ? s_x : x + base;
@@ -811,7 +817,7 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
   const T* gz = XYZ ? s_z : z + base;
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
   barrier_after_wait();
-  for (int s = 0; s < n_iso; ++s) {
+  for (int s = s0; s < n_iso; s += ds) {
     const int64_t flat = (int64_t)s * n_elem + e;
     if (slot_tris(cnt[flat]) == 0) continue;
     int64_t g = offs[flat];
@@ -823,13 +829,13 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
       cap = out.cap[s];
     }
     if constexpr (SWZ)
-      emit_element<7, 128>(iso.v[s], DmaNode{}, DmaNode{}, s_f, gx, gy, gz, s_ntri, s_tri,
-                           s_case, s_desc, s_wave, dst, g, cap, out.per_iso ? nullptr : keys,
-                           base);
+      emit_element<7, TH>(iso.v[s], DmaNode{}, DmaNode{}, s_f, gx, gy, gz, s_ntri, s_tri,
+                          s_case, s_desc, s_wave, dst, g, cap, out.per_iso ? nullptr : keys,
+                          base);
     else
-      emit_element<N, 128>(iso.v[s], StridedNode<P, P * P>{}, StridedNode<P, P * P>{}, s_f,
-                           gx, gy, gz, s_ntri, s_tri, s_case, s_desc, s_wave, dst, g, cap,
-                           out.per_iso ? nullptr : keys, base);
+      emit_element<N, TH>(iso.v[s], StridedNode<P, P * P>{}, StridedNode<P, P * P>{}, s_f, gx,
+                          gy, gz, s_ntri, s_tri, s_case, s_desc, s_wave, dst, g, cap,
+                          out.per_iso ? nullptr : keys, base);
   }
 }
 
@@ -837,9 +843,10 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
 // elements of order 7, 26 % have triangles; 31 of 124 us if none has), but
 // workgroups that take several elements and look them up together are
 // slower, 133 against 120 us: the triangles of one element must be written
-// before the tiles of the next are known to be there.
+// before the tiles of the next are known to be there.  Few
+// elements leave the chip idle: gridDim.y workgroups share each one's isovalues.
 template <int N, typename T>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(emit_threads(N))
 emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
             const T* __restrict__ z, const T* __restrict__ field, int n_iso,
             IsoList<T> iso, IsoOut<T> out, const uint8_t* __restrict__ ntri_tab,
@@ -848,13 +855,14 @@ emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* _
             int32_t* __restrict__ status) {
   const int64_t e = e_begin + blockIdx.x;
   // the last workgroup also writes the totals (in place of a kernel of its own)
-  if (e == n_elem - 1)
+  if (e == n_elem - 1 && blockIdx.y == 0)
     write_totals<T>(threadIdx.x, offs, n_elem, n_iso, tri_count, out, status);
+  const int s0 = blockIdx.y, ds = gridDim.y;
   bool any = false;
-  for (int s = 0; s < n_iso; ++s) any |= slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
+  for (int s = s0; s < n_iso; s += ds) any |= slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
   if (any)
-    emit_elem<N, T>(e, threadIdx.x, n_elem, x, y, z, field, n_iso, iso, out, ntri_tab, cnt, offs,
-                    keys);
+    emit_elem<N, T>(e, threadIdx.x, n_elem, x, y, z, field, s0, ds, n_iso, iso, out, ntri_tab,
+                    cnt, offs, keys);
 }
 
 // Counts of the elements `mine` of a wave's lanes (in == false: none) at
@@ -1591,7 +1599,7 @@ iso_batch_count(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __res
 }
 
 template <int N, typename T>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(emit_threads(N))
 iso_batch_emit(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __restrict__ jobs,
                const uint8_t* __restrict__ ntri_tab, const int32_t* __restrict__ cnt,
                const int64_t* __restrict__ offs, T* __restrict__ tri, int64_t cap) {
@@ -1609,8 +1617,8 @@ iso_batch_emit(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __rest
     bool any = false;
     for (int s = 0; s < c.n_iso; ++s) any |= slot_tris(cnt[c.slot + s * c.n_elem + e]) > 0;
     if (any)
-      emit_elem<N, T>(e, t, c.n_elem, c.x, c.y, c.z, c.field, c.n_iso, IsoPtr<T>{c.iso}, out,
-                      ntri_tab, cnt + c.slot, offs + c.slot, nullptr);
+      emit_elem<N, T>(e, t, c.n_elem, c.x, c.y, c.z, c.field, 0, 1, c.n_iso, IsoPtr<T>{c.iso},
+                      out, ntri_tab, cnt + c.slot, offs + c.slot, nullptr);
   }
 }
 
@@ -1830,6 +1838,14 @@ void scan_kernels(const CT* cnt, int64_t count, int64_t* partial, int64_t* offs,
                                                 start, stop);
 }
 
+// Workgroups that share the isovalues of each element: some 2,048 in all (64
+// isovalues, 8 order-9 elements in FP64: the extraction 319 us with one each, 90
+// so; 64 elements at 16 isovalues 88 and 43).
+unsigned iso_slices(int64_t n_elem, int n_iso) {
+  const int64_t k = 2048 / n_elem;
+  return (unsigned)(k < 1 ? 1 : k < n_iso ? k : n_iso);
+}
+
 // Workgroups of the count kernel: an element per wave while the chip has room
 // for more waves, then as many waves as it holds.
 unsigned count_grid(int64_t n_elem) {
@@ -1855,11 +1871,12 @@ hipError_t iso_scan_emit(int order, const DeviceTables& tab, int64_t n_elem, con
   if (!any_cap) return hipGetLastError();
   const PhaseTimer pe = phase_timer(SEM_PHASE_EMIT);
   SEM_ORDER_SWITCH(order, {
-    launch_parts(n_elem, 1, 128, pe.start, pe.stop,
+    launch_parts(n_elem, 1, emit_threads(N), pe.start, pe.stop,
                  [&](int64_t b, int64_t, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
-                   hipExtLaunchKernelGGL((emit_direct<N, T>), grid, dim3(128), 0, s, e0, e1, 0, b,
-                                         n_elem, (const T*)x, (const T*)y, (const T*)z,
-                                         (const T*)field, n_iso, iso, out, tab.ntri,
+                   grid.y = iso_slices(n_elem, n_iso);
+                   hipExtLaunchKernelGGL((emit_direct<N, T>), grid, dim3(emit_threads(N)), 0, s,
+                                         e0, e1, 0, b, n_elem, (const T*)x, (const T*)y,
+                                         (const T*)z, (const T*)field, n_iso, iso, out, tab.ntri,
                                          (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys,
                                          tri_count, status);
                  });
@@ -2092,7 +2109,7 @@ hipError_t iso_batch_phase(bool f64, bool emit, const IsoBatchHeader* hdr,
   // benchmark snapshots: 4.54 ms at 1x, 3.58 at 4x, 3.60 at 16x, 3.84 at 64x;
   // 48 separate sem_isosurface calls: 4.4 ms).  Workgroups that start later
   // take the slots the early finishers free.
-  const int threads = emit ? 128 : 64 * kCountWaves;
+  const int threads = emit ? emit_threads(N) : 64 * kCountWaves;
   return hipExtLaunchKernel(fn, dim3((emit ? 4 : 1) * batch_grid(fn, threads, tab.cu_count)),
                             dim3(threads), emit ? emit_args : count_args, 0, s, a, b, 0);
 }

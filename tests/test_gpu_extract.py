@@ -129,6 +129,27 @@ def test_active_totals_over_scan_tiles(elems, n_iso):
     sem.isosurface_into(*t[:3], q, isos, None, cnt, iws, minmax=mm, active=act)
     np.testing.assert_array_equal(host(act), o["active"])
 
+@pytest.mark.parametrize("n, shape", [(1, (10, 10, 7)), (4, (10, 10, 7)), (6, (5, 6, 5)),
+                                      (7, (10, 10, 7)), (8, (3, 1, 1))])
+def test_isovalues_shared_out_over_workgroups(n, shape):
+    """Few elements: their isovalues go to several workgroups each (two of
+    2 or 3 isovalues, or one of each).  Every isovalue's triangles are those
+    of a call on it alone."""
+    x, y, z, u, v, w = (dev(a) for a in _inputs(n, shape, 5))
+    q, _, mm = sem.qcrit(x, y, z, u, v, w)
+    isos = [float(c) for c in np.percentile(host(q), [20, 45, 50, 80, 97])]
+    r = sem.extract(x, y, z, u, v, w, isos)
+    s = sem.isosurface(x, y, z, q, isos, minmax=mm)
+    at = 0
+    for k, c in enumerate(isos):
+        one = sem.isosurface(x, y, z, q, [c], minmax=mm)
+        m = int(one["tri_count"][0])
+        assert m > 0 and int(r["tri_count"][k]) == m and int(s["tri_count"][k]) == m
+        assert torch.equal(r["tri"][k], one["tri_xyz"])
+        assert torch.equal(s["tri_xyz"][at:at + m], one["tri_xyz"])
+        at += m
+
+
 @pytest.mark.parametrize("dt", [np.float64, np.float32])
 def test_extract_equals_qcrit_then_isosurface(dt):
     n = 7
