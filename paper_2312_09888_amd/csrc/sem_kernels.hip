@@ -332,6 +332,13 @@ __device__ __forceinline__ uint32_t row_sum16(uint32_t v) {
   return v;
 }
 
+// Sum over each quad of lanes, in all of them (quad_perm [1,0,3,2], [2,3,0,1]).
+__device__ __forceinline__ uint32_t quad_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, false);
+  return v;
+}
+
 // Sum over the wave, left in lane 63 (other lanes hold partial sums): the
 // row sums above, then lane 15 of rows 0 and 2 added into rows 1 and 3
 // (row_bcast:15) and lane 31 into rows 2 and 3 (row_bcast:31); lanes of the
