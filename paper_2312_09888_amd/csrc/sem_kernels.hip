@@ -872,8 +872,8 @@ emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* _
                     cnt, offs, keys);
 }
 
-// Counts of the elements `mine` of a wave's lanes (in == false: none) at
-// every isovalue, and their cells' cases if case_idx.  The lanes look their
+// Counts of the elements `mine` of a wave's lanes (in == false: none) at the
+// isovalues s0, s0 + ds, ..., and their cells' cases if case_idx.  The lanes look their
 // elements' ranges up at once; elements that no isovalue crosses get zero
 // counts without being read, the others are counted one after the other from
 // bit rows (count_rows).  mm == NULL: every element is read (a value that is
@@ -882,8 +882,8 @@ emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* _
 template <int N, typename T, class IL>
 __device__ __forceinline__ void count_lanes(int64_t mine, bool in, int lane, int64_t n_elem,
                                             const T* __restrict__ field,
-                                            const T* __restrict__ mm, int n_iso, const IL& iso,
-                                            const uint8_t* tab, uint64_t* bits,
+                                            const T* __restrict__ mm, int s0, int ds, int n_iso,
+                                            const IL& iso, const uint8_t* tab, uint64_t* bits,
                                             int32_t* __restrict__ cnt,
                                             uint8_t* __restrict__ case_idx) {
   constexpr int P = N + 1, NP = P * P * P, NC = N * N * N, R = (NP + 63) / 64;
@@ -893,7 +893,7 @@ __device__ __forceinline__ void count_lanes(int64_t mine, bool in, int lane, int
     hi = mm[2 * mine + 1];
   }
   bool need = false;
-  for (int s = 0; s < n_iso; ++s) {
+  for (int s = s0; s < n_iso; s += ds) {
     const T c = iso.v[s];
     const bool crossed = in && (!mm || (hi > c && !(lo > c)));
     need |= crossed;
@@ -917,7 +917,7 @@ __device__ __forceinline__ void count_lanes(int64_t mine, bool in, int lane, int
       const int q = 64 * r + lane;
       v[r] = src[q < NP ? q : NP - 1];
     }
-    for (int s = 0; s < n_iso; ++s) {
+    for (int s = s0; s < n_iso; s += ds) {
       const T c = iso.v[s];
       if (__ballot(lane == from && (!mm || (hi > c && !(lo > c)))) == 0) continue;
       uint64_t b[R];
@@ -938,7 +938,8 @@ __device__ __forceinline__ void count_lanes(int64_t mine, bool in, int lane, int
 }
 
 // count_waves<N, T>: the count pass of the two-pass isosurface, four
-// independent waves a workgroup; wave w takes elements w, w + waves, ...
+// independent waves a workgroup; wave w takes elements w, w + waves, ...; of
+// few elements gridDim.y workgroups share the isovalues.
 // Bound by the field's elements that an isovalue crosses, read once.  A
 // workgroup per element spent its time on starting: 33 us for 24,389
 // elements of order 6 (FP32, four isovalues) with or without any to read.
@@ -961,8 +962,8 @@ count_waves(int64_t n_elem, const T* __restrict__ field, const T* __restrict__ m
   const int64_t step = (int64_t)gridDim.x * kCountWaves;
   for (int64_t e0 = (int64_t)blockIdx.x * kCountWaves + wave; e0 < n_elem; e0 += 64 * step) {
     const int64_t mine = e0 + lane * step;
-    count_lanes<N, T>(mine, mine < n_elem, lane, n_elem, field, mm, n_iso, iso,
-                      reinterpret_cast<const uint8_t*>(s_tab), s_bits[wave], cnt, case_idx);
+    count_lanes<N, T>(mine, mine < n_elem, lane, n_elem, field, mm, blockIdx.y, gridDim.y, n_iso,
+                      iso, reinterpret_cast<const uint8_t*>(s_tab), s_bits[wave], cnt, case_idx);
   }
 }
 
@@ -1597,7 +1598,7 @@ iso_batch_count(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __res
       c.seek(jobs, j0, j1, total, i);
       const int64_t stop = end < c.next_begin ? end : c.next_begin;
       const int64_t mine = i - c.begin + lane;
-      count_lanes<N, T>(mine, i + lane < stop, lane, c.n_elem, c.field, c.mm, c.n_iso,
+      count_lanes<N, T>(mine, i + lane < stop, lane, c.n_elem, c.field, c.mm, 0, 1, c.n_iso,
                         IsoPtr<T>{c.iso}, reinterpret_cast<const uint8_t*>(s_tab),
                         s_bits[wave], cnt + c.slot, nullptr);
       i = stop;
@@ -1845,9 +1846,10 @@ void scan_kernels(const CT* cnt, int64_t count, int64_t* partial, int64_t* offs,
                                                 start, stop);
 }
 
-// Workgroups that share the isovalues of each element: some 2,048 in all (64
-// isovalues, 8 order-9 elements in FP64: the extraction 319 us with one each, 90
-// so; 64 elements at 16 isovalues 88 and 43).
+// Workgroups that share the isovalues of each element in the emission and in the
+// count kernel: some 2,048 in all (order 9, FP64: the extraction of 8 elements at
+// 64 isovalues 319 us with one each, 90 so, of 64 at 16 88 and 43; order 8: the
+// isosurfaces of the same 285 and 24, 81 and 24).
 unsigned iso_slices(int64_t n_elem, int n_iso) {
   const int64_t k = 2048 / n_elem;
   return (unsigned)(k < 1 ? 1 : k < n_iso ? k : n_iso);
@@ -1903,9 +1905,10 @@ hipError_t iso_pipeline(int order, const DeviceTables& tab, int64_t n_elem, cons
   const IsoList<T> iso = make_isolist<T>(n_iso, iso_host);
   const PhaseTimer pt = phase_timer(SEM_PHASE_COUNT);
   SEM_ORDER_SWITCH(order, {
-    hipExtLaunchKernelGGL((count_waves<N, T>), dim3(count_grid(n_elem)), dim3(64 * kCountWaves), 0,
-                          s, pt.start, pt.stop, 0, n_elem, (const T*)field, (const T*)mm, n_iso,
-                          iso, tab.ntri, ws.cnt, active, case_idx);
+    hipExtLaunchKernelGGL((count_waves<N, T>), dim3(count_grid(n_elem), iso_slices(n_elem, n_iso)),
+                          dim3(64 * kCountWaves), 0, s, pt.start, pt.stop, 0, n_elem,
+                          (const T*)field, (const T*)mm, n_iso, iso, tab.ntri, ws.cnt, active,
+                          case_idx);
   });
   phase_done(pt);
   return iso_scan_emit<T>(order, tab, n_elem, x, y, z, field, n_iso, iso, out, keys, tri_count,
