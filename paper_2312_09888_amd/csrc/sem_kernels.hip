@@ -1631,12 +1631,27 @@ iso_batch_emit(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __rest
 }
 
 // Per (job, isovalue): first triangle and count (isovalues past a job's
-// n_iso get count 0 at the job's end); the overflow flag if the soup does
-// not fit.
+// n_iso get count 0 at the job's end), by the first `totals` workgroups; the
+// overflow flag if the soup does not fit.  Each later workgroup adds up the
+// active cells of one (job, isovalue) from its slots (0 past the job's isovalues).
 __global__ void __launch_bounds__(256)
 iso_batch_totals(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __restrict__ jobs,
-                 const int64_t* __restrict__ offs, int64_t* __restrict__ tri_offset,
-                 int64_t* __restrict__ tri_count, int64_t cap, int32_t* __restrict__ status) {
+                 const int32_t* __restrict__ cnt, const int64_t* __restrict__ offs,
+                 int64_t* __restrict__ tri_offset, int64_t* __restrict__ tri_count,
+                 int64_t* __restrict__ active, int totals, int64_t cap,
+                 int32_t* __restrict__ status) {
+  __shared__ int64_t sred[256 / 64];
+  if ((int)blockIdx.x >= totals) {
+    const int at = blockIdx.x - totals, s = at & 3;
+    const IsoBatchJob& jb = jobs[at >> 2];
+    int64_t a = 0;
+    if (s < jb.n_iso)
+      for (int64_t e = threadIdx.x; e < jb.n_elem; e += 256)
+        a += slot_active(cnt[jb.slot_begin + s * jb.n_elem + e]);
+    a = block_sum<256>(a, sred);
+    if (threadIdx.x == 0) active[4 * jb.job + s] = a;
+    return;
+  }
   const int idx = blockIdx.x * 256 + threadIdx.x;
   if (idx < 4 * hdr->n_job) {
     const IsoBatchJob& jb = jobs[idx >> 2];
@@ -1647,22 +1662,6 @@ iso_batch_totals(const IsoBatchHeader* __restrict__ hdr, const IsoBatchJob* __re
     tri_count[4 * jb.job + s] = offs[hi] - offs[lo];
   }
   if (idx == 0 && status && offs[hdr->n_slots] > cap) atomicOr(status, SEM_FLAG_TRI_OVERFLOW);
-}
-
-// Active cells of (job, isovalue) blockIdx.x: its slots' sum (0 past the
-// job's isovalues).
-__global__ void __launch_bounds__(256)
-iso_batch_active(const IsoBatchJob* __restrict__ jobs, const int32_t* __restrict__ cnt,
-                 int64_t* __restrict__ active) {
-  __shared__ int64_t sred[256 / 64];
-  const IsoBatchJob& jb = jobs[blockIdx.x >> 2];
-  const int s = blockIdx.x & 3;
-  int64_t a = 0;
-  if (s < jb.n_iso)
-    for (int64_t e = threadIdx.x; e < jb.n_elem; e += 256)
-      a += slot_active(cnt[jb.slot_begin + s * jb.n_elem + e]);
-  a = block_sum<256>(a, sred);
-  if (threadIdx.x == 0) active[4 * jb.job + s] = a;
 }
 
 // Synthetic unit-cube elements on a 16 x 16 x ... lattice with node
@@ -2166,14 +2165,12 @@ hipError_t launch_iso_batch(sem_dtype dt, const DeviceTables& tab, const void* p
       // isovalue) totals
       const PhaseTimer ps = phase_timer(SEM_PHASE_SCAN);
       scan_kernels<true>(ws.cnt, n_slots, ws.partial, ws.offs, nullptr, 1, s, ps.start, nullptr);
-      const unsigned tb = (unsigned)((4 * (int64_t)n_job + 255) / 256);
-      hipExtLaunchKernelGGL(iso_batch_totals, dim3(tb > 0 ? tb : 1), dim3(256), 0, s, nullptr,
-                            ps.stop, 0, hdr, jobs, (const int64_t*)ws.offs, tri_offset,
-                            tri_count, cap, status);
+      const unsigned tb = n_job > 0 ? (unsigned)((4 * (int64_t)n_job + 255) / 256) : 1;
+      hipExtLaunchKernelGGL(iso_batch_totals, dim3(tb + (active ? 4 * (unsigned)n_job : 0)),
+                            dim3(256), 0, s, nullptr, ps.stop, 0, hdr, jobs,
+                            (const int32_t*)ws.cnt, (const int64_t*)ws.offs, tri_offset,
+                            tri_count, active, (int)tb, cap, status);
       phase_done(ps);
-      if (active)
-        hipLaunchKernelGGL(iso_batch_active, dim3(4 * (unsigned)n_job), dim3(256), 0, s, jobs,
-                           (const int32_t*)ws.cnt, active);
       if (cap <= 0) break;
     }
   }
