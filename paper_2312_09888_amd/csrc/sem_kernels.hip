@@ -1428,9 +1428,19 @@ constexpr int batch_threads() {
   return FORM == kBatchLines ? LineOf<N, T>::TH : kBatchThreads;
 }
 
+// Waves per SIMD to hold: the LDS tile leaves room for three workgroups a CU in
+// FP64 and six in FP32; a few registers more than three (four) waves allow cost
+// the tile form a quarter (12,228 order-6 elements, FP64: 168 us, 226 with two).
+// Order 9 in FP64 would spill too much for three (188 us with two, 195).
 template <int N, typename T, int FORM>
-__global__ void __launch_bounds__((batch_threads<N, T, FORM>()),
-                                  (FORM == kBatchLines ? line_waves(N, sizeof(T) == 8) : 1))
+constexpr int batch_waves() {
+  return FORM == kBatchLines ? line_waves(N, sizeof(T) == 8)
+         : sizeof(T) == 4    ? 4
+                             : N < 9 ? 3 : 2;
+}
+
+template <int N, typename T, int FORM>
+__global__ void __launch_bounds__((batch_threads<N, T, FORM>()), (batch_waves<N, T, FORM>()))
 qcrit_batch(const BatchHeader* __restrict__ hdr, const BatchSnap* __restrict__ snaps,
             int32_t* __restrict__ status) {
   const int s0 = hdr->snap_begin[N], s1 = hdr->snap_begin[N + 1];
