@@ -1434,7 +1434,7 @@ constexpr int batch_threads() {
 // Order 9 in FP64 would spill too much for three (188 us with two, 195).
 template <int N, typename T, int FORM>
 constexpr int batch_waves() {
-  return FORM == kBatchLines ? line_waves(N, sizeof(T) == 8)
+  return FORM == kBatchLines ? line_waves<N, T, LineOf<N, T>>()
          : sizeof(T) == 4    ? 4
                              : N < 9 ? 3 : 2;
 }
@@ -1497,7 +1497,7 @@ qcrit_batch(const BatchHeader* __restrict__ hdr, const BatchSnap* __restrict__ s
       constexpr int E = LineOf<N, T>::E;   // the item's chunk
       const int64_t left = n_elem - e0;
       const int ne = (int)(left < E ? left : E);
-      qcrit_lines_elem<N, T, false>(e0, t, ne, dmat, f0, f1, f2, f3, f4, f5, oq, oom, oqmm,
+      qcrit_lines_elem<N, T, false, LineOf<N, T>>(e0, t, ne, dmat, f0, f1, f2, f3, f4, f5, oq, oom, oqmm,
                                     status);
     }
     __syncthreads();                   // the next item reuses the LDS
@@ -1742,7 +1742,7 @@ hipError_t derivs_t(int order, const DeviceTables& tab, int64_t n_elem, const vo
     using C = LineOf<N, T>;
     launch_parts(n_elem, C::E, C::TH, nullptr, nullptr,
                  [&](int64_t b, int64_t end, dim3 grid, hipEvent_t, hipEvent_t) {
-                   hipLaunchKernelGGL((derivs_lines<N, T>), grid, dim3(C::TH), 0, s,
+                   hipLaunchKernelGGL((derivs_lines<N, T, C>), grid, dim3(C::TH), 0, s,
                                       dmat_of<N, T>(tab), (const T*)x, (const T*)y, (const T*)z,
                                       (const T*)f, (T*)gx, (T*)gy, (T*)gz, status, b, end);
                  });
@@ -1759,7 +1759,7 @@ hipError_t qcrit_t(int order, const DeviceTables& tab, int64_t n_elem, const voi
     using C = LineOf<N, T>;
     launch_parts(n_elem, C::E, C::TH, pt.start, pt.stop,
                  [&](int64_t b, int64_t end, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
-                   hipExtLaunchKernelGGL((qcrit_lines<N, T>), grid, dim3(C::TH), 0, s, e0, e1, 0,
+                   hipExtLaunchKernelGGL((qcrit_lines<N, T, C>), grid, dim3(C::TH), 0, s, e0, e1, 0,
                                          dmat_of<N, T>(tab), (const T*)x, (const T*)y,
                                          (const T*)z, (const T*)u, (const T*)v, (const T*)w,
                                          (T*)q, (T*)om, (T*)qmm, status, b, end);
@@ -1976,7 +1976,7 @@ hipError_t extract_t(int order, sem_dtype dt, const DeviceTables& tab, int64_t n
       using C = LineOf<N, T>;
       launch_parts(n_elem, C::E, C::TH, pt.start, pt.stop,
                    [&](int64_t b, int64_t, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
-                     hipExtLaunchKernelGGL((qcount_lines<N, T>), grid, dim3(C::TH), 0, s, e0, e1,
+                     hipExtLaunchKernelGGL((qcount_lines<N, T, C>), grid, dim3(C::TH), 0, s, e0, e1,
                                            0, dmat_of<N, T>(tab), (const T*)x, (const T*)y,
                                            (const T*)z, (const T*)u, (const T*)v, (const T*)w,
                                            (T*)q, (T*)om, (T*)qmm, status, b, sink);

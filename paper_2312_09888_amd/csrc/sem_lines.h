@@ -57,10 +57,10 @@ struct LineCfg {
 // four waves on swizzled tiles fetched by direct loads: Q with the counts of
 // the 65,536-element snapshot 0.55 ms, here 0.44 with the packed slots).
 constexpr int kLineCfg64[kMaxOrder + 1][4] = {
-    {0, 0, 0, 0},   {32, 256, 2, 3}, {9, 256, 3, 3},  {1, 64, 6, 3},  {1, 128, 5, 3},
+    {0, 0, 0, 0},   {8, 64, 2, 3},  {9, 256, 3, 3},  {1, 64, 6, 3},  {1, 128, 5, 3},
     {1, 256, 6, 3}, {1, 128, 7, 3},  {1, 256, 10, 1}, {1, 256, 9, 1}, {1, 512, 10, 1}};
 constexpr int kLineCfg32[kMaxOrder + 1][4] = {
-    {0, 0, 0, 0},  {16, 128, 3, 3}, {9, 256, 3, 3}, {1, 64, 4, 3},  {2, 128, 5, 3},
+    {0, 0, 0, 0},  {16, 64, 2, 3}, {9, 256, 3, 3}, {1, 64, 4, 3},  {2, 128, 5, 3},
     {1, 64, 7, 1}, {1, 128, 7, 3},  {1, 256, 9, 3}, {1, 256, 9, 3}, {1, 512, 10, 1}};
 constexpr int line_cfg(int n, bool f64, int k) {
   return f64 ? kLineCfg64[n][k] : kLineCfg32[n][k];
@@ -71,9 +71,14 @@ using LineOf = LineCfg<N, line_cfg(N, sizeof(T) == 8, 0), line_cfg(N, sizeof(T) 
 
 // Waves per SIMD to hold (launch bound): FP64 N = 6..9 sit a few registers
 // around the limits of three and four waves; elsewhere the compiler's choice.
-constexpr int line_waves(int n, bool f64) {
-  return !f64 || n < 6 ? 1 : (n == 6 || n == 8) ? 3 : 4;
+template <int N, typename T, class C>
+constexpr int line_waves() {
+  return sizeof(T) == 4 || N < 6 ? 1 : N == 6 || N == 8 ? 3 : 4;
 }
+
+// LDS values of `fields` fields' lines (order 1 needs none).
+template <int N, class C>
+constexpr int line_tile(int fields) { return N == 1 ? 1 : fields * C::SZ; }
 
 // Offsets of an owner's nodes in their three lines.
 template <class C>
@@ -94,6 +99,24 @@ struct LineOwner {
   }
 };
 
+// Value of the lane whose number differs in bit X (0, 1 or 2) only: quad_perm
+// [1,0,3,2], [2,3,0,1]; [3,2,1,0] of the half row mirrored.
+template <int X, typename T>
+__device__ __forceinline__ T lane_across(T v) {
+  if constexpr (X == 0) return dpp_move<0xb1>(v);
+  else if constexpr (X == 1) return dpp_move<0x4e>(v);
+  else return dpp_move<0x1b>(dpp_move<0x141>(v));
+}
+
+// Order 1: an element is eight neighbouring lanes and a line two of them, so
+// the derivatives need no exchange: (f_1 - f_0) D_11 at both ends.  Q of
+// 4,194,304 elements in FP32: 363 us with pencils, 395 through LDS, 185 so.
+template <int X, class C, typename K, typename T>
+__device__ __forceinline__ T pair_deriv(T v, K d11, int t) {
+  const K own = (K)v, other = (K)lane_across<X>(v);
+  return (T)(d11 * (((t >> X) & 1) ? own - other : other - own));
+}
+
 // F fields through the exchange: values at the owner's nodes in f, reference
 // derivatives (r, s, t) there in g.  nn nodes and nl lines exist.
 template <int N, class C, int F, typename T>
@@ -101,6 +124,18 @@ __device__ __forceinline__ void line_pass(const T (*f)[C::R], const LineOwner<C>
                                           const coef_t<N, T>* __restrict__ d, T* tile, int t,
                                           int nn, int nl, T (*g)[C::R][3]) {
   constexpr int P = C::P, TASKS = F * C::NL;
+  if constexpr (N == 1) {
+    const coef_t<N, T> d11 = coef(d, 3);
+#pragma unroll
+    for (int c = 0; c < F; ++c)
+#pragma unroll
+      for (int r = 0; r < C::R; ++r) {
+        g[c][r][0] = pair_deriv<0, C>(f[c][r], d11, t);
+        g[c][r][1] = pair_deriv<1, C>(f[c][r], d11, t);
+        g[c][r][2] = pair_deriv<2, C>(f[c][r], d11, t);
+      }
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < F; ++c)
 #pragma unroll
@@ -308,15 +343,14 @@ __device__ __forceinline__ void line_count(const T (&qv)[C::R], int64_t e, int t
 // Q, |omega|, ranges and counts
 // ---------------------------------------------------------------------------
 
-template <int N, typename T, bool COUNT>
+template <int N, typename T, bool COUNT, class C>
 __device__ __forceinline__ void qcrit_lines_elem(
     int64_t e, int t, int ne, const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
     const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
     const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q, T* __restrict__ om,
     T* __restrict__ qmm, int32_t* __restrict__ status, const CountSink<T>* sink = nullptr) {
-  using C = LineOf<N, T>;
   constexpr int NP = C::NP, R = C::R, NW = C::NW;
-  __shared__ __align__(16) T tile[C::NF * C::SZ];
+  __shared__ __align__(16) T tile[line_tile<N, C>(C::NF)];
   __shared__ T red[2 * NW];
   __shared__ uint32_t s_tab[COUNT ? 64 : 1];
   const int64_t base = e * NP;
@@ -423,6 +457,23 @@ __device__ __forceinline__ void qcrit_lines_elem(
       qmm[2 * e] = mn;
       qmm[2 * e + 1] = mx;
     }
+  } else if constexpr (N == 1) {
+    // ranges over an element's eight lanes
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      T a = qv[r], b = qv[r];
+      a = fmin(a, lane_across<0>(a));
+      b = fmax(b, lane_across<0>(b));
+      a = fmin(a, lane_across<1>(a));
+      b = fmax(b, lane_across<1>(b));
+      a = fmin(a, lane_across<2>(a));
+      b = fmax(b, lane_across<2>(b));
+      const int o = t + r * C::TH;
+      if (qmm && (t & 7) == 0 && o < nn) {
+        qmm[2 * (e + o / 8)] = a;
+        qmm[2 * (e + o / 8) + 1] = b;
+      }
+    }
   } else {
     // ranges: the values through LDS, a wave per element
     __syncthreads();   // every derivative of the last pass is read
@@ -452,44 +503,41 @@ __device__ __forceinline__ void qcrit_lines_elem(
   }
 }
 
-template <int N, typename T>
-__global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) == 8)))
+template <int N, typename T, class C>
+__global__ void __launch_bounds__((C::TH), (line_waves<N, T, C>()))
 qcrit_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
             const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
             const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
             T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
             int64_t e_begin, int64_t n_elem) {
-  constexpr int E = LineOf<N, T>::E;
-  const int64_t e0 = e_begin + (int64_t)blockIdx.x * E;
-  const int ne = n_elem - e0 < E ? (int)(n_elem - e0) : E;
-  qcrit_lines_elem<N, T, false>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status);
+  const int64_t e0 = e_begin + (int64_t)blockIdx.x * C::E;
+  const int ne = n_elem - e0 < C::E ? (int)(n_elem - e0) : C::E;
+  qcrit_lines_elem<N, T, false, C>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status);
 }
 
 // Q, |omega|, range and the per-(isovalue, element) counts in one pass.
-template <int N, typename T>
-__global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) == 8)))
+template <int N, typename T, class C>
+__global__ void __launch_bounds__((C::TH), (line_waves<N, T, C>()))
 qcount_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
              const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ u,
              const T* __restrict__ v, const T* __restrict__ w, T* __restrict__ q,
              T* __restrict__ om, T* __restrict__ qmm, int32_t* __restrict__ status,
              int64_t e_begin, CountSink<T> sink) {
-  constexpr int E = LineOf<N, T>::E;
-  const int64_t e0 = e_begin + (int64_t)blockIdx.x * E;
-  const int ne = sink.n_elem - e0 < E ? (int)(sink.n_elem - e0) : E;
-  qcrit_lines_elem<N, T, true>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status,
+  const int64_t e0 = e_begin + (int64_t)blockIdx.x * C::E;
+  const int ne = sink.n_elem - e0 < C::E ? (int)(sink.n_elem - e0) : C::E;
+  qcrit_lines_elem<N, T, true, C>(e0, threadIdx.x, ne, dmat, x, y, z, u, v, w, q, om, qmm, status,
                                &sink);
 }
 
 // Physical gradient of f.
-template <int N, typename T>
-__global__ void __launch_bounds__((LineOf<N, T>::TH), (line_waves(N, sizeof(T) == 8)))
+template <int N, typename T, class C>
+__global__ void __launch_bounds__((C::TH), (line_waves<N, T, C>()))
 derivs_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
              const T* __restrict__ y, const T* __restrict__ z, const T* __restrict__ f,
              T* __restrict__ gx, T* __restrict__ gy, T* __restrict__ gz,
              int32_t* __restrict__ status, int64_t e_begin, int64_t n_elem) {
-  using C = LineOf<N, T>;
   constexpr int R = C::R;
-  __shared__ __align__(16) T tile[C::NF * C::SZ];
+  __shared__ __align__(16) T tile[line_tile<N, C>(C::NF)];
   const int t = threadIdx.x;
   const int64_t e0 = e_begin + (int64_t)blockIdx.x * C::E, base = e0 * C::NP;
   const int ne = C::E == 1 || n_elem - e0 >= C::E ? C::E : (int)(n_elem - e0);
