@@ -1756,14 +1756,20 @@ hipError_t qcrit_t(int order, const DeviceTables& tab, int64_t n_elem, const voi
                    void* q, void* om, void* qmm, int32_t* status, hipStream_t s) {
   const PhaseTimer pt = phase_timer(SEM_PHASE_QCRIT);
   SEM_ORDER_SWITCH(order, {
-    using C = LineOf<N, T>;
-    launch_parts(n_elem, C::E, C::TH, pt.start, pt.stop,
-                 [&](int64_t b, int64_t end, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
-                   hipExtLaunchKernelGGL((qcrit_lines<N, T, C>), grid, dim3(C::TH), 0, s, e0, e1, 0,
-                                         dmat_of<N, T>(tab), (const T*)x, (const T*)y,
-                                         (const T*)z, (const T*)u, (const T*)v, (const T*)w,
-                                         (T*)q, (T*)om, (T*)qmm, status, b, end);
-                 });
+    auto go = [&](auto shape) {
+      using C = decltype(shape);
+      launch_parts(n_elem, C::E, C::TH, pt.start, pt.stop,
+                   [&](int64_t b, int64_t end, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
+                     hipExtLaunchKernelGGL((qcrit_lines<N, T, C>), grid, dim3(C::TH), 0, s, e0,
+                                           e1, 0, dmat_of<N, T>(tab), (const T*)x, (const T*)y,
+                                           (const T*)z, (const T*)u, (const T*)v, (const T*)w,
+                                           (T*)q, (T*)om, (T*)qmm, status, b, end);
+                   });
+    };
+    if (n_elem * (int64_t)(8 * sizeof(T) * LineOf<N, T>::NP) > kLineNear)
+      go(typename LineQ<N, T, true>::Shape{});
+    else
+      go(typename LineQ<N, T, false>::Shape{});
   });
   phase_done(pt);
   return hipGetLastError();

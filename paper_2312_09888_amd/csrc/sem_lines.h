@@ -69,11 +69,37 @@ template <int N, typename T>
 using LineOf = LineCfg<N, line_cfg(N, sizeof(T) == 8, 0), line_cfg(N, sizeof(T) == 8, 1),
                        line_cfg(N, sizeof(T) == 8, 2), line_cfg(N, sizeof(T) == 8, 3)>;
 
+// Shape of Q alone where another one than the counting kernel's, the gradient's
+// and the batch's is faster; FAR: its eight fields exceed the shared 256 MiB
+// cache (kLineNear).  Beyond it more bytes in flight a wave win, within it the
+// shorter chain: a thread a node and all fields in one pass at order 7 in FP64
+// (512 elements 6.6 us, 7.5 with the table's shape; 8,192: 57.7 and 59.0; 65,536:
+// 489 and 475).  Order 3 in FP32: 524,288 elements 253 us with two elements a wave,
+// 260 with one; 8,192: 9.1 and 8.1.  Order 2: 1,242,756 elements 280 us with nine
+// elements a wave, 347 with the table's shape; 155,344: 42.0 and 39.9.
+template <int N, typename T, bool FAR>
+struct LineQ {
+  using Shape = LineOf<N, T>;
+};
+template <>
+struct LineQ<7, double, false> {
+  using Shape = LineCfg<7, 1, 512, 10, 3>;
+};
+template <>
+struct LineQ<3, float, true> {
+  using Shape = LineCfg<3, 2, 64, 4, 3>;
+};
+template <>
+struct LineQ<2, float, true> {
+  using Shape = LineCfg<2, 9, 64, 3, 1>;
+};
+constexpr int64_t kLineNear = int64_t(256) << 20;
+
 // Waves per SIMD to hold (launch bound): FP64 N = 6..9 sit a few registers
 // around the limits of three and four waves; elsewhere the compiler's choice.
 template <int N, typename T, class C>
 constexpr int line_waves() {
-  return sizeof(T) == 4 || N < 6 ? 1 : N == 6 || N == 8 ? 3 : 4;
+  return sizeof(T) == 4 || N < 6 ? 1 : N == 6 || N == 8 ? 3 : C::NF == 3 ? 6 : 4;
 }
 
 // LDS values of `fields` fields' lines (order 1 needs none).
@@ -189,6 +215,24 @@ __device__ __forceinline__ void line_load(const T* __restrict__ src, int t, int 
     if (C::full(r) || t + r * C::TH < nn) f[r] = src[t + r * C::TH];
 }
 
+// Where a thread owns nodes of several elements, or another shape takes over
+// with the size, a node's sums are written out in multiply-adds: which products
+// the compiler contracts depends on the code around them, and an element's
+// values must not depend on where in the list it stands.  (Elsewhere its choice
+// is as fast or faster: FP64 N = 8, 9 3 %, N = 2 5 %.)
+template <int N, typename T>
+constexpr bool kLineFixed = sizeof(T) == 4 ? N <= 4 : N == 7;
+template <bool FIXED, typename T>
+__device__ __forceinline__ T cross2(T a, T b, T c, T d) {   // a b - c d
+  if constexpr (FIXED) return fma(a, b, -(c * d));
+  else return a * b - c * d;
+}
+template <bool FIXED, typename T>
+__device__ __forceinline__ T dot3(T a0, T b0, T a1, T b1, T a2, T b2) {
+  if constexpr (FIXED) return fma(a2, b2, fma(a0, b0, a1 * b1));
+  else return a0 * b0 + a1 * b1 + a2 * b2;
+}
+
 // 1 / det J: FP32 the hardware reciprocal (1 ulp), FP64 the refined one.
 __device__ __forceinline__ float line_recip(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double line_recip(double x) { return recip_refined(x); }
@@ -208,18 +252,20 @@ __device__ __forceinline__ bool line_geometry(const T (&f)[3][C::R], const LineO
     const T xr = g[0][r][0], xs = g[0][r][1], xt = g[0][r][2];
     const T yr = g[1][r][0], ys = g[1][r][1], yt = g[1][r][2];
     const T zr = g[2][r][0], zs = g[2][r][1], zt = g[2][r][2];
-    const T c0 = ys * zt - yt * zs, c1 = yt * zr - yr * zt, c2 = yr * zs - ys * zr;
-    const T det = xr * c0 + xs * c1 + xt * c2;
+    constexpr bool FX = kLineFixed<N, T>;
+    const T c0 = cross2<FX>(ys, zt, yt, zs), c1 = cross2<FX>(yt, zr, yr, zt);
+    const T c2 = cross2<FX>(yr, zs, ys, zr);
+    const T det = dot3<FX>(xr, c0, xs, c1, xt, c2);
     const T inv = line_recip(det);
     K.rx = c0 * inv;
-    K.ry = (xt * zs - xs * zt) * inv;
-    K.rz = (xs * yt - xt * ys) * inv;
+    K.ry = cross2<FX>(xt, zs, xs, zt) * inv;
+    K.rz = cross2<FX>(xs, yt, xt, ys) * inv;
     K.sx = c1 * inv;
-    K.sy = (xr * zt - xt * zr) * inv;
-    K.sz = (xt * yr - xr * yt) * inv;
+    K.sy = cross2<FX>(xr, zt, xt, zr) * inv;
+    K.sz = cross2<FX>(xt, yr, xr, yt) * inv;
     K.tx = c2 * inv;
-    K.ty = (xs * zr - xr * zs) * inv;
-    K.tz = (xr * ys - xs * yr) * inv;
+    K.ty = cross2<FX>(xs, zr, xr, zs) * inv;
+    K.tz = cross2<FX>(xr, ys, xs, yr) * inv;
     if (C::full(r) || t + r * C::TH < nn) ok = ok && det > T(0);
   }
   return ok;
@@ -368,7 +414,38 @@ __device__ __forceinline__ void qcrit_lines_elem(
   InvJac<T> kk[R];
   const bool ok = line_geometry<N, C>(fx, own, dmat, tile, t, nn, nl, kk);
   T qv[R], ov[R];
-  if constexpr (C::NF == 3) {
+  if constexpr (kLineFixed<N, T>) {
+    // rows of the velocity gradient, folded into Q and |omega|^2 as they come
+    T a01[R], a02[R], a12[R];
+    auto row = [&](int c, const T (&g)[R][3]) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const InvJac<T>& K = kk[r];
+        const T a0 = dot3<true>(g[r][0], K.rx, g[r][1], K.sx, g[r][2], K.tx);
+        const T a1 = dot3<true>(g[r][0], K.ry, g[r][1], K.sy, g[r][2], K.ty);
+        const T a2 = dot3<true>(g[r][0], K.rz, g[r][1], K.sz, g[r][2], K.tz);
+        if (c == 0) {
+          qv[r] = a0;
+          a01[r] = a1;
+          a02[r] = a2;
+        } else if (c == 1) {
+          qv[r] = fma(T(2), a01[r] * a0, fma(qv[r], qv[r], a1 * a1));
+          ov[r] = a0 - a01[r];
+          a12[r] = a2;
+        } else {
+          qv[r] = T(-0.5) * fma(T(2), fma(a02[r], a0, a12[r] * a1), fma(a2, a2, qv[r]));
+          const T w1 = a1 - a12[r], w2 = a02[r] - a0;
+          ov[r] = vort_root(fma(w2, w2, fma(ov[r], ov[r], w1 * w1)));
+        }
+      }
+    };
+    T g[C::NF][R][3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (c % C::NF == 0) line_pass<N, C, C::NF>(fu + c, own, dmat, tile, t, nn, nl, g);
+      row(c, g[c % C::NF]);
+    }
+  } else if constexpr (C::NF == 3) {
     T g[3][R][3];
     line_pass3<N, C>(fu, own, dmat, tile, t, nn, nl, g);
 #pragma unroll
@@ -556,9 +633,10 @@ derivs_lines(const coef_t<N, T>* __restrict__ dmat, const T* __restrict__ x,
     if (C::full(r) || t + r * C::TH < nn) {
       const InvJac<T>& K = kk[r];
       const int64_t o = base + t + r * C::TH;
-      gx[o] = g[0][r][0] * K.rx + g[0][r][1] * K.sx + g[0][r][2] * K.tx;
-      gy[o] = g[0][r][0] * K.ry + g[0][r][1] * K.sy + g[0][r][2] * K.ty;
-      gz[o] = g[0][r][0] * K.rz + g[0][r][1] * K.sz + g[0][r][2] * K.tz;
+      constexpr bool FX = kLineFixed<N, T>;
+      gx[o] = dot3<FX>(g[0][r][0], K.rx, g[0][r][1], K.sx, g[0][r][2], K.tx);
+      gy[o] = dot3<FX>(g[0][r][0], K.ry, g[0][r][1], K.sy, g[0][r][2], K.ty);
+      gz[o] = dot3<FX>(g[0][r][0], K.rz, g[0][r][1], K.sz, g[0][r][2], K.tz);
     }
   }
   if (!ok && status) atomicOr(status, SEM_FLAG_BAD_JACOBIAN);

@@ -457,3 +457,42 @@ def test_q_and_counts_over_more_elements_than_one_launch_holds():
     t, a = ntri[cs].astype(np.int64).sum(1), ((cs != 0) & (cs != 255)).sum(1)
     assert int(cnt[0]) == (e - 4) * int(t[0]) + int(t[4:].sum()) and t[0] > 0
     assert int(act[0]) == (e - 4) * int(a[0]) + int(a[4:].sum())
+
+
+@pytest.mark.parametrize("n", list(range(1, 10)))
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+def test_an_element_has_the_same_q_wherever_it_stands(n, dt):
+    """The same element repeated, a number that is no multiple of what a
+    workgroup takes: every copy gets the same Q, |omega|, range and gradient,
+    bit for bit, from sem_qcrit, sem_extract and the batch."""
+    e = 77
+    rng = np.random.default_rng(n)
+    base = [a[:1] for a in warped_mesh(n, (2, 1, 1))] + \
+        [rng.normal(size=(1,) + (n + 1,) * 3) for _ in range(3)]
+    t = [dev(np.repeat(a, e, axis=0), dt) for a in base]
+    q, om, mm = sem.qcrit(*t)
+    g = sem.derivs(*t[:4])
+    for a in (q, om, mm) + tuple(g):
+        assert bool((a == a[0]).all()), n
+    r = sem.extract(*t, [float(q.mean())])
+    out = dict(q=torch.empty_like(q), omega_mag=torch.empty_like(q), minmax=torch.empty_like(mm))
+    sem.qcrit_batch(sem.BatchPlan([dict(zip("xyzuvw", t), **out)]))
+    for a, key in ((q, "q"), (om, "omega_mag"), (mm, "minmax")):
+        assert torch.equal(r[key], a) and torch.equal(out[key], a), key
+
+
+@pytest.mark.parametrize("n, dt", [(7, np.float64), (3, np.float32), (2, np.float32)])
+def test_q_is_the_same_for_snapshots_in_and_beyond_the_cache(n, dt):
+    """sem_qcrit takes another workgroup shape where eight fields exceed
+    256 MiB: an element's values stay the same bits."""
+    far = (256 << 20) // (8 * np.dtype(dt).itemsize * (n + 1) ** 3) + 3
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    x, y, z = (dev(a[:1], np.float64) for a in warped_mesh(n, (2, 1, 1)))
+    tdt = torch.float64 if dt == np.float64 else torch.float32
+    noise = [0.01 * torch.rand((far,) + (n + 1,) * 3, device=DEV, generator=gen) for _ in range(6)]
+    t = [(a + b).to(tdt).contiguous() for a, b in zip((x, y, z, 0, 0, 0), noise)]
+    q, om, mm = sem.qcrit(*t)
+    for s in (slice(0, 100), slice(far - 1001, far)):
+        near = sem.qcrit(*(a[s].contiguous() for a in t))
+        assert torch.equal(near[0], q[s]) and torch.equal(near[1], om[s])
+        assert torch.equal(near[2], mm[s])
