@@ -88,6 +88,10 @@ constexpr int64_t scan_partials_capacity(int64_t count) {
 hipError_t launch_exclusive_scan(const int32_t* cnt, int64_t count, int64_t* partial,
                                  int64_t* offs, hipStream_t s);
 
+// The same of int64 values.
+hipError_t launch_exclusive_scan(const int64_t* cnt, int64_t count, int64_t* partial,
+                                 int64_t* offs, hipStream_t s);
+
 // The same of count flags (nonzero counts as 1).
 hipError_t launch_flag_scan(const uint8_t* flag, int64_t count, int64_t* partial, int64_t* offs,
                             hipStream_t s);
@@ -185,13 +189,14 @@ struct GsWord {
 };
 struct GsLayout {
   GsHead* head;       // what sem_dsavg needs to know of the mesh
-  uint32_t* cnt;      // [n_global] copies per global node (then a fill cursor)
-  uint32_t* first;    // [n_global] first copy per global node (then its row's start)
+  uint32_t* first;    // [n_global] first copy per global node
   uint32_t* rowptr;   // [n_global + 1] rows of shared nodes, by their first copy
   GsWord* words;      // [n_words + 1], of the last only `copy`
   uint32_t* col;      // [n_nodes] storage index of the later copies, by row, ascending
-  int32_t *rows, *copies;   // [n_words] rows and listed copies of each word
-  int64_t *row0, *copy0;    // [n_words + 1] their exclusive prefixes
+  int64_t* starts;    // [n_words] rows (upper half) and listed copies of each word
+  int64_t* begin;     // [n_words + 1] their exclusive prefix
+  bool dense;         // where others[] counts: by global node, else by first copy
+  uint32_t* others;   // [n_global or n_nodes] later copies of each node (then its row's cursor)
   int64_t* partial;   // scan partials
   int64_t n_words;
   size_t bytes;

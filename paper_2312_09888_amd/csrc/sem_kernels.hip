@@ -574,12 +574,14 @@ constexpr int kScanThreads = 256;
 // Tile sums; a tile is kScanThreads x ITEMS counts (scan_tile).  PACKED: the
 // counts are slots of triangles and active cells; the active cells of the
 // isovalues that the tile holds (n_elem slots each) are added to `active`.
-// CT: int32_t counts, or uint8_t flags (nonzero counts as 1).  A tile of few
+// CT: int32_t or int64_t counts, or uint8_t flags (nonzero counts as 1).  A tile of few
 // isovalues sums each over the workgroup; from kScanActive on they are added up
 // in LDS (8 elements at 64 isovalues: 24 us by workgroup sums, 5 so).
 constexpr int kScanActive = 4;
 template <typename CT>
-__device__ __forceinline__ int32_t scan_value(CT v) {
+using scan_t = typename std::conditional<sizeof(CT) == 8, int64_t, int32_t>::type;
+template <typename CT>
+__device__ __forceinline__ scan_t<CT> scan_value(CT v) {
   if constexpr (sizeof(CT) == 1) return v != 0;
   else return v;
 }
@@ -589,7 +591,7 @@ scan_reduce(const CT* __restrict__ cnt, int64_t count, int64_t* __restrict__ par
             int64_t* __restrict__ active, int64_t n_elem) {
   __shared__ int64_t sred[kScanThreads / 64];
   const int64_t start = (int64_t)blockIdx.x * (kScanThreads * ITEMS);
-  int32_t v[ITEMS];
+  scan_t<CT> v[ITEMS];
   int64_t s = 0;
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
@@ -664,7 +666,7 @@ scan_apply(const CT* __restrict__ cnt, int64_t count, const int64_t* __restrict_
   __shared__ int64_t sred[kScanThreads / 64];
   const int64_t start =
       (int64_t)blockIdx.x * (kScanThreads * ITEMS) + (int64_t)threadIdx.x * ITEMS;
-  int32_t v[ITEMS];
+  scan_t<CT> v[ITEMS];
   int64_t s = 0;
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
@@ -2211,6 +2213,12 @@ hipError_t launch_tune_fill(sem_dtype dt, int order, int64_t n_elem, void* const
 hipError_t launch_flag_scan(const uint8_t* flag, int64_t count, int64_t* partial, int64_t* offs,
                             hipStream_t s) {
   scan_kernels<false>(flag, count, partial, offs, nullptr, 1, s, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_exclusive_scan(const int64_t* cnt, int64_t count, int64_t* partial,
+                                 int64_t* offs, hipStream_t s) {
+  scan_kernels<false>(cnt, count, partial, offs, nullptr, 1, s, nullptr, nullptr);
   return hipGetLastError();
 }
 

@@ -196,3 +196,19 @@ def test_weld_of_any_keys(n_tri, share):
     np.testing.assert_array_equal(host(idx).ravel(), want)
     np.testing.assert_array_equal(host(verts), xyz.reshape(-1, 3)[good[at[order]]])
     assert bool(int(st.item()) & sem.SEM_FLAG_BAD_ID) == (good.size < n_ref)
+
+
+def test_dsavg_takes_the_mesh_from_the_structure():
+    """The structure knows its mesh: a call that names fewer elements averages
+    the nodes of the set-up all the same."""
+    shape, n = (3, 2, 2), 2
+    e = 12
+    gid = dev(W.lattice_gid(shape, n)).contiguous()
+    gs = sem.GatherScatter(gid)
+    f = torch.rand((e, 3, 3, 3), dtype=torch.float64, device=DEV)
+    want = sem.dsavg(f, gs)
+    for k in (1, 5):
+        out = torch.empty_like(f)
+        rc = sem.lib().sem_dsavg(k, n, sem.SEM_F64, gs.buf.data_ptr(), gs.n_global, f.data_ptr(),
+                                 out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert rc == 0 and torch.equal(out, want)
