@@ -26,7 +26,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr uint64_t kEmpty = ~0ull;
-constexpr int kGsWords = 4;              // flag words (64 nodes each) a wave averages at once
 constexpr int kGsExt = 2048;             // listed copies a workgroup holds in LDS
 constexpr int kWeldT = 512;              // threads of weld_insert
 constexpr int kWeldPer = 4;              // corners of each of them
@@ -215,8 +214,11 @@ __global__ void gs_sort(const int64_t* __restrict__ end, const uint32_t* __restr
 // elements of order 7 in FP64).  Measured there: 162 us with 64-bit rows for
 // all global nodes, 195 with words and per-lane walks, 92 so; the rest is
 // the chain flags -> list -> copies -> average -> copies of each workgroup
-// (8 words a wave: 121 us, too few waves; 2 words: 107).
-template <typename T>
+// (8 words a wave: 121 us, too few waves; 2 words: 107).  Where nodes have more
+// than eight copies on average (no mesh of hexahedra does) the first words own
+// nearly all of them, and a wave takes one word (4.2 million nodes at random, 64
+// copies each: 235 us, 509 with four; a thread for each node took 124).
+template <typename T, int kGsWords>
 __global__ void __launch_bounds__(kThreads)
     dsavg_k(const GsHead* __restrict__ head, const uint32_t* __restrict__ rowptr,
             const GsWord* __restrict__ words, const T* in, T* out) {
@@ -476,6 +478,7 @@ GsLayout gs_layout(void* base, int64_t n_nodes, int64_t n_global) {
   l.starts = reinterpret_cast<int64_t*>(take((size_t)nw * 8));
   l.begin = reinterpret_cast<int64_t*>(take((size_t)(nw + 1) * 8));
   l.dense = n_global < n_nodes / 2;
+  l.many = n_global < n_nodes / 8;
   l.others = reinterpret_cast<uint32_t*>(take((size_t)(l.dense ? n_global : n_nodes) * 4));
   l.partial = reinterpret_cast<int64_t*>(take((size_t)(scan_partials_capacity(nw) + 1) * 8));
   l.bytes = o;
@@ -520,15 +523,16 @@ hipError_t launch_gs_setup(int64_t n_nodes, const int64_t* gid, int64_t n_global
 
 hipError_t launch_dsavg(sem_dtype dt, const GsLayout& gs, const void* in, void* out,
                         hipStream_t s) {
-  const unsigned nb = blocks_for((gs.n_words * 64 + kGsWords - 1) / kGsWords);
+  auto go = [&](auto kern, int words, auto zero) {
+    using T = decltype(zero);
+    hipLaunchKernelGGL(kern, dim3(blocks_for((gs.n_words * 64 + words - 1) / words)),
+                       dim3(kThreads), 0, s, (const GsHead*)gs.head, (const uint32_t*)gs.rowptr,
+                       (const GsWord*)gs.words, (const T*)in, (T*)out);
+  };
   if (dt == SEM_F64)
-    hipLaunchKernelGGL(dsavg_k<double>, dim3(nb), dim3(kThreads), 0, s, (const GsHead*)gs.head,
-                       (const uint32_t*)gs.rowptr, (const GsWord*)gs.words, (const double*)in,
-                       (double*)out);
+    gs.many ? go(dsavg_k<double, 1>, 1, 0.0) : go(dsavg_k<double, 4>, 4, 0.0);
   else
-    hipLaunchKernelGGL(dsavg_k<float>, dim3(nb), dim3(kThreads), 0, s, (const GsHead*)gs.head,
-                       (const uint32_t*)gs.rowptr, (const GsWord*)gs.words, (const float*)in,
-                       (float*)out);
+    gs.many ? go(dsavg_k<float, 1>, 1, 0.f) : go(dsavg_k<float, 4>, 4, 0.f);
   return hipGetLastError();
 }
 

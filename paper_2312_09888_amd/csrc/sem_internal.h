@@ -195,6 +195,7 @@ struct GsLayout {
   uint32_t* col;      // [n_nodes] storage index of the later copies, by row, ascending
   int64_t* starts;    // [n_words] rows (upper half) and listed copies of each word
   int64_t* begin;     // [n_words + 1] their exclusive prefix
+  bool many;          // more than eight copies a node on average
   bool dense;         // where others[] counts: by global node, else by first copy
   uint32_t* others;   // [n_global or n_nodes] later copies of each node (then its row's cursor)
   int64_t* partial;   // scan partials

@@ -212,3 +212,19 @@ def test_dsavg_takes_the_mesh_from_the_structure():
         rc = sem.lib().sem_dsavg(k, n, sem.SEM_F64, gs.buf.data_ptr(), gs.n_global, f.data_ptr(),
                                  out.data_ptr(), torch.cuda.current_stream().cuda_stream)
         assert rc == 0 and torch.equal(out, want)
+
+
+@pytest.mark.parametrize("dt", [np.float64, np.float32])
+@pytest.mark.parametrize("pool", [1, 149, 160])
+def test_dsavg_of_nodes_with_many_copies(dt, pool):
+    """More than eight copies a node on average (and just under: 160 ids for
+    1,280 nodes): lists that fit a workgroup's LDS and lists that do not."""
+    rng = np.random.default_rng(pool)
+    for e in (160, 1600):
+        k = pool if e == 160 else 10 * pool
+        gid = np.minimum(rng.integers(0, 8 * k, size=(e, 2, 2, 2)) // 8, k - 1)
+        f = rng.normal(size=gid.shape).astype(dt)
+        gs = sem.GatherScatter(dev(gid), n_global=k)
+        t = dev(f)
+        sem.dsavg(t, gs, out=t)
+        np.testing.assert_array_equal(host(t), c0.dsavg(f, gid))
