@@ -27,9 +27,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr uint64_t kEmpty = ~0ull;
 constexpr int kGsExt = 2048;             // listed copies a workgroup holds in LDS
-constexpr int kWeldT = 512;              // threads of weld_insert
-constexpr int kWeldPer = 4;              // corners of each of them
-constexpr int kWeldRefs = kWeldT * kWeldPer;
+constexpr int kWeldT = 512;              // threads of weld_insert, a corner each
 
 inline unsigned blocks_for(int64_t n) {
   return (unsigned)((n + kThreads - 1) / kThreads > 0 ? (n + kThreads - 1) / kThreads : 1);
@@ -325,85 +323,64 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 // twice the number of corners, so a free slot is always reached).  A slot
 // holds the smallest corner of its key, and the key is looked up there: one
 // atomic claims a slot and records the corner, and an entry is 4 bytes.  A
-// workgroup finds the distinct keys of its kWeldRefs consecutive corners in
-// LDS first, in the same way (also at most half full), and only the first
-// corner of each goes to the table in memory; local[] marks these corners,
-// 64 to a word.  535,000 triangles of two isovalues: 165 us with an atomic
-// each for key and corner of every corner, 48 with the distinct keys of a
-// workgroup only, 26 with the key looked up at the corner.
+// workgroup finds the distinct keys of its kWeldT consecutive corners in LDS
+// first, in the same way (also at most half full), and only the first corner
+// of each goes to the table in memory; local[] marks these corners, 64 to a
+// word.  535,000 triangles of two isovalues: 165 us with an atomic each for
+// key and corner of every corner, 48 with the distinct keys of a workgroup
+// only, 26 with the key looked up at the corner.  A thread has one corner: a
+// probe is a round trip to memory, and only other waves hide it.  All passes
+// of the weld, four corners a thread against one: 1,000 triangles that share
+// no key 39 and 22 us, 100,000 that share each key six times, in order 28.6
+// and 25.1, at random 52 and 47; only where a workgroup of four times the
+// corners has hardly more keys does it lose (2,000,000 triangles, each key
+// 1,000 times, 90 and 94).
 __global__ void __launch_bounds__(kWeldT)
     weld_insert(int64_t n_ref, const uint64_t* __restrict__ keys, uint32_t* __restrict__ table,
                 int32_t* __restrict__ slot, uint64_t* __restrict__ local, int64_t cap,
                 int32_t* __restrict__ status) {
-  __shared__ uint64_t lkey[kWeldRefs];
-  __shared__ uint32_t lpos[2 * kWeldRefs];
-  const int t = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kWeldRefs;
-  uint64_t k[kWeldPer], hash[kWeldPer];
-  uint32_t ls[kWeldPer];
-  bool own[kWeldPer], bad = false;
-#pragma unroll
-  for (int j = 0; j < kWeldPer; ++j) {
-    const int64_t r = base + j * kWeldT + t;
-    k[j] = r < n_ref ? keys[r] : kEmpty;
-    bad |= r < n_ref && k[j] == kEmpty;
-    hash[j] = mix64(k[j]);
-    lkey[j * kWeldT + t] = k[j];
-    lpos[2 * j * kWeldT + t] = lpos[(2 * j + 1) * kWeldT + t] = ~0u;
-  }
+  __shared__ uint64_t lkey[kWeldT];
+  __shared__ uint32_t lpos[2 * kWeldT];
+  const uint32_t t = threadIdx.x;
+  const int64_t r = (int64_t)blockIdx.x * kWeldT + t;
+  const uint64_t k = r < n_ref ? keys[r] : kEmpty, hash = mix64(k);
+  uint32_t l = (uint32_t)(hash >> 40) & (2 * kWeldT - 1);
+  lkey[t] = k;
+  lpos[t] = lpos[kWeldT + t] = ~0u;
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kWeldPer; ++j) {
-    if (k[j] == kEmpty) continue;
-    const uint32_t me = j * kWeldT + t;
-    uint32_t h = (uint32_t)(hash[j] >> 40) & (2 * kWeldRefs - 1);
-    for (;;) {   // ends: at most kWeldRefs of the 2 kWeldRefs entries are taken
-      const uint32_t prev = atomicCAS(&lpos[h], ~0u, me);
+  if (k != kEmpty) {
+    for (;;) {   // ends: at most kWeldT of the 2 kWeldT entries are taken
+      const uint32_t prev = atomicCAS(&lpos[l], ~0u, t);
       if (prev == ~0u) break;
-      if (lkey[prev] == k[j]) {
-        if (me < prev) atomicMin(&lpos[h], me);
+      if (lkey[prev] == k) {
+        if (t < prev) atomicMin(&lpos[l], t);
         break;
       }
-      h = (h + 1) & (2 * kWeldRefs - 1);
+      l = (l + 1) & (2 * kWeldT - 1);
     }
-    ls[j] = h;
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kWeldPer; ++j)
-    own[j] = k[j] != kEmpty && lpos[ls[j]] == (uint32_t)(j * kWeldT + t);
+  const bool own = k != kEmpty && lpos[l] == t;
+  const uint64_t marks = __ballot(own);
+  if ((t & 63) == 0 && r < n_ref) local[r >> 6] = marks;
   __syncthreads();
-  const uint64_t mask = (uint64_t)cap - 1;
-  uint32_t prev[kWeldPer];
-#pragma unroll
-  for (int j = 0; j < kWeldPer; ++j)
-    if (own[j])
-      prev[j] = atomicCAS(&table[hash[j] & mask], ~0u, (uint32_t)(base + j * kWeldT + t));
-#pragma unroll
-  for (int j = 0; j < kWeldPer; ++j) {
-    const int64_t r = base + j * kWeldT + t;
-    const uint64_t marks = __ballot(own[j]);
-    if ((t & 63) == 0 && r < n_ref) local[r >> 6] = marks;
-    if (!own[j]) continue;
-    uint64_t h = hash[j] & mask;
-    for (int64_t probe = 1; prev[j] != ~0u; ++probe) {
-      if (keys[prev[j]] == k[j]) {
-        if ((uint32_t)r < prev[j]) atomicMin(&table[h], (uint32_t)r);
+  if (own) {
+    const uint64_t mask = (uint64_t)cap - 1;
+    uint64_t h = hash & mask;
+    for (int64_t probe = 0; probe < cap; ++probe) {   // a half-empty table ends it before
+      const uint32_t prev = atomicCAS(&table[h], ~0u, (uint32_t)r);
+      if (prev == ~0u) break;
+      if (keys[prev] == k) {
+        if ((uint32_t)r < prev) atomicMin(&table[h], (uint32_t)r);
         break;
       }
-      if (probe == cap) break;   // not reached in a half-empty table
       h = (h + 1) & mask;
-      prev[j] = atomicCAS(&table[h], ~0u, (uint32_t)r);
     }
-    lpos[ls[j]] = (uint32_t)h;
+    lpos[l] = (uint32_t)h;
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kWeldPer; ++j) {
-    const int64_t r = base + j * kWeldT + t;
-    if (r < n_ref) slot[r] = k[j] != kEmpty ? (int32_t)lpos[ls[j]] : -1;
-  }
-  if (bad && status) atomicOr(status, SEM_FLAG_BAD_ID);
+  if (r < n_ref) slot[r] = k != kEmpty ? (int32_t)lpos[l] : -1;
+  if (r < n_ref && k == kEmpty && status) atomicOr(status, SEM_FLAG_BAD_ID);
 }
 
 // first corners of the keys, 64 corners a wave
@@ -578,7 +555,7 @@ hipError_t weld_t(int64_t n_ref, const T* tri_xyz, const uint64_t* keys, int64_t
   if (n_ref > 0) {
     hipLaunchKernelGGL(fill_ones, dim3(blocks_for(w.cap / 4)), dim3(kThreads), 0, s,
                        reinterpret_cast<uint64_t*>(w.table), w.cap / 4);
-    hipLaunchKernelGGL(weld_insert, dim3((unsigned)((n_ref + kWeldRefs - 1) / kWeldRefs)),
+    hipLaunchKernelGGL(weld_insert, dim3((unsigned)((n_ref + kWeldT - 1) / kWeldT)),
                        dim3(kWeldT), 0, s, n_ref, keys, w.table, w.slot, w.marks, w.cap, status);
     hipLaunchKernelGGL(weld_flag, dim3(blocks_for(w.n_words * 64)), dim3(kThreads), 0, s,
                        w.n_words, (const int32_t*)w.slot, (const uint32_t*)w.table, w.marks,
