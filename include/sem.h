@@ -316,7 +316,9 @@ int sem_qcrit_batch(const void* plan, unsigned launch_code, sem_dtype dt, int32_
 /* Time the batched kernel on 8,192 synthetic elements of this order with
  * every variant that applies, keep the fastest for (order, dt) on the
  * current device and return it in *variant_out (may be NULL); ms_out (may
- * be NULL) receives the six timings in ms (-1 = variant not applicable).
+ * be NULL) receives the six timings in ms (-1 = variant not applicable;
+ * variants that name the same kernel are timed once and share the figure, and
+ * the first of them stands for all).
  * A setup call: allocates temporary device memory and synchronises the
  * device. */
 int sem_autotune(int order, sem_dtype dt, int* variant_out, float* ms_out);

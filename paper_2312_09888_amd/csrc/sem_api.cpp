@@ -632,12 +632,25 @@ int sem_autotune(int order, sem_dtype dt, int* variant_out, float* ms_out) {
   float best_ms = 0.f;
   int best = -1;
   const int ti = dt == SEM_F64 ? 0 : 1;
+  float took[kBatchVariants];
   if (launch_tune_fill(dt, order, n_elem, f, nullptr) != hipSuccess ||
       hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     rc = SEM_ERR_HIP;
   for (int var = 0; var < kBatchVariants && rc == SEM_OK; ++var) {
     if (ms_out) ms_out[var] = -1.f;
     if (!batch_variant_ok(order, dt, var)) continue;
+    // variants that name one kernel with one chunk have one time
+    int same = 0;
+    while (same < var && !(batch_variant_ok(order, dt, same) &&
+                           batch_variant_form(same) == batch_variant_form(var) &&
+                           batch_variant_chunk(order, dt, same) ==
+                               batch_variant_chunk(order, dt, var)))
+      ++same;
+    if (same < var) {
+      took[var] = took[same];
+      if (ms_out) ms_out[var] = took[var];
+      continue;
+    }
     {
       std::lock_guard<std::mutex> lock(g_mutex);
       g_dev[dev].tab.tuned_variant[ti][order] = var + 1;
@@ -661,6 +674,7 @@ int sem_autotune(int order, sem_dtype dt, int* variant_out, float* ms_out) {
       break;
     }
     ms /= 5.f;
+    took[var] = ms;
     if (ms_out) ms_out[var] = ms;
     if (best < 0 || ms < best_ms) {
       best_ms = ms;

@@ -224,9 +224,10 @@ __device__ __forceinline__ bool invert_jacobian(T xr, T xs, T xt, T yr, T ys, T 
   return det > T(0);
 }
 
-// 1 / x from the hardware estimate and two Newton steps (within an ulp or
-// two; the correctly rounded division adds range scaling and a final
-// correction); x outside [2^-1000, 2^1000] in magnitude, 0 and NaN take the
+// 1 / x from the hardware estimate and two Newton steps (an ulp at most; none
+// of 8,388,608 random determinants differed from the correctly rounded
+// division, which adds range scaling and a final correction and takes about
+// 1 % longer in Q of orders 6 to 9); x outside [2^-1000, 2^1000] in magnitude, 0 and NaN take the
 // division (a branch that a wave skips unless one of its lanes needs it).
 __device__ __forceinline__ double recip_refined(double x) {
   double r = __builtin_amdgcn_rcp(x);
@@ -778,12 +779,13 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
                                           uint64_t* __restrict__ keys) {
   constexpr int P = N + 1, NP = P * P * P, NC = N * N * N, TH = emit_threads(N), W = TH / 64;
   constexpr bool SWZ = N == 7 && std::is_same<T, double>::value;
-  // The coordinate tiles are staged in LDS too, except for FP32 at N = 9,
-  // which reads the coordinates where the vertices need them (edge
-  // endpoints only, through the caches) and so needs 16 instead of 28 KB of
-  // LDS. Measured: staged is faster for FP64 N = 7 (0.319 against 0.379 ms)
-  // and FP32 N = 7 (the FP32 step 0.679 against 0.712 ms); reading made the
-  // FP32 batched step (orders 5, 7, 9) 11.90 instead of 12.20 ms.
+  // The coordinate tiles are staged in LDS too, except for FP32 at N = 8 and
+  // 9, which read the coordinates where the vertices need them (edge
+  // endpoints only, through the caches) and so need 13 and 16 instead of 22
+  // and 28 KB of LDS. Staged against read: FP64 N = 7 0.319 and 0.379 ms, the
+  // FP32 step at N = 7 0.679 and 0.712 ms; FP32 N = 8, 5,753 elements, four
+  // isovalues, 71 and 58 us (the isosurface call), N = 9, 4,194 elements, 63.6
+  // and 60.5 us, the FP32 batched step (orders 5, 7, 9) 12.20 and 11.90 ms.
   constexpr bool XYZ = std::is_same<T, double>::value || N <= 7;
   __shared__ __attribute__((aligned(16))) T s_f[NP];
   __shared__ __attribute__((aligned(16))) T s_x[XYZ ? NP : 1];

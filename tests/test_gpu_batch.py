@@ -187,3 +187,18 @@ def test_batch_graph_replays_match_eager():
             assert torch.equal(s["omega_mag"], om), rep
             assert torch.equal(s["minmax"], mm), rep
     _check(snaps, host, dt)
+
+
+@pytest.mark.parametrize("code", [sem.SEM_F64, sem.SEM_F32])
+def test_autotune_times_a_kernel_once(code):
+    """Variants 3, 4 and 5 name the line form: one time, and the choice among
+    them is the first, not the luckiest."""
+    sem.init(0)
+    for n in (1, 5, 7, 9):
+        before = sem.batch_variant(n, code)
+        try:
+            var, ms = sem.autotune(n, code)
+            lines = [ms[v] for v in (3, 4, 5) if ms[v] > 0]
+            assert len(set(lines)) == 1 and var not in (4, 5)
+        finally:
+            sem.batch_set_variant(n, code, before)

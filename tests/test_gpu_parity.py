@@ -496,3 +496,23 @@ def test_q_is_the_same_for_snapshots_in_and_beyond_the_cache(n, dt):
         near = sem.qcrit(*(a[s].contiguous() for a in t))
         assert torch.equal(near[0], q[s]) and torch.equal(near[1], om[s])
         assert torch.equal(near[2], mm[s])
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_derivs_divide_by_det_correctly_rounded(n):
+    """Boxes whose edges have 20 bits: all sums of the derivatives are exact,
+    and what is left to round is J, its cofactors, 1 / det J and the products,
+    each once, so NumPy gives the bits."""
+    rng = np.random.default_rng(n)
+    e, p = 8192, n + 1
+    a, b, c, s = (rng.integers(1, 2 ** 20, size=(4, e, 1, 1, 1)) * 2.0 ** -18)
+    g = np.arange(p) / n
+    one = np.ones((p, p, p))
+    x, y, z = a * g[None, None, None, :] * one, b * g[None, None, :, None] * one, \
+        c * g[None, :, None, None] * one
+    f = s * (g[None, None, None, :] + g[None, None, :, None] + g[None, :, None, None]) * one
+    out = sem.derivs(*[dev(t) for t in (x, y, z, f)])
+    xr, ys, zt, fr = 0.5 * a, 0.5 * b, 0.5 * c, 0.5 * s
+    inv = 1.0 / (xr * (ys * zt))
+    for got, cof in zip(out, (ys * zt, xr * zt, xr * ys)):
+        np.testing.assert_array_equal(host(got), (fr * (cof * inv)) * one)
