@@ -48,10 +48,6 @@ __device__ __forceinline__ int morton8(int i, int j, int k) {
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ __forceinline__ float half_round(float v) {
-  return __half2float(__float2half_rn(v));
-}
-
 // One DPP move of a 32-bit value; lanes of rows that ROWS leaves out read 0.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float dpp_or_zero(float v) {
@@ -179,13 +175,12 @@ ae_pack(int64_t e_begin, const float* __restrict__ u, const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// One layer as a GEMM with a fused epilogue (FP32)
+// One layer as a GEMM (FP32)
 // ---------------------------------------------------------------------------
 //
-// C[m][n] = sum_k A[m][k] B[k][n] + bias[n % bias_mod], row-major operands,
-// then (flags) tanh and binary16 rounding.  16-deep k steps.
+// C[m][n] = sum_k A[m][k] B[k][n] + bias[n % bias_mod], row-major operands;
+// 16-deep k steps.
 
-enum : int { kEpiTanh = 1, kEpiHalf = 2 };
 constexpr int kBK = 16;
 
 struct GemmArgs {
@@ -197,7 +192,6 @@ struct GemmArgs {
   float* C;              // [M][N]
   const float* bias;
   int bias_mod;
-  int flags;
 };
 
 // BM x BN tile on the matrix cores: four waves in a 2 x 2 arrangement, each
@@ -267,8 +261,6 @@ __global__ void __launch_bounds__(kT) gemm_f32(GemmArgs g) {
         if (n >= g.N) continue;
         float v = acc[i][j][r];
         v += g.bias[n % g.bias_mod];
-        if (g.flags & kEpiTanh) v = tanhf(v);
-        if (g.flags & kEpiHalf) v = half_round(v);
         g.C[m * g.N + n] = v;
       }
     }
@@ -290,11 +282,6 @@ __global__ void adam_step(int64_t n, float* __restrict__ p, const float* __restr
   m[i] = mi;
   v[i] = vi;
   p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-}
-
-__global__ void from_half_bits(const uint16_t* __restrict__ h, int64_t n, float* __restrict__ z) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i < n) z[i] = __half2float(__ushort_as_half(h[i]));
 }
 
 // W^T: out[c][r] = in[r][c]
@@ -1272,9 +1259,9 @@ hipError_t gemm(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Y = act(X W + b) for layer l on n elements
+// Y = X W + b for layer l on n elements
 hipError_t layer_forward(int l, int64_t n, const float* params, const float* x, float* y,
-                         int flags, hipStream_t s) {
+                         hipStream_t s) {
   const Layer& L = layers()[l];
   GemmArgs g{};
   g.M = out_rows(l, n);
@@ -1285,7 +1272,6 @@ hipError_t layer_forward(int l, int64_t n, const float* params, const float* x, 
   g.C = y;
   g.bias = params + L.b_off;
   g.bias_mod = L.cout;
-  g.flags = flags;
   return gemm(g, s);
 }
 
@@ -1320,12 +1306,6 @@ AeWs ae_layout(void* base, int64_t n) {
   w.n = n;
   w.bytes = off;
   return w;
-}
-
-int act_flags(int l, int tanh_mask) {
-  int f = ((tanh_mask >> l) & 1) ? kEpiTanh : 0;
-  if (l == 2) f |= kEpiHalf;   // the latent is binary16
-  return f;
 }
 
 }  // namespace
@@ -1477,7 +1457,7 @@ hipError_t launch_ae_pca_init(int64_t n_pool, const float* pool, float* params, 
                                   params + L[l].w_off, eig_ws, nullptr, s);
     if (e != hipSuccess) return e;
     if (l == 1) {
-      e = layer_forward(1, n_pool, params, pool, a2, 0, s);   // [n_pool * 8][64]
+      e = layer_forward(1, n_pool, params, pool, a2, s);   // [n_pool * 8][64]
       if (e != hipSuccess) return e;
       in = a2;                               // layer-2 inputs: [n_pool][512]
     }
@@ -1635,12 +1615,8 @@ hipError_t launch_ae_decompress(int64_t n_elem, const uint16_t* latent, const fl
   }
   for (int64_t b = 0; b < n_elem; b += kChunk) {
     const int64_t n = n_elem - b < kChunk ? n_elem - b : kChunk;
-    hipLaunchKernelGGL(from_half_bits, dim3((unsigned)cdiv(n * 32, kT)), dim3(kT), 0, s,
-                       latent + b * 32, n * 32, c.ae.act[3]);
-    for (int l = 3; l < kLayers; ++l) {
-      e = layer_forward(l, n, params, c.ae.act[l], c.ae.act[l + 1], act_flags(l, tanh_mask), s);
-      if (e != hipSuccess) return e;
-    }
+    e = launch_net_decode(n, latent + b * 32, params, tanh_mask, c.ae.act[kLayers], s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(ae_unpack, dim3((unsigned)n), dim3(kT), 0, s, b, c.ae.act[kLayers], scale,
                        flags, c.offs, raw, raw_count, f[0], f[1], f[2], f[3], status);
   }

@@ -116,6 +116,7 @@ struct NetArgs {
   float inv2;              // 2 / (values or channels of the loss)
   float* act[6];           // outputs of layers 0..4 at [1..5] (NULL: not kept)
   float* g;                // output gradient [n][2048] (NULL: no loss)
+  const uint16_t* given;   // binary16 latent [n][32] to decode
   float* recon;            // output [n][2048] or NULL
   uint16_t* latent;        // binary16 latent [n][32] or NULL
   double* lpart;           // loss partial per workgroup
@@ -135,7 +136,11 @@ constexpr int kP2 = 516;    // layer-2 input row (512)
 constexpr int kP3 = 36;     // latent row, layer-5 input row (32)
 constexpr int kP4 = 68;     // layer-4 input row (64)
 
-template <bool TANH>
+// DECODE starts from given latents: the reconstruction that a compressor
+// checked is what its receiver gets, bit for bit, because both come from
+// this body.  Decoding 65,536 elements took 1,090 us with a GEMM launch for
+// each of the layers 3 to 5, and takes 764; 64 elements 39 and 25.
+template <bool TANH, bool DECODE>
 __global__ void __launch_bounds__(kNT) net_forward(NetArgs a) {
   // layer-1 input, later the layer-5 input (512 rows x kP3)
   __shared__ __align__(16) float s_big[512 * kP3];
@@ -151,8 +156,8 @@ __global__ void __launch_bounds__(kNT) net_forward(NetArgs a) {
   for (int64_t c0 = (int64_t)blockIdx.x * kNB; c0 < a.n; c0 += (int64_t)gridDim.x * kNB) {
     const int64_t blk = c0 + w;
     const bool own = blk < a.n;
-    const float* __restrict__ x = net_input(a, blk);
-    if (own && !x && lane == 0 && a.status) atomicOr(a.status, SEM_FLAG_BAD_ID);
+    const float* __restrict__ x = DECODE ? nullptr : net_input(a, blk);
+    if (!DECODE && own && !x && lane == 0 && a.status) atomicOr(a.status, SEM_FLAG_BAD_ID);
     const int ct1 = w & 3, rp1 = 2 * (w >> 2);
     const uint32_t xo = pass_offset(32 * lr + lk), o32 = pass_offset(32 * lk + lr),
                    o1 = pass_offset(64 * lk + 16 * ct1 + lr),
@@ -160,64 +165,67 @@ __global__ void __launch_bounds__(kNT) net_forward(NetArgs a) {
                    o4 = pass_offset(256 * lk + 32 * w + lr), ob = pass_offset(lr),
                    oc32 = pass_offset(128 * lk + lr), oc64 = pass_offset(256 * lk + lr),
                    oc256 = pass_offset(1024 * lk + lr), oc512 = pass_offset(2048 * lk + lr);
-    // ---- layer 0: the wave's own block, 64 rows x 32 -> 32
-    float xa[4][8], wb[2][8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) xa[i][s] = x ? ld(x + 512 * i + 4 * s, xo) : 0.f;
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) wb[j][s] = ld(prm + kW0 + 128 * s + 16 * j, o32);
-    // layer 1's weights of this wave's column tile, requested early
-    float w1[64];
-#pragma unroll
-    for (int s = 0; s < 64; ++s) w1[s] = ld(prm + kW1 + 256 * s, o1);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 8; ++s) acc = mfma4(xa[i][s], wb[j][s], acc);
-        const int col = 16 * j + lr;
-        const float bias = ld(prm + kB0 + 16 * j, ob);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = 16 * i + 4 * lk + r;
-          const float v = epi<TANH>(acc[r] + bias, a.tanh_mask, 0);
-          s_big[(8 * w + (row >> 3)) * kP1 + kperm((row & 7) * 32 + col)] = v;
-          if (a.act[1] && own) 
-            st(a.act[1] + blk * 2048 + 512 * i + 32 * r + 16 * j, oc32, v);
+    float wb[2][8];
+    if constexpr (!DECODE) {
+      // ---- layer 0: the wave's own block, 64 rows x 32 -> 32
+      float xa[4][8];
+  #pragma unroll
+      for (int i = 0; i < 4; ++i)
+  #pragma unroll
+        for (int s = 0; s < 8; ++s) xa[i][s] = x ? ld(x + 512 * i + 4 * s, xo) : 0.f;
+  #pragma unroll
+      for (int j = 0; j < 2; ++j)
+  #pragma unroll
+        for (int s = 0; s < 8; ++s) wb[j][s] = ld(prm + kW0 + 128 * s + 16 * j, o32);
+      // layer 1's weights of this wave's column tile, requested early
+      float w1[64];
+  #pragma unroll
+      for (int s = 0; s < 64; ++s) w1[s] = ld(prm + kW1 + 256 * s, o1);
+  #pragma unroll
+      for (int i = 0; i < 4; ++i) {
+  #pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  #pragma unroll
+          for (int s = 0; s < 8; ++s) acc = mfma4(xa[i][s], wb[j][s], acc);
+          const int col = 16 * j + lr;
+          const float bias = ld(prm + kB0 + 16 * j, ob);
+  #pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = 16 * i + 4 * lk + r;
+            const float v = epi<TANH>(acc[r] + bias, a.tanh_mask, 0);
+            s_big[(8 * w + (row >> 3)) * kP1 + kperm((row & 7) * 32 + col)] = v;
+            if (a.act[1] && own) 
+              st(a.act[1] + blk * 2048 + 512 * i + 32 * r + 16 * j, oc32, v);
+          }
         }
       }
-    }
-    __syncthreads();
-    // ---- layer 1: 64 rows x 256 -> 64, a column tile and two row tiles a wave
-    {
-      f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const f32x4 b = {w1[4 * c], w1[4 * c + 1], w1[4 * c + 2], w1[4 * c + 3]};
-#pragma unroll
+      __syncthreads();
+      // ---- layer 1: 64 rows x 256 -> 64, a column tile and two row tiles a wave
+      {
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  #pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const f32x4 b = {w1[4 * c], w1[4 * c + 1], w1[4 * c + 2], w1[4 * c + 3]};
+  #pragma unroll
+          for (int i = 0; i < 2; ++i)
+            acc[i] = mfma16(*reinterpret_cast<const f32x4*>(
+                                &s_big[(16 * (rp1 + i) + lr) * kP1 + 16 * c + 4 * lk]),
+                            b, acc[i]);
+        }
+        const int col = 16 * ct1 + lr;
+        const float bias = ld(prm + kB1 + 16 * ct1, ob);
+  #pragma unroll
         for (int i = 0; i < 2; ++i)
-          acc[i] = mfma16(*reinterpret_cast<const f32x4*>(
-                              &s_big[(16 * (rp1 + i) + lr) * kP1 + 16 * c + 4 * lk]),
-                          b, acc[i]);
+  #pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int R = 16 * (rp1 + i) + 4 * lk + r;
+            const float v = epi<TANH>(acc[i][r] + bias, a.tanh_mask, 1);
+            s_mid[(R >> 3) * kP2 + kperm((R & 7) * 64 + col)] = v;
+            if (a.act[2] && c0 + (R >> 3) < a.n)
+              st(a.act[2] + c0 * 512 + 1024 * (rp1 + i) + 64 * r + 16 * ct1, oc64, v);
+          }
       }
-      const int col = 16 * ct1 + lr;
-      const float bias = ld(prm + kB1 + 16 * ct1, ob);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int R = 16 * (rp1 + i) + 4 * lk + r;
-          const float v = epi<TANH>(acc[i][r] + bias, a.tanh_mask, 1);
-          s_mid[(R >> 3) * kP2 + kperm((R & 7) * 64 + col)] = v;
-          if (a.act[2] && c0 + (R >> 3) < a.n)
-            st(a.act[2] + c0 * 512 + 1024 * (rp1 + i) + 64 * r + 16 * ct1, oc64, v);
-        }
     }
     // layer 3's weights of this wave's 64 columns, requested before the wait
     float w3[4][8];
@@ -226,45 +234,53 @@ __global__ void __launch_bounds__(kNT) net_forward(NetArgs a) {
 #pragma unroll
       for (int s = 0; s < 8; ++s)
         w3[j][s] = ld(prm + kW3 + 2048 * s + 16 * j, o3);
-    __syncthreads();
-    // ---- layer 2: 8 rows x 512 -> 32 on two waves (rows 8..15 of the tile
-    // repeat rows 0..7; one chain of 128 steps per column tile)
-    if (w < 2) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      float b0[32], b1[32];
-      const float* wp = prm + kW2 + 16 * w;
-#pragma unroll
-      for (int s = 0; s < 32; ++s) b0[s] = ld(wp + s * 128, o32);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (q < 3) {
-#pragma unroll
-          for (int s = 0; s < 32; ++s) b1[s] = ld(wp + (32 * (q + 1) + s) * 128, o32);
-        }
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const f32x4 b = {b0[4 * c], b0[4 * c + 1], b0[4 * c + 2], b0[4 * c + 3]};
-          acc = mfma16(*reinterpret_cast<const f32x4*>(
-                           &s_mid[(lr & 7) * kP2 + 16 * (8 * q + c) + 4 * lk]),
-                       b, acc);
-        }
-        if (q < 3) {
-#pragma unroll
-          for (int s = 0; s < 32; ++s) b0[s] = b1[s];
-        }
+    if constexpr (DECODE) {
+      if (t < kNB * 32) {
+        const int b = t >> 5, col = t & 31;
+        s_lat[b * kP3 + kperm(col)] =
+            c0 + b < a.n ? __half2float(__ushort_as_half(a.given[(c0 + b) * 32 + col])) : 0.f;
       }
-      const int col = 16 * w + lr;
-      const float bias = ld(prm + kB2 + 16 * w, ob);
-      if (lk < 2) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int b = 4 * lk + r;
-          const __half h = __float2half_rn(epi<TANH>(acc[r] + bias, a.tanh_mask, 2));
-          const float v = __half2float(h);
-          s_lat[b * kP3 + kperm(col)] = v;
-          if (c0 + b < a.n) {
-            if (a.act[3]) a.act[3][(c0 + b) * 32 + col] = v;
-            if (a.latent) a.latent[(c0 + b) * 32 + col] = __half_as_ushort(h);
+    } else {
+      __syncthreads();
+      // ---- layer 2: 8 rows x 512 -> 32 on two waves (rows 8..15 of the tile
+      // repeat rows 0..7; one chain of 128 steps per column tile)
+      if (w < 2) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float b0[32], b1[32];
+        const float* wp = prm + kW2 + 16 * w;
+  #pragma unroll
+        for (int s = 0; s < 32; ++s) b0[s] = ld(wp + s * 128, o32);
+  #pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (q < 3) {
+  #pragma unroll
+            for (int s = 0; s < 32; ++s) b1[s] = ld(wp + (32 * (q + 1) + s) * 128, o32);
+          }
+  #pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            const f32x4 b = {b0[4 * c], b0[4 * c + 1], b0[4 * c + 2], b0[4 * c + 3]};
+            acc = mfma16(*reinterpret_cast<const f32x4*>(
+                             &s_mid[(lr & 7) * kP2 + 16 * (8 * q + c) + 4 * lk]),
+                         b, acc);
+          }
+          if (q < 3) {
+  #pragma unroll
+            for (int s = 0; s < 32; ++s) b0[s] = b1[s];
+          }
+        }
+        const int col = 16 * w + lr;
+        const float bias = ld(prm + kB2 + 16 * w, ob);
+        if (lk < 2) {
+  #pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int b = 4 * lk + r;
+            const __half h = __float2half_rn(epi<TANH>(acc[r] + bias, a.tanh_mask, 2));
+            const float v = __half2float(h);
+            s_lat[b * kP3 + kperm(col)] = v;
+            if (c0 + b < a.n) {
+              if (a.act[3]) a.act[3][(c0 + b) * 32 + col] = v;
+              if (a.latent) a.latent[(c0 + b) * 32 + col] = __half_as_ushort(h);
+            }
           }
         }
       }
@@ -878,8 +894,21 @@ hipError_t launch_net_forward(int64_t n, const float* blocks, const float* param
   a.tanh_mask = tanh_mask;
   a.recon = recon;
   a.latent = latent;
-  hipLaunchKernelGGL((tanh_mask ? net_forward<true> : net_forward<false>),
+  hipLaunchKernelGGL((tanh_mask ? net_forward<true, false> : net_forward<false, false>),
                      dim3((unsigned)ae_net_groups(n)), dim3(kNT), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_net_decode(int64_t n, const uint16_t* latent, const float* params,
+                             int tanh_mask, float* recon, hipStream_t s) {
+  NetArgs a{};
+  a.n = n;
+  a.params = params;
+  a.tanh_mask = tanh_mask;
+  a.given = latent;
+  a.recon = recon;
+  hipLaunchKernelGGL((net_forward<true, true>), dim3((unsigned)ae_net_groups(n)), dim3(kNT), 0, s,
+                     a);
   return hipGetLastError();
 }
 
@@ -904,7 +933,7 @@ hipError_t launch_net_grad(int64_t n, const float* pool, int64_t n_pool, const i
   a.slices = slices;
   a.status = status;
   const int groups = ae_net_groups(n);
-  hipLaunchKernelGGL((tanh_mask ? net_forward<true> : net_forward<false>),
+  hipLaunchKernelGGL((tanh_mask ? net_forward<true, false> : net_forward<false, false>),
                      dim3((unsigned)groups), dim3(kNT), 0, s, a);
   hipLaunchKernelGGL((tanh_mask ? net_backward<true> : net_backward<false>),
                      dim3((unsigned)groups), dim3(kNT), 0, s, a);

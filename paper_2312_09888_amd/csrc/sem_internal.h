@@ -296,6 +296,8 @@ constexpr int kAeNetParams = 67812;
 constexpr int ae_net_groups(int64_t n) { return n < 256 * 8 ? (int)((n + 7) / 8) : 256; }
 hipError_t launch_net_forward(int64_t n, const float* blocks, const float* params, int tanh_mask,
                               float* recon, uint16_t* latent, hipStream_t s);
+hipError_t launch_net_decode(int64_t n, const uint16_t* latent, const float* params,
+                             int tanh_mask, float* recon, hipStream_t s);
 hipError_t launch_net_grad(int64_t n, const float* pool, int64_t n_pool, const int64_t* idx,
                            const float* params, int tanh_mask, int loss_kind, float* const* act,
                            float* g, float* slices, double* lpart, float* grad, float* loss,

@@ -460,3 +460,65 @@ def test_training_beats_the_pca_network_and_the_modal_baseline():
     assert frac_ae <= 0.95 * frac_pca and ratio_ae > ratio_pca
     assert frac_ae <= 0.25 and frac_mod >= 0.9
     assert ratio_ae >= 3 * ratio_mod
+
+
+@pytest.mark.parametrize("loss_kind", [sem.SEM_AE_LOSS_MSE, sem.SEM_AE_LOSS_MAX])
+@pytest.mark.parametrize("n", [3, 9, 2061])
+def test_gradient_over_passes_with_tanh(n, loss_kind):
+    """The batches of test_gradient_over_passes_and_partial_workgroups through
+    the tanh network."""
+    r = np.random.default_rng(26)
+    params = (ae.init_params(25) + r.normal(scale=0.02, size=ae.param_count())).astype(np.float32)
+    pool = r.uniform(-1, 1, size=(4, 4, 8, 8, 8)).astype(np.float32)
+    idx = np.resize(np.array([2, 0, 3], dtype=np.int64), n)
+    mask = sem.SEM_AE_TANH_HIDDEN
+    loss, grad = sem.ae_grad(dev(to_morton(pool)), dev(params), idx=dev(idx), tanh_mask=mask,
+                             loss_kind=loss_kind)
+    ol, og = ae.gradient(params, pool[idx[:3]], quantize=True, tanh_mask=mask,
+                         loss_kind=loss_kind)
+    assert abs(float(loss.item()) - ol) <= 1e-5 * ol
+    assert normwise(grad.cpu().numpy().astype(np.float64), og) <= 2e-4
+
+
+@pytest.mark.parametrize("mask", [sem.SEM_AE_TANH_HIDDEN, 0x01, 0x12])
+@pytest.mark.parametrize("e", [1, 9, 2061])
+def test_tanh_codec_roundtrip(e, mask):
+    """Compression and decompression with tanh: part of a workgroup's eight
+    elements, one over, and more than one pass of every workgroup.  The
+    network is the principal components with small hidden values (exact
+    powers of two in, and out again after), where tanh is nearly linear and
+    smooth elements pass the check."""
+    host = lambda t: t.cpu().numpy()
+    r = np.random.default_rng(31)
+    params, _ = sem.ae_pca_init(sem.ae_blocks(
+        list(W.ae_fields(20, DEV, elements=np.arange(2048), dtype=torch.float32)))[0])
+    off, span = 0, []
+    for (w, b) in ae.layer_sizes():
+        span.append(slice(off, off + w))
+        off += w + b
+    for layer, factor in ((0, 2.0 ** -11), (2, 2.0 ** 11), (3, 2.0 ** -11), (5, 2.0 ** 11)):
+        params[span[layer]] *= factor
+    noise = 0.05 * (np.arange(e).reshape(e, 1, 1, 1) % 3 == 1)
+    f = [(b + torch.from_numpy(noise * r.normal(size=(e, 8, 8, 8))).to(DEV, torch.float32))
+         .contiguous() for b in W.ae_fields(20, DEV, elements=np.arange(e), dtype=torch.float32)]
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    pk = sem.ae_compress(f, params, tanh_mask=mask, status=st)
+    out = [host(t) for t in sem.ae_decompress(pk, params, tanh_mask=mask)]
+    hf = [host(t) for t in f]
+    flags = host(pk["flags"]).astype(bool)
+    assert int(st.item()) == 0 and pk["n_raw"] == int(flags.sum())
+    assert flags.sum() < e and (e == 1 or flags.any())
+    for a, b in zip(out, hf):
+        np.testing.assert_array_equal(a[flags], b[flags])
+    # flags: the rule applied in FP32 to what a receiver decodes
+    pure = dict(pk, flags=torch.zeros_like(pk["flags"]), raw=pk["raw"][:0])
+    rec = [host(t) for t in sem.ae_decompress(pure, params, tanh_mask=mask)]
+    gmax = host(pk["scale"]).max(axis=0)
+    np.testing.assert_array_equal(ae.fallback(hf, rec, gmax), flags)
+    assert not ae.fallback(hf, out, gmax).any()
+    # and that is the forward pass's reconstruction and latent, bit for bit
+    blocks, scale = sem.ae_blocks(f)
+    recon, latent = sem.ae_forward(blocks, params, tanh_mask=mask)
+    assert torch.equal(latent.view(torch.int16), pk["latent"].view(torch.int16))
+    want = to_natural(host(recon)) * host(scale)[:, :, None, None, None]
+    np.testing.assert_array_equal(np.stack(rec, 1), want)
