@@ -513,7 +513,9 @@ int sem_stream_copy(const void* src, void* dst, size_t bytes, void* stream);
 
 int64_t sem_ae_param_count(void);
 
-/* Workspace of sem_ae_forward / sem_ae_grad for a batch of n elements. */
+/* Workspace of sem_ae_grad for a batch of n elements (28 KiB each, and the
+ * gradients of at most 256 workgroups).  sem_ae_forward asks for the same size
+ * and does not touch it. */
 size_t sem_ae_workspace_bytes(int64_t n);
 
 /* Normalised blocks [E][512][4] and element maxima scale[E][4] of four
@@ -575,7 +577,10 @@ int sem_ae_pca_init(int64_t n_pool, const float* pool, float* params, double* la
 /* Compress E elements: binary16 latent [E][32], scale [E][4], flags [E]
  * (1 = raw), the raw elements' fields packed in element order into
  * raw[raw_cap][4][512] and their count into *n_raw (device int64; exact even
- * when raw_cap is too small, which sets SEM_FLAG_RAW_OVERFLOW). */
+ * when raw_cap is too small, which sets SEM_FLAG_RAW_OVERFLOW).  The size of
+ * the workspace, 16 KiB for each of the first 16,384 elements and some 8 bytes
+ * an element more, serves every tanh_mask and sem_modal_compress; only a tanh
+ * network uses the first part. */
 size_t sem_ae_compress_workspace_bytes(int64_t n_elem);
 int sem_ae_compress(int64_t n_elem, const float* u, const float* v, const float* w,
                     const float* theta, const float* params, int tanh_mask, uint16_t* latent,

@@ -1277,12 +1277,12 @@ hipError_t layer_forward(int l, int64_t n, const float* params, const float* x, 
 
 constexpr int64_t kSplitRows = 512;   // least rows per Gram-matrix slice
 
+// Workspace of a training step
 struct AeWs {
-  float* act[kLayers + 1];   // act[0] = input blocks, act[l + 1] = layer l output
-  float* g;                  // output gradient
-  float* slices;             // weight-gradient slice per workgroup
-  double* lpart;             // loss partial per workgroup
-  int64_t n;
+  float* act[kLayers];   // act[l + 1] = output of layer l < 5 (act[0] unused)
+  float* g;              // output gradient
+  float* slices;         // weight-gradient slice per workgroup
+  double* lpart;         // loss partial per workgroup
   size_t bytes;
 };
 
@@ -1297,13 +1297,11 @@ AeWs ae_layout(void* base, int64_t n) {
     off += align256(b);
     return q;
   };
-  w.act[0] = reinterpret_cast<float*>(take((size_t)n * 2048 * 4));
-  for (int l = 0; l < kLayers; ++l)
+  for (int l = 0; l < kLayers - 1; ++l)
     w.act[l + 1] = reinterpret_cast<float*>(take((size_t)out_rows(l, n) * out_width(l) * 4));
   w.g = reinterpret_cast<float*>(take((size_t)n * 2048 * 4));
   w.slices = reinterpret_cast<float*>(take((size_t)ae_net_groups(n) * kAeNetParams * 4));
   w.lpart = reinterpret_cast<double*>(take((size_t)ae_net_groups(n) * 8));
-  w.n = n;
   w.bytes = off;
   return w;
 }
@@ -1478,7 +1476,8 @@ constexpr int64_t kChunk = 16384;
 constexpr int kCodecGroups = 256;
 
 struct CompressWs {
-  AeWs ae;
+  float* blocks;    // packed elements of a chunk and their reconstruction
+  float* recon;     //   (tanh network; the linear one needs neither)
   int64_t* offs;
   int64_t* partial;
   uint32_t* gmax;
@@ -1490,14 +1489,15 @@ struct CompressWs {
 CompressWs compress_layout(void* base, int64_t n_elem) {
   CompressWs c{};
   const int64_t chunk = n_elem < kChunk ? n_elem : kChunk;
-  c.ae = ae_layout(base, chunk > 0 ? chunk : 1);
   char* p = static_cast<char*>(base);
-  size_t off = c.ae.bytes;
+  size_t off = 0;
   auto take = [&](size_t b) {
     char* q = p ? p + off : nullptr;
     off += align256(b);
     return q;
   };
+  c.blocks = reinterpret_cast<float*>(take((size_t)chunk * 2048 * 4));
+  c.recon = reinterpret_cast<float*>(take((size_t)chunk * 2048 * 4));
   c.offs = reinterpret_cast<int64_t*>(take((size_t)(n_elem + 1) * 8));
   c.partial = reinterpret_cast<int64_t*>(take((size_t)(scan_partials_capacity(n_elem) + 1) * 8));
   c.gmax = reinterpret_cast<uint32_t*>(take(16));
@@ -1578,13 +1578,13 @@ hipError_t launch_ae_compress(int64_t n_elem, const float* const* f, const float
   }
   for (int64_t b = 0; b < n_elem && tanh_mask != 0; b += kChunk) {
     const int64_t n = n_elem - b < kChunk ? n_elem - b : kChunk;
-    e = launch_ae_pack(b, n, f, scale, c.ae.act[0], s);
+    e = launch_ae_pack(b, n, f, scale, c.blocks, s);
     if (e != hipSuccess) return e;
-    e = launch_net_forward(n, c.ae.act[0], params, tanh_mask, c.ae.act[kLayers],
+    e = launch_net_forward(n, c.blocks, params, tanh_mask, c.recon,
                            latent + b * 32, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(ae_check, dim3((unsigned)n), dim3(kT), 0, s, b, f[0], f[1], f[2], f[3],
-                       scale, c.gmax, c.ae.act[kLayers], flags);
+                       scale, c.gmax, c.recon, flags);
   }
   e = launch_flag_scan(flags, n_elem, c.partial, c.offs, s);
   if (e != hipSuccess) return e;
@@ -1615,9 +1615,9 @@ hipError_t launch_ae_decompress(int64_t n_elem, const uint16_t* latent, const fl
   }
   for (int64_t b = 0; b < n_elem; b += kChunk) {
     const int64_t n = n_elem - b < kChunk ? n_elem - b : kChunk;
-    e = launch_net_decode(n, latent + b * 32, params, tanh_mask, c.ae.act[kLayers], s);
+    e = launch_net_decode(n, latent + b * 32, params, tanh_mask, c.recon, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ae_unpack, dim3((unsigned)n), dim3(kT), 0, s, b, c.ae.act[kLayers], scale,
+    hipLaunchKernelGGL(ae_unpack, dim3((unsigned)n), dim3(kT), 0, s, b, c.recon, scale,
                        flags, c.offs, raw, raw_count, f[0], f[1], f[2], f[3], status);
   }
   return hipGetLastError();

@@ -390,3 +390,18 @@ def test_bench_finds_committed_profile_summaries():
     assert os.path.basename(path) == "qcount_dma7_channel65536_f64_traffic.json"
     assert os.path.exists(path)
     assert os.path.exists(bench.MFMA_FILE)
+
+
+def test_compressor_workspaces_hold_what_is_used():
+    L = _lib.lib()
+    # a training step keeps the outputs of five layers and the output gradient
+    # of each block, and a slice of the parameters for each workgroup
+    block = 4 * (2048 + 512 + 32 + 512 + 2048 + 2048)
+    n = 10000
+    need = n * block + 256 * (67812 * 4 + 8)
+    assert need <= L.sem_ae_workspace_bytes(n) <= need + 4096
+    # compression keeps a chunk's blocks and reconstructions, and an offset for
+    # each element with their scan's sums
+    n = 100000
+    need = 16384 * 2 * 2048 * 4 + 8 * n
+    assert need <= L.sem_ae_compress_workspace_bytes(n) <= need + (1 << 20)
