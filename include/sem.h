@@ -432,7 +432,8 @@ int sem_global_edge_keys(int64_t n_ref, int order, int64_t n_elem, const uint64_
                          const int64_t* gid, uint64_t* global_keys, int32_t* status_word,
                          void* stream);
 
-/* Bytes of device workspace sem_weld needs for n_ref = 3 * triangles. */
+/* Bytes of device workspace sem_weld needs for n_ref = 3 * triangles (12 to
+ * 21 bytes a corner, 16 KiB at least). */
 size_t sem_weld_workspace_bytes(int64_t n_ref);
 
 /* Weld a triangle soup (tri_xyz [n_ref / 3][3][3] of dtype dt, keys [n_ref]

@@ -541,9 +541,9 @@ WeldLayout weld_layout(void* base, int64_t n_ref) {
   w.offs = reinterpret_cast<int64_t*>(take((size_t)(w.n_words + 1) * 8));
   w.partial =
       reinterpret_cast<int64_t*>(take((size_t)(scan_partials_capacity(w.n_words) + 1) * 8));
-  // callers may count on 16 bytes a corner and as many a table slot
-  const size_t told = (size_t)n_ref * 16 + (size_t)cap * 16;
-  w.bytes = o > told ? o : told;
+  // one size for all small soups: a workspace kept between them fits
+  constexpr size_t kLeast = 16 << 10;
+  w.bytes = o > kLeast ? o : kLeast;
   return w;
 }
 

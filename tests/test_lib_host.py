@@ -405,3 +405,16 @@ def test_compressor_workspaces_hold_what_is_used():
     n = 100000
     need = 16384 * 2 * 2048 * 4 + 8 * n
     assert need <= L.sem_ae_compress_workspace_bytes(n) <= need + (1 << 20)
+
+
+@pytest.mark.parametrize("n_ref", [1, 300, 1 << 20, (1 << 20) + 1, 24000000])
+def test_weld_workspace_holds_what_is_used(n_ref):
+    # table entries of 4 bytes, at least two a corner and a power of two of
+    # them; 4 bytes of slot a corner; flags, counts and offsets (20 bytes) for
+    # 64 corners, and the sums of their scan
+    cap = 64
+    while cap < 2 * n_ref:
+        cap *= 2
+    need = 4 * cap + 4 * n_ref + 20 * ((n_ref + 63) // 64)
+    have = _lib.lib().sem_weld_workspace_bytes(n_ref)
+    assert need <= have <= max(need + need // 100 + 4096, 16384)
