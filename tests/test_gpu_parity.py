@@ -464,8 +464,11 @@ def test_q_and_counts_over_more_elements_than_one_launch_holds():
 def test_an_element_has_the_same_q_wherever_it_stands(n, dt):
     """The same element repeated, a number that is no multiple of what a
     workgroup takes: every copy gets the same Q, |omega|, range and gradient,
-    bit for bit, from sem_qcrit, sem_extract and the batch."""
+    bit for bit, from sem_qcrit, sem_extract and the batch (in the form of
+    sem_qcrit, whatever the tuner left)."""
     e = 77
+    code = sem.SEM_F64 if dt == np.float64 else sem.SEM_F32
+    sem.init(0)
     rng = np.random.default_rng(n)
     base = [a[:1] for a in warped_mesh(n, (2, 1, 1))] + \
         [rng.normal(size=(1,) + (n + 1,) * 3) for _ in range(3)]
@@ -476,7 +479,12 @@ def test_an_element_has_the_same_q_wherever_it_stands(n, dt):
         assert bool((a == a[0]).all()), n
     r = sem.extract(*t, [float(q.mean())])
     out = dict(q=torch.empty_like(q), omega_mag=torch.empty_like(q), minmax=torch.empty_like(mm))
-    sem.qcrit_batch(sem.BatchPlan([dict(zip("xyzuvw", t), **out)]))
+    tuned = sem.batch_variant(n, code)
+    sem.batch_set_variant(n, code, 3)
+    try:
+        sem.qcrit_batch(sem.BatchPlan([dict(zip("xyzuvw", t), **out)]))
+    finally:
+        sem.batch_set_variant(n, code, tuned)
     for a, key in ((q, "q"), (om, "omega_mag"), (mm, "minmax")):
         assert torch.equal(r[key], a) and torch.equal(out[key], a), key
 
