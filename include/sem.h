@@ -207,12 +207,11 @@ size_t sem_extract_workspace_bytes(int64_t n_elem, int order, int n_iso, sem_dty
 /* Q-criterion, vorticity magnitude and the isosurfaces of Q in one call:
  * the results of sem_qcrit followed by sem_isosurface on Q (same case
  * table, vertex rule, NaN and tie rules, same triangles in the same order),
- * with Q never re-read for classification.  For N = 7 in FP64 the first
- * kernel stages each element's six tiles in LDS, computes Q and |omega|,
- * and counts every isovalue's triangles from the Q tile; the counts are
- * exclusive-scanned, and a second kernel re-stages the Q and coordinate
- * tiles of the elements that have triangles and emits them.  Other orders
- * and FP32 run sem_qcrit's kernel, then sem_isosurface's count and emission.
+ * with Q never re-read for classification: the first kernel computes Q and
+ * |omega| of an element and counts every isovalue's triangles while Q is on
+ * the chip; the counts are exclusive-scanned, and the emission reads Q and the
+ * coordinates of the elements that have triangles.  The mixed dtypes do the
+ * same at N = 7.
  *   q, omega_mag, q_minmax  optional device outputs, as in sem_qcrit (when
  *                 q or q_minmax is NULL the workspace holds them).
  *   iso_host      HOST array of n_iso isovalues.
@@ -452,9 +451,9 @@ int sem_weld(int64_t n_ref, sem_dtype dt, const void* tri_xyz, const uint64_t* k
  * Kernel-phase timing (a tracing aid, not part of the method)
  * ------------------------------------------------------------------- */
 
-/* Phases the timing reports: the Q / |omega| kernel (which also counts
- * triangles in sem_extract's N = 7 FP64 path), the separate classify-and-
- * count kernel, the exclusive scan with the totals, and triangle emission. */
+/* Phases the timing reports: the Q / |omega| kernel (which also counts the
+ * triangles in sem_extract), the classify-and-count kernel of
+ * sem_isosurface, the exclusive scan, and triangle emission with the totals. */
 enum { SEM_PHASE_QCRIT = 0, SEM_PHASE_COUNT = 1, SEM_PHASE_SCAN = 2, SEM_PHASE_EMIT = 3,
        SEM_NUM_PHASES = 4 };
 

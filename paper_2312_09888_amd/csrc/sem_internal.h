@@ -56,8 +56,8 @@ struct IsoOut {
 
 // Isosurface workspace layout (offsets in bytes from the workspace start).
 struct IsoWorkspace {
-  int32_t* cnt;       // [n_iso * n_elem] triangles per (isovalue, element)
-  int64_t* offs;      // [n_iso * n_elem + 1] exclusive prefix of cnt
+  int32_t* cnt;       // [n_iso * n_elem] slots: triangles | active cells << 16
+  int64_t* offs;      // [n_iso * n_elem + 1] exclusive prefix of the triangles
   int64_t* partial;   // [scan blocks + 1]
   size_t bytes;
 };

@@ -227,8 +227,9 @@ __device__ __forceinline__ bool invert_jacobian(T xr, T xs, T xt, T yr, T ys, T 
 // 1 / x from the hardware estimate and two Newton steps (an ulp at most; none
 // of 8,388,608 random determinants differed from the correctly rounded
 // division, which adds range scaling and a final correction and takes about
-// 1 % longer in Q of orders 6 to 9); x outside [2^-1000, 2^1000] in magnitude, 0 and NaN take the
-// division (a branch that a wave skips unless one of its lanes needs it).
+// 1 % longer in Q of orders 6 to 9); x outside [2^-1000, 2^1000] in magnitude,
+// 0 and NaN take the division (a branch that a wave skips unless one of its
+// lanes needs it).
 __device__ __forceinline__ double recip_refined(double x) {
   double r = __builtin_amdgcn_rcp(x);
   double e = fma(-x, r, 1.0);
@@ -1317,10 +1318,10 @@ mixed7(const double* __restrict__ dmat, const float* __restrict__ x,
 // Work item = `chunk` consecutive elements of one snapshot; snapshots may
 // differ in order N and element count.  Each workgroup takes items
 // blockIdx.x, blockIdx.x + gridDim.x, ... ; for an item it finds the
-// snapshot (binary search over the items' prefix), stages the chunk's six
-// tiles and D in LDS and computes Q, |omega| and the element ranges with
-// the order's instantiation.  The chunk per (order, precision) is what the
-// autotuner measured fastest: small elements leave threads idle unless
+// snapshot (binary search over the items' prefix) and computes Q, |omega| and
+// the element ranges with the order's instantiation: by default the line
+// exchange of sem_qcrit, or the LDS-tile form (six tiles and D staged) if the
+// caller or the tuner chose it, where small elements leave threads idle unless
 // several share a workgroup.
 
 constexpr int kBatchThreads = 256;
@@ -1435,7 +1436,10 @@ constexpr int batch_threads() {
 // Waves per SIMD to hold: the LDS tile leaves room for three workgroups a CU in
 // FP64 and six in FP32; a few registers more than three (four) waves allow cost
 // the tile form a quarter (12,228 order-6 elements, FP64: 168 us, 226 with two).
-// Order 9 in FP64 would spill too much for three (188 us with two, 195).
+// Order 9 in FP64 would spill too much for three (188 us with two, 195).  The
+// line form at FP64 N = 8 and 9 spills two registers in the loop over items
+// (12 bytes a lane; a launch of sem_qcrit holds them): within 10 % of sem_qcrit,
+// and a wave less would cost more.
 template <int N, typename T, int FORM>
 constexpr int batch_waves() {
   return FORM == kBatchLines ? line_waves<N, T, LineOf<N, T>>()

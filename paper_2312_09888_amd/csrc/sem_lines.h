@@ -48,14 +48,17 @@ struct LineCfg {
 // modulo 64 words for wide accesses): FP32 N = 7 10.4 with 8 and 7.0 with 9.
 // Three fields per pass halve the barriers where LDS allows it without losing
 // a wave (FP64 N = 4 17.6 against 14.1), one where it does not (FP64 N = 8
-// 16.5 against 17.9).  ps per point, this form against the fastest of the
-// replaced ones, on one box: FP32 N = 1..9 12.2 / 9.8 / 7.2 / 8.1 / 8.5 / 8.1
-// / 7.3 / 7.9 / 13.1 against 12.3 / 10.3 / 7.5 / 9.5 / 10.9 / 13.9 / 9.3 /
-// 13.9 / 21.6; FP64 18.0 / 14.8 / 13.1 / 14.1 / 14.9 / 15.2 / 14.3 / 16.5 /
-// 17.8 against 18.2 / 21.7 / 13.6 / 22.9 / 22.4 / 27.8 / 15.1 / 42.1 / 39.4
-// (6.4 and 12.8 are the bytes at 5 TB/s; N = 7 FP64 had a form of its own,
-// four waves on swizzled tiles fetched by direct loads: Q with the counts of
-// the 65,536-element snapshot 0.55 ms, here 0.44 with the packed slots).
+// 16.5 against 17.9).  ps per point of Q alone at 16,384 elements and more,
+// this form against the fastest of the replaced ones, on one box: FP32 N =
+// 2..9 9.8 / 7.2 / 8.1 / 8.5 / 8.1 / 7.3 / 7.9 / 13.1 against 10.3 / 7.5 / 9.5
+// / 10.9 / 13.9 / 9.3 / 13.9 / 21.6; FP64 14.8 / 13.1 / 14.1 / 14.9 / 15.2 /
+// 14.3 / 16.5 / 17.8 against 21.7 / 13.6 / 22.9 / 22.4 / 27.8 / 12.4 / 42.1 /
+// 39.4 (6.4 and 12.8 are the bytes at 5 TB/s).  N = 1 has no lines in LDS
+// (pair_deriv); its shapes are whole waves.  N = 7 FP64 had a form of its own,
+// four waves on swizzled tiles fetched by direct loads, 2 to 5 % faster for Q
+// alone of 65,536 elements: LineQ gives Q alone a shape of its own; with the
+// counts this form is the faster one (the Q phase of the 65,536-element
+// snapshot 0.555 before, 0.527 ms with the packed slots).
 constexpr int kLineCfg64[kMaxOrder + 1][4] = {
     {0, 0, 0, 0},   {8, 64, 2, 3},  {9, 256, 3, 3},  {1, 64, 6, 3},  {1, 128, 5, 3},
     {1, 256, 6, 3}, {1, 128, 7, 3},  {1, 256, 10, 1}, {1, 256, 9, 1}, {1, 512, 10, 1}};
