@@ -33,6 +33,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -1021,6 +1022,11 @@ def _short(name):
     return name.split("(")[0] if not name.startswith("void ") else name[5:].split("(")[0]
 
 
+def _kernel(name):
+    """The short name without the workgroup shape of a line kernel."""
+    return re.sub(r", LineCfg<[^<>]*> ?", "", _short(name))
+
+
 def summarize_trace(directory, out, command):
     """Text table of a rocprofv3 --kernel-trace --stats run (library kernels,
     the copy kernel; torch's input-generation kernels summed in one line)."""
@@ -1086,7 +1092,7 @@ def summarize_pmc(fetch_dir, write_dir, out, command):
         for r in _csv(directory, "counter_collection.csv"):
             if r["Counter_Name"] != counter:
                 continue
-            per.setdefault(_short(r["Kernel_Name"]), []).append(float(r["Counter_Value"]))
+            per.setdefault(_kernel(r["Kernel_Name"]), []).append(float(r["Counter_Value"]))
         # the run's 1 GiB copies (the calibration call and the bandwidth
         # reps; the 512 MiB cache flushes read about half as much): the
         # median counter value of one such dispatch

@@ -418,3 +418,14 @@ def test_weld_workspace_holds_what_is_used(n_ref):
     need = 4 * cap + 4 * n_ref + 20 * ((n_ref + 63) // 64)
     have = _lib.lib().sem_weld_workspace_bytes(n_ref)
     assert need <= have <= max(need + need // 100 + 4096, 16384)
+
+
+def test_bench_names_kernels_without_their_shape():
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    ns = "sem::(anonymous namespace)::"
+    full = f"void {ns}qcount_lines<7, double, {ns}LineCfg<7, 1, 256, 10, 1> >(double const*, int)"
+    assert bench._kernel(full) == bench.q_kernel_name("f64")
+    assert bench._kernel(f"void {ns}emit_direct<7, double>(int)") == "emit_direct<7, double>"
