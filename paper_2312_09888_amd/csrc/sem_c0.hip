@@ -27,7 +27,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr uint64_t kEmpty = ~0ull;
 constexpr int kGsExt = 2048;             // listed copies a workgroup holds in LDS
-constexpr int kWeldT = 512;              // threads of weld_insert, a corner each
+constexpr int kWeldT = 512;              // threads of weld_insert
+constexpr int64_t kWeldMany = 1 << 22;   // corners from which a thread takes four
 
 inline unsigned blocks_for(int64_t n) {
   return (unsigned)((n + kThreads - 1) / kThreads > 0 ? (n + kThreads - 1) / kThreads : 1);
@@ -323,64 +324,93 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 // twice the number of corners, so a free slot is always reached).  A slot
 // holds the smallest corner of its key, and the key is looked up there: one
 // atomic claims a slot and records the corner, and an entry is 4 bytes.  A
-// workgroup finds the distinct keys of its kWeldT consecutive corners in LDS
-// first, in the same way (also at most half full), and only the first corner
-// of each goes to the table in memory; local[] marks these corners, 64 to a
-// word.  535,000 triangles of two isovalues: 165 us with an atomic each for
-// key and corner of every corner, 48 with the distinct keys of a workgroup
-// only, 26 with the key looked up at the corner.  A thread has one corner: a
-// probe is a round trip to memory, and only other waves hide it.  All passes
-// of the weld, four corners a thread against one: 1,000 triangles that share
-// no key 39 and 22 us, 100,000 that share each key six times, in order 28.6
-// and 25.1, at random 52 and 47; only where a workgroup of four times the
-// corners has hardly more keys does it lose (2,000,000 triangles, each key
-// 1,000 times, 90 and 94).
+// workgroup finds the distinct keys of its consecutive corners in LDS first,
+// in the same way (also at most half full), and only the first corner of each
+// goes to the table in memory; local[] marks these corners, 64 to a word.
+// 535,000 triangles of two isovalues: 165 us with an atomic each for key and
+// corner of every corner, 48 with the distinct keys of a workgroup only, 26
+// with the key looked up at the corner.  Corners a thread (PER): one up to
+// kWeldMany, where a probe's round trip is hidden by other waves only; four
+// beyond, where the table is far larger than the caches and a workgroup of
+// four times the corners sends fewer of them there.  All passes of the weld,
+// one corner and four: 1,000 triangles that share no key 22 and 39 us; the
+// first 100,000 triangles of a channel snapshot's soup 29 and 32, 1,000,000
+// 115 and 117, 2,000,000 218 and 214, 7,900,000 873 and 834.
+template <int PER>
 __global__ void __launch_bounds__(kWeldT)
     weld_insert(int64_t n_ref, const uint64_t* __restrict__ keys, uint32_t* __restrict__ table,
                 int32_t* __restrict__ slot, uint64_t* __restrict__ local, int64_t cap,
                 int32_t* __restrict__ status) {
-  __shared__ uint64_t lkey[kWeldT];
-  __shared__ uint32_t lpos[2 * kWeldT];
-  const uint32_t t = threadIdx.x;
-  const int64_t r = (int64_t)blockIdx.x * kWeldT + t;
-  const uint64_t k = r < n_ref ? keys[r] : kEmpty, hash = mix64(k);
-  uint32_t l = (uint32_t)(hash >> 40) & (2 * kWeldT - 1);
-  lkey[t] = k;
-  lpos[t] = lpos[kWeldT + t] = ~0u;
+  constexpr int kRefs = kWeldT * PER;
+  __shared__ uint64_t lkey[kRefs];
+  __shared__ uint32_t lpos[2 * kRefs];
+  const int64_t base = (int64_t)blockIdx.x * kRefs;
+  uint64_t k[PER], hash[PER];
+  uint32_t l[PER];
+  bool own[PER], bad = false;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const uint32_t me = j * kWeldT + threadIdx.x;
+    k[j] = base + me < n_ref ? keys[base + me] : kEmpty;
+    bad |= base + me < n_ref && k[j] == kEmpty;
+    hash[j] = mix64(k[j]);
+    lkey[me] = k[j];
+    lpos[me] = lpos[kRefs + me] = ~0u;
+  }
   __syncthreads();
-  if (k != kEmpty) {
-    for (;;) {   // ends: at most kWeldT of the 2 kWeldT entries are taken
-      const uint32_t prev = atomicCAS(&lpos[l], ~0u, t);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (k[j] == kEmpty) continue;
+    const uint32_t me = j * kWeldT + threadIdx.x;
+    l[j] = (uint32_t)(hash[j] >> 40) & (2 * kRefs - 1);
+    for (;;) {   // ends: at most kRefs of the 2 kRefs entries are taken
+      const uint32_t prev = atomicCAS(&lpos[l[j]], ~0u, me);
       if (prev == ~0u) break;
-      if (lkey[prev] == k) {
-        if (t < prev) atomicMin(&lpos[l], t);
+      if (lkey[prev] == k[j]) {
+        if (me < prev) atomicMin(&lpos[l[j]], me);
         break;
       }
-      l = (l + 1) & (2 * kWeldT - 1);
+      l[j] = (l[j] + 1) & (2 * kRefs - 1);
     }
   }
   __syncthreads();
-  const bool own = k != kEmpty && lpos[l] == t;
-  const uint64_t marks = __ballot(own);
-  if ((t & 63) == 0 && r < n_ref) local[r >> 6] = marks;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const uint32_t me = j * kWeldT + threadIdx.x;
+    own[j] = k[j] != kEmpty && lpos[l[j]] == me;
+    const uint64_t marks = __ballot(own[j]);
+    if ((me & 63) == 0 && base + me < n_ref) local[(base + me) >> 6] = marks;
+  }
   __syncthreads();
-  if (own) {
-    const uint64_t mask = (uint64_t)cap - 1;
-    uint64_t h = hash & mask;
-    for (int64_t probe = 0; probe < cap; ++probe) {   // a half-empty table ends it before
-      const uint32_t prev = atomicCAS(&table[h], ~0u, (uint32_t)r);
-      if (prev == ~0u) break;
-      if (keys[prev] == k) {
-        if ((uint32_t)r < prev) atomicMin(&table[h], (uint32_t)r);
+  const uint64_t mask = (uint64_t)cap - 1;
+  uint32_t prev[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (own[j])
+      prev[j] = atomicCAS(&table[hash[j] & mask], ~0u, (uint32_t)(base + j * kWeldT + threadIdx.x));
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (!own[j]) continue;
+    const uint32_t r = (uint32_t)(base + j * kWeldT + threadIdx.x);
+    uint64_t h = hash[j] & mask;
+    for (int64_t probe = 1; prev[j] != ~0u; ++probe) {
+      if (keys[prev[j]] == k[j]) {
+        if (r < prev[j]) atomicMin(&table[h], r);
         break;
       }
+      if (probe == cap) break;   // not reached in a half-empty table
       h = (h + 1) & mask;
+      prev[j] = atomicCAS(&table[h], ~0u, r);
     }
-    lpos[l] = (uint32_t)h;
+    lpos[l[j]] = (uint32_t)h;
   }
   __syncthreads();
-  if (r < n_ref) slot[r] = k != kEmpty ? (int32_t)lpos[l] : -1;
-  if (r < n_ref && k == kEmpty && status) atomicOr(status, SEM_FLAG_BAD_ID);
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int64_t r = base + j * kWeldT + threadIdx.x;
+    if (r < n_ref) slot[r] = k[j] != kEmpty ? (int32_t)lpos[l[j]] : -1;
+  }
+  if (bad && status) atomicOr(status, SEM_FLAG_BAD_ID);
 }
 
 // first corners of the keys, 64 corners a wave
@@ -555,8 +585,13 @@ hipError_t weld_t(int64_t n_ref, const T* tri_xyz, const uint64_t* keys, int64_t
   if (n_ref > 0) {
     hipLaunchKernelGGL(fill_ones, dim3(blocks_for(w.cap / 4)), dim3(kThreads), 0, s,
                        reinterpret_cast<uint64_t*>(w.table), w.cap / 4);
-    hipLaunchKernelGGL(weld_insert, dim3((unsigned)((n_ref + kWeldT - 1) / kWeldT)),
-                       dim3(kWeldT), 0, s, n_ref, keys, w.table, w.slot, w.marks, w.cap, status);
+    auto insert = [&](auto kern, int per) {
+      const int64_t refs = (int64_t)kWeldT * per;
+      hipLaunchKernelGGL(kern, dim3((unsigned)((n_ref + refs - 1) / refs)), dim3(kWeldT), 0, s,
+                         n_ref, keys, w.table, w.slot, w.marks, w.cap, status);
+    };
+    if (n_ref > kWeldMany) insert(weld_insert<4>, 4);
+    else insert(weld_insert<1>, 1);
     hipLaunchKernelGGL(weld_flag, dim3(blocks_for(w.n_words * 64)), dim3(kThreads), 0, s,
                        w.n_words, (const int32_t*)w.slot, (const uint32_t*)w.table, w.marks,
                        w.count);

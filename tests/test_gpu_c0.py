@@ -228,3 +228,18 @@ def test_dsavg_of_nodes_with_many_copies(dt, pool):
         t = dev(f)
         sem.dsavg(t, gs, out=t)
         np.testing.assert_array_equal(host(t), c0.dsavg(f, gid))
+
+
+@pytest.mark.parametrize("n_tri", [(1 << 22) // 3, (1 << 22) // 3 + 1])
+def test_weld_on_both_sides_of_four_corners_a_thread(n_tri):
+    """2^22 - 1 corners (one a thread) and two more (four a thread)."""
+    r = np.arange(3 * n_tri)
+    keys = ((r // 7) * 2654435761) % (1 << 20)      # in runs, and again far away
+    xyz = r.astype(np.float32).reshape(n_tri, 3, 1).repeat(3, axis=2)
+    verts, idx = sem.weld(dev(xyz, np.float32), dev(keys))
+    _, at, inv = np.unique(keys, return_index=True, return_inverse=True)
+    order = np.argsort(at)
+    number = np.empty_like(order)
+    number[order] = np.arange(order.size)
+    np.testing.assert_array_equal(host(idx).ravel(), number[inv])
+    np.testing.assert_array_equal(host(verts)[:, 0], at[order].astype(np.float32))
