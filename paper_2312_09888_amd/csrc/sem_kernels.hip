@@ -856,8 +856,10 @@ __device__ __forceinline__ void emit_elem(int64_t e, int t, int64_t n_elem,
 // workgroups that take several elements and look them up together are
 // slower, 133 against 120 us: the triangles of one element must be written
 // before the tiles of the next are known to be there.  Few
-// elements leave the chip idle: gridDim.y workgroups share each one's isovalues.
-template <int N, typename T>
+// elements leave the chip idle: if SLICED, gridDim.y workgroups share each
+// one's isovalues (a kernel of its own: strides that are read cost the others
+// 2 %, 12,228 elements of order 6 45.3 us against 44.1).
+template <int N, typename T, bool SLICED>
 __global__ void __launch_bounds__(emit_threads(N))
 emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* __restrict__ y,
             const T* __restrict__ z, const T* __restrict__ field, int n_iso,
@@ -867,9 +869,9 @@ emit_direct(int64_t e_begin, int64_t n_elem, const T* __restrict__ x, const T* _
             int32_t* __restrict__ status) {
   const int64_t e = e_begin + blockIdx.x;
   // the last workgroup also writes the totals (in place of a kernel of its own)
-  if (e == n_elem - 1 && blockIdx.y == 0)
+  if (e == n_elem - 1 && (!SLICED || blockIdx.y == 0))
     write_totals<T>(threadIdx.x, offs, n_elem, n_iso, tri_count, out, status);
-  const int s0 = blockIdx.y, ds = gridDim.y;
+  const int s0 = SLICED ? blockIdx.y : 0, ds = SLICED ? gridDim.y : 1;
   bool any = false;
   for (int s = s0; s < n_iso; s += ds) any |= slot_tris(cnt[(int64_t)s * n_elem + e]) > 0;
   if (any)
@@ -1906,11 +1908,15 @@ hipError_t iso_scan_emit(int order, const DeviceTables& tab, int64_t n_elem, con
     launch_parts(n_elem, 1, emit_threads(N), pe.start, pe.stop,
                  [&](int64_t b, int64_t, dim3 grid, hipEvent_t e0, hipEvent_t e1) {
                    grid.y = iso_slices(n_elem, n_iso);
-                   hipExtLaunchKernelGGL((emit_direct<N, T>), grid, dim3(emit_threads(N)), 0, s,
-                                         e0, e1, 0, b, n_elem, (const T*)x, (const T*)y,
-                                         (const T*)z, (const T*)field, n_iso, iso, out, tab.ntri,
-                                         (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys,
-                                         tri_count, status);
+                   auto go = [&](auto kern) {
+                     hipExtLaunchKernelGGL(kern, grid, dim3(emit_threads(N)), 0, s, e0, e1, 0, b,
+                                           n_elem, (const T*)x, (const T*)y, (const T*)z,
+                                           (const T*)field, n_iso, iso, out, tab.ntri,
+                                           (const int32_t*)ws.cnt, (const int64_t*)ws.offs, keys,
+                                           tri_count, status);
+                   };
+                   if (grid.y > 1) go(emit_direct<N, T, true>);
+                   else go(emit_direct<N, T, false>);
                  });
   });
   phase_done(pe);
